@@ -159,9 +159,10 @@ typedef struct {
                                 the host side of sp_score cannot see them; with B == 1 the length is T and
                                 nothing need be stated).  With it sp_score can take, for
                                 batches of prompts of up to 8192 keys (4096 with 5..8 query rows per KV
-                                head) whose KV heads carry at most eight query rows, a kernel that reads
-                                the K cache once and keeps all logits of a sequence on chip.  A sequence
-                                longer than promised is not scored: all of its scores (and its rows of
+                                head, 3072 with 9..32), a kernel that reads the K cache once and keeps all
+                                logits of a sequence on chip.  (Rows: queries times the heads per KV head,
+                                those counted as four up to four and as eight beyond.)  A sequence longer
+                                than the kernel holds is not scored: all of its scores (and its rows of
                                 d_lse) are NaN, which sp_pool_select reports in band; never silently
                                 wrong.  Nothing else depends on the promise.                            */
   int32_t k_dtype;           /* sp_k_dtype, 0 = bf16.  With SP_K_FP8_E4M3 the layers hold bytes: the strides

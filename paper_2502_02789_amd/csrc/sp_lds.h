@@ -18,6 +18,14 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 #endif
 constexpr int kKeyLoadPolicy = SP_KEY_LOAD_POLICY;
 
+// A table that no kernel writes while it is read, looked up at a wave-uniform index through the scalar cache.  (As
+// an ordinary global pointer the compiler makes it a vector load and waits for it with vmcnt(0), i.e. for every
+// tile load of the wave in flight.)
+typedef const __attribute__((address_space(4))) int32_t* ScalarTable;
+__device__ __forceinline__ ScalarTable scalar_table(const int32_t* table) {
+  return reinterpret_cast<ScalarTable>(reinterpret_cast<uintptr_t>(table));
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 template <int N>
@@ -75,6 +83,19 @@ __device__ __forceinline__ uint64_t lds_peek64(uint32_t lds_addr) {
   uint64_t v;
   asm volatile("ds_read_b64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(lds_addr) : "memory");
   return v;
+}
+// four 8-byte reads STRIDE bytes apart, one wait for all of them
+struct u64x4 { uint64_t v[4]; };
+template <int STRIDE>
+__device__ __forceinline__ u64x4 lds_peek64x4(uint32_t lds_addr) {
+  u64x4 r;
+  asm volatile(
+      "ds_read_b64 %0, %4\n\tds_read_b64 %1, %4 offset:%5\n\tds_read_b64 %2, %4 offset:%6\n\t"
+      "ds_read_b64 %3, %4 offset:%7\n\ts_waitcnt lgkmcnt(0)"
+      : "=&v"(r.v[0]), "=&v"(r.v[1]), "=&v"(r.v[2]), "=&v"(r.v[3])
+      : "v"(lds_addr), "n"(STRIDE), "n"(2 * STRIDE), "n"(3 * STRIDE)
+      : "memory");
+  return r;
 }
 __device__ __forceinline__ uint32_t lds_or_rtn(uint32_t lds_addr, uint32_t v) {
   uint32_t old;

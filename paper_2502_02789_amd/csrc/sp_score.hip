@@ -287,7 +287,7 @@ bool single_pass_wanted(const sp_score_args* a) {
   // Few query rows per KV head and a prompt short enough for the batch kernel, which keeps a sequence's logits
   // on chip and needs no exchange between workgroups: measured faster than the all-workgroup kernel up to 8K
   // keys (one query, 32 layers, head dim 128; us): 2K keys 38 against 135, 4K 57 against 137, 8K 127 against 159.
-  if (tiled_supported(a) && seq_supported(a)) return false;
+  if (tiled_supported(a) && (seq_supported(a) || wide_supported(a))) return false;
   return (a->flags & SP_SCORE_EXCLUSIVE_DEVICE) != 0 && (team_supported(a) || stream_supported(a));
 }
 // where the single-pass kernel that sp_score would pick keeps its "a wait expired" word
@@ -348,8 +348,8 @@ sp_status general_score(const sp_score_args* a, hipStream_t stream, bool allow_m
     p.q = q_rot;
   }
 
-  // (the single-pass batch kernel does not look at the tile table)
-  if (!(allow_mfma && tiled_supported(a) && seq_supported(a)))
+  // (the single-pass batch kernels do not look at the tile table)
+  if (!(allow_mfma && tiled_supported(a) && (seq_supported(a) || wide_supported(a))))
     hipLaunchKernelGGL(tile_table_kernel, dim3(1), dim3(1024), 0, stream, p.B, p.cu, p.tile_cu);
   if (allow_mfma && tiled_supported(a)) {
     const sp_status st = tiled_score(a, p, ws, stream);

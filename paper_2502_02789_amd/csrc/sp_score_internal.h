@@ -79,6 +79,8 @@ sp_status tiled_score(const sp_score_args* a, const ScoreDev& gen, void* extra, 
 
 // single-pass kernel for batches of short prompts with few query rows per KV head (sp_score_seq.hip)
 bool seq_supported(const sp_score_args* a);
+// ... and with up to 32 of them (sp_score_wide.hip)
+bool wide_supported(const sp_score_args* a);
 
 // single-pass streaming kernel (sp_score_stream.hip)
 bool stream_supported(const sp_score_args* a);

@@ -24,12 +24,12 @@
 //   * The stream of tiles never stops, neither at a slab's end nor between units: the loads run two
 //     tiles ahead of the arithmetic straight into the next slab or unit, and the barrier is a bare
 //     s_barrier (no vector-memory wait in front of it).
-//   * Each unit writes its [N][M] partial result; seq_finish_kernel merges the units of a sequence and
+//   * Each unit writes its [N][M] partial result; units_finish_kernel merges the units of a sequence and
 //     averages over the valid queries.
 //
 // A sequence must fit the registers: 64 * 8 * SeqLimits<R>::kMaxTiles keys.  The host cannot see the
 // sequence lengths of a batch (they live on the device), so for B > 1 this path is taken only on the caller's
-// promise sp_score_args.max_seqlen; a sequence that breaks the promise gets NaN scores (seq_finish_kernel).
+// promise sp_score_args.max_seqlen; a sequence that breaks the promise gets NaN scores (units_finish_kernel).
 #include <mutex>
 
 #include "sp_tile_walker.h"
@@ -48,38 +48,6 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-// One unit of work: sequence b for the slabs [s0, s1) of slab group grp (slab s = KV head s % H_kv of layer
-// s / H_kv; with SP_LAYER_MEAN a group holds whole layers).  Units are numbered with the longest sequences
-// first (all groups of a sequence next to each other).
-struct SeqUnit {
-  int k;  // position in this workgroup's list of units
-  int b, grp, seq0, M, nt, s0, s1;
-};
-
-// Units are dealt out to the gridDim.x workgroups in rounds, the direction changing with every round
-// (workgroup j: units j, 2W-1-j, 2W+j, ...): with the sizes in descending order every workgroup gets
-// nearly the same number of keys, and no counter has to be shared.
-template <int MAXT>
-__device__ __forceinline__ bool seq_next_unit(const TiledDev& p, int wave, int k, SeqUnit* u) {
-  const int W = gridDim.x, n_units = p.B * p.n_groups;
-  for (;; ++k) {
-    const int idx = k * W + ((k & 1) ? W - 1 - (int)blockIdx.x : (int)blockIdx.x);
-    if (idx >= n_units) return false;
-    const int grp = idx % p.n_groups;
-    const int b = p.seq_order ? p.seq_order[idx / p.n_groups] : idx / p.n_groups;  // (no table: batch order)
-    const int seq0 = p.cu[b];
-    const int M = p.cu[b + 1] - seq0;
-    const int n_tiles = (M + kWaveKeys - 1) / kWaveKeys;
-    const int s0 = grp * p.slabs_per_group;
-    const int s1 = min(p.L * p.H_kv, s0 + p.slabs_per_group);
-    // (no keys, or more than the registers hold: nothing to do here, see seq_order_kernel and seq_finish_kernel)
-    if (M <= 0 || n_tiles > MAXT * kTiledWaves || s0 >= s1) continue;
-    u->k = k; u->b = b; u->grp = grp; u->seq0 = seq0; u->M = M; u->s0 = s0; u->s1 = s1;
-    u->nt = __builtin_amdgcn_readfirstlane((n_tiles - wave + kTiledWaves - 1) / kTiledWaves);  // this wave's tiles
-    return true;
-  }
-}
-
 template <int D, int R, int LG, bool MEAN, bool FP8>
 __global__ __launch_bounds__(kTiledThreads) void seq_score_kernel(const TiledDev p) {
   extern __shared__ __align__(1024) unsigned char smem[];
@@ -89,12 +57,16 @@ __global__ __launch_bounds__(kTiledThreads) void seq_score_kernel(const TiledDev
   constexpr int NQ = R >> LG;   // queries whose rows fit the R held rows
   TW w(p, smem, typename TW::WholeSequence{}, 0);
   SeqUnit cur;
-  if (!seq_next_unit<MAXT>(p, w.wave, 0, &cur)) return;
+  if (!seq_next_unit(p, 0, &cur)) return;
+  auto tiles_of = [&](int M) __attribute__((always_inline)) {  // this wave's 64-key tiles
+    return __builtin_amdgcn_readfirstlane(((M + kWaveKeys - 1) / kWaveKeys - w.wave + kTiledWaves - 1) / kTiledWaves);
+  };
   const uint32_t xchg = (uint32_t)reinterpret_cast<uintptr_t>(smem) + kTiledWaves * 2 * TW::TILE_B;  // [2][waves][R] (max, sum)
 
   // The stream of tiles runs two items ahead of the arithmetic and straight on into the workgroup's
   // next unit: `ah` is the unit, slab and item that is requested next.
   SeqUnit ahu = cur;
+  int ah_nt = tiles_of(cur.M);
   bool ah_live = true;  // false: past the last unit (the last slab is requested again, nobody consumes it)
   int ah_s = cur.s0, ah_ph = -1;  // the slab; ph < 0: its query tile, else 32-key half-tile ph of this wave
   auto issue_next = [&](int slot) __attribute__((always_inline)) {
@@ -108,11 +80,12 @@ __global__ __launch_bounds__(kTiledThreads) void seq_score_kernel(const TiledDev
       const int rows = min(32, ahu.M - key_first);
       w.issue_key_rows(ah_l, ah_g, rows > 0 ? key_first : 0, rows, slot);
     }
-    if (++ah_ph == 2 * ahu.nt) {
+    if (++ah_ph == 2 * ah_nt) {
       ah_ph = -1;
       if (++ah_s == ahu.s1) {
-        if (ah_live && seq_next_unit<MAXT>(p, w.wave, ahu.k + 1, &ahu)) {
+        if (ah_live && seq_next_unit(p, ahu.k + 1, &ahu)) {
           ah_s = ahu.s0;
+          ah_nt = tiles_of(ahu.M);
         } else {
           ah_live = false;
           ah_s = ahu.s1 - 1;
@@ -130,7 +103,7 @@ __global__ __launch_bounds__(kTiledThreads) void seq_score_kernel(const TiledDev
 
 #pragma unroll 1
   for (;;) {
-  const int nt = cur.nt, M = cur.M, b = cur.b;
+  const int nt = tiles_of(cur.M), M = cur.M, b = cur.b;
 #pragma unroll
   for (int t = 0; t < MAXT; ++t)
 #pragma unroll
@@ -265,7 +238,7 @@ __global__ __launch_bounds__(kTiledThreads) void seq_score_kernel(const TiledDev
       }
     }
   });
-  if (!seq_next_unit<MAXT>(p, w.wave, cur.k + 1, &cur)) break;
+  if (!seq_next_unit(p, cur.k + 1, &cur)) break;
   }
   wait_vmcnt<0>();  // loads issued past the end land before the wave (and its LDS) goes away
 }
@@ -296,42 +269,68 @@ __global__ __launch_bounds__(1024) void seq_order_kernel(int B, const int32_t* _
   }
 }
 
-// Merge of the units' partial results and the average over the valid queries (Sec. 3.2.2): a workgroup takes 64
-// tokens, each of its 16 waves every sixteenth slab group (one 256-byte read per group and query), the waves'
-// results meet in LDS.  Sequences the scoring kernel left out (longer than promised) get NaN.
-constexpr int kSeqFinishParts = 16;
-__global__ __launch_bounds__(64 * kSeqFinishParts) void seq_finish_kernel(const TiledDev p) {
-  __shared__ float red[kSeqFinishParts][2][64];
-  const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
-  const int64_t tok = (int64_t)blockIdx.x * 64 + lane;
+// Merge of the units' partial results and the average over the valid queries (Sec. 3.2.2).  A workgroup takes TOK
+// tokens; its 1024 / TOK groups of TOK threads take every so-many-th slab group (one TOK * 4 byte read per group and
+// query), the lanes of a wave fold by shuffles, the sixteen waves' results meet in LDS.  Sequences the scoring
+// kernel left out (longer than it holds) get NaN.  Bound by the latency of the reads for one short prompt, whose
+// few tokens make few workgroups of 64 (2K tokens, 256 groups of one query: 7.6 us): narrower workgroups there.
+constexpr int kFinishWaves = 16;
+template <int NQ, int TOK>
+__global__ __launch_bounds__(64 * kFinishWaves) void units_finish_kernel(const TiledDev p) {
+  __shared__ float red[kFinishWaves][NQ][TOK];
+  __shared__ float prob[NQ][TOK];
+  constexpr int kParts = 64 * kFinishWaves / TOK;
+  const int k = threadIdx.x % TOK, part = threadIdx.x / TOK;
+  const int64_t tok = (int64_t)blockIdx.x * TOK + k;
   const bool inside = tok < p.T;
   const bool mean = p.layer_reduce != SP_LAYER_MAX;
-  float v[2] = {mean ? 0.f : -INFINITY, mean ? 0.f : -INFINITY};  // (this path has at most two queries per sequence)
+  float v[NQ];
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) v[n] = mean ? 0.f : -INFINITY;
   if (inside && mean && p.groups_per_layer > 0) {
-    // mean over layers from units smaller than a layer: the groups of a layer hold the log2 of its maxima over
+    // mean over layers from units that are parts of a layer: the groups of a layer hold the log2 of its maxima over
     // their KV heads; the layer's maximum over all heads is their maximum, and the layers' maxima add up
-    for (int l = part; l < p.L; l += kSeqFinishParts)
+    for (int l = part; l < p.L; l += kParts) {
+      float m[NQ];
 #pragma unroll
-      for (int n = 0; n < 2; ++n)
-        if (n < p.N) {
-          float m = -INFINITY;
-          for (int j = 0; j < p.groups_per_layer; ++j)
-            m = fmaxf(m, p.group_scores[((int64_t)(l * p.groups_per_layer + j) * p.N + n) * p.T + tok]);
-          v[n] += fast_exp2(m);
-        }
+      for (int n = 0; n < NQ; ++n) m[n] = -INFINITY;
+      for (int j = 0; j < p.groups_per_layer; ++j)
+#pragma unroll
+        for (int n = 0; n < NQ; ++n)
+          if (n < p.N) m[n] = fmaxf(m[n], p.group_scores[((int64_t)(l * p.groups_per_layer + j) * p.N + n) * p.T + tok]);
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) v[n] += fast_exp2(m[n]);
+    }
   } else if (inside) {
-    for (int g = part; g < p.n_groups; g += kSeqFinishParts)
+#pragma unroll 4
+    for (int g = part; g < p.n_groups; g += kParts)
 #pragma unroll
-      for (int n = 0; n < 2; ++n)
+      for (int n = 0; n < NQ; ++n)
         if (n < p.N) {
           const float x = p.group_scores[((int64_t)g * p.N + n) * p.T + tok];
           v[n] = mean ? v[n] + x : fmaxf(v[n], x);
         }
   }
-  red[part][0][lane] = v[0];
-  red[part][1][lane] = v[1];
+#pragma unroll
+  for (int off = TOK; off < 64; off <<= 1)
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+      const float x = __shfl_xor(v[n], off, kWave);
+      v[n] = mean ? v[n] + x : fmaxf(v[n], x);
+    }
+  if ((threadIdx.x & 63) < TOK)
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) red[threadIdx.x >> 6][n][k] = v[n];
   __syncthreads();
-  if (part != 0 || !inside) return;
+  if (threadIdx.x < NQ * TOK) {
+    const int n = threadIdx.x / TOK;
+    float x = red[0][n][k];
+#pragma unroll
+    for (int q = 1; q < kFinishWaves; ++q) x = mean ? x + red[q][n][k] : fmaxf(x, red[q][n][k]);
+    prob[n][k] = mean ? x : fast_exp2(x);
+  }
+  __syncthreads();
+  if (threadIdx.x >= TOK || !inside) return;
   const int b = upper_segment(p.cu, p.B, (int)tok);
   if (p.cu[b + 1] - p.cu[b] > p.seq_limit) {
     p.scores[tok] = __uint_as_float(0x7FC00000u);
@@ -341,13 +340,26 @@ __global__ __launch_bounds__(64 * kSeqFinishParts) void seq_finish_kernel(const 
   nv = max(1, min(nv, p.N));
   float sum = 0.f;
 #pragma unroll
-  for (int n = 0; n < 2; ++n)
-    if (n < nv) {
-      float x = red[0][n][lane];
-      for (int q = 1; q < kSeqFinishParts; ++q) x = mean ? x + red[q][n][lane] : fmaxf(x, red[q][n][lane]);
-      sum += mean ? x : fast_exp2(x);
-    }
+  for (int n = 0; n < NQ; ++n)
+    if (n < nv) sum += prob[n][k];
   p.scores[tok] = sum / (mean ? (float)nv * (float)p.L : (float)nv);
+}
+
+template <int NQ>
+static sp_status finish_by_tokens(const TiledDev& dev, hipStream_t stream) {
+  // tokens per workgroup: 64 where that makes at least two workgroups per compute unit, else 16
+  if (dev.T >= 64 * 512) hipLaunchKernelGGL((units_finish_kernel<NQ, 64>), dim3((unsigned)((dev.T + 63) / 64)), dim3(64 * kFinishWaves), 0, stream, dev);
+  else hipLaunchKernelGGL((units_finish_kernel<NQ, 16>), dim3((unsigned)((dev.T + 15) / 16)), dim3(64 * kFinishWaves), 0, stream, dev);
+  return launch_status();
+}
+sp_status launch_units_finish(const TiledDev& dev, hipStream_t stream) {  // (at most eight queries on these paths)
+  return dev.N == 1 ? finish_by_tokens<1>(dev, stream) : dev.N == 2 ? finish_by_tokens<2>(dev, stream)
+       : dev.N <= 4 ? finish_by_tokens<4>(dev, stream) : finish_by_tokens<8>(dev, stream);
+}
+
+void launch_seq_order(const sp_score_args* a, int32_t* order, int limit, hipStream_t stream) {
+  hipLaunchKernelGGL(seq_order_kernel, dim3(1), dim3(1024), 0, stream, a->B, a->d_cu_seqlens, order, a->d_lse, limit,
+                     a->L, a->N * a->H);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -427,7 +439,7 @@ size_t seq_workspace_bytes(const sp_score_args* a) {
   return seq_scores_bytes(a) + align_up(sizeof(int32_t) * (size_t)a->B, 256);  // partial results, then the sequence order
 }
 
-static int seq_cu_count() {  // compute units of the current device
+int seq_cu_count() {  // compute units of the current device
   static std::mutex mu;
   static int cached[kMaxDevices] = {};
   std::lock_guard<std::mutex> lock(mu);
@@ -482,8 +494,7 @@ sp_status seq_score(const sp_score_args* a, const TiledDev& dev_, hipStream_t st
   dev.seq_order = nullptr;
   if (a->B > 1) {  // (one sequence: nothing to order, and the host has seen that its length fits)
     int32_t* order = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(dev.group_scores) + seq_scores_bytes(a));
-    hipLaunchKernelGGL(seq_order_kernel, dim3(1), dim3(1024), 0, stream, a->B, a->d_cu_seqlens, order, a->d_lse,
-                       seq_max_keys(a), a->L, a->N * a->H);
+    launch_seq_order(a, order, seq_max_keys(a), stream);
     dev.seq_order = order;
   }
   const int R = seq_rows(a);
@@ -493,8 +504,7 @@ sp_status seq_score(const sp_score_args* a, const TiledDev& dev_, hipStream_t st
   const sp_status st = a->d == 64 ? (fp8 ? seq_by_mode<64, true>(dev, R, mean, stream) : seq_by_mode<64, false>(dev, R, mean, stream))
                                   : (fp8 ? seq_by_mode<128, true>(dev, R, mean, stream) : seq_by_mode<128, false>(dev, R, mean, stream));
   if (st != SP_OK) return st;
-  hipLaunchKernelGGL(seq_finish_kernel, dim3((unsigned)((dev.T + 63) / 64)), dim3(64 * kSeqFinishParts), 0, stream, dev);
-  return launch_status();
+  return launch_units_finish(dev, stream);
 }
 
 }  // namespace sp

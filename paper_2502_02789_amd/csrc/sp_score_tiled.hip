@@ -353,6 +353,7 @@ static bool keep_mode(const sp_score_args* a) {
 
 static size_t tiled_main_workspace_bytes(const sp_score_args* a) {
   if (seq_supported(a)) return seq_workspace_bytes(a);
+  if (wide_supported(a)) return wide_workspace_bytes(a);
   if (keep_mode(a)) return align_up(keep_bytes(a), 256);
   int lpg, groups;
   tiled_grouping(a, &lpg, &groups);
@@ -428,7 +429,7 @@ sp_status tiled_score(const sp_score_args* a, const ScoreDev& gen, void* extra, 
   dev.k_scale = a->d_k_scale;
   dev.seq_limit = 0;
   dev.seq_order = nullptr;
-  if (seq_supported(a)) {  // one pass over K, a workgroup per (sequence, layer group)
+  if (seq_supported(a) || wide_supported(a)) {  // one pass over K, a workgroup per (sequence, slab group)
     seq_grouping(a, &dev.slabs_per_group, &dev.n_groups, &dev.groups_per_layer);
     if (dev.lgG < 2) { dev.lgG = 2; dev.Gp = 4; }  // (one or two heads per KV head: padded to four on this path)
     dev.layers_per_group = 0;
@@ -441,7 +442,7 @@ sp_status tiled_score(const sp_score_args* a, const ScoreDev& gen, void* extra, 
     for (int l = 0; l < SP_MAX_LAYERS; ++l) dev.k[l] = gen.k[l];
     dev.rope_tiles = nullptr;
     dev.seq_limit = seq_max_keys(a);
-    return seq_score(a, dev, stream);
+    return seq_supported(a) ? seq_score(a, dev, stream) : wide_score(a, dev, stream);
   }
   const bool keep = keep_mode(a);
   dev.group_scores = keep ? nullptr : static_cast<float*>(extra);

@@ -494,11 +494,46 @@ struct TileWalker {
   }
 };
 
-// single-pass kernel for batches of short prompts (sp_score_seq.hip)
+// One unit of work of the single-pass batch kernels: sequence b for the slabs [s0, s1) of slab group grp (slab s =
+// KV head s % H_kv of layer s / H_kv).  Units are numbered with the longest sequences first (all groups of a
+// sequence next to each other).
+struct SeqUnit {
+  int k;  // position in this workgroup's list of units
+  int b, grp, seq0, M, s0, s1;
+};
+
+// Units are dealt out to the gridDim.x workgroups in rounds, the direction changing with every round
+// (workgroup j: units j, 2W-1-j, 2W+j, ...): with the sizes in descending order every workgroup gets
+// nearly the same number of keys, and no counter has to be shared.
+__device__ __forceinline__ bool seq_next_unit(const TiledDev& p, int k, SeqUnit* u) {
+  const int W = gridDim.x, n_units = p.B * p.n_groups;
+  for (;; ++k) {
+    const int idx = k * W + ((k & 1) ? W - 1 - (int)blockIdx.x : (int)blockIdx.x);
+    if (idx >= n_units) return false;
+    const int grp = idx % p.n_groups;
+    const int b = p.seq_order ? scalar_table(p.seq_order)[idx / p.n_groups] : idx / p.n_groups;  // (no table: batch order)
+    const int seq0 = scalar_table(p.cu)[b];
+    const int M = scalar_table(p.cu)[b + 1] - seq0;
+    const int s0 = grp * p.slabs_per_group;
+    const int s1 = min(p.L * p.H_kv, s0 + p.slabs_per_group);
+    // (no keys, or more than the kernel holds: nothing to do here, see seq_order_kernel and units_finish_kernel)
+    if (M <= 0 || M > p.seq_limit || s0 >= s1) continue;
+    u->k = k; u->b = b; u->grp = grp; u->seq0 = seq0; u->M = M; u->s0 = s0; u->s1 = s1;
+    return true;
+  }
+}
+
+// single-pass kernels for batches of short prompts: few query rows per KV head (sp_score_seq.hip) ...
 bool seq_supported(const sp_score_args* a);
 int seq_max_keys(const sp_score_args* a);
 void seq_grouping(const sp_score_args* a, int* slabs_per_group, int* n_groups, int* groups_per_layer);
 size_t seq_workspace_bytes(const sp_score_args* a);
 sp_status seq_score(const sp_score_args* a, const TiledDev& dev, hipStream_t stream);
+// ... and up to 32 of them (sp_score_wide.hip); what the two share
+size_t wide_workspace_bytes(const sp_score_args* a);
+sp_status wide_score(const sp_score_args* a, const TiledDev& dev, hipStream_t stream);
+int seq_cu_count();
+void launch_seq_order(const sp_score_args* a, int32_t* order, int limit, hipStream_t stream);
+sp_status launch_units_finish(const TiledDev& dev, hipStream_t stream);
 
 }  // namespace sp

@@ -1,0 +1,81 @@
+"""GPU parity of the single-pass kernel for short prompts with look-ahead (nine to 32 query rows per KV head, all
+logits of a sequence on chip) against the fp64 oracle, element by element (Sec. 3.2 equation, Sec. 3.2.2)."""
+import math
+
+import numpy as np
+import pytest
+
+from oracle import specprefill_oracle as orc
+from paper_2502_02789_amd import synth
+from tests import helpers as hp
+from tests.test_gpu_batch_single_pass import _check, _lens
+
+pytestmark = pytest.mark.gpu
+
+MODES = [orc.LAYER_MAX, orc.LAYER_MEAN]
+# empty, one key, the edges of 32- and 64-key tiles, waves without a tile, all eight waves with a ragged last one
+LENS = (0, 1, 31, 32, 33, 63, 64, 65, 127, 129, 255, 256, 257, 500, 512, 513, 1029, 1100)
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("shape", [
+    dict(H=8, H_kv=2, N=8, d=128),      # Llama-shaped draft, eight look-ahead steps: all 32 columns
+    dict(H=8, H_kv=2, N=8, d=64),
+    dict(H=6, H_kv=2, N=5, d=128),      # three heads padded to four, unused query slots
+    dict(H=4, H_kv=2, N=3, d=64),       # two heads padded to four
+    dict(H=16, H_kv=2, N=4, d=128),     # eight heads per KV head
+    dict(H=10, H_kv=2, N=3, d=64),      # five heads padded to eight
+])
+def test_batch_with_look_ahead(shape, mode):
+    w = synth.scaled(synth.workload(4), seqlens=LENS, L=4, salient_frac=0.02, salient_run=1, **shape)
+    inp = synth.make_qk(w)
+    _check(w, inp, mode, max_seqlen=1100)
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("longest", [2048, 2049, 2304, 2305, 3072, 3073])
+def test_edges_of_what_the_registers_hold(longest, d, mode):
+    """Up to 2304 keys (bf16, d = 128) or 2048 the running maximum over a unit's slabs is all in registers, up to 3072
+    partly in memory (units of one slab and of several); one more and the other kernels take over."""
+    for B_small, L in ((2, 4), (40, 8)):
+        w = synth.scaled(synth.workload(4), seqlens=(longest, longest - 31) + _lens(longest, B_small, 1, 90), L=L,
+                         H=8, H_kv=2, N=8, d=d, salient_frac=0.02, salient_run=1)
+        _check(w, synth.make_qk(w), mode, max_seqlen=longest)
+
+
+@pytest.mark.parametrize("mode", MODES)
+def test_valid_query_counts_pages_and_many_units(mode):
+    """Enough sequences that a workgroup walks over many units of several slabs."""
+    w = synth.scaled(synth.workload(4), seqlens=_lens(17, 80, 1, 400), L=12, H=8, H_kv=2, N=8, salient_frac=0.02, salient_run=1)
+    inp = synth.make_qk(w)
+    nv = np.random.default_rng(18).integers(1, 9, size=80).astype(np.int32)
+    _check(w, inp, mode, max_seqlen=400, n_valid=nv)
+    _check(w, inp, mode, max_seqlen=400, n_valid=nv, paged=16)
+    _check(w, inp, mode, max_seqlen=400, paged=8)
+    _check(w, inp, mode, max_seqlen=3000, paged=128)
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("n_keys", [1, 300, 2048, 3001])
+def test_one_prompt_with_look_ahead(n_keys, mode):
+    w = synth.scaled(synth.workload(3), seqlens=(n_keys,), L=8, N=8)
+    inp = synth.make_qk(w)
+    a = _check(w, inp, mode, max_seqlen=0, exclusive_device=True)
+    b = _check(w, inp, mode, max_seqlen=0, exclusive_device=False)
+    assert (a.view(np.uint32) == b.view(np.uint32)).all()   # the flag does not matter here
+    _check(w, inp, mode, max_seqlen=0, paged=16)
+
+
+def test_a_sequence_longer_than_the_kernel_holds_gets_nan_scores():
+    lens = _lens(10, 20, 50, 400)
+    w = synth.scaled(synth.workload(4), seqlens=lens[:9] + (3073,) + lens[10:], L=8, H=8, H_kv=2, N=8)
+    inp = synth.make_qk(w)
+    scale = 1.0 / math.sqrt(w.d)
+    want, _ = orc.token_importance(inp["q"], inp["k"], inp["cu_seqlens"], scale, orc.LAYER_MAX)
+    got, lse = hp.gpu_score(inp["q"], inp["k"], inp["cu_seqlens"], w.H_kv, scale, orc.LAYER_MAX, max_seqlen=400)
+    cu = np.asarray(inp["cu_seqlens"])
+    inside = np.zeros(len(got), dtype=bool)
+    inside[cu[9]:cu[10]] = True
+    assert np.isnan(got[inside]).all() and np.isnan(lse[:, 9]).all()
+    hp.assert_scores_close(got[~inside], want[~inside], "the other sequences")
