@@ -78,7 +78,7 @@ typedef enum { SP_K_BF16 = 0, SP_K_FP8_E4M3 = 1 } sp_k_dtype;
                                         Without the flag sp_score uses kernels that never wait for
                                         another workgroup (two passes over K or kept logits).
                                         If the promise is broken a bounded wait can expire; the
-                                        affected scores are then NaN (see sp_score_check and
+                                        call's scores are then NaN (see sp_score_check and
                                         sp_pool_select), never silently wrong. */
 #define SP_SCORE_WORKSPACE_KEPT 2u   /* The caller promises that args->d_workspace was last written by
                                         an sp_score call with the same shape fields (B, T, N, L, H,
@@ -192,13 +192,13 @@ SP_API sp_status sp_score_general(const sp_score_args* args, void* hip_stream);
 /* Optional post-check of the most recent sp_score call that used args->d_workspace.  The
  * single-pass kernels (SP_SCORE_EXCLUSIVE_DEVICE) exchange row statistics between workgroups
  * that must all be resident on the device at once.  Their waits are bounded: a workgroup whose
- * wait expired writes NaN for all of its tokens' scores and records the event in the workspace
- * instead of hanging.  This call SYNCHRONISES hip_stream (the only entry point that does), reads
+ * wait expired records the event in the workspace instead of hanging, and all of the call's scores
+ * become NaN.  This call SYNCHRONISES hip_stream (the only entry point that does), reads
  * that record and returns SP_ETIMEOUT if a wait expired, SP_OK otherwise.  Recovery: call
  * sp_score again without the flag (or sp_score_general). */
 SP_API sp_status sp_score_check(const sp_score_args* args, void* hip_stream);
 
-/* Upper bound on the polls one wave may spend waiting for other workgroups during one sp_score
+/* Upper bound on the polls a workgroup may spend waiting for other workgroups during one sp_score
  * call (process-wide, applies to later calls; default 65536, about 0.1 s).  0 makes every wait
  * give up at once, which turns every score of a single-pass call into NaN: that is how the
  * failure path is exercised without ever making a kernel hang.  Returns the previous value;

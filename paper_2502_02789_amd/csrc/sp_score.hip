@@ -5,9 +5,9 @@
 // This file holds the argument checks, the dispatcher and the GENERAL kernels, which accept
 // every shape the header allows (ragged batches, any G = H/H_kv <= 8, N <= 16, d in {64,128}).
 // They read the K cache twice (once for the row statistics, once for the probabilities) and
-// use plain fp32 FMAs.  The single-pass MFMA kernel for one long prompt lives in
-// sp_score_stream.hip, the two-pass MFMA kernels for ragged batches in sp_score_tiled.hip; the
-// dispatcher takes the first of the three that fits the shape.
+// use plain fp32 FMAs.  The single-pass MFMA kernels live in sp_score_seq.hip (few query rows, short prompts),
+// sp_score_wide.hip (up to 32 query rows, short prompts) and sp_score_wide_team.hip (one long prompt), the two-pass
+// MFMA kernels in sp_score_tiled.hip; the dispatcher takes the first that fits the shape.
 #include "sp_common.h"
 #include "sp_score_internal.h"
 
@@ -263,7 +263,7 @@ __global__ __launch_bounds__(256) void score_accum_kernel(const ScoreDev p) {
   }
 }
 
-// the status words (and, for the team kernel's layout, its epoch: sp_score_check then looks at word 1)
+// the status words and the epoch (sp_score_check then looks at word 1)
 __global__ void clear_word_kernel(uint32_t* word) { word[0] = word[1] = word[2] = word[3] = 0; }
 
 // ---------------------------------------------------------------------------------------
@@ -284,15 +284,9 @@ static int general_max_tiles(const sp_score_args* a) { return (int)(a->T / kTile
 
 // the single-pass kernels are taken only on the caller's promise of an otherwise idle device
 bool single_pass_wanted(const sp_score_args* a) {
-  // Few query rows per KV head and a prompt short enough for the batch kernel, which keeps a sequence's logits
-  // on chip and needs no exchange between workgroups: measured faster than the all-workgroup kernel up to 8K
-  // keys (one query, 32 layers, head dim 128; us): 2K keys 38 against 135, 4K 57 against 137, 8K 127 against 159.
+  // (the batch kernels keep a sequence's logits inside a workgroup and need no exchange at all)
   if (tiled_supported(a) && (seq_supported(a) || wide_supported(a))) return false;
-  return (a->flags & SP_SCORE_EXCLUSIVE_DEVICE) != 0 && (team_supported(a) || stream_supported(a));
-}
-// where the single-pass kernel that sp_score would pick keeps its "a wait expired" word
-static size_t single_pass_status_offset(const sp_score_args* a) {
-  return team_supported(a) ? team_status_offset(a) : stream_status_offset(a);
+  return (a->flags & SP_SCORE_EXCLUSIVE_DEVICE) != 0 && wide_team_supported(a);
 }
 
 size_t general_workspace_bytes(const sp_score_args* a, bool with_tiled) {
@@ -313,7 +307,7 @@ void launch_lse_combine(const ScoreDev& p, hipStream_t stream) {
 
 // these paths have no bounded waits: leave "no wait expired" where sp_score_check looks
 static void clear_stream_status(const sp_score_args* a, hipStream_t stream) {
-  const size_t status_off = single_pass_wanted(a) ? single_pass_status_offset(a) : 0;
+  const size_t status_off = single_pass_wanted(a) ? wide_team_status_offset(a) : 0;
   if (status_off)
     hipLaunchKernelGGL(clear_word_kernel, dim3(1), dim3(1), 0, stream,
                        reinterpret_cast<uint32_t*>(static_cast<char*>(a->d_workspace) + status_off));
@@ -405,9 +399,9 @@ extern "C" size_t sp_score_workspace_bytes(const sp_score_args* a) {
   // (sp_score_general uses the plain kernels), so their kept-logits buffer is not asked for
   const bool single = sp::single_pass_wanted(a);
   const size_t general = sp::general_workspace_bytes(a, /*with_tiled=*/!single);
-  const size_t stream = single ? std::max(sp::stream_workspace_bytes(a), sp::team_workspace_bytes(a)) : 0;
+  const size_t team = single ? sp::wide_team_workspace_bytes(a) : 0;
   // (sp_score_pool_select takes its logits' room from the same workspace)
-  return std::max(std::max(general, stream), sp::fused_workspace_bytes(a));
+  return std::max({general, team, sp::fused_workspace_bytes(a)});
 }
 
 static sp_status check_score_args(const sp_score_args* a) {
@@ -445,7 +439,7 @@ extern "C" sp_status sp_score(const sp_score_args* a, void* hip_stream) {
   const sp_status st = check_score_args(a);
   if (st != SP_OK) return st;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (sp::single_pass_wanted(a)) return sp::team_supported(a) ? sp::team_score(a, stream) : sp::stream_score(a, stream);
+  if (sp::single_pass_wanted(a)) return sp::wide_team_score(a, stream);
   return sp::general_score(a, stream, /*allow_mfma=*/true);
 }
 
@@ -454,14 +448,14 @@ extern "C" sp_status sp_score_check(const sp_score_args* a, void* hip_stream) {
   if (st != SP_OK) return st;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   if (hipStreamSynchronize(stream) != hipSuccess) return SP_ELAUNCH;
-  const size_t off = sp::single_pass_wanted(a) ? sp::single_pass_status_offset(a) : 0;
+  const size_t off = sp::single_pass_wanted(a) ? sp::wide_team_status_offset(a) : 0;
   if (off == 0) return SP_OK;
   uint32_t words[4] = {0, 0, 0, 0};  // (every single-pass workspace has 256 bytes at `off`)
   if (hipMemcpy(words, static_cast<const char*>(a->d_workspace) + off, sizeof(words), hipMemcpyDeviceToHost) !=
       hipSuccess)
     return SP_ELAUNCH;
-  // the team kernel keeps one status word per epoch parity and has moved on to the next epoch
-  const uint32_t word = sp::team_supported(a) ? words[(words[2] + 1u) & 1u] : words[0];
+  // there is one status word per epoch parity, and the call has moved on to the next epoch
+  const uint32_t word = words[(words[2] + 1u) & 1u];
   return word == 0 ? SP_OK : SP_ETIMEOUT;
 }
 

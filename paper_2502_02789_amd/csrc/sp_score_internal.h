@@ -82,18 +82,11 @@ bool seq_supported(const sp_score_args* a);
 // ... and with up to 32 of them (sp_score_wide.hip)
 bool wide_supported(const sp_score_args* a);
 
-// single-pass streaming kernel (sp_score_stream.hip)
-bool stream_supported(const sp_score_args* a);
-size_t stream_workspace_bytes(const sp_score_args* a);
-sp_status stream_score(const sp_score_args* a, hipStream_t stream);
-size_t stream_status_offset(const sp_score_args* a);
-
-// single-pass kernel with per-KV-head teams of workgroups (sp_score_team.hip): one prompt of up
-// to 32K keys, SP_LAYER_MAX
-bool team_supported(const sp_score_args* a);
-size_t team_workspace_bytes(const sp_score_args* a);
-sp_status team_score(const sp_score_args* a, hipStream_t stream);
-size_t team_status_offset(const sp_score_args* a);
+// single-pass kernel for one long prompt with small teams of workgroups (sp_score_wide_team.hip)
+bool wide_team_supported(const sp_score_args* a);
+size_t wide_team_workspace_bytes(const sp_score_args* a);
+sp_status wide_team_score(const sp_score_args* a, hipStream_t stream);
+size_t wide_team_status_offset(const sp_score_args* a);
 
 // single-launch scoring + selection of one short prompt (sp_fused.hip); 0 if the shape is not covered
 size_t fused_workspace_bytes(const sp_score_args* a);

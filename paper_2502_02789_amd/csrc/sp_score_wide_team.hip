@@ -1,0 +1,417 @@
+// Single-pass scorer for one long prompt: small teams of workgroups, each holding ALL logits of its keys for a slab.
+//
+// Same quantity as the other scoring kernels: row softmax of the stored queries against the prompt keys
+// (Sec. 3.2 equation of arXiv 2502.02789), max over heads, max/mean over layers, mean over queries (Sec. 3.2.2).
+// Stream, products, statistics and the fold over heads are those of sp_score_wide.hip (sp_wide_core.h).  There one
+// workgroup owns a whole prompt; a longer prompt is cut into P pieces of up to 2048 keys, and the P workgroups of a
+// team walk together over the team's (layer, KV head) slabs:
+//
+//   * per slab every member publishes ONE 128-byte line, the base-2 log-sum-exps of its keys for the 32 rows (agent
+//     scope); its first wave then reads the team's P lines (contiguous) until none is "empty" any more, folds them
+//     into the rows' log-sum-exps and hands those to the other waves through LDS;
+//   * a slab is 18 us of stream for a workgroup (2048 keys, d = 128) and the ring holds 5 us of it, so the exchange
+//     is short against a slab, and the teams, which never meet, drift apart: while one waits the others have the
+//     memory.  Where an item is one tile (bf16, d = 128) the next slab's first item is computed while the lines
+//     travel, its logits in registers of their own: 32K keys 350 -> 339 us, 128K 1378 -> 1352.  (Without any exchange,
+//     wrong results: 333 and 1248; with an exchange four times as often hidden behind three slabs of a quarter of
+//     the keys each, and the query tile fetched once per wave, as before: 349 and 1570.)
+//   * 256 / P teams take the slabs in runs; a team's maxima go out as one group of the result array, merged by the
+//     kernel that merges the units of short prompts.  Mean over layers: a team owns whole layers and adds their
+//     maxima up (or, with more teams than layers, a part of one layer).
+//
+// The lines exist twice: a call works in copy (epoch mod 2) and puts "empty" back into the other one as it publishes,
+// so the next call finds it clean; a small kernel sets that up in front of a call that cannot rely on the previous one
+// (no SP_SCORE_WORKSPACE_KEPT).  All workgroups must be resident together (SP_SCORE_EXCLUSIVE_DEVICE); every wait is
+// bounded, and an expired wait turns the call's scores into NaN.
+//
+// Bound by the HBM stream of K for bf16 caches (32 layers, 8 KV heads, d = 128, eight queries, before -> now: 32K keys
+// 349 -> 339 us = 6.3 TB/s, mean over layers 30011 keys 375 -> 336, 128K keys 1570 -> 1352, 9000 keys 168 -> 116;
+// 16 layers, d = 64, 8K keys 61 -> 41), by the waves' own work for 8-bit caches (32K keys 318 -> 232 us).
+// Tried: polling by every wave instead of one and a barrier 355 against 350 us, polls that read the die's own L2 451.
+#include <atomic>
+#include <mutex>
+
+#include "sp_wide_core.h"
+
+namespace sp {
+
+constexpr int kWideTeamWGs = 256;
+constexpr int kWideTeamTiles = 8;        // 32-key tiles per wave
+constexpr int kWideTeamKeys = kWideTeamTiles * 32 * kTiledWaves;
+constexpr int kWideTeamMaxPartners = 64;
+constexpr uint32_t kEmptyLine = 0xffffffffu;
+constexpr int kDefaultSpinBudget = 1 << 16;  // polls per workgroup and call before giving up (~0.1 s)
+static std::atomic<int> g_spin_budget{kDefaultSpinBudget};
+
+struct WideTeamDev : TiledDev {
+  int lgP, chunk;          // members of a team (a power of two), keys of a member
+  int sum;                 // units hold whole layers, whose maxima (as probabilities) are added up
+  int n_units;             // runs of slabs_per_group slabs; team t takes units t, t + teams, ...
+  int spin_budget;
+  uint32_t* lines;         // two copies of [slab][member][32]
+  size_t copy_words;
+  uint32_t* status;        // [epoch & 1] != 0: a wait of this call expired; [2]: epoch, calls since the last fill
+};
+
+// the lines' first copy "empty", status and epoch 0
+__global__ __launch_bounds__(256) void wide_team_fill_kernel(uint4* lines, size_t n_vec, uint32_t* status) {
+  const size_t stride = (size_t)gridDim.x * 256;
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n_vec; i += stride)
+    lines[i] = make_uint4(kEmptyLine, kEmptyLine, kEmptyLine, kEmptyLine);
+  if (blockIdx.x == 0 && threadIdx.x < 4) status[threadIdx.x] = 0;
+}
+
+template <int D, int LG, bool FP8, bool PAGED>
+__global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeamDev p) {
+  extern __shared__ __align__(1024) unsigned char smem[];
+  using W = WideKernel<D, LG, FP8, PAGED>;
+  constexpr int KEEP = W::KEEP, SUB = W::SUB, MAXT = kWideTeamTiles;
+  using vkeep = typename W::vkeep;
+  W w(p, smem);
+  const uint32_t lse_lds = (uint32_t)reinterpret_cast<uintptr_t>(smem) + W::kSmem;  // 32 row log-sum-exps
+  // The members of a team sit on one die where one has enough compute units (workgroups are dealt out to the eight dies
+  // in turn).
+  // (measured, whole call: 32K keys, 16 members, next to each other on one die 352 us, over all dies 363; 128K keys, 64
+  // members, on two dies 1457 us, over all dies 1390)
+  const int P = 1 << p.lgP, place = P > 32 ? (int)blockIdx.x : (int)(blockIdx.x & 7) * (kWideTeamWGs / 8) + (int)(blockIdx.x >> 3);
+  const int team = place >> p.lgP, member = place & (P - 1), teams = kWideTeamWGs >> p.lgP;
+  if (team >= p.n_units) return;
+  const uint32_t epoch = __builtin_amdgcn_readfirstlane(p.status[2]);  // (turned by the merge kernel)
+  uint32_t* const lines_cur = p.lines + (size_t)(epoch & 1u) * p.copy_words;
+  uint32_t* const lines_nxt = p.lines + (size_t)(~epoch & 1u) * p.copy_words;
+  if (blockIdx.x == 0 && threadIdx.x == 0) p.status[~epoch & 1u] = 0;  // the next call's status word
+  const int key0 = member * p.chunk;
+  const int M = max(0, min((int)p.T - key0, p.chunk));
+  const int nt = w.items_of(M);
+  const int n_slabs = p.L * p.H_kv;
+  int polls = p.spin_budget;
+  bool expired = polls <= 0;
+
+  int u = team, s = u * p.slabs_per_group, s_end = min(n_slabs, s + p.slabs_per_group);
+  int l = s / p.H_kv, g = s - l * p.H_kv;
+  w.ah = {w.slab_keys(l, g, 0), 0, key0, M, nt};
+  w.issue_queries(l, g, 0, 0);
+  if (w.ah.left > 0) w.issue_one();
+  if (w.ah.left > 0) w.issue_one();
+  if (w.sent == 2) wait_vmcnt<2 * kItemLoads>(); else wait_vmcnt<0>();  // the query tile
+  __builtin_amdgcn_s_barrier();
+
+  f32x16 held[MAXT];
+  vkeep run[MAXT];
+  // The first item of the next slab is computed while the lines of this one travel (its logits wait in registers of
+  // their own, so where an item is one tile).
+  constexpr bool EARLY = SUB == 1;
+  f32x16 spare[1];
+  bool early = false;  // the first item of the slab at hand is in spare[0], its statistics in (rm, rs)
+  float rm = -INFINITY, rs = 0.f;
+#pragma unroll
+  for (int t = 0; t < MAXT; ++t)
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k) run[t][k] = -INFINITY;
+  int buf = 0;
+  bool first_layer = true;  // of the unit
+#pragma unroll 1
+  for (;;) {
+    // the slab behind this one: of this unit or the team's next one
+    int nu = u, ns = s + 1, ns_end = s_end, nl = l, ng = g + 1;
+    if (ng == p.H_kv) { ng = 0; ++nl; }
+    if (ns == s_end) {
+      nu = u + teams;
+      ns = nu * p.slabs_per_group;
+      ns_end = min(n_slabs, ns + p.slabs_per_group);
+      nl = ns / p.H_kv;
+      ng = ns - nl * p.H_kv;
+    }
+    const bool more = nu < p.n_units;
+    w.nx.left = 0;
+    if (more) {
+      w.nx = {w.slab_keys(nl, ng, 0), 0, key0, M, nt};
+      w.issue_queries(nl, ng, 0, buf ^ 1);
+    }
+    w.begin_slab();
+    w.slab_scale(l, g);
+    if constexpr (EARLY) {
+      if (early) {
+        held[0] = spare[0];
+      } else {
+        rm = -INFINITY;
+        rs = 0.f;
+        if (nt > 0) w.template item_logits<0>(&held[0], nt, M, buf, rm, rs);
+      }
+      w.template slab_logits<MAXT, 1>(held, nt, M, buf, rm, rs);
+    } else {
+      rm = -INFINITY;
+      rs = 0.f;
+      w.slab_logits(held, nt, M, buf, rm, rs);
+    }
+    const float own = w.workgroup_lse(rm, rs, buf);
+    uint32_t* const line = lines_cur + ((size_t)s << (p.lgP + 5));
+    if (w.wave == 0) {
+      const int ln = W::lane_id();
+      if (ln < 32) {  // (-inf -- no key of the prompt in this workgroup -- is a value, not "empty")
+        store32_agent(line + member * 32 + ln, __float_as_uint(own));
+        lines_nxt[((size_t)s << (p.lgP + 5)) + member * 32 + ln] = kEmptyLine;
+      }
+    }
+    if constexpr (EARLY) {
+      early = more && nt > 0;
+      if (early) {
+        rm = -INFINITY;
+        rs = 0.f;
+        w.template item_logits<0>(&spare[0], nt, M, buf ^ 1, rm, rs);
+      }
+    }
+    if (w.wave == 0) {
+      const int ln = W::lane_id();
+      // Lane ln holds, of load i, rows 4 * (ln % 8) .. + 3 of member i * 8 + ln / 8 (lanes beyond the last member read
+      // nothing and get zeros).
+      const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(line, 0, (uint32_t)P * 128u, 0x00020000);
+      const int loads = P <= 8 ? 1 : P >> 3;
+      float m[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY}, z[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int i0 = 0; i0 < loads; i0 += 4) {  // four loads at a time: more registers are not free
+        u32x4 x[4];
+        while (!expired) {
+          bool empty = false;
+          asm volatile("" ::: "memory");  // (a new look at the lines every time)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            x[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, ln * 16 + (i0 + i) * 1024, 0, /*sc1*/ 16));
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            empty |= x[i].x == kEmptyLine || x[i].y == kEmptyLine || x[i].z == kEmptyLine || x[i].w == kEmptyLine;
+          if (!__any(empty)) break;
+          if (--polls <= 0) expired = true;
+          __builtin_amdgcn_s_sleep(2);
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          float mn = m[c];
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if ((i0 + i) * 8 + (ln >> 3) < P) mn = fmaxf(mn, __uint_as_float(x[i][c]));
+          const float ref = (mn == -INFINITY) ? 0.f : mn;
+          z[c] *= fast_exp2(m[c] - ref);
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if ((i0 + i) * 8 + (ln >> 3) < P) z[c] += fast_exp2(__uint_as_float(x[i][c]) - ref);
+          m[c] = mn;
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        float mx = fmaxf(m[c], __shfl_xor(m[c], 8, kWave));
+        mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));  // finite: the prompt is not empty
+        z[c] *= fast_exp2(m[c] - mx);
+        m[c] = mx;
+      }
+      u32x4 out;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        z[c] += __shfl_xor(z[c], 8, kWave);
+        z[c] += __shfl_xor(z[c], 16, kWave);
+        z[c] += __shfl_xor(z[c], 32, kWave);
+        out[c] = __float_as_uint(m[c] + __builtin_amdgcn_logf(z[c]));
+      }
+      if (ln < 8) lds_poke128(lse_lds + ln * 16, out);  // rows 4 * ln .. + 3
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+    __builtin_amdgcn_s_barrier();
+    const float lse2 = __uint_as_float(lds_peek(lse_lds + (W::lane_id() & 31) * 4));
+    if (p.lse_out && member == 0 && w.wave == 0) w.store_lse(l, g, 0, lse2);
+
+    // log2-probabilities; maximum over the heads of a group and over the slabs
+    wide_static_for<0, MAXT>([&](auto tc) __attribute__((always_inline)) {
+      constexpr int t = decltype(tc)::value;
+      if (t / SUB < nt) {
+        float y[KEEP];
+        w.fold_heads(held[t], -lse2, y);
+#pragma unroll
+        for (int k = 0; k < KEEP; ++k) run[t][k] = fmaxf(run[t][k], y[k]);
+      }
+    });
+    // The unit's result; where units hold whole layers (p.sum) each layer's maxima join the sum in the result array
+    // (once every H_kv slabs: registers for the sums would be a quarter of what the logits leave).
+    if (s + 1 == s_end || (p.sum && g == p.H_kv - 1)) {
+      const int q_n = W::lane_id() & (W::NS - 1);
+      const int64_t step = (int64_t)p.n_groups * p.N * 32;  // from tile to tile
+      float* const out = p.group_scores + ((int64_t)((key0 >> 5) + SUB * (w.wave + (nt - 1) * kTiledWaves)) * p.n_groups + u) * p.N * 32 +
+                         q_n * 32 + w.fold_key();
+      auto place_of = [&](int t) __attribute__((always_inline)) {
+        return reinterpret_cast<vkeep*>(out + (t % SUB - t / SUB * (SUB * kTiledWaves)) * step);
+      };
+      // (sub-tiles of the ragged item that lie beyond the prompt have no place in the result array)
+      auto live = [&](int t) __attribute__((always_inline)) {
+        return t / SUB < nt && (SUB == 1 || t >= SUB || (w.wave + (nt - 1) * kTiledWaves) * W::KPI + t % SUB * 32 < M);
+      };
+      if (p.sum) {
+#pragma unroll
+        for (int t = 0; t < MAXT; ++t)
+#pragma unroll
+          for (int k = 0; k < KEEP; ++k) run[t][k] = fast_exp2(run[t][k]);
+        if (!first_layer && q_n < p.N) {
+#pragma unroll
+          for (int t0 = 0; t0 < MAXT; t0 += 4) {  // (four tiles' loads at a time)
+            vkeep old[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (live(t0 + i)) old[i] = *place_of(t0 + i);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (live(t0 + i)) run[t0 + i] += old[i];
+          }
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < MAXT; ++t) {
+        if (q_n < p.N && live(t)) __builtin_nontemporal_store(run[t], place_of(t));
+#pragma unroll
+        for (int k = 0; k < KEEP; ++k) run[t][k] = -INFINITY;
+      }
+      first_layer = s + 1 == s_end;
+    }
+    w.end_slab();
+    if (!more) break;
+    u = nu; s = ns; s_end = ns_end; l = nl; g = ng;
+    buf ^= 1;
+  }
+  if (w.wave == 0 && expired && W::lane_id() == 0) atomicOr(p.status + (epoch & 1u), 1u);
+  wait_vmcnt<0>();
+}
+
+// ---------------------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------------------
+struct WideTeamPlan {
+  bool ok;
+  int lgP, chunk, per, n_units, gpl;  // gpl > 0: units are parts of layers whose maxima the merge adds up
+  bool sum;
+  size_t copy_bytes, result_bytes;
+};
+
+static WideTeamPlan make_wide_team_plan(const sp_score_args* a) {
+  WideTeamPlan pl = {};
+  if (a->B != 1 || a->rope_theta > 0.f || a->T <= 0 || a->T > (int64_t)kWideTeamMaxPartners * kWideTeamKeys) return pl;
+  if (a->H / a->H_kv > 8 || (a->N << wide_lg(a)) > 32) return pl;
+  if (a->k_dtype == SP_K_FP8_E4M3 && a->d_block_table && a->page_size < (a->d == 64 ? 16 : 8)) return pl;
+  if (a->k_token_stride > (INT32_MAX / 256)) return pl;  // (a ring slot's keys must span less than 2 GiB)
+  const int slabs = a->L * a->H_kv;
+  if (slabs < 8) return pl;
+  int lgP = 1;
+  while (((int64_t)kWideTeamKeys << lgP) < a->T) ++lgP;
+  // (fewer slabs than teams: more members per team instead, as long as each still has a wave's worth of keys)
+  while ((kWideTeamWGs >> lgP) > slabs && (1 << lgP) < kWideTeamMaxPartners) ++lgP;
+  const int P = 1 << lgP, teams = kWideTeamWGs >> lgP;
+  pl.lgP = lgP;
+  pl.chunk = (int)(((a->T + P - 1) / P + 255) / 256 * 256);
+  if (a->layer_reduce == SP_LAYER_MEAN) {
+    if (a->L >= teams) {  // whole layers, one run per team
+      pl.sum = true;
+      pl.per = (a->L + teams - 1) / teams * a->H_kv;
+    } else {              // the largest part of a layer that still gives every team one
+      int per = 1;
+      for (int cand = a->H_kv; cand >= 1; --cand)
+        if (a->H_kv % cand == 0 && a->L * (a->H_kv / cand) >= teams) { per = cand; break; }
+      pl.per = per;
+      pl.gpl = a->H_kv / per;
+    }
+  } else {
+    pl.per = (slabs + teams - 1) / teams;
+  }
+  pl.n_units = (slabs + pl.per - 1) / pl.per;
+  pl.copy_bytes = (size_t)slabs * P * 128;
+  pl.result_bytes = align_up(sizeof(float) * 32 * (size_t)pl.n_units * a->N * wide_tiles(a), 256);
+  pl.ok = true;
+  return pl;
+}
+
+bool wide_team_supported(const sp_score_args* a) { return make_wide_team_plan(a).ok && seq_cu_count() >= kWideTeamWGs; }
+size_t wide_team_workspace_bytes(const sp_score_args* a) {
+  const WideTeamPlan pl = make_wide_team_plan(a);
+  return pl.ok ? align_up(2 * pl.copy_bytes, 256) + pl.result_bytes + 256 : 0;
+}
+size_t wide_team_status_offset(const sp_score_args* a) {
+  const WideTeamPlan pl = make_wide_team_plan(a);
+  return pl.ok ? align_up(2 * pl.copy_bytes, 256) + pl.result_bytes : 0;
+}
+
+template <int D, int LG, bool FP8, bool PAGED>
+static sp_status launch_wide_team(const WideTeamDev& dev, hipStream_t stream) {
+  auto kernel = wide_team_kernel<D, LG, FP8, PAGED>;
+  constexpr int smem = WideKernel<D, LG, FP8, PAGED>::kSmem + 128;
+  // once per kernel and device, under a lock: allow the large dynamic LDS size and make sure the whole grid can be
+  // resident at once (one workgroup per compute unit)
+  static std::mutex mu;
+  static bool prepared[kMaxDevices] = {};
+  {
+    std::lock_guard<std::mutex> lock(mu);
+    const int slot = current_device();
+    if (!prepared[slot]) {
+      int per_cu = 0;
+      if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess ||
+          hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel), kTiledThreads, smem) != hipSuccess ||
+          per_cu < 1)
+        return SP_ELAUNCH;
+      prepared[slot] = true;
+    }
+  }
+  hipLaunchKernelGGL(kernel, dim3(kWideTeamWGs), dim3(kTiledThreads), smem, stream, dev);
+  return launch_status();
+}
+template <int D, int LG, bool FP8>
+static sp_status wide_team_by_pages(const WideTeamDev& dev, hipStream_t stream) {
+  return dev.block_table ? launch_wide_team<D, LG, FP8, true>(dev, stream) : launch_wide_team<D, LG, FP8, false>(dev, stream);
+}
+template <int D>
+static sp_status wide_team_by_kind(const sp_score_args* a, const WideTeamDev& dev, hipStream_t stream) {
+  if (a->k_dtype == SP_K_FP8_E4M3)
+    return dev.lgG == 2 ? wide_team_by_pages<D, 2, true>(dev, stream) : wide_team_by_pages<D, 3, true>(dev, stream);
+  return dev.lgG == 2 ? wide_team_by_pages<D, 2, false>(dev, stream) : wide_team_by_pages<D, 3, false>(dev, stream);
+}
+
+sp_status wide_team_score(const sp_score_args* a, hipStream_t stream) {
+  const WideTeamPlan pl = make_wide_team_plan(a);
+  if (!pl.ok) return SP_EUNSUPPORTED;
+  WideTeamDev dev = {};
+  dev.B = 1; dev.N = a->N; dev.L = a->L; dev.H = a->H; dev.H_kv = a->H_kv; dev.G = a->H / a->H_kv;
+  dev.lgG = wide_lg(a);
+  dev.Gp = 1 << dev.lgG;
+  dev.layer_reduce = a->layer_reduce;
+  dev.scale = a->scale;
+  dev.c = a->scale * 1.4426950408889634f;
+  dev.ts = a->k_token_stride; dev.hs = a->k_head_stride; dev.T = a->T;
+  dev.q = static_cast<const uint16_t*>(a->d_q);
+  dev.cu = a->d_cu_seqlens; dev.n_valid = a->d_n_valid;
+  dev.scores = a->d_scores; dev.lse_out = a->d_lse;
+  dev.slabs_per_group = pl.per; dev.n_groups = dev.n_units = pl.n_units; dev.groups_per_layer = pl.gpl;
+  dev.block_table = a->d_block_table;
+  while (a->d_block_table && (1 << dev.lg_page) < a->page_size) ++dev.lg_page;
+  dev.blocks_per_seq = a->blocks_per_seq;
+  dev.page_stride = a->k_page_stride;
+  dev.k_scale = a->d_k_scale;
+  for (int l = 0; l < a->L; ++l) dev.k[l] = static_cast<const uint16_t*>(a->k_layers[l]);
+  dev.lgP = pl.lgP; dev.chunk = pl.chunk; dev.sum = pl.sum;
+  dev.spin_budget = g_spin_budget.load(std::memory_order_relaxed);
+  char* ws = static_cast<char*>(a->d_workspace);
+  dev.lines = reinterpret_cast<uint32_t*>(ws);
+  dev.copy_words = pl.copy_bytes / 4;
+  dev.group_scores = reinterpret_cast<float*>(ws + align_up(2 * pl.copy_bytes, 256));
+  dev.status = reinterpret_cast<uint32_t*>(ws + wide_team_status_offset(a));
+  if (!(a->flags & SP_SCORE_WORKSPACE_KEPT)) {
+    const size_t n_vec = pl.copy_bytes / 16;
+    hipLaunchKernelGGL(wide_team_fill_kernel, dim3((unsigned)std::min<size_t>((n_vec + 255) / 256, 1024)), dim3(256), 0, stream,
+                       reinterpret_cast<uint4*>(ws), n_vec, dev.status);
+    if (hipGetLastError() != hipSuccess) return SP_ELAUNCH;
+  }
+  const sp_status st = a->d == 64 ? wide_team_by_kind<64>(a, dev, stream) : wide_team_by_kind<128>(a, dev, stream);
+  if (st != SP_OK) return st;
+  return launch_wide_finish(dev, (unsigned)wide_tiles(a), dev.status, stream);
+}
+
+}  // namespace sp
+
+extern "C" int32_t sp_set_wait_budget(int32_t polls) {
+  if (polls < 0) return sp::g_spin_budget.load(std::memory_order_relaxed);
+  return sp::g_spin_budget.exchange(polls, std::memory_order_relaxed);
+}

@@ -1,0 +1,77 @@
+"""GPU parity of the single-pass kernel for one long prompt (small teams of workgroups exchange row statistics;
+SP_SCORE_EXCLUSIVE_DEVICE) against the fp64 oracle, element by element (Sec. 3.2 equation, Sec. 3.2.2), at the edges
+of its cut into members, teams and units."""
+import math
+
+import numpy as np
+import pytest
+
+from oracle import specprefill_oracle as orc
+from paper_2502_02789_amd import synth
+from tests import helpers as hp
+from tests import test_gpu_fp8_cache as fp8
+from tests.test_gpu_batch_single_pass import _check
+
+pytestmark = pytest.mark.gpu
+
+MODES = [orc.LAYER_MAX, orc.LAYER_MEAN]
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("shape", [
+    dict(tokens=3073, L=4, H=32, H_kv=8, N=8, d=128),    # the shortest prompt: more members than the keys need, ...
+    dict(tokens=3100, L=1, H=32, H_kv=8, N=8, d=64),     # ... so few slabs that most members have no keys at all
+    dict(tokens=4097, L=32, H=8, H_kv=4, N=5, d=64),     # two heads padded to four, a member with one key
+    dict(tokens=4096, L=24, H=48, H_kv=16, N=8, d=64),   # three heads padded to four, several slabs per unit, full members
+    dict(tokens=6150, L=8, H=64, H_kv=8, N=4, d=128),    # eight heads per KV head
+    dict(tokens=5000, L=6, H=40, H_kv=8, N=3, d=64),     # five heads padded to eight, units that do not divide evenly
+    dict(tokens=9000, L=3, H=32, H_kv=8, N=1, d=128),    # one query
+])
+def test_one_long_prompt(shape, mode):
+    shape = dict(shape)
+    w = synth.scaled(synth.workload(3), seqlens=(shape.pop("tokens"),), salient_run=1, **shape)
+    inp = synth.make_qk(w)
+    _check(w, inp, mode, max_seqlen=0, exclusive_device=True)
+    if w.T == 4097:
+        for page in (8, 64):
+            _check(w, inp, mode, max_seqlen=0, paged=page)
+
+
+def test_valid_query_count_and_head_major_cache():
+    w = synth.scaled(synth.workload(3), seqlens=(7001,), L=5, H=16, H_kv=4, N=8, salient_run=1)
+    inp = synth.make_qk(w)
+    scale = 1.0 / math.sqrt(w.d)
+    nv = np.array([3], dtype=np.int32)
+    want, _ = orc.token_importance(inp["q"], inp["k"], inp["cu_seqlens"], scale, orc.LAYER_MAX, nv)
+    for head_major in (False, True):
+        got, _ = hp.gpu_score(inp["q"], inp["k"], inp["cu_seqlens"], w.H_kv, scale, orc.LAYER_MAX, n_valid=nv, head_major=head_major)
+        hp.assert_scores_close(got, want, f"head_major={head_major}")
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("d, paged", [(64, 0), (128, 0), (64, 16), (128, 8)])
+def test_8_bit_cache(d, paged, mode):
+    w = synth.scaled(synth.workload(3), seqlens=(5003,), L=4, H=32, H_kv=8, N=8, d=d, salient_run=1)
+    fp8._check(w, mode, False, paged=paged)
+
+
+@pytest.mark.parametrize("mode", MODES)
+def test_kept_workspace_and_changed_inputs_over_consecutive_calls(mode):
+    """Both copies of the exchange lines in turn, on other keys each time."""
+    import torch
+    from paper_2502_02789_amd import device as dev
+    w = synth.scaled(synth.workload(3), seqlens=(4500,), L=4, H=32, H_kv=8, N=8, d=64, salient_run=1)
+    inp = synth.make_qk(w)
+    scale = 1.0 / math.sqrt(w.d)
+    ks = [dev.bf16_from_bits(k) for k in inp["k"]]
+    s = dev.Scorer(dev.bf16_from_bits(inp["q"]), ks, torch.from_numpy(np.asarray(inp["cu_seqlens"], dtype=np.int32)).cuda(),
+                   H_kv=w.H_kv, scale=scale, layer_reduce=mode, keep_workspace=True)
+    for turn in range(5):
+        keys = [np.roll(k, 37 * turn, axis=0) for k in inp["k"]]
+        for t, k in zip(ks, keys):
+            t.copy_(dev.bf16_from_bits(k))
+        want, _ = orc.token_importance(inp["q"], keys, inp["cu_seqlens"], scale, mode)
+        s.scores.fill_(float("nan"))
+        s.run()
+        s.check()
+        hp.assert_scores_close(s.scores.cpu().numpy(), want, f"call {turn}")
