@@ -270,16 +270,15 @@ __global__ __launch_bounds__(1024) void seq_order_kernel(int B, const int32_t* _
 }
 
 // Merge of the units' partial results and the average over the valid queries (Sec. 3.2.2).  A workgroup takes TOK
-// tokens; its 1024 / TOK groups of TOK threads take every so-many-th slab group (one TOK * 4 byte read per group and
-// query), the lanes of a wave fold by shuffles, the sixteen waves' results meet in LDS.  Sequences the scoring
+// tokens; its 64 * WAVES / TOK groups of TOK threads take every so-many-th slab group (one TOK * 4 byte read per group and
+// query), the lanes of a wave fold by shuffles, the waves' results meet in LDS.  Sequences the scoring
 // kernel left out (longer than it holds) get NaN.  Bound by the latency of the reads for one short prompt, whose
 // few tokens make few workgroups of 64 (2K tokens, 256 groups of one query: 7.6 us): narrower workgroups there.
-constexpr int kFinishWaves = 16;
-template <int NQ, int TOK>
-__global__ __launch_bounds__(64 * kFinishWaves) void units_finish_kernel(const TiledDev p) {
-  __shared__ float red[kFinishWaves][NQ][TOK];
+template <int NQ, int TOK, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void units_finish_kernel(const TiledDev p) {
+  __shared__ float red[WAVES][NQ][TOK];
   __shared__ float prob[NQ][TOK];
-  constexpr int kParts = 64 * kFinishWaves / TOK;
+  constexpr int kParts = 64 * WAVES / TOK;
   const int k = threadIdx.x % TOK, part = threadIdx.x / TOK;
   const int64_t tok = (int64_t)blockIdx.x * TOK + k;
   const bool inside = tok < p.T;
@@ -322,11 +321,11 @@ __global__ __launch_bounds__(64 * kFinishWaves) void units_finish_kernel(const T
 #pragma unroll
     for (int n = 0; n < NQ; ++n) red[threadIdx.x >> 6][n][k] = v[n];
   __syncthreads();
-  if (threadIdx.x < NQ * TOK) {
-    const int n = threadIdx.x / TOK;
+  for (int i = threadIdx.x; i < NQ * TOK; i += 64 * WAVES) {
+    const int n = i / TOK;
     float x = red[0][n][k];
 #pragma unroll
-    for (int q = 1; q < kFinishWaves; ++q) x = mean ? x + red[q][n][k] : fmaxf(x, red[q][n][k]);
+    for (int q = 1; q < WAVES; ++q) x = mean ? x + red[q][n][k] : fmaxf(x, red[q][n][k]);
     prob[n][k] = mean ? x : fast_exp2(x);
   }
   __syncthreads();
@@ -347,14 +346,15 @@ __global__ __launch_bounds__(64 * kFinishWaves) void units_finish_kernel(const T
 
 template <int NQ>
 static sp_status finish_by_tokens(const TiledDev& dev, hipStream_t stream) {
-  // tokens per workgroup: 64 where that makes at least two workgroups per compute unit, else 16
-  if (dev.T >= 64 * 512) hipLaunchKernelGGL((units_finish_kernel<NQ, 64>), dim3((unsigned)((dev.T + 63) / 64)), dim3(64 * kFinishWaves), 0, stream, dev);
-  else hipLaunchKernelGGL((units_finish_kernel<NQ, 16>), dim3((unsigned)((dev.T + 15) / 16)), dim3(64 * kFinishWaves), 0, stream, dev);
+  // Tokens per workgroup: 64 where that makes at least two workgroups per compute unit, else 16; waves: sixteen where
+  // there are that many groups for each, else four (64 prompts, 168K tokens in eight groups: 12 us with sixteen).
+  if (dev.T < 64 * 512) hipLaunchKernelGGL((units_finish_kernel<NQ, 16, 16>), dim3((unsigned)((dev.T + 15) / 16)), dim3(1024), 0, stream, dev);
+  else if (dev.n_groups > 64) hipLaunchKernelGGL((units_finish_kernel<NQ, 64, 16>), dim3((unsigned)((dev.T + 63) / 64)), dim3(1024), 0, stream, dev);
+  else hipLaunchKernelGGL((units_finish_kernel<NQ, 64, 4>), dim3((unsigned)((dev.T + 63) / 64)), dim3(256), 0, stream, dev);
   return launch_status();
 }
-sp_status launch_units_finish(const TiledDev& dev, hipStream_t stream) {  // (at most eight queries on these paths)
-  return dev.N == 1 ? finish_by_tokens<1>(dev, stream) : dev.N == 2 ? finish_by_tokens<2>(dev, stream)
-       : dev.N <= 4 ? finish_by_tokens<4>(dev, stream) : finish_by_tokens<8>(dev, stream);
+static sp_status launch_units_finish(const TiledDev& dev, hipStream_t stream) {  // (at most two queries on this path)
+  return dev.N == 1 ? finish_by_tokens<1>(dev, stream) : finish_by_tokens<2>(dev, stream);
 }
 
 void launch_seq_order(const sp_score_args* a, int32_t* order, int limit, hipStream_t stream) {

@@ -5,8 +5,8 @@
 //
 // All arithmetic is fp64 on the fp32 input scores, summed in index order with adds and
 // divides only, so the chunk scores (and therefore the kept set) do not depend on how the
-// work is split over lanes.  Top-k is an 8-pass radix select on order-preserving 64-bit
-// keys followed by an ordered scan that resolves equal scores to the lower chunk index.
+// work is split over lanes.  Top-k is a radix select on order-preserving 64-bit keys held in registers, followed by
+// an ordered count that resolves equal scores to the lower chunk index.
 #include <mutex>
 
 // the k formula below must stay a separate multiply and subtract
@@ -15,6 +15,21 @@
 #include "sp_select_core.h"
 
 namespace sp {
+
+// Where the chunks of sequence b sit in cs and chunk_off: without a table at cu[b] / chunk + b (every sequence has room
+// for its chunks that way, T / chunk + B places in all); with one (the caller wants the chunk scores, which are
+// numbered without gaps) where it says.
+__device__ __forceinline__ int chunk_base(const SelDev& p, int b) {
+  return p.table ? p.cu_chunks[b] : p.cu[b] / p.chunk + b;
+}
+__device__ __forceinline__ int sequence_of_chunk(const SelDev& p, int j) {
+  int lo = 0, hi = p.B;  // the largest b whose first chunk is <= j
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (chunk_base(p, mid) <= j) lo = mid; else hi = mid;
+  }
+  return lo;
+}
 
 __global__ __launch_bounds__(1024) void chunk_table_kernel(const SelDev p) {
   block_prefix_table(p.B, [&](int b) { return (p.cu[b + 1] - p.cu[b] + p.chunk - 1) / p.chunk; }, p.cu_chunks);
@@ -27,53 +42,105 @@ __device__ __forceinline__ double shfl_f64(double v, int src) {
   return __hiloint2double(hi, lo);
 }
 
-// One wave serves a group of 64/chunk consecutive chunks (one chunk when chunk >= 64).
-// Lanes pool one token each; every lane then adds its chunk's pooled values in token order.
-template <bool SINGLE>  // SINGLE: one sequence of T tokens, no chunk table
-__global__ __launch_bounds__(256) void pool_chunk_kernel(const SelDev p) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int n_chunks = SINGLE ? (p.T + p.chunk - 1) / p.chunk : p.cu_chunks[p.B];
-  const bool wide = p.chunk >= kWave;
-  const int cpw = wide ? 1 : kWave / p.chunk;          // chunks per wave
-  const int seg_len = wide ? kWave : p.chunk;          // tokens of a chunk handled per step
-  const int n_seg = (p.chunk + seg_len - 1) / seg_len;
-  const int n_groups = (n_chunks + cpw - 1) / cpw;
-  const int q = wide ? 0 : lane / p.chunk;             // chunk of the group this lane serves
-  const int t_in = lane - q * seg_len;
-  for (int grp = blockIdx.x * 4 + wave; grp < n_groups; grp += gridDim.x * 4) {
-    const int j = grp * cpw + q;
-    const bool live = (q < cpw) && (j < n_chunks);
+// tokens from chunk place j's start to the end of its sequence (<= 0: a place without a chunk)
+template <bool SINGLE>
+__device__ __forceinline__ int chunk_tokens(const SelDev& p, int j, int n_chunks) {
+  if (j >= n_chunks) return 0;
+  if (SINGLE) return p.T - j * p.chunk;
+  const int b = sequence_of_chunk(p, j);
+  return p.cu[b + 1] - p.cu[b] - (j - chunk_base(p, b)) * p.chunk;
+}
+
+// A workgroup serves 256 / chunk chunks (chunk <= 256): a thread pools one token (window sums in index order, the
+// window's loads all in flight at once), then one lane per chunk adds the chunk's pooled values in token order.
+// Bound by its dependent steps (loads, window, chunk sum), not by any throughput: 5.1 us before for 256 and 1024 chunks
+// of 32 tokens with the chunk sums by shuffles, one value after the other.
+constexpr int kPoolThreads = 256;
+template <bool SINGLE>  // SINGLE: one sequence of T tokens
+__global__ __launch_bounds__(kPoolThreads) void pool_chunk_kernel(const SelDev p) {
+  __shared__ double pooled[2 * kPoolThreads];
+  const int cpb = kPoolThreads / p.chunk;              // chunks per workgroup
+  const int n_chunks = SINGLE ? (p.T + p.chunk - 1) / p.chunk : p.table ? p.cu_chunks[p.B] : p.T / p.chunk + p.B;
+  const int t = threadIdx.x;
+  if (!SINGLE && !p.table && blockIdx.x == 0 && t == 0) *p.arrived = 0;  // (for the selection kernel behind this one)
+  const int q = t / p.chunk, t_in = t - q * p.chunk;
+  for (int j0 = blockIdx.x * cpb; j0 < n_chunks; j0 += gridDim.x * cpb) {
+    const int j = j0 + q;
     int lo = 0, hi = 0, s0 = 0, s1 = 0;
-    if (live) {
+    if (q < cpb && j < n_chunks) {
       if (SINGLE) {
         hi = p.T;
         s0 = j * p.chunk;
       } else {
-        const int b = upper_segment(p.cu_chunks, p.B, j);
+        const int b = sequence_of_chunk(p, j);
         lo = p.cu[b];
         hi = p.cu[b + 1];
-        s0 = lo + (j - p.cu_chunks[b]) * p.chunk;
+        s0 = lo + (j - chunk_base(p, b)) * p.chunk;
       }
-      s1 = min(s0 + p.chunk, hi);
+      s1 = min(s0 + p.chunk, hi);                       // (<= s0: a place without a chunk)
     }
+    const int i = s0 + t_in;
+    if (i < s1) {
+      const int a = max(lo, i - p.radius), e = min(hi - 1, i + p.radius);
+      double sum = 0.0;
+      for (int x0 = a; x0 <= e; x0 += 8) {              // eight loads at a time; adding zeros changes no sum
+        float v[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) v[x] = p.scores[min(x0 + x, e)];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) sum += x0 + x <= e ? (double)v[x] : 0.0;
+      }
+      pooled[q * (p.chunk + 1) + t_in] = sum / (double)(e - a + 1);
+    }
+    __syncthreads();
+    if (t < cpb) {                                      // lane t: chunk j0 + t
+      const int len = min(p.chunk, chunk_tokens<SINGLE>(p, j0 + t, n_chunks));
+      if (len > 0) {
+        double tot = 0.0;
+#pragma unroll 8
+        for (int x = 0; x < len; ++x) tot += pooled[t * (p.chunk + 1) + x];
+        const double mean = tot / (double)len;
+        p.cs[j0 + t] = mean;
+        if (p.chunk_scores_out) p.chunk_scores_out[j0 + t] = (float)mean;
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// The same for longer chunks: a wave per chunk, 64 tokens at a time, every lane adding the values in token order.
+template <bool SINGLE>
+__global__ __launch_bounds__(256) void pool_long_chunk_kernel(const SelDev p) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int n_chunks = SINGLE ? (p.T + p.chunk - 1) / p.chunk : p.table ? p.cu_chunks[p.B] : p.T / p.chunk + p.B;
+  if (!SINGLE && !p.table && blockIdx.x == 0 && threadIdx.x == 0) *p.arrived = 0;
+  for (int j = blockIdx.x * 4 + wave; j < n_chunks; j += gridDim.x * 4) {
+    int lo = 0, hi = p.T, s0 = j * p.chunk;
+    if (!SINGLE) {
+      const int b = sequence_of_chunk(p, j);
+      lo = p.cu[b];
+      hi = p.cu[b + 1];
+      s0 = lo + (j - chunk_base(p, b)) * p.chunk;
+    }
+    const int s1 = min(s0 + p.chunk, hi);
+    if (s1 <= s0) continue;
     double tot = 0.0;
-    for (int seg = 0; seg < n_seg; ++seg) {
-      const int i = s0 + seg * seg_len + t_in;
-      double pooled = 0.0;
-      if (live && i < s1) {
+    for (int seg = s0; seg < s1; seg += kWave) {
+      const int i = seg + lane;
+      double v = 0.0;
+      if (i < s1) {
         const int a = max(lo, i - p.radius), e = min(hi - 1, i + p.radius);
         double sum = 0.0;
         for (int x = a; x <= e; ++x) sum += (double)p.scores[x];
-        pooled = sum / (double)(e - a + 1);
+        v = sum / (double)(e - a + 1);
       }
-      const int base = q * seg_len;
-      const int have = min(seg_len, s1 - (s0 + seg * seg_len));  // tokens of this chunk in this step
-      for (int t = 0; t < seg_len; ++t) {                         // uniform trip count
-        const double v = shfl_f64(pooled, base + t);
-        if (t < have) tot += v;
+      const int have = min(kWave, s1 - seg);
+      for (int x = 0; x < kWave; ++x) {  // uniform trip count
+        const double y = shfl_f64(v, x);
+        if (x < have) tot += y;
       }
     }
-    if (live && t_in == 0) {
+    if (lane == 0) {
       const double mean = tot / (double)(s1 - s0);
       p.cs[j] = mean;
       if (p.chunk_scores_out) p.chunk_scores_out[j] = (float)mean;
@@ -81,66 +148,119 @@ __global__ __launch_bounds__(256) void pool_chunk_kernel(const SelDev p) {
   }
 }
 
-// One workgroup per sequence.
-__global__ __launch_bounds__(1024) void select_kernel(const SelDev p) {
-  __shared__ int hist[3 * 256];
-  __shared__ int sh[16];
-  const int b = blockIdx.x, t = threadIdx.x;
-  const int c0 = p.cu_chunks[b];
-  const int n = p.cu_chunks[b + 1] - c0;
-  const int lo = p.cu[b], hi = p.cu[b + 1];
-  if (n == 0) {
-    if (t == 0) p.seq_keep[b] = 0;
-    return;
-  }
-  const double scaled = p.keep_rate * (double)n;
-  const double kd = ceil(scaled - 1e-9);
-  const int k = (int)fmin((double)n, fmax(1.0, kd));
-  const double* cs = p.cs + c0;
+// cu_keep from the sequences' counts, by one workgroup of 1024 threads
+__device__ __forceinline__ void scan_seq_keep(const SelDev& p) {
+  auto count = [&](int b) { return __hip_atomic_load(p.seq_keep + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  int bad = 0;
+  for (int b = threadIdx.x; b < p.B; b += 1024) bad |= count(b) < 0 ? 1 : 0;
+  bad = __syncthreads_or(bad);
+  block_prefix_table(p.B, [&](int b) { return max(count(b), 0); }, p.cu_keep);
+  if (bad)  // some sequence had invalid scores: no keep set is handed on
+    for (int b = 1 + threadIdx.x; b <= p.B; b += 1024) p.cu_keep[b] = -1;
+}
 
-  // invalid scores (NaN: the scorer's mark for "a device-side wait expired") are reported in band:
-  // a negative count here turns every cu_keep entry after the first into -1
-  {
-    int bad = 0;
-    for (int j = t; j < n; j += 1024) bad |= is_nan_bits(cs[j]) ? 1 : 0;
-    if (__syncthreads_or(bad)) {
-      for (int j = t; j < n; j += 1024) p.chunk_off[c0 + j] = -1;
-      if (t == 0) p.seq_keep[b] = -1;
-      return;
-    }
-  }
-
-  // radix select: after the loop `prefix` is the key of the k-th largest chunk score and
-  // `need` is how many chunks with exactly that score are still to be taken
-  uint64_t prefix;
-  int need;
-  radix_select_kth([&](int j) { return order_key(cs[j]); }, n, k, hist, &prefix, &need);
-
-  // ordered pass: thread t owns chunks [j0, j1) in index order
-  const int per = (n + 1023) / 1024;
-  const int j0 = min(n, t * per), j1 = min(n, j0 + per);
-  int eq = 0;
-  for (int j = j0; j < j1; ++j) eq += (order_key(cs[j]) == prefix) ? 1 : 0;
-  int total_eq;
-  int eq_rank = block_exclusive_scan_1024(eq, sh, &total_eq);
-  int tokens = 0;
-  {
-    int r = eq_rank;
-    for (int j = j0; j < j1; ++j) {
+// More chunks than registers hold (a sequence of more than 16384): the same selection with the scores read again in
+// every pass, thread t owning chunks [j0, j1) in the ordered count.
+__device__ __forceinline__ int select_chunks_from_memory(const double* cs, int n, int k, int* hist, int* sh, bool* last_kept,
+                                                         int32_t* rank_out) {
+  const int t = threadIdx.x;
+  __shared__ int last_sh;
+  int bad = 0;
+  for (int j = t; j < n; j += 1024) bad |= is_nan_bits(cs[j]) ? 1 : 0;
+  if (t == 0) last_sh = 0;
+  if (__syncthreads_or(bad)) return -1;
+  uint64_t prefix = 0;
+  int need = k;
+#pragma unroll 1
+  for (int pass = 0; pass < 8; ++pass) {
+    if (t < 256) hist[t] = 0;
+    __syncthreads();
+    const int shift = (7 - pass) * 8;
+    const uint64_t himask = (pass == 0) ? 0ull : (~0ull << (shift + 8));
+    for (int j = t; j < n; j += 1024) {
       const uint64_t key = order_key(cs[j]);
-      const bool keep = key > prefix || (key == prefix && r++ < need);
-      if (keep) tokens += min(p.chunk, (hi - lo) - j * p.chunk);
+      if ((key & himask) == prefix) atomicAdd(&hist[(int)((key >> shift) & 255u)], 1);
     }
+    __syncthreads();
+    int bucket;
+    bool all;
+    find_bucket(hist, need, &bucket, &need, &all);
+    prefix |= (uint64_t)bucket << shift;
+    __syncthreads();
+    if (all) { need = n; break; }
   }
-  int total_tokens;
-  int off = block_exclusive_scan_1024(tokens, sh, &total_tokens);
+  const int per = (n + 1023) / 1024, j0 = min(n, t * per), j1 = min(n, j0 + per);
+  int above = 0, equal = 0;
   for (int j = j0; j < j1; ++j) {
     const uint64_t key = order_key(cs[j]);
-    const bool keep = key > prefix || (key == prefix && eq_rank++ < need);
-    p.chunk_off[c0 + j] = keep ? off : -1;
-    if (keep) off += min(p.chunk, (hi - lo) - j * p.chunk);
+    above += key > prefix ? 1 : 0;
+    equal += key == prefix ? 1 : 0;
   }
-  if (t == 0) p.seq_keep[b] = total_tokens;
+  const int wave = t >> 6;
+  int wave_above, wave_equal;
+  int kept_before = wave_inclusive_scan(above, &wave_above) - above;
+  int eq_before = wave_inclusive_scan(equal, &wave_equal) - equal;
+  if ((t & 63) == 0) { sh[wave] = wave_above; sh[16 + wave] = wave_equal; }
+  __syncthreads();
+  int total = 0, eq_total = 0;
+  for (int w = 0; w < 16; ++w) {
+    if (w < wave) { kept_before += sh[w]; eq_before += sh[16 + w]; }
+    total += sh[w];
+    eq_total += sh[16 + w];
+  }
+  kept_before += min(eq_before, need);
+  total += min(eq_total, need);
+  for (int j = j0; j < j1; ++j) {
+    const uint64_t key = order_key(cs[j]);
+    const bool keep = key > prefix || (key == prefix && eq_before++ < need);
+    rank_out[j] = keep ? kept_before++ : -1;
+    if (keep && j == n - 1) last_sh = 1;
+  }
+  __syncthreads();
+  *last_kept = last_sh != 0;
+  return total;
+}
+
+// One workgroup per sequence; chunk_off gets the rank of every kept chunk among its sequence's, -1 for the others.
+// Without a chunk table the workgroup that finishes last (a word the pooling kernel has cleared counts them) adds the
+// sequences' counts up, which the table variant leaves to a launch of its own.
+__global__ __launch_bounds__(1024) void select_kernel(const SelDev p) {
+  __shared__ int hist[3 * 256];
+  __shared__ int sh[32];
+  const int b = blockIdx.x, t = threadIdx.x;
+  const int M = p.cu[b + 1] - p.cu[b];
+  const int c0 = chunk_base(p, b), n = (M + p.chunk - 1) / p.chunk;
+  int keep_tokens = 0;
+  if (n > 0) {
+    const double scaled = p.keep_rate * (double)n;
+    const double kd = ceil(scaled - 1e-9);
+    const int k = (int)fmin((double)n, fmax(1.0, kd));
+    const double* cs = p.cs + c0;
+    int32_t* rank_out = p.chunk_off + c0;
+    auto emit = [&](int j, int rank) __attribute__((always_inline)) { rank_out[j] = rank; };
+    bool last_kept = false;
+    int kept;
+    if (n <= 1024) kept = select_chunks<1>(cs, n, k, hist, sh, &last_kept, emit);
+    else if (n <= 4096) kept = select_chunks<4>(cs, n, k, hist, sh, &last_kept, emit);
+    else if (n <= 16384) kept = select_chunks<16>(cs, n, k, hist, sh, &last_kept, emit);
+    else kept = select_chunks_from_memory(cs, n, k, hist, sh, &last_kept, rank_out);
+    // invalid scores (NaN: the scorer's mark for "a device-side wait expired") are reported in band:
+    // a negative count here turns every cu_keep entry after the first into -1
+    keep_tokens = kept < 0 ? -1 : (int)((int64_t)kept * p.chunk - (last_kept ? (int64_t)n * p.chunk - M : 0));
+    if (kept < 0)
+      for (int j = t; j < n; j += 1024) rank_out[j] = -1;
+  }
+  if (p.table) {
+    if (t == 0) p.seq_keep[b] = keep_tokens;
+    return;
+  }
+  __shared__ int arrived;
+  if (t == 0) {
+    __hip_atomic_store(p.seq_keep + b, keep_tokens, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    arrived = __hip_atomic_fetch_add(p.arrived, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (arrived == p.B - 1) scan_seq_keep(p);
 }
 
 __global__ __launch_bounds__(1024) void select_emit_single_kernel(const SelDev p) {
@@ -148,14 +268,7 @@ __global__ __launch_bounds__(1024) void select_emit_single_kernel(const SelDev p
   select_emit_single(p, p.cs, keys);
 }
 
-__global__ __launch_bounds__(1024) void cu_keep_kernel(const SelDev p) {
-  int bad = 0;
-  for (int b = threadIdx.x; b < p.B; b += 1024) bad |= p.seq_keep[b] < 0 ? 1 : 0;
-  bad = __syncthreads_or(bad);
-  block_prefix_table(p.B, [&](int b) { return max(p.seq_keep[b], 0); }, p.cu_keep);
-  if (bad)  // some sequence had invalid scores: no keep set is handed on
-    for (int b = 1 + threadIdx.x; b <= p.B; b += 1024) p.cu_keep[b] = -1;
-}
+__global__ __launch_bounds__(1024) void cu_keep_kernel(const SelDev p) { scan_seq_keep(p); }
 
 // one thread per prompt token: if its chunk is kept, write its flat index to its slot
 __global__ __launch_bounds__(256) void emit_kernel(const SelDev p) {
@@ -164,9 +277,9 @@ __global__ __launch_bounds__(256) void emit_kernel(const SelDev p) {
   const int b = upper_segment(p.cu, p.B, i);
   const int in_seq = i - p.cu[b];
   const int j = in_seq / p.chunk;
-  const int off = p.chunk_off[p.cu_chunks[b] + j];
-  if (off < 0) return;
-  const int64_t slot = (int64_t)p.cu_keep[b] + off + (in_seq - j * p.chunk);
+  const int rank = p.chunk_off[chunk_base(p, b) + j];
+  if (rank < 0) return;
+  const int64_t slot = (int64_t)p.cu_keep[b] + (int64_t)rank * p.chunk + (in_seq - j * p.chunk);
   if (slot < p.capacity) p.kept_idx[slot] = i;
 }
 
@@ -231,19 +344,24 @@ static sp_status run_pool_select(const sp_pool_select_args* a, void* scratch, hi
   p.cs = reinterpret_cast<double*>(ws);         ws += align_up(8 * mc, 256);
   p.chunk_off = reinterpret_cast<int32_t*>(ws);
 
-  const int cpw = a->chunk >= kWave ? 1 : kWave / a->chunk;
-  const size_t groups = (mc + cpw - 1) / cpw;
-  const int pool_blocks = (int)std::min<size_t>((groups + 3) / 4, 65535);
+  // (without a table its place holds the count of the workgroups that have finished)
+  p.table = a->d_chunk_scores != nullptr;
+  p.arrived = p.cu_chunks;
+  const bool long_chunks = a->chunk > kPoolThreads;
+  const size_t per_block = long_chunks ? 4 : kPoolThreads / a->chunk;
+  const unsigned pool_blocks = (unsigned)std::max<size_t>(1, std::min<size_t>((mc + per_block - 1) / per_block, 65535));
   if (a->B == 1 && (a->T + a->chunk - 1) / a->chunk <= kSingleMaxChunks) {
     // one sequence (its length is T, known here): no chunk table, no cross-sequence scan
-    hipLaunchKernelGGL(pool_chunk_kernel<true>, dim3(std::max(pool_blocks, 1)), dim3(256), 0, stream, p);
+    if (long_chunks) hipLaunchKernelGGL(pool_long_chunk_kernel<true>, dim3(pool_blocks), dim3(256), 0, stream, p);
+    else hipLaunchKernelGGL(pool_chunk_kernel<true>, dim3(pool_blocks), dim3(kPoolThreads), 0, stream, p);
     hipLaunchKernelGGL(select_emit_single_kernel, dim3(1), dim3(1024), 0, stream, p);
     return launch_status();
   }
-  hipLaunchKernelGGL(chunk_table_kernel, dim3(1), dim3(1024), 0, stream, p);
-  hipLaunchKernelGGL(pool_chunk_kernel<false>, dim3(std::max(pool_blocks, 1)), dim3(256), 0, stream, p);
+  if (p.table) hipLaunchKernelGGL(chunk_table_kernel, dim3(1), dim3(1024), 0, stream, p);
+  if (long_chunks) hipLaunchKernelGGL(pool_long_chunk_kernel<false>, dim3(pool_blocks), dim3(256), 0, stream, p);
+  else hipLaunchKernelGGL(pool_chunk_kernel<false>, dim3(pool_blocks), dim3(kPoolThreads), 0, stream, p);
   hipLaunchKernelGGL(select_kernel, dim3(a->B), dim3(1024), 0, stream, p);
-  hipLaunchKernelGGL(cu_keep_kernel, dim3(1), dim3(1024), 0, stream, p);
+  if (p.table) hipLaunchKernelGGL(cu_keep_kernel, dim3(1), dim3(1024), 0, stream, p);
   if (a->T > 0)
     hipLaunchKernelGGL(emit_kernel, dim3((unsigned)((a->T + 255) / 256)), dim3(256), 0, stream, p);
   return launch_status();

@@ -22,10 +22,12 @@ struct SelDev {
   int32_t* kept_idx;
   int32_t* cu_keep;
   float* chunk_scores_out;
+  int table;            // the chunks are numbered without gaps by cu_chunks (the caller wants their scores)
   int32_t* cu_chunks;   // [B+1]
+  int32_t* arrived;     // no table: sequences selected so far
   int32_t* seq_keep;    // [B]
   double* cs;           // [max_chunks]
-  int32_t* chunk_off;   // [max_chunks]: offset of the chunk's first token inside its sequence's kept list, or -1
+  int32_t* chunk_off;   // [max_chunks]: rank of the chunk among its sequence's kept ones, or -1
 };
 
 // NaN, decided on the bit pattern (device code is compiled on the assumption that there are none)
@@ -55,31 +57,11 @@ __device__ __forceinline__ int wave_inclusive_scan(int v, int* total) {
   return v + (lane >= 16 ? r0 : 0) + (lane >= 32 ? r1 : 0) + (lane >= 48 ? r2 : 0);
 }
 
-// exclusive prefix sum over the 1024 threads of the workgroup (the 16 wave totals go through
-// `sh`): two barriers
-__device__ __forceinline__ int block_exclusive_scan_1024(int v, int* sh, int* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int wave_total;
-  const int incl = wave_inclusive_scan(v, &wave_total);
-  if (lane == kWave - 1) sh[wave] = incl;
-  __syncthreads();
-  int before = 0, all = 0;
-#pragma unroll
-  for (int w = 0; w < 16; ++w) {
-    const int s = sh[w];
-    all += s;
-    before += (w < wave) ? s : 0;
-  }
-  *total = all;
-  __syncthreads();  // `sh` may be written again
-  return before + incl - v;
-}
-
 // The bucket holding the need-th largest of the keys still in play: the highest bucket whose
 // count, added to the counts above it, reaches `need`.  Done by a whole wave (four buckets per
-// lane, suffix sums by shuffles); every lane gets the bucket and how many keys of that bucket are
-// still needed.
-__device__ __forceinline__ void find_bucket(const int* hist, int need, int* bucket_out, int* need_left) {
+// lane, suffix sums by shuffles); every lane gets the bucket, how many keys of that bucket are
+// still needed, and whether that is all of them.
+__device__ __forceinline__ void find_bucket(const int* hist, int need, int* bucket_out, int* need_left, bool* all_of_it) {
   const int lane = threadIdx.x & 63;
   int h[4];
 #pragma unroll
@@ -89,12 +71,12 @@ __device__ __forceinline__ void find_bucket(const int* hist, int need, int* buck
   const int upto = wave_inclusive_scan(own, &all);
   const int suffix = all - upto + own;  // counts of this lane's buckets and of all higher lanes'
   int above = suffix - own;
-  int bucket = -1, left = 0;
+  int bucket = -1, left = 0, size = 0;
   if (above < need && need <= suffix) {  // exactly one lane: the keys still in play number at least `need`
     bucket = 4 * lane;
 #pragma unroll
     for (int u = 3; u >= 0; --u) {
-      if (above + h[u] >= need) { bucket = 4 * lane + u; break; }
+      if (above + h[u] >= need) { bucket = 4 * lane + u; size = h[u]; break; }
       above += h[u];
     }
     left = need - above;
@@ -102,31 +84,43 @@ __device__ __forceinline__ void find_bucket(const int* hist, int need, int* buck
   const int src = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)__ballot(bucket >= 0)) - 1);
   *bucket_out = __builtin_amdgcn_readlane(bucket, src);
   *need_left = __builtin_amdgcn_readlane(left, src);
+  *all_of_it = __builtin_amdgcn_readlane(size, src) == *need_left;
 }
 
-// Radix select over 64-bit keys, eight bits a pass from the top: afterwards `prefix` is the k-th
-// largest key and `need` says how many keys equal to it are among the k largest.  key_at(j) gives
-// key j of n.  Call with all 1024 threads; `hist` has room for 3 x 256 counters.  One barrier per
+// Chunks of a sequence in registers: wave w of the workgroup's sixteen owns chunks [w * 64 I, (w + 1) * 64 I), lane x of it
+// chunk (w * I + i) * 64 + x as key[i].  (Re-reading the scores in every pass, a thread at a time in index order, made
+// the selection of 9000 single tokens 71 us, nearly all of it memory latency.)
+template <int I>
+__device__ __forceinline__ int reg_chunk(int i) {
+  return ((int)(threadIdx.x >> 6) * I + i) * 64 + (int)(threadIdx.x & 63);
+}
+
+// Radix select over 64-bit keys in registers, eight bits a pass from the top: a chunk is kept if its key is above
+// `prefix`, or equal to it and among the first `need` of those in index order.  Stops as soon as all keys of the bucket
+// in hand are needed (usually after two or three passes; then need = n).  `skip_top`: all keys share their top
+// byte, which is prefix's.  Call with all 1024 threads; `hist` has room for 3 x 256 counters.  One barrier per
 // pass: the counters of pass i live in hist[i % 3], the next pass's are cleared meanwhile (their
 // last readers finished two barriers ago), and every wave finds the bucket for itself.
-template <typename KeyAt>
-__device__ __forceinline__ void radix_select_kth(KeyAt key_at, int n, int k, int* hist, uint64_t* prefix_out, int* need_out) {
+template <int I>
+__device__ __forceinline__ void radix_select_kth(const uint64_t (&key)[I], int n, int k, bool skip_top, uint64_t top, int* hist,
+                                                 uint64_t* prefix_out, int* need_out) {
   const int t = threadIdx.x;
-  if (t < 256) hist[t] = 0;
+  const int first_pass = skip_top ? 1 : 0;
+  if (t < 256) hist[first_pass * 256 + t] = 0;
   __syncthreads();
-  uint64_t prefix = 0;
+  uint64_t prefix = skip_top ? top : 0;
   int need = k;
 #pragma unroll 1
-  for (int i = 0; i < 8; ++i) {
-    int* cur = hist + (i % 3) * 256;
-    int* nxt = hist + ((i + 1) % 3) * 256;
+  for (int pass = first_pass; pass < 8; ++pass) {
+    int* cur = hist + (pass % 3) * 256;
+    int* nxt = hist + ((pass + 1) % 3) * 256;
     if (t < 256) nxt[t] = 0;
-    const int shift = (7 - i) * 8;
-    const uint64_t himask = (i == 0) ? 0ull : (~0ull << (shift + 8));
-    for (int j = t; j < n; j += 1024) {
-      const uint64_t key = key_at(j);
-      const bool in_play = (key & himask) == prefix;
-      const int digit = (int)((key >> shift) & 255u);
+    const int shift = (7 - pass) * 8;
+    const uint64_t himask = (pass == 0) ? 0ull : (~0ull << (shift + 8));
+#pragma unroll
+    for (int i = 0; i < I; ++i) {
+      const bool in_play = reg_chunk<I>(i) < n && (key[i] & himask) == prefix;
+      const int digit = (int)((key[i] >> shift) & 255u);
       // Scores of one prompt share their sign and most exponent bits, so in the upper passes a
       // whole wave lands in one counter, and 64 additions to one LDS word are done one after
       // the other: where the wave's digits all agree, one lane adds the count.
@@ -142,24 +136,95 @@ __device__ __forceinline__ void radix_select_kth(KeyAt key_at, int n, int k, int
     }
     __syncthreads();
     int bucket;
-    find_bucket(cur, need, &bucket, &need);
+    bool all;
+    find_bucket(cur, need, &bucket, &need, &all);
     prefix |= (uint64_t)bucket << shift;
+    if (all) {  // every key with this prefix is kept, and none has smaller lower bits than zero
+      need = n;
+      break;
+    }
   }
   *prefix_out = prefix;
   *need_out = need;
 }
 
+// The k best of n chunks (scores cs[0..n), equal scores to the lower index) by one workgroup of 1024 threads:
+// emit(j, rank) for every kept chunk j, the rank-th of them in index order, emit(j, -1) for the others; returns
+// the number of kept chunks (*last_kept: chunk n - 1 among them), or -1 if a score is NaN (nothing is emitted then).
+template <int I, typename Emit>
+__device__ __forceinline__ int select_chunks(const double* cs, int n, int k, int* hist, int* sh, bool* last_kept, Emit emit) {
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+  __shared__ uint64_t key0;
+  __shared__ int last_sh;
+  uint64_t key[I];
+  int bad = 0;
+#pragma unroll
+  for (int i = 0; i < I; ++i) {
+    const int j = reg_chunk<I>(i);
+    double v = 0.0;
+    if (j < n) v = cs[j];
+    bad |= is_nan_bits(v) ? 1 : 0;
+    key[i] = order_key(v);
+  }
+  if (t == 0) { key0 = key[0]; last_sh = 0; }
+  if (__syncthreads_or(bad)) return -1;
+  const uint64_t top = key0 & (255ull << 56);
+  int differs = 0;
+#pragma unroll
+  for (int i = 0; i < I; ++i) differs |= (reg_chunk<I>(i) < n && (key[i] & (255ull << 56)) != top) ? 1 : 0;
+  const bool skip_top = !__syncthreads_or(differs);
+  uint64_t prefix;
+  int need;
+  radix_select_kth<I>(key, n, k, skip_top, top, hist, &prefix, &need);
+
+  // in index order: rows of 64 chunks by ballots, the waves' totals through LDS
+  int above = 0, equal = 0;
+#pragma unroll
+  for (int i = 0; i < I; ++i) {
+    const bool in = reg_chunk<I>(i) < n;
+    above += __popcll(__ballot(in && key[i] > prefix));
+    equal += __popcll(__ballot(in && key[i] == prefix));
+  }
+  if (lane == 0) { sh[wave] = above; sh[16 + wave] = equal; }
+  __syncthreads();
+  int kept_before = 0, eq_before = 0, total = 0, eq_total = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    const int a = sh[w], e = sh[16 + w];
+    if (w < wave) { kept_before += a; eq_before += e; }
+    total += a;
+    eq_total += e;
+  }
+  kept_before += min(eq_before, need);
+  total += min(eq_total, need);
+  const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int i = 0; i < I; ++i) {
+    const int j = reg_chunk<I>(i);
+    const bool eq = j < n && key[i] == prefix;
+    const unsigned long long eq_mask = __ballot(eq);
+    const bool keep = j < n && (key[i] > prefix || (eq && eq_before + __popcll(eq_mask & below) < need));
+    const unsigned long long mask = __ballot(keep);
+    if (j < n) emit(j, keep ? kept_before + __popcll(mask & below) : -1);
+    if (keep && j == n - 1) last_sh = 1;
+    eq_before += __popcll(eq_mask);
+    kept_before += __popcll(mask);
+  }
+  __syncthreads();
+  *last_kept = last_sh != 0;
+  return total;
+}
+
 // Single sequence with at most kSingleMaxChunks chunks: top-k, compaction and the kept-index
-// list in one workgroup and one launch.  Above kCountMaxChunks chunks the k-th largest key is
-// found by the same 8-pass radix select as in select_kernel, on keys held in LDS; ties at the
-// threshold go to the lower chunk indices by an ordered scan; kept tokens are written straight away.
+// list in one workgroup and one launch.  Above kCountMaxChunks chunks the chunks are selected as in
+// select_kernel; kept tokens are written straight away.
 constexpr int kSingleMaxChunks = 2048;
 constexpr int kCountMaxChunks = 256;  // up to here the chunks are ranked by counting instead
 // `cs`: the chunk scores (global or LDS memory); `keys`: LDS room for kSingleMaxChunks 64-bit keys.
 // Call with all 1024 threads of the workgroup.
 __device__ __forceinline__ void select_emit_single(const SelDev& p, const double* cs, uint64_t* keys) {
   __shared__ int hist[3 * 256];
-  __shared__ int sh[16];
+  __shared__ int sh[32];
   const int t = threadIdx.x;
   const int M = p.T;
   const int n = (M + p.chunk - 1) / p.chunk;
@@ -171,23 +236,22 @@ __device__ __forceinline__ void select_emit_single(const SelDev& p, const double
   const double scaled = p.keep_rate * (double)n;
   const double kd = ceil(scaled - 1e-9);
   const int k = (int)fmin((double)n, fmax(1.0, kd));
-  int bad = 0;
-  for (int j = t; j < n; j += 1024) {
-    const double v = cs[j];
-    bad |= is_nan_bits(v) ? 1 : 0;
-    keys[j] = order_key(v);
-  }
-  if (__syncthreads_or(bad)) {  // invalid scores: reported in band, nothing kept
-    if (t == 0) p.cu_keep[1] = -1;
-    return;
-  }
-
   if (n <= kCountMaxChunks) {
     // Few chunks: thread t ranks chunk t by counting the chunks that come before it in the order
     // (larger score, or equal score and lower index); the k first are kept.  All chunks but the
     // last have the same length, so a kept token's place follows from the number of kept chunks
     // before its own: no scan, two barriers.
     __shared__ uint64_t kept_mask[kCountMaxChunks / 64];
+    int bad = 0;
+    if (t < n) {
+      const double v = cs[t];
+      bad = is_nan_bits(v) ? 1 : 0;
+      keys[t] = order_key(v);
+    }
+    if (__syncthreads_or(bad)) {  // invalid scores: reported in band, nothing kept
+      if (t == 0) p.cu_keep[1] = -1;
+      return;
+    }
     bool keep = false;
     if (t < n) {
       const uint64_t mine = keys[t];
@@ -220,47 +284,27 @@ __device__ __forceinline__ void select_emit_single(const SelDev& p, const double
     return;
   }
 
-  uint64_t prefix;
-  int need;
-  radix_select_kth([&](int j) { return keys[j]; }, n, k, hist, &prefix, &need);
-
-  // ordered pass: thread t owns chunks [j0, j1) in index order
-  const int per = (n + 1023) / 1024;
-  const int j0 = min(n, t * per), j1 = min(n, j0 + per);
-  int eq = 0;
-  for (int j = j0; j < j1; ++j) eq += (keys[j] == prefix) ? 1 : 0;
-  int total_eq;
-  int eq_rank = block_exclusive_scan_1024(eq, sh, &total_eq);
-  int tokens = 0;
-  {
-    int r = eq_rank;
-    for (int j = j0; j < j1; ++j) {
-      const uint64_t key = keys[j];
-      const bool keep = key > prefix || (key == prefix && r++ < need);
-      if (keep) tokens += min(p.chunk, M - j * p.chunk);
-    }
-  }
-  int total_tokens;
-  int off = block_exclusive_scan_1024(tokens, sh, &total_tokens);
-  // Kept chunks by rank: all kept chunks but possibly the very last are full, so a chunk that
-  // starts at token offset `off` of the kept list is kept chunk number off / chunk ...
+  // all kept chunks but possibly the very last are full: kept chunk number q starts at token q * chunk of the list ...
   __shared__ unsigned short kept_list[kSingleMaxChunks];
-  for (int j = j0; j < j1; ++j) {
-    const uint64_t key = keys[j];
-    const bool keep = key > prefix || (key == prefix && eq_rank++ < need);
-    if (!keep) continue;
-    kept_list[off / p.chunk] = (unsigned short)j;
-    off += min(p.chunk, M - j * p.chunk);
+  auto emit = [&](int j, int rank) __attribute__((always_inline)) {
+    if (rank >= 0) kept_list[rank] = (unsigned short)j;
+  };
+  bool last_kept;
+  const int kept_chunks = n <= 1024 ? select_chunks<1>(cs, n, k, hist, sh, &last_kept, emit)
+                                    : select_chunks<2>(cs, n, k, hist, sh, &last_kept, emit);
+  if (kept_chunks < 0) {
+    if (t == 0) p.cu_keep[1] = -1;
+    return;
   }
+  const int64_t total_tokens = (int64_t)kept_chunks * p.chunk - (last_kept ? (int64_t)n * p.chunk - M : 0);
   __syncthreads();
   // ... and the kept tokens are written by all threads, a token each
-  const int64_t n_write = min((int64_t)total_tokens, p.capacity);
+  const int64_t n_write = min(total_tokens, p.capacity);
   for (int64_t pos = t; pos < n_write; pos += 1024) {
     const int q = (int)(pos / p.chunk);
     p.kept_idx[pos] = (int)kept_list[q] * p.chunk + (int)(pos - (int64_t)q * p.chunk);
   }
-  if (t == 0) p.cu_keep[1] = total_tokens;
+  if (t == 0) p.cu_keep[1] = (int32_t)total_tokens;
 }
-
 
 }  // namespace sp
