@@ -143,6 +143,18 @@ __global__ __launch_bounds__(kFusedThreads) void fused_short_kernel(const FusedD
     }
   }
 
+  // What the finisher needs of the arguments is tabulated here, by all, while the stores travel.
+  int nv = p.n_valid ? p.n_valid[0] : p.N;
+  nv = max(1, min(nv, p.N));
+  const int heads_total = p.L * p.H;   // head f of all layers: softmax row (f / G) * rows + nq * G + f % G
+  const int items = nv * heads_total;  // per key, item i: query i / heads_total, head i % heads_total
+  // (divisions are dear: each item's row and its end-of-layer / end-of-query marks are tabulated once)
+  for (int i = tid; i < items; i += kFusedThreads) {
+    const int nq = i / heads_total, f = i - nq * heads_total;
+    const int row = (f / p.G) * rows + nq * p.G + f % p.G;
+    item_tab[i] = (unsigned short)(row | ((f + 1) % p.H == 0 ? kLayerEnds : 0) | (f + 1 == heads_total ? kQueryEnds : 0));
+  }
+
   // ---- count in; all but the last to arrive are done ----
   wait_vmcnt<0>();  // this thread's workspace stores have been performed
   __syncthreads();
@@ -154,17 +166,6 @@ __global__ __launch_bounds__(kFusedThreads) void fused_short_kernel(const FusedD
 
   // Reads of what other workgroups wrote cost a trip to memory each (microseconds): the first
   // logits phase 2b needs are requested now, so that they travel together with 2a's partials.
-  int nv = p.n_valid ? p.n_valid[0] : p.N;
-  nv = max(1, min(nv, p.N));
-  const int heads_total = p.L * p.H;   // head f of all layers: softmax row (f / G) * rows + nq * G + f % G
-  const int items = nv * heads_total;  // per key, item i: query i / heads_total, head i % heads_total
-  // (divisions are dear: each item's row and its end-of-layer / end-of-query marks are tabulated once)
-  for (int i = tid; i < items; i += kFusedThreads) {
-    const int nq = i / heads_total, f = i - nq * heads_total;
-    const int row = (f / p.G) * rows + nq * p.G + f % p.G;
-    item_tab[i] = (unsigned short)(row | ((f + 1) % p.H == 0 ? kLayerEnds : 0) | (f + 1 == heads_total ? kQueryEnds : 0));
-  }
-  __syncthreads();
   constexpr int kAhead = 16;
   float ahead[kAhead];
 #pragma unroll
