@@ -164,25 +164,33 @@ __global__ __launch_bounds__(64) void lse_partial_kernel(const ScoreDev p) {
 // ---------------------------------------------------------------------------------------
 // pass 1b: combine the tile partials of a row into its log-sum-exp
 // ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void lse_combine_kernel(const ScoreDev p) {
-  const int row = blockIdx.x;  // ((l*B + b)*N + n)*H + h
-  const int lane = threadIdx.x;
+// LANES lanes per row: a wave for one long prompt, a quarter of one where the sequences are short and the rows many
+// (16 prompts of 300..3000 keys, 131072 rows of 27 tiles: 40 us with a wave each).
+template <int LANES>
+__global__ __launch_bounds__(256) void lse_combine_kernel(const ScoreDev p, int rows) {
+  const int row = blockIdx.x * (256 / LANES) + threadIdx.x / LANES;  // ((l*B + b)*N + n)*H + h
+  const int lane = threadIdx.x % LANES;
+  const bool live = row < rows;
   const int h = row % p.H;
   const int n = (row / p.H) % p.N;
-  const int b = (row / (p.H * p.N)) % p.B;
+  const int b = live ? (row / (p.H * p.N)) % p.B : 0;
   const int l = row / (p.H * p.N * p.B);
-  const int t0 = p.tile_cu[b], t1 = p.tile_cu[b + 1];
+  const int t0 = p.tile_cu[b], t1 = live ? p.tile_cu[b + 1] : t0;
   const float2* part = p.part + ((int64_t)(l * p.N + n) * p.H + h) * p.max_tiles;
   float m = -INFINITY, z = 0.f;
-  for (int t = t0 + lane; t < t1; t += kWave) {
+  for (int t = t0 + lane; t < t1; t += LANES) {
     const float2 v = part[t];
     const float mn = fmaxf(m, v.x);
     z = z * expf(m - mn) + v.y * expf(v.x - mn);  // first step: z = 0 * exp(-inf) = 0
     m = mn;
   }
-  const float mw = wave_max(m);
-  const float zw = wave_sum(m == -INFINITY ? 0.f : z * expf(m - mw));
-  if (lane == 0) {
+  float mw = m;
+#pragma unroll
+  for (int off = LANES / 2; off >= 1; off >>= 1) mw = fmaxf(mw, __shfl_xor(mw, off, kWave));
+  float zw = m == -INFINITY ? 0.f : z * expf(m - mw);
+#pragma unroll
+  for (int off = LANES / 2; off >= 1; off >>= 1) zw += __shfl_xor(zw, off, kWave);
+  if (live && lane == 0) {
     const float lse = (t1 > t0) ? mw + logf(zw) : 0.f;
     p.ws_lse[row] = lse;
     if (p.lse_out) p.lse_out[row] = lse;
@@ -302,7 +310,10 @@ size_t general_workspace_bytes(const sp_score_args* a, bool with_tiled) {
 }
 
 void launch_lse_combine(const ScoreDev& p, hipStream_t stream) {
-  hipLaunchKernelGGL(lse_combine_kernel, dim3(p.L * p.B * p.N * p.H), dim3(64), 0, stream, p);
+  const int rows = p.L * p.B * p.N * p.H;
+  // (tiles per row: T / 64 / B on average)
+  if (p.T / 64 >= 64 * p.B) hipLaunchKernelGGL(lse_combine_kernel<64>, dim3((rows + 3) / 4), dim3(256), 0, stream, p, rows);
+  else hipLaunchKernelGGL(lse_combine_kernel<16>, dim3((rows + 15) / 16), dim3(256), 0, stream, p, rows);
 }
 
 // these paths have no bounded waits: leave "no wait expired" where sp_score_check looks
@@ -351,14 +362,13 @@ sp_status general_score(const sp_score_args* a, hipStream_t stream, bool allow_m
     return st != SP_OK ? st : launch_status();
   }
   const dim3 grid1(p.max_tiles, p.H_kv, p.L);
-  const int rows = p.L * p.B * p.N * p.H;
   if (p.d == 64) {
     hipLaunchKernelGGL(lse_partial_kernel<64>, grid1, dim3(64), 0, stream, p);
-    hipLaunchKernelGGL(lse_combine_kernel, dim3(rows), dim3(64), 0, stream, p);
+    launch_lse_combine(p, stream);
     hipLaunchKernelGGL(score_accum_kernel<64>, dim3(p.max_tiles), dim3(256), 0, stream, p);
   } else {
     hipLaunchKernelGGL(lse_partial_kernel<128>, grid1, dim3(64), 0, stream, p);
-    hipLaunchKernelGGL(lse_combine_kernel, dim3(rows), dim3(64), 0, stream, p);
+    launch_lse_combine(p, stream);
     hipLaunchKernelGGL(score_accum_kernel<128>, dim3(p.max_tiles), dim3(256), 0, stream, p);
   }
   clear_stream_status(a, stream);

@@ -269,7 +269,8 @@ __global__ __launch_bounds__(1024) void seq_order_kernel(int B, const int32_t* _
   }
 }
 
-// Merge of the units' partial results and the average over the valid queries (Sec. 3.2.2).  A workgroup takes TOK
+// Merge of the units' (or the two-pass kernels' layer groups') partial results and the average over the valid queries
+// (Sec. 3.2.2).  A workgroup takes TOK
 // tokens; its 64 * WAVES / TOK groups of TOK threads take every so-many-th slab group (one TOK * 4 byte read per group and
 // query), the lanes of a wave fold by shuffles, the waves' results meet in LDS.  Sequences the scoring
 // kernel left out (longer than it holds) get NaN.  Bound by the latency of the reads for one short prompt, whose
@@ -331,7 +332,7 @@ __global__ __launch_bounds__(64 * WAVES) void units_finish_kernel(const TiledDev
   __syncthreads();
   if (threadIdx.x >= TOK || !inside) return;
   const int b = upper_segment(p.cu, p.B, (int)tok);
-  if (p.cu[b + 1] - p.cu[b] > p.seq_limit) {
+  if (p.seq_limit > 0 && p.cu[b + 1] - p.cu[b] > p.seq_limit) {
     p.scores[tok] = __uint_as_float(0x7FC00000u);
     return;
   }
@@ -349,12 +350,13 @@ static sp_status finish_by_tokens(const TiledDev& dev, hipStream_t stream) {
   // Tokens per workgroup: 64 where that makes at least two workgroups per compute unit, else 16; waves: sixteen where
   // there are that many groups for each, else four (64 prompts, 168K tokens in eight groups: 12 us with sixteen).
   if (dev.T < 64 * 512) hipLaunchKernelGGL((units_finish_kernel<NQ, 16, 16>), dim3((unsigned)((dev.T + 15) / 16)), dim3(1024), 0, stream, dev);
-  else if (dev.n_groups > 64) hipLaunchKernelGGL((units_finish_kernel<NQ, 64, 16>), dim3((unsigned)((dev.T + 63) / 64)), dim3(1024), 0, stream, dev);
+  else if (dev.n_groups > 64 && NQ <= 8) hipLaunchKernelGGL((units_finish_kernel<NQ, 64, NQ <= 8 ? 16 : 4>), dim3((unsigned)((dev.T + 63) / 64)), dim3(NQ <= 8 ? 1024 : 256), 0, stream, dev);
   else hipLaunchKernelGGL((units_finish_kernel<NQ, 64, 4>), dim3((unsigned)((dev.T + 63) / 64)), dim3(256), 0, stream, dev);
   return launch_status();
 }
-static sp_status launch_units_finish(const TiledDev& dev, hipStream_t stream) {  // (at most two queries on this path)
-  return dev.N == 1 ? finish_by_tokens<1>(dev, stream) : finish_by_tokens<2>(dev, stream);
+sp_status launch_units_finish(const TiledDev& dev, hipStream_t stream) {
+  return dev.N == 1 ? finish_by_tokens<1>(dev, stream) : dev.N == 2 ? finish_by_tokens<2>(dev, stream)
+       : dev.N <= 4 ? finish_by_tokens<4>(dev, stream) : dev.N <= 8 ? finish_by_tokens<8>(dev, stream) : finish_by_tokens<16>(dev, stream);
 }
 
 void launch_seq_order(const sp_score_args* a, int32_t* order, int limit, hipStream_t stream) {

@@ -289,27 +289,6 @@ __global__ __launch_bounds__(256) void logit_score_kernel(const TiledDev p) {
   p.scores[tok] = sum / (MEAN ? (float)nv * (float)p.L : (float)nv);
 }
 
-// merge the layer groups and average over the valid queries; one thread per token
-__global__ __launch_bounds__(256) void tiled_finish_kernel(const TiledDev p) {
-  const int64_t tok = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (tok >= p.T) return;
-  const int b = upper_segment(p.cu, p.B, (int)tok);
-  int nv = p.n_valid ? p.n_valid[b] : p.N;
-  nv = max(1, min(nv, p.N));
-  float sum = 0.f;
-  for (int n = 0; n < nv; ++n) {
-    if (p.layer_reduce == SP_LAYER_MAX) {
-      float m = -INFINITY;
-      for (int g = 0; g < p.n_groups; ++g) m = fmaxf(m, p.group_scores[((int64_t)g * p.N + n) * p.T + tok]);
-      sum += fast_exp2(m);
-    } else {
-      for (int g = 0; g < p.n_groups; ++g) sum += p.group_scores[((int64_t)g * p.N + n) * p.T + tok];
-    }
-  }
-  const float denom = (p.layer_reduce == SP_LAYER_MAX) ? (float)nv : (float)nv * (float)p.L;
-  p.scores[tok] = sum / denom;
-}
-
 // ---------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------
@@ -406,8 +385,7 @@ static sp_status tiled_passes(const TiledDev& dev, const ScoreDev& gen, hipStrea
   st = dev.layer_reduce == SP_LAYER_MEAN ? launch_tiled<D, 1, true, ROPE, FP8>(dev, stream)
                                          : launch_tiled<D, 1, false, ROPE, FP8>(dev, stream);
   if (st != SP_OK) return st;
-  hipLaunchKernelGGL(tiled_finish_kernel, dim3((unsigned)((dev.T + 255) / 256)), dim3(256), 0, stream, dev);
-  return launch_status();
+  return launch_units_finish(dev, stream);
 }
 
 // `gen` carries the general kernels' workspace pointers (tile table, partials, log-sum-exps),
@@ -428,6 +406,7 @@ sp_status tiled_score(const sp_score_args* a, const ScoreDev& gen, void* extra, 
   dev.lse_out = a->d_lse;
   dev.k_scale = a->d_k_scale;
   dev.seq_limit = 0;
+  dev.groups_per_layer = 0;
   dev.seq_order = nullptr;
   if (seq_supported(a) || wide_supported(a)) {  // one pass over K, a workgroup per (sequence, slab group)
     seq_grouping(a, &dev.slabs_per_group, &dev.n_groups, &dev.groups_per_layer);

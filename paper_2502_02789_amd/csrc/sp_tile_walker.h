@@ -534,5 +534,6 @@ size_t wide_workspace_bytes(const sp_score_args* a);
 sp_status wide_score(const sp_score_args* a, const TiledDev& dev, hipStream_t stream);
 int seq_cu_count();
 void launch_seq_order(const sp_score_args* a, int32_t* order, int limit, hipStream_t stream);
+sp_status launch_units_finish(const TiledDev& dev, hipStream_t stream);
 
 }  // namespace sp
