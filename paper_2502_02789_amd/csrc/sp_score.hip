@@ -353,8 +353,7 @@ sp_status general_score(const sp_score_args* a, hipStream_t stream, bool allow_m
     p.q = q_rot;
   }
 
-  // (the single-pass batch kernels do not look at the tile table)
-  if (!(allow_mfma && tiled_supported(a) && (seq_supported(a) || wide_supported(a))))
+  if (!(allow_mfma && tiled_supported(a) && !tiled_needs_tile_table(a)))
     hipLaunchKernelGGL(tile_table_kernel, dim3(1), dim3(1024), 0, stream, p.B, p.cu, p.tile_cu);
   if (allow_mfma && tiled_supported(a)) {
     const sp_status st = tiled_score(a, p, ws, stream);

@@ -75,12 +75,15 @@ void launch_lse_combine(const ScoreDev& p, hipStream_t stream);
 // tile table, partials and log-sum-exps (`gen`), `extra` is their own workspace part
 bool tiled_supported(const sp_score_args* a);
 size_t tiled_extra_workspace_bytes(const sp_score_args* a);
+bool tiled_needs_tile_table(const sp_score_args* a);
 sp_status tiled_score(const sp_score_args* a, const ScoreDev& gen, void* extra, hipStream_t stream);
 
 // single-pass kernel for batches of short prompts with few query rows per KV head (sp_score_seq.hip)
 bool seq_supported(const sp_score_args* a);
 // ... and with up to 32 of them (sp_score_wide.hip)
 bool wide_supported(const sp_score_args* a);
+// two passes with up to 32 query rows per KV head (sp_score_wide_passes.hip)
+bool wide_passes_supported(const sp_score_args* a);
 
 // single-pass kernel for one long prompt with small teams of workgroups (sp_score_wide_team.hip)
 bool wide_team_supported(const sp_score_args* a);

@@ -330,10 +330,15 @@ static bool keep_mode(const sp_score_args* a) {
   return padded_group(a) * a->N <= kKeepMaxRows && keep_bytes(a) <= SP_TILED_KEEP_MAX_BYTES;
 }
 
+bool tiled_needs_tile_table(const sp_score_args* a) {
+  return !seq_supported(a) && !wide_supported(a) && (keep_mode(a) || !wide_passes_supported(a));
+}
+
 static size_t tiled_main_workspace_bytes(const sp_score_args* a) {
   if (seq_supported(a)) return seq_workspace_bytes(a);
   if (wide_supported(a)) return wide_workspace_bytes(a);
   if (keep_mode(a)) return align_up(keep_bytes(a), 256);
+  if (wide_passes_supported(a)) return wide_passes_workspace_bytes(a);
   int lpg, groups;
   tiled_grouping(a, &lpg, &groups);
   return align_up(sizeof(float) * (size_t)groups * a->N * (size_t)a->T, 256);
@@ -432,6 +437,7 @@ sp_status tiled_score(const sp_score_args* a, const ScoreDev& gen, void* extra, 
   dev.page_stride = gen.k_page_stride;
   for (int l = 0; l < SP_MAX_LAYERS; ++l) dev.k[l] = gen.k[l];
   dev.rope_tiles = nullptr;
+  if (!keep && wide_passes_supported(a)) return wide_passes_score(a, dev, extra, stream);
   if (a->rope_theta > 0.f) {  // the table follows this path's other workspace part
     float4* table = reinterpret_cast<float4*>(static_cast<char*>(extra) + tiled_main_workspace_bytes(a));
     const int64_t n = rope_tile_table_entries(a);

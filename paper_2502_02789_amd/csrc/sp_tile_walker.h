@@ -532,6 +532,8 @@ sp_status seq_score(const sp_score_args* a, const TiledDev& dev, hipStream_t str
 // ... and up to 32 of them (sp_score_wide.hip); what the two share
 size_t wide_workspace_bytes(const sp_score_args* a);
 sp_status wide_score(const sp_score_args* a, const TiledDev& dev, hipStream_t stream);
+size_t wide_passes_workspace_bytes(const sp_score_args* a);
+sp_status wide_passes_score(const sp_score_args* a, const TiledDev& dev, void* extra, hipStream_t stream);
 int seq_cu_count();
 void launch_seq_order(const sp_score_args* a, int32_t* order, int limit, hipStream_t stream);
 sp_status launch_units_finish(const TiledDev& dev, hipStream_t stream);

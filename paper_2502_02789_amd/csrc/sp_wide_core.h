@@ -281,10 +281,13 @@ struct WideKernel {
     }
   }
 
-  // Item IT of the wave's nt items of a slab: its logits into tile[], and the lane's row's statistics over the wave's
-  // keys so far: (rm, rs) = maximum of the base-2 logits (as rounded) and sum of exp2 relative to it
-  template <int IT>
-  __device__ __forceinline__ void item_logits(f32x16* tile, int nt, int M, int buf, float& rm, float& rs) {
+  // 64 words (the 32 of a line, twice) straight into LDS
+  __device__ __forceinline__ void load_line(const float* line, uint32_t dst) const {
+    __builtin_amdgcn_global_load_lds(line + (lane_id() & 31), lds_ptr(dst), 4, 0, 0);
+  }
+
+  // the next item's products with the query rows of buffer `buf`, tile by tile
+  __device__ __forceinline__ void item_products(f32x16* tile, int buf) {
     const int slot = pos & 1;
     // (vector-memory instructions of a wave complete in order; those of the next item are the only key loads behind
     // this one's; result stores there only make the wait stricter)
@@ -294,6 +297,12 @@ struct WideKernel {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot's reads are done: it may be overwritten
     ++pos;
     refill();
+  }
+  // Item IT of the wave's nt items of a slab: its logits into tile[], and the lane's row's statistics over the wave's
+  // keys so far: (rm, rs) = maximum of the base-2 logits (as rounded) and sum of exp2 relative to it
+  template <int IT>
+  __device__ __forceinline__ void item_logits(f32x16* tile, int nt, int M, int buf, float& rm, float& rs) {
+    item_products(tile, buf);
 #pragma unroll
     for (int sub = 0; sub < SUB; ++sub) {
       f32x16& a = tile[sub];
@@ -340,6 +349,14 @@ struct WideKernel {
     const float ref = (m == -INFINITY) ? 0.f : m;
     z = __uint_as_float(sz[0]) * fast_exp2(ma - ref) + __uint_as_float(sz[1]) * fast_exp2(mb - ref);
   }
+  // the barrier at the end of a slab
+  __device__ __forceinline__ void slab_barrier() const {
+    // this wave's share of the next slab's query tile has landed (it was sent before this slab's refills; a wave
+    // whose items in flight are older than that waits for them too)
+    if (sent - pos == 2) wait_vmcnt<2 * kItemLoads>(); else if (sent - pos == 1) wait_vmcnt<kItemLoads>(); else wait_vmcnt<0>();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+  }
   // The rows' statistics over the wave's keys (two half-waves), then over the workgroup's: the lane's row's base-2
   // log-sum-exp (-inf where the workgroup has no keys).  One barrier; on the way the next slab's query tile lands.
   __device__ __forceinline__ float workgroup_lse(float rm, float rs, int buf) {
@@ -347,11 +364,7 @@ struct WideKernel {
     int ln = lane_id();
     if (ln < 32)
       lds_poke64<0>(xchg + ((buf * kTiledWaves + wave) * 32 + ln) * 8, ((uint64_t)__float_as_uint(rs) << 32) | __float_as_uint(rm));
-    // this wave's share of the next slab's query tile has landed (it was sent before this slab's refills; a wave
-    // whose items in flight are older than that waits for them too)
-    if (sent - pos == 2) wait_vmcnt<2 * kItemLoads>(); else if (sent - pos == 1) wait_vmcnt<kItemLoads>(); else wait_vmcnt<0>();
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
+    slab_barrier();
     // a half-wave folds four of the eight waves' pairs, then the halves meet
     const u64x4 v = lds_peek64x4<256>(xchg + ((buf * kTiledWaves + 4 * (ln >> 5)) * 32 + (ln & 31)) * 8);
     float m = -INFINITY, z = 0.f;
