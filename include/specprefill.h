@@ -167,8 +167,8 @@ typedef struct {
                                 wrong.  Nothing else depends on the promise.                            */
   int32_t k_dtype;           /* sp_k_dtype, 0 = bf16.  With SP_K_FP8_E4M3 the layers hold bytes: the strides
                                 (token, head, page) still count ELEMENTS and must then be multiples of 16;
-                                rope_theta must be 0 (SP_EUNSUPPORTED otherwise), and sp_score runs its
-                                two-pass kernels (half the bytes per pass).                              */
+                                rope_theta must be 0 (SP_EUNSUPPORTED otherwise).  The same kernels run as for a
+                                bf16 cache (half the bytes per pass).                                    */
   const float* d_k_scale;    /* fp32 [L, H_kv] scales of an SP_K_FP8_E4M3 cache, or NULL (all 1)          */
 } sp_score_args;
 
@@ -177,7 +177,8 @@ typedef struct {
  * decide which kernels run).  The size grows with T: per-tile row statistics
  * (L*N*H*8 bytes per 64 tokens) always, plus, for batches whose KV heads have at most eight
  * query rows (H/H_kv * N <= 8), 16 or 32 bytes per token, layer and KV head of logits kept
- * between the two passes (0.7 GB for 167K tokens of a 32-layer, 8-KV-head model). */
+ * between the two passes (0.7 GB for 167K tokens of a 32-layer, 8-KV-head model), or, for the
+ * kernels that take up to 32 rows, one to 64 partial results of 4 bytes per token and query. */
 SP_API size_t sp_score_workspace_bytes(const sp_score_args* args);
 
 /* Enqueue the scoring on hip_stream.  Errors: SP_ENULL, SP_EINVAL (shape limits above),

@@ -50,8 +50,8 @@ __device__ __forceinline__ void wait_vmcnt_upto(int n) {
   }
 }
 
-// LDS accesses the compiler does not see as such.  The words touched this way (deposits, counters,
-// fetched log-sum-exps, the running maxima) are never the target of a direct-to-LDS TILE load, so
+// LDS accesses the compiler does not see as such.  The words touched this way (row statistics,
+// fetched log-sum-exps, staged logits) are never the target of a direct-to-LDS TILE load, so
 // there is no reason to wait for the tile loads in flight before touching them -- which an
 // ordinary LDS access would be made to do.  LDS operations of one wave are performed in order.
 __device__ __forceinline__ uint32_t lds_peek(uint32_t lds_addr) {
@@ -69,15 +69,6 @@ __device__ __forceinline__ void lds_poke32(uint32_t lds_addr, uint32_t v) {
 }
 __device__ __forceinline__ void lds_poke128(uint32_t lds_addr, u32x4 v) {
   asm volatile("ds_write_b128 %0, %1" : : "v"(lds_addr), "v"(v) : "memory");
-}
-__device__ __forceinline__ void lds_add(uint32_t lds_addr, uint32_t v) {
-  asm volatile("ds_add_u32 %0, %1" : : "v"(lds_addr), "v"(v) : "memory");
-}
-__device__ __forceinline__ void lds_or(uint32_t lds_addr, uint32_t v) {
-  asm volatile("ds_or_b32 %0, %1" : : "v"(lds_addr), "v"(v) : "memory");
-}
-__device__ __forceinline__ void lds_and(uint32_t lds_addr, uint32_t v) {
-  asm volatile("ds_and_b32 %0, %1" : : "v"(lds_addr), "v"(v) : "memory");
 }
 __device__ __forceinline__ uint64_t lds_peek64(uint32_t lds_addr) {
   uint64_t v;
@@ -97,16 +88,6 @@ __device__ __forceinline__ u64x4 lds_peek64x4(uint32_t lds_addr) {
       : "memory");
   return r;
 }
-__device__ __forceinline__ uint32_t lds_or_rtn(uint32_t lds_addr, uint32_t v) {
-  uint32_t old;
-  asm volatile("ds_or_rtn_b32 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)" : "=v"(old) : "v"(lds_addr), "v"(v) : "memory");
-  return old;
-}
-__device__ __forceinline__ uint32_t lds_add_rtn(uint32_t lds_addr, uint32_t v) {
-  uint32_t old;
-  asm volatile("ds_add_rtn_u32 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)" : "=v"(old) : "v"(lds_addr), "v"(v) : "memory");
-  return old;
-}
 // 16-byte store with agent-scope coherence (written through to where every XCD can see it)
 __device__ __forceinline__ void store128_agent(void* dst, u32x4 v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(dst), "v"(v) : "memory");
@@ -115,42 +96,9 @@ template <int OFF>
 __device__ __forceinline__ void lds_poke64(uint32_t lds_addr, uint64_t v) {
   asm volatile("ds_write_b64 %0, %1 offset:%2" : : "v"(lds_addr), "v"(v), "n"(OFF) : "memory");
 }
-template <int OFF>
-__device__ __forceinline__ void lds_poke32_at(uint32_t lds_addr, uint32_t v) {
-  asm volatile("ds_write_b32 %0, %1 offset:%2" : : "v"(lds_addr), "v"(v), "n"(OFF) : "memory");
-}
-// four words STRIDE bytes apart, one wait for all of them
-template <int STRIDE>
-__device__ __forceinline__ u32x4 lds_peek4(uint32_t lds_addr) {
-  uint32_t a, b, c, d;
-  asm volatile(
-      "ds_read_b32 %0, %4\n\tds_read_b32 %1, %4 offset:%5\n\tds_read_b32 %2, %4 offset:%6\n\t"
-      "ds_read_b32 %3, %4 offset:%7\n\ts_waitcnt lgkmcnt(0)"
-      : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d)
-      : "v"(lds_addr), "n"(STRIDE), "n"(2 * STRIDE), "n"(3 * STRIDE)
-      : "memory");
-  return u32x4{a, b, c, d};
-}
-// four 16-byte reads STRIDE bytes apart, one wait for all of them
-struct u32x4x4 { u32x4 v[4]; };
-template <int STRIDE>
-__device__ __forceinline__ u32x4x4 lds_peek128x4(uint32_t lds_addr) {
-  u32x4x4 r;
-  asm volatile(
-      "ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:%5\n\tds_read_b128 %2, %4 offset:%6\n\t"
-      "ds_read_b128 %3, %4 offset:%7\n\ts_waitcnt lgkmcnt(0)"
-      : "=&v"(r.v[0]), "=&v"(r.v[1]), "=&v"(r.v[2]), "=&v"(r.v[3])
-      : "v"(lds_addr), "n"(STRIDE), "n"(2 * STRIDE), "n"(3 * STRIDE)
-      : "memory");
-  return r;
-}
 // 4-byte store with agent-scope coherence
 __device__ __forceinline__ void store32_agent(void* dst, uint32_t v) {
   asm volatile("global_store_dword %0, %1, off sc1" : : "v"(dst), "v"(v) : "memory");
-}
-template <int OFF>
-__device__ __forceinline__ void lds_fmax(uint32_t lds_addr, float v) {
-  asm volatile("ds_max_f32 %0, %1 offset:%2" : : "v"(lds_addr), "v"(v), "n"(OFF) : "memory");
 }
 // max with the value of lane ^ 1 / lane ^ 2 (inside the quad); folds into v_max_f32_dpp
 __device__ __forceinline__ float max_quad_xor1(float v) {

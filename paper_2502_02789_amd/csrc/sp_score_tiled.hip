@@ -1,5 +1,7 @@
-// Two-pass MFMA scorer for ragged batches (and every other shape the single-pass kernel does
-// not take, as long as the query rows of one KV head fit a 32-column MFMA tile).
+// Two-pass MFMA scorer for what neither the single-pass kernels nor the two passes with the query tile once per
+// workgroup take (batches of unstated length, un-rotated caches, up to eight rows on prompts too long for the registers),
+// as long as the query rows of one KV head fit a 32-column MFMA tile.  Also the routing among the MFMA kernels that
+// wait for nobody.
 //
 // Same quantity as the other scoring kernels: row softmax of the stored queries against the
 // prompt keys (Sec. 3.2 equation of arXiv 2502.02789), max over heads, max/mean over layers,
