@@ -209,8 +209,13 @@ static WidePassPlan make_wide_pass_plan(const sp_score_args* a) {
   WidePassPlan best = {};
   int64_t best_cost = INT64_MAX;
   // The cut into pieces and runs of slabs whose rounds over 256 workgroups are fullest: keys of a round's longest
-  // unit, plus about 200 keys' time for the end of a slab and 300 for that of a unit.  (For a batch the sequences'
-  // lengths are not known here: pieces of fixed size, and only the runs are chosen.)
+  // unit, plus about 200 keys' time for the end of a slab and 300 for that of a unit, plus its results, written and
+  // read back, at three times their bytes.  (Without that term the mean over layers of 24577 keys was cut into 256
+  // parts of layers for 8-bit keys, 407 us against 294 with 32, and 16 layers of d = 64 into 128, 202 against 157.
+  // Few KV heads are better off here than on the tiled kernels even where results outweigh keys: 16 layers, 2 KV
+  // heads of 8-bit d = 64, mean: 55 us against 98.)  For a batch the sequences' lengths are not known here: pieces of
+  // fixed size, and only the runs are chosen.
+  const int64_t result_bytes = 3 * 4 * a->N, key_bytes = a->d * (a->k_dtype == SP_K_FP8_E4M3 ? 1 : 2);
   const int n0 = a->B > 1 ? 0 : (int)((a->T + kPassMaxKeys - 1) / kPassMaxKeys);
   for (int extra = 0; extra < (a->B > 1 ? 1 : 8); ++extra) {
     WidePassPlan pl = {};
@@ -221,7 +226,7 @@ static WidePassPlan make_wide_pass_plan(const sp_score_args* a) {
       if (mean && a->H_kv % per != 0) continue;
       const int groups = (slabs + per - 1) / per;
       const int64_t rounds = ((int64_t)pl.slots * groups + 255) / 256;
-      const int64_t cost = rounds * (per * (keys + 200) + 300);
+      const int64_t cost = rounds * (per * (keys + 200) + 300 + keys * result_bytes / key_bytes);
       if (cost < best_cost) {
         best_cost = cost;
         best = pl;
@@ -242,7 +247,10 @@ bool wide_passes_supported(const sp_score_args* a) {
   if (a->B > 1 && a->max_seqlen <= 0) return false;
   if (a->H / a->H_kv > 8 || (a->N << wide_lg(a)) > 32) return false;
   if (a->k_dtype == SP_K_FP8_E4M3 && a->d_block_table && a->page_size < (a->d == 64 ? 16 : 8)) return false;
-  return a->k_token_stride <= INT32_MAX / 256;  // (a ring slot's keys must span less than 2 GiB)
+  if (a->k_token_stride > INT32_MAX / 256) return false;  // (a ring slot's keys must span less than 2 GiB)
+  // results of at most 16 GiB, as for kept logits; the tiled kernels beyond (the plan is made only where it matters)
+  constexpr size_t kMostBytes = (size_t)16 << 30;
+  return (size_t)a->L * a->H_kv * a->N * 128 * wide_tiles(a) <= kMostBytes / 2 || wide_passes_workspace_bytes(a) <= kMostBytes;
 }
 
 static size_t pass_lines_bytes(const sp_score_args* a, const WidePassPlan& pl) { return align_up((size_t)a->L * a->H_kv * pl.slots * 128, 256); }

@@ -20,6 +20,7 @@ MODES = [orc.LAYER_MAX, orc.LAYER_MEAN]
     dict(tokens=4097, L=3, H=6, H_kv=2, N=5, d=128),     # three heads padded to four, two pieces
     dict(tokens=12345, L=2, H=64, H_kv=8, N=4, d=64),    # eight heads per KV head
     dict(tokens=8225, L=5, H=8, H_kv=1, N=3, d=128),     # few slabs, ragged pieces
+    dict(tokens=5001, L=3, H=4, H_kv=1, N=8, d=64),      # results that outweigh the keys
 ])
 def test_one_prompt_on_a_shared_device(shape, mode):
     shape = dict(shape)
