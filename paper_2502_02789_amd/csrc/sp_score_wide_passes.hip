@@ -184,7 +184,8 @@ __global__ __launch_bounds__(64) void wide_pass_combine_kernel(const WidePassDev
   for (int i = ln >> 5; i < pieces; i += 2) {
     const float v = src[(int64_t)i * 32];
     const float mn = fmaxf(m, v);
-    z = z * fast_exp2(m - mn) + fast_exp2(v - mn);
+    const float ref = mn == -INFINITY ? 0.f : mn;  // (a piece whose logits of this row all overflowed)
+    z = z * fast_exp2(m - ref) + fast_exp2(v - ref);
     m = mn;
   }
   const float pm = __shfl_xor(m, 32, kWave), pz = __shfl_xor(z, 32, kWave);

@@ -319,7 +319,8 @@ struct WideKernel {
 #pragma unroll
       for (int i = 1; i < 16; ++i) tm = fmaxf(tm, a[i]);
       const float m_new = fmaxf(rm, tm * c2);
-      const float off = (IT == 0 && m_new == -INFINITY) ? 0.f : -m_new;
+      // (-inf: no key of the lane so far, or none whose logit fits fp32)
+      const float off = (m_new == -INFINITY) ? 0.f : -m_new;
       float s0 = rs * fast_exp2(rm + off), s1 = 0.f, s2 = 0.f, s3 = 0.f;
 #pragma unroll
       for (int i = 0; i < 16; i += 4) {
