@@ -153,8 +153,8 @@ __global__ __launch_bounds__(64) void lse_partial_kernel(const ScoreDev p) {
       const int h = g * p.G + j;
       const uint16_t* qp = p.q + ((((int64_t)l * p.B + b) * p.N + n) * p.H + h) * D;
       const float s = valid ? scale * dot_row<D>(qp, kf) : -INFINITY;
-      const float m = wave_max(s);                       // finite: lane 0 of a tile is always valid
-      const float e = valid ? expf(s - m) : 0.f;
+      const float m = wave_max(s);                       // (-inf: none of the tile's logits fits fp32)
+      const float e = valid && m != -INFINITY ? expf(s - m) : 0.f;
       const float z = wave_sum(e);
       if (lane == 0) p.part[((int64_t)(l * p.N + n) * p.H + h) * p.max_tiles + tile] = make_float2(m, z);
     }
@@ -181,7 +181,8 @@ __global__ __launch_bounds__(256) void lse_combine_kernel(const ScoreDev p, int 
   for (int t = t0 + lane; t < t1; t += LANES) {
     const float2 v = part[t];
     const float mn = fmaxf(m, v.x);
-    z = z * expf(m - mn) + v.y * expf(v.x - mn);  // first step: z = 0 * exp(-inf) = 0
+    const float ref = (mn == -INFINITY) ? 0.f : mn;  // (a tile whose logits of this row all overflowed)
+    z = z * expf(m - ref) + v.y * expf(v.x - ref);  // first step: z = 0 * exp(-inf) = 0
     m = mn;
   }
   float mw = m;
