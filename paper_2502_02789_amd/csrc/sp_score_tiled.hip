@@ -413,7 +413,7 @@ sp_status tiled_score(const sp_score_args* a, const ScoreDev& gen, void* extra, 
   dev.lse_out = a->d_lse;
   dev.k_scale = a->d_k_scale;
   dev.seq_limit = 0;
-  dev.groups_per_layer = 0;
+  dev.groups_per_layer = dev.plain_groups = 0;
   dev.seq_order = nullptr;
   if (seq_supported(a) || wide_supported(a)) {  // one pass over K, a workgroup per (sequence, slab group)
     seq_grouping(a, &dev.slabs_per_group, &dev.n_groups, &dev.groups_per_layer);

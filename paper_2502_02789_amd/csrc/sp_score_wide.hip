@@ -217,7 +217,10 @@ __global__ __launch_bounds__(THREADS) void wide_finish_kernel(const TiledDev p, 
     const float* src = p.group_scores + ((int64_t)tile * p.n_groups * p.N + n) * 32 + part * KEYS + quad * 4;
     const int64_t step = (int64_t)p.N * 32;
     if (mean && p.groups_per_layer > 0) {  // the groups of a layer hold the log2 of its maxima over their KV heads; the layers' maxima add up
-      for (int l = g0; l < p.L; l += per) {
+      for (int g = g0; g < p.plain_groups; g += per) v += *reinterpret_cast<const f32x4*>(src + g * step);
+      const int layers = (p.n_groups - p.plain_groups) / p.groups_per_layer;
+      src += p.plain_groups * step;
+      for (int l = g0; l < layers; l += per) {
         f32x4 m = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll 4
         for (int j = 0; j < p.groups_per_layer; ++j) {

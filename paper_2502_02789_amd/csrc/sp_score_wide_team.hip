@@ -15,9 +15,9 @@
 //     travel, its logits in registers of their own: 32K keys 350 -> 339 us, 128K 1378 -> 1352.  (Without any exchange,
 //     wrong results: 333 and 1248; with an exchange four times as often hidden behind three slabs of a quarter of
 //     the keys each, and the query tile fetched once per wave, as before: 349 and 1570.)
-//   * 256 / P teams take the slabs in runs; a team's maxima go out as one group of the result array, merged by the
-//     kernel that merges the units of short prompts.  Mean over layers: a team owns whole layers and adds their
-//     maxima up (or, with more teams than layers, a part of one layer).
+//   * 256 / P teams are dealt the slabs in turn, a few at a time (sp_wide_team_plan.h); a team's maxima go out as one
+//     group of the result array, merged by the kernel that merges the units of short prompts.  Mean over layers: whole
+//     layers in turn, a team adds their maxima up; the layers left over in parts, each a group of its own.
 //
 // The lines exist twice: a call works in copy (epoch mod 2) and puts "empty" back into the other one as it publishes,
 // so the next call finds it clean; a small kernel sets that up in front of a call that cannot rely on the previous one
@@ -32,21 +32,18 @@
 #include <mutex>
 
 #include "sp_wide_core.h"
+#include "sp_wide_team_plan.h"
 
 namespace sp {
 
-constexpr int kWideTeamWGs = 256;
-constexpr int kWideTeamTiles = 8;        // 32-key tiles per wave
-constexpr int kWideTeamKeys = kWideTeamTiles * 32 * kTiledWaves;
-constexpr int kWideTeamMaxPartners = 64;
+static_assert(kWideTeamWaves == kTiledWaves, "a member's keys are those of its waves");
 constexpr uint32_t kEmptyLine = 0xffffffffu;
 constexpr int kDefaultSpinBudget = 1 << 16;  // polls per workgroup and call before giving up (~0.1 s)
 static std::atomic<int> g_spin_budget{kDefaultSpinBudget};
 
 struct WideTeamDev : TiledDev {
   int lgP, chunk;          // members of a team (a power of two), keys of a member
-  int sum;                 // units hold whole layers, whose maxima (as probabilities) are added up
-  int n_units;             // runs of slabs_per_group slabs; team t takes units t, t + teams, ...
+  WideTeamDeal deal;
   int spin_budget;
   uint32_t* lines;         // two copies of [slab][member][32]
   size_t copy_words;
@@ -74,8 +71,11 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
   // (measured, whole call: 32K keys, 16 members, next to each other on one die 352 us, over all dies 363; 128K keys, 64
   // members, on two dies 1457 us, over all dies 1390)
   const int P = 1 << p.lgP, place = P > 32 ? (int)blockIdx.x : (int)(blockIdx.x & 7) * (kWideTeamWGs / 8) + (int)(blockIdx.x >> 3);
-  const int team = place >> p.lgP, member = place & (P - 1), teams = kWideTeamWGs >> p.lgP;
-  if (team >= p.n_units) return;
+  const int team = place >> p.lgP, member = place & (P - 1);
+  const WideTeamDeal& deal = p.deal;
+  const bool mean = p.layer_reduce != SP_LAYER_MAX;
+  int q = 0, s = deal.start(team, 0), s_end = deal.end(0, s);
+  if (s >= deal.n_slabs) return;
   const uint32_t epoch = __builtin_amdgcn_readfirstlane(p.status[2]);  // (turned by the merge kernel)
   uint32_t* const lines_cur = p.lines + (size_t)(epoch & 1u) * p.copy_words;
   uint32_t* const lines_nxt = p.lines + (size_t)(~epoch & 1u) * p.copy_words;
@@ -83,11 +83,9 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
   const int key0 = member * p.chunk;
   const int M = max(0, min((int)p.T - key0, p.chunk));
   const int nt = w.items_of(M);
-  const int n_slabs = p.L * p.H_kv;
   int polls = p.spin_budget;
   bool expired = polls <= 0;
 
-  int u = team, s = u * p.slabs_per_group, s_end = min(n_slabs, s + p.slabs_per_group);
   int l = s / p.H_kv, g = s - l * p.H_kv;
   w.ah = {w.slab_keys(l, g, 0), 0, key0, M, nt};
   w.issue_queries(l, g, 0, 0);
@@ -109,20 +107,19 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
 #pragma unroll
     for (int k = 0; k < KEEP; ++k) run[t][k] = -INFINITY;
   int buf = 0;
-  bool first_layer = true;  // of the unit
 #pragma unroll 1
   for (;;) {
-    // the slab behind this one: of this unit or the team's next one
-    int nu = u, ns = s + 1, ns_end = s_end, nl = l, ng = g + 1;
+    // the slab behind this one: of this run or the team's next one
+    int nq = q, ns = s + 1, ns_end = s_end, nl = l, ng = g + 1;
     if (ng == p.H_kv) { ng = 0; ++nl; }
     if (ns == s_end) {
-      nu = u + teams;
-      ns = nu * p.slabs_per_group;
-      ns_end = min(n_slabs, ns + p.slabs_per_group);
+      ++nq;
+      ns = deal.start(team, nq);
+      ns_end = deal.end(nq, ns);
       nl = ns / p.H_kv;
       ng = ns - nl * p.H_kv;
     }
-    const bool more = nu < p.n_units;
+    const bool more = ns < deal.n_slabs;
     w.nx.left = 0;
     if (more) {
       w.nx = {w.slab_keys(nl, ng, 0), 0, key0, M, nt};
@@ -231,12 +228,15 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
         for (int k = 0; k < KEEP; ++k) run[t][k] = fmaxf(run[t][k], y[k]);
       }
     });
-    // The unit's result; where units hold whole layers (p.sum) each layer's maxima join the sum in the result array
-    // (once every H_kv slabs: registers for the sums would be a quarter of what the logits leave).
-    if (s + 1 == s_end || (p.sum && g == p.H_kv - 1)) {
+    // The results.  Maximum over layers: one group per team, at its end.  Mean: a run of a round is a layer, whose
+    // maxima join the sum in the team's group (registers for the sums would be a quarter of what the logits leave); a
+    // part of a layer has a group of its own behind the teams'.
+    if (mean ? s + 1 == s_end : !more) {
+      const bool sum = mean && q < deal.rounds;
+      const int group = !mean || sum ? team : p.plain_groups + (s - deal.base()) / deal.part;
       const int q_n = W::lane_id() & (W::NS - 1);
       const int64_t step = (int64_t)p.n_groups * p.N * 32;  // from tile to tile
-      float* const out = p.group_scores + ((int64_t)((key0 >> 5) + SUB * (w.wave + (nt - 1) * kTiledWaves)) * p.n_groups + u) * p.N * 32 +
+      float* const out = p.group_scores + ((int64_t)((key0 >> 5) + SUB * (w.wave + (nt - 1) * kTiledWaves)) * p.n_groups + group) * p.N * 32 +
                          q_n * 32 + w.fold_key();
       auto place_of = [&](int t) __attribute__((always_inline)) {
         return reinterpret_cast<vkeep*>(out + (t % SUB - t / SUB * (SUB * kTiledWaves)) * step);
@@ -245,12 +245,12 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
       auto live = [&](int t) __attribute__((always_inline)) {
         return t / SUB < nt && (SUB == 1 || t >= SUB || (w.wave + (nt - 1) * kTiledWaves) * W::KPI + t % SUB * 32 < M);
       };
-      if (p.sum) {
+      if (sum) {
 #pragma unroll
         for (int t = 0; t < MAXT; ++t)
 #pragma unroll
           for (int k = 0; k < KEEP; ++k) run[t][k] = fast_exp2(run[t][k]);
-        if (!first_layer && q_n < p.N) {
+        if (q > 0 && q_n < p.N) {
 #pragma unroll
           for (int t0 = 0; t0 < MAXT; t0 += 4) {  // (four tiles' loads at a time)
             vkeep old[4];
@@ -269,11 +269,10 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
 #pragma unroll
         for (int k = 0; k < KEEP; ++k) run[t][k] = -INFINITY;
       }
-      first_layer = s + 1 == s_end;
     }
     w.end_slab();
     if (!more) break;
-    u = nu; s = ns; s_end = ns_end; l = nl; g = ng;
+    q = nq; s = ns; s_end = ns_end; l = nl; g = ng;
     buf ^= 1;
   }
   if (w.wave == 0 && expired && W::lane_id() == 0) atomicOr(p.status + (epoch & 1u), 1u);
@@ -283,57 +282,20 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
 // ---------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------
-struct WideTeamPlan {
-  bool ok;
-  int lgP, chunk, per, n_units, gpl;  // gpl > 0: units are parts of layers whose maxima the merge adds up
-  bool sum;
-  size_t copy_bytes, result_bytes;
-};
-
-static WideTeamPlan make_wide_team_plan(const sp_score_args* a) {
-  WideTeamPlan pl = {};
-  if (a->B != 1 || a->rope_theta > 0.f || a->T <= 0 || a->T > (int64_t)kWideTeamMaxPartners * kWideTeamKeys) return pl;
-  if (a->H / a->H_kv > 8 || (a->N << wide_lg(a)) > 32) return pl;
-  if (a->k_dtype == SP_K_FP8_E4M3 && a->d_block_table && a->page_size < (a->d == 64 ? 16 : 8)) return pl;
-  if (a->k_token_stride > (INT32_MAX / 256)) return pl;  // (a ring slot's keys must span less than 2 GiB)
-  const int slabs = a->L * a->H_kv;
-  if (slabs < 8) return pl;
-  int lgP = 1;
-  while (((int64_t)kWideTeamKeys << lgP) < a->T) ++lgP;
-  // (fewer slabs than teams: more members per team instead, as long as each still has a wave's worth of keys)
-  while ((kWideTeamWGs >> lgP) > slabs && (1 << lgP) < kWideTeamMaxPartners) ++lgP;
-  const int P = 1 << lgP, teams = kWideTeamWGs >> lgP;
-  pl.lgP = lgP;
-  pl.chunk = (int)(((a->T + P - 1) / P + 255) / 256 * 256);
-  if (a->layer_reduce == SP_LAYER_MEAN) {
-    if (a->L >= teams) {  // whole layers, one run per team
-      pl.sum = true;
-      pl.per = (a->L + teams - 1) / teams * a->H_kv;
-    } else {              // the largest part of a layer that still gives every team one
-      int per = 1;
-      for (int cand = a->H_kv; cand >= 1; --cand)
-        if (a->H_kv % cand == 0 && a->L * (a->H_kv / cand) >= teams) { per = cand; break; }
-      pl.per = per;
-      pl.gpl = a->H_kv / per;
-    }
-  } else {
-    pl.per = (slabs + teams - 1) / teams;
-  }
-  pl.n_units = (slabs + pl.per - 1) / pl.per;
-  pl.copy_bytes = (size_t)slabs * P * 128;
-  pl.result_bytes = align_up(sizeof(float) * 32 * (size_t)pl.n_units * a->N * wide_tiles(a), 256);
-  pl.ok = true;
-  return pl;
+static WideTeamPlan make_plan(const sp_score_args* a) { return make_wide_team_plan(a, wide_lg(a)); }
+static size_t copy_bytes(const WideTeamPlan& pl) { return (size_t)pl.deal.n_slabs * 128 << pl.lgP; }
+static size_t result_bytes(const WideTeamPlan& pl, const sp_score_args* a) {
+  return align_up(sizeof(float) * 32 * (size_t)pl.n_groups * a->N * wide_tiles(a), 256);
 }
 
-bool wide_team_supported(const sp_score_args* a) { return make_wide_team_plan(a).ok && seq_cu_count() >= kWideTeamWGs; }
+bool wide_team_supported(const sp_score_args* a) { return make_plan(a).ok && seq_cu_count() >= kWideTeamWGs; }
 size_t wide_team_workspace_bytes(const sp_score_args* a) {
-  const WideTeamPlan pl = make_wide_team_plan(a);
-  return pl.ok ? align_up(2 * pl.copy_bytes, 256) + pl.result_bytes + 256 : 0;
+  const WideTeamPlan pl = make_plan(a);
+  return pl.ok ? align_up(2 * copy_bytes(pl), 256) + result_bytes(pl, a) + 256 : 0;
 }
 size_t wide_team_status_offset(const sp_score_args* a) {
-  const WideTeamPlan pl = make_wide_team_plan(a);
-  return pl.ok ? align_up(2 * pl.copy_bytes, 256) + pl.result_bytes : 0;
+  const WideTeamPlan pl = make_plan(a);
+  return pl.ok ? align_up(2 * copy_bytes(pl), 256) + result_bytes(pl, a) : 0;
 }
 
 template <int D, int LG, bool FP8, bool PAGED>
@@ -371,7 +333,7 @@ static sp_status wide_team_by_kind(const sp_score_args* a, const WideTeamDev& de
 }
 
 sp_status wide_team_score(const sp_score_args* a, hipStream_t stream) {
-  const WideTeamPlan pl = make_wide_team_plan(a);
+  const WideTeamPlan pl = make_plan(a);
   if (!pl.ok) return SP_EUNSUPPORTED;
   WideTeamDev dev = {};
   dev.B = 1; dev.N = a->N; dev.L = a->L; dev.H = a->H; dev.H_kv = a->H_kv; dev.G = a->H / a->H_kv;
@@ -384,22 +346,23 @@ sp_status wide_team_score(const sp_score_args* a, hipStream_t stream) {
   dev.q = static_cast<const uint16_t*>(a->d_q);
   dev.cu = a->d_cu_seqlens; dev.n_valid = a->d_n_valid;
   dev.scores = a->d_scores; dev.lse_out = a->d_lse;
-  dev.slabs_per_group = pl.per; dev.n_groups = dev.n_units = pl.n_units; dev.groups_per_layer = pl.gpl;
+  dev.deal = pl.deal;
+  dev.n_groups = pl.n_groups; dev.plain_groups = pl.plain_groups; dev.groups_per_layer = pl.gpl;
   dev.block_table = a->d_block_table;
   while (a->d_block_table && (1 << dev.lg_page) < a->page_size) ++dev.lg_page;
   dev.blocks_per_seq = a->blocks_per_seq;
   dev.page_stride = a->k_page_stride;
   dev.k_scale = a->d_k_scale;
   for (int l = 0; l < a->L; ++l) dev.k[l] = static_cast<const uint16_t*>(a->k_layers[l]);
-  dev.lgP = pl.lgP; dev.chunk = pl.chunk; dev.sum = pl.sum;
+  dev.lgP = pl.lgP; dev.chunk = pl.chunk;
   dev.spin_budget = g_spin_budget.load(std::memory_order_relaxed);
   char* ws = static_cast<char*>(a->d_workspace);
   dev.lines = reinterpret_cast<uint32_t*>(ws);
-  dev.copy_words = pl.copy_bytes / 4;
-  dev.group_scores = reinterpret_cast<float*>(ws + align_up(2 * pl.copy_bytes, 256));
+  dev.copy_words = copy_bytes(pl) / 4;
+  dev.group_scores = reinterpret_cast<float*>(ws + align_up(2 * copy_bytes(pl), 256));
   dev.status = reinterpret_cast<uint32_t*>(ws + wide_team_status_offset(a));
   if (!(a->flags & SP_SCORE_WORKSPACE_KEPT)) {
-    const size_t n_vec = pl.copy_bytes / 16;
+    const size_t n_vec = copy_bytes(pl) / 16;
     hipLaunchKernelGGL(wide_team_fill_kernel, dim3((unsigned)std::min<size_t>((n_vec + 255) / 256, 1024)), dim3(256), 0, stream,
                        reinterpret_cast<uint4*>(ws), n_vec, dev.status);
     if (hipGetLastError() != hipSuccess) return SP_ELAUNCH;

@@ -42,6 +42,7 @@ struct TiledDev {
   const int32_t* seq_order;  // single-pass batch kernel: sequence numbers, longest first
   int slabs_per_group;   // single-pass batch kernel: (layer, KV head) slabs per unit (n_groups of them cover the L * H_kv slabs)
   int groups_per_layer;  // single-pass batch kernel, mean over layers with units smaller than a layer: slab groups per layer, else 0
+  int plain_groups;      // ... that many groups before them hold sums over whole layers
   int seq_limit;         // single-pass batch kernel: sequences longer than this many keys are not scored (NaN), 0 = no limit
   const int32_t* block_table;  // paged cache: [B][blocks_per_seq] page numbers, else null
   int lg_page, blocks_per_seq;

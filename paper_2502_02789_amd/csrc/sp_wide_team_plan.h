@@ -1,0 +1,100 @@
+// How the single-pass kernel for one long prompt (sp_score_wide_team.hip) cuts a call: the prompt into the members of a
+// team, the (layer, KV head) slabs into the teams' runs.  Plain C++ (the host's sizes and the kernel's walk come from the
+// same functions, and a test without a GPU goes through them).
+#pragma once
+
+#include <stdint.h>
+
+#include <algorithm>
+
+#include "specprefill.h"
+
+#ifdef __HIPCC__
+#define SP_PLAN_FN __host__ __device__ __forceinline__
+#else
+#define SP_PLAN_FN inline
+#endif
+
+namespace sp {
+
+constexpr int kWideTeamWGs = 256;
+constexpr int kWideTeamWaves = 8;
+constexpr int kWideTeamTiles = 8;        // 32-key tiles per wave
+constexpr int kWideTeamKeys = kWideTeamTiles * 32 * kWideTeamWaves;
+constexpr int kWideTeamMaxPartners = 64;
+
+// The slabs are dealt out to the teams in turn: `rounds` rounds of `run` slabs to each team, the others in parts of
+// `part`, again in turn.
+struct WideTeamDeal {
+  int teams, n_slabs, run, rounds, part;
+  SP_PLAN_FN int base() const { return rounds * run * teams; }  // slabs of the whole rounds
+  // team `team`'s q-th run: where it starts (n_slabs or more: there is none) and ends
+  SP_PLAN_FN int start(int team, int q) const {
+    return q < rounds ? (q * teams + team) * run : base() + ((q - rounds) * teams + team) * part;
+  }
+  SP_PLAN_FN int end(int q, int start_) const {
+    const int e = start_ + (q < rounds ? run : part);
+    return e < n_slabs ? e : n_slabs;
+  }
+};
+
+struct WideTeamPlan {
+  bool ok;
+  int lgP, chunk;          // members of a team (a power of two), keys of a member
+  WideTeamDeal deal;
+  // Groups of the result array.  Maximum over layers: one per team that has a slab.  Mean: the teams' sums over whole
+  // layers (plain_groups of them), then the parts of the layers left, gpl of a layer.
+  int n_groups, plain_groups, gpl;
+};
+
+// Slabs of a run (maximum over layers).  What the teams read at a time is spread over so many layers: with one run
+// per team (16 of them at 32K keys, each in two layers of its own) the first pass over new buffers met 1 GB of pages at
+// once; with single slabs the teams crowd into one or two layers.  First / later pass of 32K keys (32 layers, 8 KV
+// heads, d = 128, eight queries) in us: one slab 403 / 356, two 386 / 341, four 385 / 340, eight 393 / 339, all sixteen
+// 429 / 340; 8-bit keys 312 / 259, 290 / 244, 283 / 236, 300 / 238, 300 / 239; 128K keys 1537 / 1409, 1478 / 1345,
+// 1486 / 1311, 1556 / 1370, 1535 / 1360 (all 128).
+constexpr int kWideTeamRun = 4;
+
+inline WideTeamPlan make_wide_team_plan(const sp_score_args* a, int lg_heads) {
+  WideTeamPlan pl = {};
+  if (a->B != 1 || a->rope_theta > 0.f || a->T <= 0 || a->T > (int64_t)kWideTeamMaxPartners * kWideTeamKeys) return pl;
+  if (a->H / a->H_kv > 8 || (a->N << lg_heads) > 32) return pl;
+  if (a->k_dtype == SP_K_FP8_E4M3 && a->d_block_table && a->page_size < (a->d == 64 ? 16 : 8)) return pl;
+  if (a->k_token_stride > (INT32_MAX / 256)) return pl;  // (a ring slot's keys must span less than 2 GiB)
+  const int slabs = a->L * a->H_kv;
+  if (slabs < 8) return pl;
+  int lgP = 1;
+  while (((int64_t)kWideTeamKeys << lgP) < a->T) ++lgP;
+  // (fewer slabs than teams: more members per team instead, as long as each still has a wave's worth of keys)
+  while ((kWideTeamWGs >> lgP) > slabs && (1 << lgP) < kWideTeamMaxPartners) ++lgP;
+  const int P = 1 << lgP, teams = kWideTeamWGs >> lgP;
+  pl.lgP = lgP;
+  pl.chunk = (int)(((a->T + P - 1) / P + 255) / 256 * 256);
+  WideTeamDeal& d = pl.deal;
+  d.teams = teams;
+  d.n_slabs = slabs;
+  if (a->layer_reduce == SP_LAYER_MEAN) {
+    // whole layers, in turn, where every team gets one; else the largest part of a layer that still gives every team one
+    int part = a->H_kv;
+    if (a->L < teams) {
+      part = 1;
+      for (int cand = a->H_kv; cand >= 1; --cand)
+        if (a->H_kv % cand == 0 && a->L * (a->H_kv / cand) >= teams) { part = cand; break; }
+    }
+    d.run = a->H_kv;
+    d.rounds = a->L / teams;
+    d.part = part;
+    pl.plain_groups = d.rounds > 0 ? teams : 0;
+    pl.gpl = a->H_kv / part;
+    pl.n_groups = pl.plain_groups + (a->L - d.rounds * teams) * pl.gpl;
+  } else {
+    d.run = std::min(kWideTeamRun, (slabs + teams - 1) / teams);
+    d.rounds = slabs / (d.run * teams);
+    d.part = std::max(1, (slabs - d.base() + teams - 1) / teams);
+    pl.n_groups = d.rounds > 0 ? teams : (slabs + d.part - 1) / d.part;
+  }
+  pl.ok = true;
+  return pl;
+}
+
+}  // namespace sp
