@@ -102,3 +102,18 @@ def test_maximum_over_layers_even_shares_close_together(walk):
         for k in range(counts.max()):
             at = np.flatnonzero(p["place"] == k)
             assert at.max() - at.min() < 4 * p["teams"], shape
+
+
+def test_mean_over_layers_even_shares(walk):
+    """Layer counts that the number of teams does not divide: what a busiest team has beyond its share costs no more than
+    the results that even shares would cost (a part of a layer is a result of its own: eight times its bytes in keys)."""
+    for L in range(1, 129):
+        for T in (3073, 4000, 9000, 16000, 32768, 131072):
+            for bits in (16, 8):
+                p = walk(L=L, T=T, layer_reduce=sp.SP_LAYER_MEAN, k_dtype=sp.SP_K_FP8_E4M3 if bits == 8 else sp.SP_K_BF16)
+                share = -(-p["slabs"] // p["teams"])
+                busiest = np.bincount(p["team"], minlength=p["teams"]).max()
+                result = 8 * 4 * 8 / (128 * bits / 8)               # slabs' time for a part's result
+                assert busiest <= share + 1 + result * share, (L, T, bits, busiest, share)
+                if L >= p["teams"]:                                 # whole layers to everybody, few left over
+                    assert busiest <= share + 4, (L, T, bits, busiest, share)
