@@ -367,9 +367,10 @@ sp_status wide_score(const sp_score_args* a, const TiledDev& dev_, hipStream_t s
 
 sp_status launch_wide_finish(const TiledDev& dev, unsigned tiles, uint32_t* status, hipStream_t stream) {
   // Two workgroups per 32-key tile where the tiles alone would not give every compute unit two; small workgroups
-  // where a tile has few rows to read (128K keys in four groups of eight queries: 24 us with 1024 threads).
+  // where a tile has few rows to read (128K keys in four groups of eight queries: 24 us with 1024 threads) and at most
+  // eight queries (a thread per key and query).
   if (tiles < 512) hipLaunchKernelGGL((wide_finish_kernel<16, 1024>), dim3(2 * tiles), dim3(1024), 0, stream, dev, status);
-  else if (dev.n_groups * dev.N > 256) hipLaunchKernelGGL((wide_finish_kernel<32, 1024>), dim3(tiles), dim3(1024), 0, stream, dev, status);
+  else if (dev.n_groups * dev.N > 256 || dev.N > 8) hipLaunchKernelGGL((wide_finish_kernel<32, 1024>), dim3(tiles), dim3(1024), 0, stream, dev, status);
   else hipLaunchKernelGGL((wide_finish_kernel<32, 256>), dim3(tiles), dim3(256), 0, stream, dev, status);
   return launch_status();
 }

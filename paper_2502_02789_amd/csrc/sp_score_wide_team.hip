@@ -3,7 +3,8 @@
 // Same quantity as the other scoring kernels: row softmax of the stored queries against the prompt keys
 // (Sec. 3.2 equation of arXiv 2502.02789), max over heads, max/mean over layers, mean over queries (Sec. 3.2.2).
 // Stream, products, statistics and the fold over heads are those of sp_score_wide.hip (sp_wide_core.h).  There one
-// workgroup owns a whole prompt; a longer prompt is cut into P pieces of up to 2048 keys, and the P workgroups of a
+// workgroup owns a whole prompt; a longer prompt is cut into P pieces of up to 2048 keys (1024 with more than eight
+// queries), and the P workgroups of a
 // team walk together over the team's (layer, KV head) slabs:
 //
 //   * per slab every member publishes ONE 128-byte line, the base-2 log-sum-exps of its keys for the 32 rows (agent
@@ -62,7 +63,7 @@ template <int D, int LG, bool FP8, bool PAGED>
 __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeamDev p) {
   extern __shared__ __align__(1024) unsigned char smem[];
   using W = WideKernel<D, LG, FP8, PAGED>;
-  constexpr int KEEP = W::KEEP, SUB = W::SUB, MAXT = kWideTeamTiles;
+  constexpr int KEEP = W::KEEP, SUB = W::SUB, MAXT = wide_team_tiles(LG);
   using vkeep = typename W::vkeep;
   W w(p, smem);
   const uint32_t lse_lds = (uint32_t)reinterpret_cast<uintptr_t>(smem) + W::kSmem;  // 32 row log-sum-exps
@@ -239,7 +240,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
       float* const out = p.group_scores + ((int64_t)((key0 >> 5) + SUB * (w.wave + (nt - 1) * kTiledWaves)) * p.n_groups + group) * p.N * 32 +
                          q_n * 32 + w.fold_key();
       auto place_of = [&](int t) __attribute__((always_inline)) {
-        return reinterpret_cast<vkeep*>(out + (t % SUB - t / SUB * (SUB * kTiledWaves)) * step);
+        return out + (t % SUB - t / SUB * (SUB * kTiledWaves)) * step;
       };
       // (sub-tiles of the ragged item that lie beyond the prompt have no place in the result array)
       auto live = [&](int t) __attribute__((always_inline)) {
@@ -250,22 +251,23 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
         for (int t = 0; t < MAXT; ++t)
 #pragma unroll
           for (int k = 0; k < KEEP; ++k) run[t][k] = fast_exp2(run[t][k]);
+        constexpr int STEP = LG == 1 ? 2 : 4;  // tiles whose loads go out together
         if (q > 0 && q_n < p.N) {
 #pragma unroll
-          for (int t0 = 0; t0 < MAXT; t0 += 4) {  // (four tiles' loads at a time)
-            vkeep old[4];
+          for (int t0 = 0; t0 < MAXT; t0 += STEP) {
+            vkeep old[STEP];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (live(t0 + i)) old[i] = *place_of(t0 + i);
+            for (int i = 0; i < STEP; ++i)
+              if (live(t0 + i)) old[i] = W::load_keep(place_of(t0 + i));
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < STEP; ++i)
               if (live(t0 + i)) run[t0 + i] += old[i];
           }
         }
       }
 #pragma unroll
       for (int t = 0; t < MAXT; ++t) {
-        if (q_n < p.N && live(t)) __builtin_nontemporal_store(run[t], place_of(t));
+        if (q_n < p.N && live(t)) W::store_keep(place_of(t), run[t]);
 #pragma unroll
         for (int k = 0; k < KEEP; ++k) run[t][k] = -INFINITY;
       }
@@ -282,19 +284,18 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
 // ---------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------
-static WideTeamPlan make_plan(const sp_score_args* a) { return make_wide_team_plan(a, wide_lg(a)); }
 static size_t copy_bytes(const WideTeamPlan& pl) { return (size_t)pl.deal.n_slabs * 128 << pl.lgP; }
 static size_t result_bytes(const WideTeamPlan& pl, const sp_score_args* a) {
   return align_up(sizeof(float) * 32 * (size_t)pl.n_groups * a->N * wide_tiles(a), 256);
 }
 
-bool wide_team_supported(const sp_score_args* a) { return make_plan(a).ok && seq_cu_count() >= kWideTeamWGs; }
+bool wide_team_supported(const sp_score_args* a) { return make_wide_team_plan(a).ok && seq_cu_count() >= kWideTeamWGs; }
 size_t wide_team_workspace_bytes(const sp_score_args* a) {
-  const WideTeamPlan pl = make_plan(a);
+  const WideTeamPlan pl = make_wide_team_plan(a);
   return pl.ok ? align_up(2 * copy_bytes(pl), 256) + result_bytes(pl, a) + 256 : 0;
 }
 size_t wide_team_status_offset(const sp_score_args* a) {
-  const WideTeamPlan pl = make_plan(a);
+  const WideTeamPlan pl = make_wide_team_plan(a);
   return pl.ok ? align_up(2 * copy_bytes(pl), 256) + result_bytes(pl, a) : 0;
 }
 
@@ -327,17 +328,18 @@ static sp_status wide_team_by_pages(const WideTeamDev& dev, hipStream_t stream) 
 }
 template <int D>
 static sp_status wide_team_by_kind(const sp_score_args* a, const WideTeamDev& dev, hipStream_t stream) {
-  if (a->k_dtype == SP_K_FP8_E4M3)
-    return dev.lgG == 2 ? wide_team_by_pages<D, 2, true>(dev, stream) : wide_team_by_pages<D, 3, true>(dev, stream);
-  return dev.lgG == 2 ? wide_team_by_pages<D, 2, false>(dev, stream) : wide_team_by_pages<D, 3, false>(dev, stream);
+  const bool fp8 = a->k_dtype == SP_K_FP8_E4M3;
+  if (dev.lgG == 1) return fp8 ? wide_team_by_pages<D, 1, true>(dev, stream) : wide_team_by_pages<D, 1, false>(dev, stream);
+  if (dev.lgG == 2) return fp8 ? wide_team_by_pages<D, 2, true>(dev, stream) : wide_team_by_pages<D, 2, false>(dev, stream);
+  return fp8 ? wide_team_by_pages<D, 3, true>(dev, stream) : wide_team_by_pages<D, 3, false>(dev, stream);
 }
 
 sp_status wide_team_score(const sp_score_args* a, hipStream_t stream) {
-  const WideTeamPlan pl = make_plan(a);
+  const WideTeamPlan pl = make_wide_team_plan(a);
   if (!pl.ok) return SP_EUNSUPPORTED;
   WideTeamDev dev = {};
   dev.B = 1; dev.N = a->N; dev.L = a->L; dev.H = a->H; dev.H_kv = a->H_kv; dev.G = a->H / a->H_kv;
-  dev.lgG = wide_lg(a);
+  dev.lgG = wide_team_lg(a);
   dev.Gp = 1 << dev.lgG;
   dev.layer_reduce = a->layer_reduce;
   dev.scale = a->scale;

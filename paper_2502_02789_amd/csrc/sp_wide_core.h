@@ -41,7 +41,7 @@ struct WideKernel {
   static constexpr int QTILE_B = 32 * QROW_B;
   static constexpr int QLOADS = QTILE_B / 1024;   // one load each by the first QLOADS waves
   static constexpr int NS = 32 >> LG;             // query slots
-  static constexpr int KEEP = 16 >> LG;           // keys per lane and tile after the fold over heads: 4 or 2
+  static constexpr int KEEP = 16 >> LG;           // keys per lane and tile after the fold over heads: 8, 4 or 2
   typedef float vkeep __attribute__((ext_vector_type(KEEP)));
   static constexpr int kRingB = kTiledWaves * 2 * kItemBytes;
   static constexpr int kSmem = kRingB + 2 * QTILE_B + 2 * kTiledWaves * 32 * 8;
@@ -239,11 +239,29 @@ struct WideKernel {
     return a;
   }
 
-  // log2-probabilities of a held tile, maximum over the heads of a group: the lane's KEEP consecutive keys, the
-  // first of which is fold_key() of the tile, of query col & (NS - 1)
+  // log2-probabilities of a held tile, maximum over the heads of a group: the lane's KEEP keys, of query col & (NS - 1).
+  // The first is fold_key() of the tile, the others follow it (with two heads per group: four, and four from eight on).
   __device__ __forceinline__ int fold_key() const {
     const int ln = lane_id(), c = ln & 31, h = ln >> 5;
+    if constexpr (LG == 1) return (c >> 4) * 16 + h * 4;
     return (((c >> 4) << 1) | ((c >> 3) & 1)) * 8 + h * 4 + (LG == 3 ? ((c >> 2) & 1) * 2 : 0);
+  }
+  // a lane's keys of a tile in the result array, `at` being fold_key()'s
+  __device__ __forceinline__ static void store_keep(float* at, const vkeep& v) {
+    if constexpr (LG == 1) {
+      __builtin_nontemporal_store(f32x4{v[0], v[1], v[2], v[3]}, reinterpret_cast<f32x4*>(at));
+      __builtin_nontemporal_store(f32x4{v[4], v[5], v[6], v[7]}, reinterpret_cast<f32x4*>(at + 8));
+    } else {
+      __builtin_nontemporal_store(v, reinterpret_cast<vkeep*>(at));
+    }
+  }
+  __device__ __forceinline__ static vkeep load_keep(const float* at) {
+    if constexpr (LG == 1) {
+      const f32x4 lo = *reinterpret_cast<const f32x4*>(at), hi = *reinterpret_cast<const f32x4*>(at + 8);
+      return vkeep{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    } else {
+      return *reinterpret_cast<const vkeep*>(at);
+    }
   }
   __device__ __forceinline__ void fold_heads(const f32x16& a, float neg_lse2, float (&out)[KEEP]) const {
     float y[8];
@@ -252,6 +270,11 @@ struct WideKernel {
       const float lo = fmaf(a[i], c2, neg_lse2), hi = fmaf(a[i + 8], c2, neg_lse2);
       const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
       y[i] = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    }
+    if constexpr (LG == 1) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) out[k] = y[k];
+      return;
     }
     // bit 3: lanes 0..7 of a row take y[0..3], lanes 8..15 y[4..7].  (s_nop: a DPP operand must not have been
     // written by the two instructions before)
@@ -275,7 +298,7 @@ struct WideKernel {
           "v_max_f32_dpp %1, %5, %5 row_ror:4 row_mask:0xf bank_mask:0xa"
           : "=&v"(out[0]), "=&v"(out[1])
           : "v"(z[0]), "v"(z[1]), "v"(z[2]), "v"(z[3]));
-    } else {
+    } else if constexpr (LG == 2) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) out[k] = z[k];
     }

@@ -19,9 +19,19 @@ namespace sp {
 
 constexpr int kWideTeamWGs = 256;
 constexpr int kWideTeamWaves = 8;
-constexpr int kWideTeamTiles = 8;        // 32-key tiles per wave
-constexpr int kWideTeamKeys = kWideTeamTiles * 32 * kWideTeamWaves;
 constexpr int kWideTeamMaxPartners = 64;
+
+// The 32 columns are the queries times the heads of a group, padded to 2^this: four or eight, and two where more than eight
+// queries leave no room for four.  (32 layers, 8 KV heads of two heads, d = 128, in us: the kernels before the teams of this
+// kind, two passes for want of this variant, now: twelve queries on 12000 keys 300, 336, 152; nine on 32K keys 348, 853,
+// 366, the one shape tried that is not as fast as it was: half the keys per member, so twice the exchanges.)
+inline int wide_team_lg(const sp_score_args* a) {
+  const int heads = a->H / a->H_kv;
+  return heads > 4 ? 3 : heads <= 2 && a->N > 8 ? 1 : 2;
+}
+// 32-key tiles per wave, whole ring slots (one, two or four): what the registers hold of logits (16 each) and running
+// maxima (16 >> lg each).
+constexpr int wide_team_tiles(int lg) { return lg > 1 ? 8 : 4; }
 
 // The slabs are dealt out to the teams in turn: `rounds` rounds of `run` slabs to each team, the others in parts of
 // `part`, again in turn.
@@ -55,16 +65,19 @@ struct WideTeamPlan {
 // 1486 / 1311, 1556 / 1370, 1535 / 1360 (all 128).
 constexpr int kWideTeamRun = 4;
 
-inline WideTeamPlan make_wide_team_plan(const sp_score_args* a, int lg_heads) {
+inline WideTeamPlan make_wide_team_plan(const sp_score_args* a) {
   WideTeamPlan pl = {};
-  if (a->B != 1 || a->rope_theta > 0.f || a->T <= 0 || a->T > (int64_t)kWideTeamMaxPartners * kWideTeamKeys) return pl;
-  if (a->H / a->H_kv > 8 || (a->N << lg_heads) > 32) return pl;
+  if (a->B != 1 || a->rope_theta > 0.f) return pl;
+  const int lg = wide_team_lg(a);
+  if (a->H / a->H_kv > 8 || (a->N << lg) > 32) return pl;
+  const int64_t most = wide_team_tiles(lg) * 32 * kWideTeamWaves;   // keys of a member
+  if (a->T <= 0 || a->T > kWideTeamMaxPartners * most) return pl;
   if (a->k_dtype == SP_K_FP8_E4M3 && a->d_block_table && a->page_size < (a->d == 64 ? 16 : 8)) return pl;
   if (a->k_token_stride > (INT32_MAX / 256)) return pl;  // (a ring slot's keys must span less than 2 GiB)
   const int slabs = a->L * a->H_kv;
   if (slabs < 8) return pl;
   int lgP = 1;
-  while (((int64_t)kWideTeamKeys << lgP) < a->T) ++lgP;
+  while ((most << lgP) < a->T) ++lgP;
   // (fewer slabs than teams: more members per team instead, as long as each still has a wave's worth of keys)
   while ((kWideTeamWGs >> lgP) > slabs && (1 << lgP) < kWideTeamMaxPartners) ++lgP;
   const int P = 1 << lgP, teams = kWideTeamWGs >> lgP;
@@ -89,8 +102,8 @@ inline WideTeamPlan make_wide_team_plan(const sp_score_args* a, int lg_heads) {
     int64_t least = INT64_MAX;
     for (int part = a->H_kv; part >= 1; --part) {
       if (a->H_kv % part != 0) continue;
-      const int64_t most = ((int64_t)left * (a->H_kv / part) + teams - 1) / teams;  // parts of the busiest team
-      const int64_t cost = most * ((part * (pl.chunk + 200) + 300) * key_bytes + pl.chunk * result_bytes);
+      const int64_t parts = ((int64_t)left * (a->H_kv / part) + teams - 1) / teams;  // parts of the busiest team
+      const int64_t cost = parts * ((part * (pl.chunk + 200) + 300) * key_bytes + pl.chunk * result_bytes);
       if (cost < least) { least = cost; d.part = part; }
     }
     pl.plain_groups = d.rounds > 0 ? teams : 0;

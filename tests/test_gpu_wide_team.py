@@ -75,3 +75,25 @@ def test_kept_workspace_and_changed_inputs_over_consecutive_calls(mode):
         s.run()
         s.check()
         hp.assert_scores_close(s.scores.cpu().numpy(), want, f"call {turn}")
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("shape", [
+    dict(tokens=9001, L=3, H=8, H_kv=4, N=12, d=128),      # two heads per KV head
+    dict(tokens=8193, L=4, H=4, H_kv=4, N=9, d=128),       # one
+    dict(tokens=5003, L=2, H=16, H_kv=8, N=16, d=64),      # two tiles per slot; all 32 columns
+    dict(tokens=20001, L=9, H=2, H_kv=1, N=13, d=128),     # 32 members, eight teams: whole layers and a part (mean)
+    dict(tokens=17000, L=9, H=4, H_kv=2, N=16, d=64),      # ... with ragged slots of two tiles
+    dict(tokens=100, L=4, H=8, H_kv=4, N=9, d=128),        # shorter than a member
+])
+def test_more_than_eight_queries(shape, mode):
+    """One or two heads per KV head with nine to sixteen queries: the heads padded to two, four 32-key tiles per wave."""
+    shape = dict(shape)
+    w = synth.scaled(synth.workload(3), seqlens=(shape.pop("tokens"),), salient_run=1, **shape)
+    inp = synth.make_qk(w)
+    nv = np.array([w.N - 2], dtype=np.int32)
+    _check(w, inp, mode, max_seqlen=0, n_valid=nv, exclusive_device=True)
+    _check(w, inp, mode, max_seqlen=0, paged=16)
+    if w.T < 10000:
+        fp8._check(w, mode, False, paged=0)
+        fp8._check(w, mode, False, n_valid=nv, paged=16)

@@ -18,7 +18,7 @@ SHIM = r"""
 // out: ok, lgP, chunk, teams, run, rounds, part, n_groups, plain_groups, gpl; per slab: the team, its place in the team's
 // order, the number of the run, the first slab of the run
 extern "C" int walk(const sp_score_args* a, int* out, int* team_of, int* place_of, int* run_of, int* first_of) {
-  const sp::WideTeamPlan pl = sp::make_wide_team_plan(a, a->H / a->H_kv <= 4 ? 2 : 3);
+  const sp::WideTeamPlan pl = sp::make_wide_team_plan(a);
   const int fields[] = {pl.ok, pl.lgP, pl.chunk, pl.deal.teams, pl.deal.run, pl.deal.rounds, pl.deal.part, pl.n_groups, pl.plain_groups, pl.gpl};
   for (int i = 0; i < 10; ++i) out[i] = fields[i];
   if (!pl.ok) return 0;
@@ -117,3 +117,13 @@ def test_mean_over_layers_even_shares(walk):
                 assert busiest <= share + 1 + result * share, (L, T, bits, busiest, share)
                 if L >= p["teams"]:                                 # whole layers to everybody, few left over
                     assert busiest <= share + 4, (L, T, bits, busiest, share)
+
+
+def test_more_than_eight_queries(walk):
+    """One or two heads per KV head leave room for sixteen queries (padded to four they would not); three do not."""
+    for heads, N in ((1, 9), (1, 16), (2, 9), (2, 12), (2, 16)):
+        for T in (3073, 8193, 16384, 32768, 65536):
+            for mean in (sp.SP_LAYER_MAX, sp.SP_LAYER_MEAN):
+                p = walk(H=8 * heads, N=N, T=T, layer_reduce=mean)
+                assert p["ok"] and p["visits"] == p["slabs"] and p["chunk"] <= 1024 and (p["chunk"] << p["lgP"]) >= T, (heads, N, T)
+    assert not walk(H=16, N=12, T=65537)["ok"] and not walk(H=24, N=9, T=9000)["ok"]
