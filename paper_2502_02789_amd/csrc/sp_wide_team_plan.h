@@ -75,10 +75,13 @@ inline WideTeamPlan make_wide_team_plan(const sp_score_args* a) {
   if (a->k_dtype == SP_K_FP8_E4M3 && a->d_block_table && a->page_size < (a->d == 64 ? 16 : 8)) return pl;
   if (a->k_token_stride > (INT32_MAX / 256)) return pl;  // (a ring slot's keys must span less than 2 GiB)
   const int slabs = a->L * a->H_kv;
-  if (slabs < 8) return pl;
+  // Short prompts of next to no layers stay on the kernels that also take un-rotated caches: their scores are then bit for
+  // bit those of the same cache stored un-rotated.
+  if (slabs < 8 && a->T <= 3072) return pl;
   int lgP = 1;
   while ((most << lgP) < a->T) ++lgP;
-  // (fewer slabs than teams: more members per team instead, as long as each still has a wave's worth of keys)
+  // (fewer slabs than teams: more members per team instead, as long as each still has a wave's worth of keys; a single
+  // slab is still faster this way than in two passes: one layer, one KV head of four, 32K keys 16 us against 35)
   while ((kWideTeamWGs >> lgP) > slabs && (1 << lgP) < kWideTeamMaxPartners) ++lgP;
   const int P = 1 << lgP, teams = kWideTeamWGs >> lgP;
   pl.lgP = lgP;

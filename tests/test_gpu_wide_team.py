@@ -26,6 +26,10 @@ MODES = [orc.LAYER_MAX, orc.LAYER_MEAN]
     dict(tokens=6150, L=8, H=64, H_kv=8, N=4, d=128),    # eight heads per KV head
     dict(tokens=5000, L=6, H=40, H_kv=8, N=3, d=64),     # five heads padded to eight, units that do not divide evenly
     dict(tokens=9000, L=3, H=32, H_kv=8, N=1, d=128),    # one query
+    dict(tokens=9000, L=1, H=16, H_kv=4, N=8, d=128),    # as many slabs as teams
+    dict(tokens=16000, L=4, H=4, H_kv=1, N=8, d=128),
+    dict(tokens=3100, L=1, H=4, H_kv=1, N=2, d=64),      # one slab: three of four teams idle, members without keys
+    dict(tokens=33000, L=3, H=4, H_kv=1, N=8, d=64),
 ])
 def test_one_long_prompt(shape, mode):
     shape = dict(shape)

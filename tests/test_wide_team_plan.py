@@ -61,9 +61,9 @@ def walk(tmp_path_factory):
 
 
 def _shapes():
-    rng = random.Random(7)
+    rng = random.Random(7)   # (prompts of more than 3072 keys: few slabs are taken beyond)
     fixed = [dict(L=L, H_kv=K, T=T) for L in (1, 2, 16, 24, 28, 32, 33, 36, 48, 80, 128) for K in (1, 2, 4, 5, 8, 16) for T in (3073, 9000, 32768, 131072)]
-    drawn = [dict(L=rng.randint(1, 128), H_kv=rng.randint(1, 32), T=int(3000 * 44 ** rng.random())) for _ in range(400)]
+    drawn = [dict(L=rng.randint(1, 128), H_kv=rng.randint(1, 32), T=int(3073 * 43 ** rng.random())) for _ in range(400)]
     return [dict(s, H=s["H_kv"] * 4, layer_reduce=m) for s in fixed + drawn for m in (sp.SP_LAYER_MAX, sp.SP_LAYER_MEAN)]
 
 
@@ -71,7 +71,7 @@ def test_every_slab_and_key_is_taken_once(walk):
     for shape in _shapes():
         p = walk(**shape)
         if not p["ok"]:
-            assert p["slabs"] < 8 or shape["T"] > 131072, shape
+            assert shape["T"] > 131072, shape
             continue
         P = 1 << p["lgP"]
         assert p["visits"] == p["slabs"] and (p["team"] >= 0).all(), shape
