@@ -20,15 +20,14 @@
 #include <mutex>
 
 #include "sp_wide_core.h"
+#include "sp_wide_pass_plan.h"
 
 namespace sp {
 
-constexpr int kPassTiles = 16;                                   // 32-key tiles per wave
-constexpr int kPassMaxKeys = kPassTiles * 32 * kTiledWaves;      // keys of a piece
-constexpr int kPassBatchKeys = 2048;                             // ... where the sequences' lengths are not known here
+static_assert(kPassWaves == kTiledWaves && kPassSlotBytes == kItemBytes, "the plan counts in items of the stream");
 
 struct WidePassDev : TiledDev {
-  int chunk, slots;     // keys of a piece; places for pieces: sequence b's pieces start at place cu[b] / chunk + b
+  int chunk, slots;     // keys of a piece; places for pieces: sequence b's pieces start at place pass_first_place
   float* lines;         // [slab][place][32]
   float* row_lse;       // [slab][sequence][32]
 };
@@ -40,12 +39,12 @@ __device__ __forceinline__ Piece piece_at(const WidePassDev& p, int slot) {
   int lo = 0, hi = p.B;  // the largest b whose first place is <= slot
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;
-    if (cu[mid] / p.chunk + mid <= slot) lo = mid; else hi = mid;
+    if (pass_first_place(cu[mid], mid, p.chunk) <= slot) lo = mid; else hi = mid;
   }
   Piece u;
   u.b = lo;
   u.seq0 = cu[lo];
-  u.key0 = (slot - (u.seq0 / p.chunk + lo)) * p.chunk;
+  u.key0 = (slot - pass_first_place(u.seq0, lo, p.chunk)) * p.chunk;
   u.M = min(p.chunk, cu[lo + 1] - u.seq0 - u.key0);
   return u;
 }
@@ -177,7 +176,7 @@ template <int LG>
 __global__ __launch_bounds__(64) void wide_pass_combine_kernel(const WidePassDev p) {
   const int slab = blockIdx.x / p.B, b = blockIdx.x % p.B;
   const int ln = threadIdx.x, row = ln & 31;
-  const int first = p.cu[b] / p.chunk + b, pieces = (p.cu[b + 1] - p.cu[b] + p.chunk - 1) / p.chunk;
+  const int first = pass_first_place(p.cu[b], b, p.chunk), pieces = (p.cu[b + 1] - p.cu[b] + p.chunk - 1) / p.chunk;
   const float* src = p.lines + ((int64_t)slab * p.slots + first) * 32 + row;
   float m = -INFINITY, z = 0.f;
 #pragma unroll 4
@@ -202,45 +201,6 @@ __global__ __launch_bounds__(64) void wide_pass_combine_kernel(const WidePassDev
 // ---------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------
-struct WidePassPlan { int chunk, slots, per, n_groups, gpl; };
-
-static WidePassPlan make_wide_pass_plan(const sp_score_args* a) {
-  const int slabs = a->L * a->H_kv, kpi = kItemBytes / (a->d * (a->k_dtype == SP_K_FP8_E4M3 ? 1 : 2));
-  const bool mean = a->layer_reduce == SP_LAYER_MEAN;
-  WidePassPlan best = {};
-  int64_t best_cost = INT64_MAX;
-  // The cut into pieces and runs of slabs whose rounds over 256 workgroups are fullest: keys of a round's longest
-  // unit, plus about 200 keys' time for the end of a slab and 300 for that of a unit, plus its results, written and
-  // read back, at three times their bytes.  (Without that term the mean over layers of 24577 keys was cut into 256
-  // parts of layers for 8-bit keys, 407 us against 294 with 32, and 16 layers of d = 64 into 128, 202 against 157.
-  // Few KV heads are better off here than on the tiled kernels even where results outweigh keys: 16 layers, 2 KV
-  // heads of 8-bit d = 64, mean: 55 us against 98.)  For a batch the sequences' lengths are not known here: pieces of
-  // fixed size, and only the runs are chosen.
-  const int64_t result_bytes = 3 * 4 * a->N, key_bytes = a->d * (a->k_dtype == SP_K_FP8_E4M3 ? 1 : 2);
-  const int n0 = a->B > 1 ? 0 : (int)((a->T + kPassMaxKeys - 1) / kPassMaxKeys);
-  for (int extra = 0; extra < (a->B > 1 ? 1 : 8); ++extra) {
-    WidePassPlan pl = {};
-    pl.chunk = a->B > 1 ? kPassBatchKeys : (int)((a->T + n0 + extra - 1) / (n0 + extra) + 31) / 32 * 32;
-    pl.slots = a->B > 1 ? (int)(a->T / kPassBatchKeys) + a->B : (int)((a->T + pl.chunk - 1) / pl.chunk);
-    const int64_t keys = (int64_t)((pl.chunk + kpi * kTiledWaves - 1) / (kpi * kTiledWaves)) * kpi * kTiledWaves;
-    for (int per = 1; per <= (mean ? a->H_kv : slabs); per = per < 16 ? per + 1 : per + per / 8) {
-      if (mean && a->H_kv % per != 0) continue;
-      const int groups = (slabs + per - 1) / per;
-      const int64_t rounds = ((int64_t)pl.slots * groups + 255) / 256;
-      const int64_t cost = rounds * (per * (keys + 200) + 300 + keys * result_bytes / key_bytes);
-      if (cost < best_cost) {
-        best_cost = cost;
-        best = pl;
-        best.per = per;
-        best.n_groups = groups;
-        best.gpl = mean ? a->H_kv / per : 0;
-      }
-    }
-  }
-  if (a->B == 1) ++best.slots;  // (the numbering T / chunk + 1 of one sequence)
-  return best;
-}
-
 bool wide_passes_supported(const sp_score_args* a) {
   if (a->rope_theta > 0.f || a->T < 1) return false;
   // A batch whose longest sequence is not stated stays on the kernels that also take un-rotated caches: its scores are

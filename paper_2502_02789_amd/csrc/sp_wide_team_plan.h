@@ -9,7 +9,7 @@
 
 #include "specprefill.h"
 
-#ifdef __HIPCC__
+#ifdef __HIPCC__  // (as in sp_wide_pass_plan.h)
 #define SP_PLAN_FN __host__ __device__ __forceinline__
 #else
 #define SP_PLAN_FN inline

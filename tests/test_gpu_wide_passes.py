@@ -41,6 +41,16 @@ def test_batch_with_long_sequences(d, mode):
     _check(w, inp, mode, max_seqlen=5000, paged=16)
 
 
+@pytest.mark.parametrize("mode", MODES)
+def test_batch_of_one_slab(mode):
+    """Next to no slabs: pieces of 256 keys."""
+    w = synth.scaled(synth.workload(4), seqlens=(5000, 0, 255, 256, 257, 3100), L=1, H=4, H_kv=1, N=8, d=64, salient_frac=0.02, salient_run=1)
+    inp = synth.make_qk(w)
+    _check(w, inp, mode, max_seqlen=5000)
+    _check(w, inp, mode, max_seqlen=5000, paged=16)
+    fp8._check(w, mode, False, max_seqlen=5000)
+
+
 @pytest.mark.parametrize("d, paged", [(64, 0), (128, 0), (64, 16), (128, 8)])
 def test_8_bit_cache(d, paged):
     w = synth.scaled(synth.workload(3), seqlens=(300, 4500, 7), L=2, H=32, H_kv=8, N=8, d=d, salient_run=1)
