@@ -67,11 +67,12 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
   using vkeep = typename W::vkeep;
   W w(p, smem);
   const uint32_t lse_lds = (uint32_t)reinterpret_cast<uintptr_t>(smem) + W::kSmem;  // 32 row log-sum-exps
-  // The members of a team sit on one die where one has enough compute units (workgroups are dealt out to the eight dies
+  // The members of a team sit on one die where one has enough compute units (workgroups are dealt out to the dies
   // in turn).
   // (measured, whole call: 32K keys, 16 members, next to each other on one die 352 us, over all dies 363; 128K keys, 64
   // members, on two dies 1457 us, over all dies 1390)
-  const int P = 1 << p.lgP, place = P > 32 ? (int)blockIdx.x : (int)(blockIdx.x & 7) * (kWideTeamWGs / 8) + (int)(blockIdx.x >> 3);
+  const int P = 1 << p.lgP, dies = (int)gridDim.x / kWideTeamDieWGs;
+  const int place = P > kWideTeamDieWGs ? (int)blockIdx.x : (int)blockIdx.x % dies * kWideTeamDieWGs + (int)blockIdx.x / dies;
   const int team = place >> p.lgP, member = place & (P - 1);
   const WideTeamDeal& deal = p.deal;
   const bool mean = p.layer_reduce != SP_LAYER_MAX;
@@ -289,13 +290,14 @@ static size_t result_bytes(const WideTeamPlan& pl, const sp_score_args* a) {
   return align_up(sizeof(float) * 32 * (size_t)pl.n_groups * a->N * wide_tiles(a), 256);
 }
 
-bool wide_team_supported(const sp_score_args* a) { return make_wide_team_plan(a).ok && seq_cu_count() >= kWideTeamWGs; }
+static WideTeamPlan make_plan(const sp_score_args* a) { return make_wide_team_plan(a, wide_team_wgs(seq_cu_count())); }
+bool wide_team_supported(const sp_score_args* a) { return make_plan(a).ok; }
 size_t wide_team_workspace_bytes(const sp_score_args* a) {
-  const WideTeamPlan pl = make_wide_team_plan(a);
+  const WideTeamPlan pl = make_plan(a);
   return pl.ok ? align_up(2 * copy_bytes(pl), 256) + result_bytes(pl, a) + 256 : 0;
 }
 size_t wide_team_status_offset(const sp_score_args* a) {
-  const WideTeamPlan pl = make_wide_team_plan(a);
+  const WideTeamPlan pl = make_plan(a);
   return pl.ok ? align_up(2 * copy_bytes(pl), 256) + result_bytes(pl, a) : 0;
 }
 
@@ -319,7 +321,7 @@ static sp_status launch_wide_team(const WideTeamDev& dev, hipStream_t stream) {
       prepared[slot] = true;
     }
   }
-  hipLaunchKernelGGL(kernel, dim3(kWideTeamWGs), dim3(kTiledThreads), smem, stream, dev);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(dev.deal.teams << dev.lgP)), dim3(kTiledThreads), smem, stream, dev);
   return launch_status();
 }
 template <int D, int LG, bool FP8>
@@ -335,7 +337,7 @@ static sp_status wide_team_by_kind(const sp_score_args* a, const WideTeamDev& de
 }
 
 sp_status wide_team_score(const sp_score_args* a, hipStream_t stream) {
-  const WideTeamPlan pl = make_wide_team_plan(a);
+  const WideTeamPlan pl = make_plan(a);
   if (!pl.ok) return SP_EUNSUPPORTED;
   WideTeamDev dev = {};
   dev.B = 1; dev.N = a->N; dev.L = a->L; dev.H = a->H; dev.H_kv = a->H_kv; dev.G = a->H / a->H_kv;

@@ -17,7 +17,10 @@
 
 namespace sp {
 
-constexpr int kWideTeamWGs = 256;
+#ifndef SP_TEAM_MAX_WGS
+#define SP_TEAM_MAX_WGS 256
+#endif
+constexpr int kWideTeamDieWGs = 32;      // compute units of a die
 constexpr int kWideTeamWaves = 8;
 constexpr int kWideTeamMaxPartners = 64;
 
@@ -48,6 +51,14 @@ struct WideTeamDeal {
   }
 };
 
+// Workgroups of a call, which must all be resident: one per compute unit, as many as a power of two allows (256 on the
+// whole chip, 128, 64 or 32 on a partition of it); 0: too few.
+inline int wide_team_wgs(int compute_units) {
+  int wgs = SP_TEAM_MAX_WGS;
+  while (wgs > compute_units) wgs >>= 1;
+  return wgs >= kWideTeamDieWGs ? wgs : 0;
+}
+
 struct WideTeamPlan {
   bool ok;
   int lgP, chunk;          // members of a team (a power of two), keys of a member
@@ -65,13 +76,14 @@ struct WideTeamPlan {
 // 1486 / 1311, 1556 / 1370, 1535 / 1360 (all 128).
 constexpr int kWideTeamRun = 4;
 
-inline WideTeamPlan make_wide_team_plan(const sp_score_args* a) {
+inline WideTeamPlan make_wide_team_plan(const sp_score_args* a, int wgs) {
   WideTeamPlan pl = {};
+  const int most_partners = std::min(kWideTeamMaxPartners, wgs);
   if (a->B != 1 || a->rope_theta > 0.f) return pl;
   const int lg = wide_team_lg(a);
   if (a->H / a->H_kv > 8 || (a->N << lg) > 32) return pl;
   const int64_t most = wide_team_tiles(lg) * 32 * kWideTeamWaves;   // keys of a member
-  if (a->T <= 0 || a->T > kWideTeamMaxPartners * most) return pl;
+  if (a->T <= 0 || a->T > most_partners * most) return pl;
   if (a->k_dtype == SP_K_FP8_E4M3 && a->d_block_table && a->page_size < (a->d == 64 ? 16 : 8)) return pl;
   if (a->k_token_stride > (INT32_MAX / 256)) return pl;  // (a ring slot's keys must span less than 2 GiB)
   const int slabs = a->L * a->H_kv;
@@ -82,8 +94,8 @@ inline WideTeamPlan make_wide_team_plan(const sp_score_args* a) {
   while ((most << lgP) < a->T) ++lgP;
   // (fewer slabs than teams: more members per team instead, as long as each still has a wave's worth of keys; a single
   // slab is still faster this way than in two passes: one layer, one KV head of four, 32K keys 16 us against 35)
-  while ((kWideTeamWGs >> lgP) > slabs && (1 << lgP) < kWideTeamMaxPartners) ++lgP;
-  const int P = 1 << lgP, teams = kWideTeamWGs >> lgP;
+  while ((wgs >> lgP) > slabs && (1 << lgP) < most_partners) ++lgP;
+  const int P = 1 << lgP, teams = wgs >> lgP;
   pl.lgP = lgP;
   pl.chunk = (int)(((a->T + P - 1) / P + 255) / 256 * 256);
   WideTeamDeal& d = pl.deal;

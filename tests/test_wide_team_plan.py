@@ -17,8 +17,9 @@ SHIM = r"""
 #include "sp_wide_team_plan.h"
 // out: ok, lgP, chunk, teams, run, rounds, part, n_groups, plain_groups, gpl; per slab: the team, its place in the team's
 // order, the number of the run, the first slab of the run
-extern "C" int walk(const sp_score_args* a, int* out, int* team_of, int* place_of, int* run_of, int* first_of) {
-  const sp::WideTeamPlan pl = sp::make_wide_team_plan(a);
+extern "C" int wgs_of(int compute_units) { return sp::wide_team_wgs(compute_units); }
+extern "C" int walk(const sp_score_args* a, int wgs, int* out, int* team_of, int* place_of, int* run_of, int* first_of) {
+  const sp::WideTeamPlan pl = sp::make_wide_team_plan(a, wgs);
   const int fields[] = {pl.ok, pl.lgP, pl.chunk, pl.deal.teams, pl.deal.run, pl.deal.rounds, pl.deal.part, pl.n_groups, pl.plain_groups, pl.gpl};
   for (int i = 0; i < 10; ++i) out[i] = fields[i];
   if (!pl.ok) return 0;
@@ -45,7 +46,7 @@ def walk(tmp_path_factory):
                     "-I", os.path.join(ROOT, "paper_2502_02789_amd", "csrc"), "shim.cpp", "-o", "shim.so"], cwd=where, check=True)
     lib = C.CDLL(str(where / "shim.so"))
 
-    def run(**fields):
+    def run(wgs=256, **fields):
         a = sp.ScoreArgs()
         for k, v in dict(dict(B=1, N=8, L=32, H=32, H_kv=8, d=128, T=32768, k_token_stride=1024, k_head_stride=128, scale=0.1), **fields).items():
             setattr(a, k, v)
@@ -53,10 +54,11 @@ def walk(tmp_path_factory):
         arrays = [np.full(n, -1, dtype=np.int32) for _ in range(4)]
         out = np.zeros(10, dtype=np.int32)
         ptr = lambda x: x.ctypes.data_as(C.POINTER(C.c_int))  # noqa: E731
-        visits = lib.walk(C.byref(a), ptr(out), *[ptr(x) for x in arrays])
+        visits = lib.walk(C.byref(a), wgs, ptr(out), *[ptr(x) for x in arrays])
         p = dict(zip("ok lgP chunk teams run rounds part n_groups plain_groups gpl".split(), (int(x) for x in out)))
         p.update(visits=visits, slabs=n, **dict(zip("team place run_of first".split(), arrays)))
         return p
+    run.wgs_of = lib.wgs_of
     return run
 
 
@@ -67,15 +69,16 @@ def _shapes():
     return [dict(s, H=s["H_kv"] * 4, layer_reduce=m) for s in fixed + drawn for m in (sp.SP_LAYER_MAX, sp.SP_LAYER_MEAN)]
 
 
-def test_every_slab_and_key_is_taken_once(walk):
+@pytest.mark.parametrize("wgs", [256, 128, 64, 32])
+def test_every_slab_and_key_is_taken_once(walk, wgs):
     for shape in _shapes():
-        p = walk(**shape)
+        p = walk(wgs, **shape)
         if not p["ok"]:
-            assert shape["T"] > 131072, shape
+            assert shape["T"] > 2048 * min(64, wgs), shape
             continue
         P = 1 << p["lgP"]
         assert p["visits"] == p["slabs"] and (p["team"] >= 0).all(), shape
-        assert P * p["teams"] == 256 and p["chunk"] % 256 == 0 and p["chunk"] <= 2048 and P * p["chunk"] >= shape["T"], shape
+        assert P * p["teams"] == wgs and p["chunk"] % 256 == 0 and p["chunk"] <= 2048 and P * p["chunk"] >= shape["T"], shape
         if shape["layer_reduce"] == sp.SP_LAYER_MAX:
             assert p["n_groups"] == len(set(p["team"])) and set(p["team"]) == set(range(p["n_groups"])), shape
             continue
@@ -127,3 +130,9 @@ def test_more_than_eight_queries(walk):
                 p = walk(H=8 * heads, N=N, T=T, layer_reduce=mean)
                 assert p["ok"] and p["visits"] == p["slabs"] and p["chunk"] <= 1024 and (p["chunk"] << p["lgP"]) >= T, (heads, N, T)
     assert not walk(H=16, N=12, T=65537)["ok"] and not walk(H=24, N=9, T=9000)["ok"]
+
+
+def test_workgroups_by_compute_units(walk):
+    """The whole chip and its partitions; every workgroup has a compute unit of its own."""
+    assert [walk.wgs_of(n) for n in (256, 304, 255, 128, 64, 32, 31, 8)] == [256, 256, 128, 128, 64, 32, 0, 0]
+    assert not walk(0)["ok"]
