@@ -12,7 +12,6 @@ constexpr int kItemBytes = 8192;  // a ring slot
 constexpr int kItemLoads = kItemBytes / 1024;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 template <int I, int N, typename F>
 __device__ __forceinline__ void wide_static_for(F&& f) {
