@@ -67,7 +67,7 @@ def test_valid_query_count_on_one_long_prompt(n_valid, mode, paged):
     """One prompt, eight KV heads, eight look-ahead rows of which only the first n_valid count
     (Sec. 3.3: look-ahead tokens after an end-of-sequence are not valid): the shape the single-pass
     kernels take, contiguous and behind a block table, against the oracle."""
-    w = synth.scaled(synth.workload(3), seqlens=(9000 + 13,), L=3)   # (long enough for either single-pass kernel)
+    w = synth.scaled(synth.workload(3), seqlens=(9000 + 13,), L=3)   # (long enough for the teams of workgroups)
     inp = synth.make_qk(w)
     scale = 1.0 / math.sqrt(w.d)
     nv = np.array([n_valid], dtype=np.int32)
@@ -201,7 +201,7 @@ def test_one_long_prompt_without_the_exclusive_device_promise(mode):
     np.testing.assert_allclose(lse, want_lse, rtol=0, atol=2e-4)
 
 
-@pytest.mark.parametrize("tokens", [4096 + 40, 9000])     # the all-workgroup kernel / the team kernel
+@pytest.mark.parametrize("tokens", [4096 + 40, 9000])     # pieces of 512 and of 768 keys
 def test_expired_wait_is_impossible_to_miss(tokens):
     """The single-pass kernels' waits for other workgroups are bounded.  With the bound set to
     zero from the host every wait gives up at once (all kernels still run to their end): the scores
@@ -298,17 +298,16 @@ def test_kept_workspace_over_consecutive_calls(shape):
 
 
 @pytest.mark.parametrize("shape", [
-    dict(tokens=9001, H=32, H_kv=8, N=8),      # eight teams, two key tiles per wave and slab, ragged tail
-    dict(tokens=16384, H=8, H_kv=8, N=8),      # one query head per KV head, exactly full
-    dict(tokens=20011, H=16, H_kv=8, N=3),     # four teams of 64 workgroups, two heads per KV head
+    dict(tokens=9001, H=32, H_kv=8, N=8),      # 24 slabs in runs of two: four of sixteen teams have none; ragged tail
+    dict(tokens=16384, H=8, H_kv=8, N=8),      # one query head per KV head, members of whole tiles
+    dict(tokens=20011, H=16, H_kv=8, N=3),     # two heads per KV head
     dict(tokens=11000, H=64, H_kv=8, N=4),     # eight heads per KV head
-    dict(tokens=10007, H=16, H_kv=4, N=8),     # four KV heads: four teams, one KV head each
-    dict(tokens=9500, H=32, H_kv=16, N=2),     # sixteen KV heads: two per team
+    dict(tokens=10007, H=16, H_kv=4, N=8),     # four KV heads: teams of 32 workgroups
+    dict(tokens=9500, H=32, H_kv=16, N=2),     # sixteen KV heads
 ])
 def test_team_kernel_shapes(shape):
     """One prompt of 8K..32K keys, head dim 128, SP_LAYER_MAX: the kernel whose workgroups form teams
-    per group of KV heads, in each of its team / tile configurations, against the oracle; twice on
-    one workspace, bitwise equal."""
+    that share a prompt's keys, against the oracle; twice, bitwise equal."""
     tokens = shape.pop("tokens")
     w = synth.scaled(synth.workload(3), seqlens=(tokens,), L=3, **shape)
     inp = synth.make_qk(w)
@@ -319,15 +318,15 @@ def test_team_kernel_shapes(shape):
 
 
 @pytest.mark.parametrize("shape", [
-    dict(tokens=9001, L=8, H=32, H_kv=8, N=8, n_valid=5),   # eight teams of one layer each, ragged tail, invalid rows
-    dict(tokens=20011, L=4, H=16, H_kv=8, N=3),             # four teams, two heads per KV head
-    dict(tokens=10007, L=12, H=16, H_kv=4, N=8),            # four KV heads, three layers per team
+    dict(tokens=9001, L=8, H=32, H_kv=8, N=8, n_valid=5),   # layers in parts of two KV heads, ragged tail, invalid rows
+    dict(tokens=20011, L=4, H=16, H_kv=8, N=3),             # two heads per KV head
+    dict(tokens=10007, L=12, H=16, H_kv=4, N=8),            # parts of two of four KV heads, fewer than teams
     dict(tokens=9500, L=4, H=16, H_kv=16, N=2, paged=True), # sixteen KV heads, behind a block table
 ])
 def test_team_kernel_mean_over_layers(shape):
-    """SP_LAYER_MEAN on the team kernel: a team owns every TC-th layer (the maximum over a layer's
-    heads is then complete inside a workgroup, and the teams' sums over their layers add up),
-    against the oracle; twice on one workspace, bitwise equal."""
+    """SP_LAYER_MEAN on the team kernel with fewer layers than teams: parts of layers, whose maxima the merge
+    completes and adds up (teams that own whole layers: test_gpu_wide_team.py), against the oracle; twice,
+    bitwise equal."""
     shape = dict(shape)
     tokens, n_valid, paged = shape.pop("tokens"), shape.pop("n_valid", None), shape.pop("paged", False)
     w = synth.scaled(synth.workload(3), seqlens=(tokens,), **shape)

@@ -56,3 +56,10 @@ def test_8_bit_cache(d, paged):
     w = synth.scaled(synth.workload(3), seqlens=(300, 4500, 7), L=2, H=32, H_kv=8, N=8, d=d, salient_run=1)
     for mode in MODES:
         fp8._check(w, mode, False, paged=paged, max_seqlen=4500)
+
+
+@pytest.mark.parametrize("mode", MODES)
+def test_8_bit_cache_eight_heads_per_kv_head(mode):
+    for d in (64, 128):
+        w = synth.scaled(synth.workload(3), seqlens=(300, 4500, 7), L=2, H=32, H_kv=4, N=4, d=d, salient_run=1)
+        fp8._check(w, mode, False, paged=16 if d == 64 else 0, max_seqlen=4500)

@@ -8,6 +8,7 @@ import pytest
 from oracle import specprefill_oracle as orc
 from paper_2502_02789_amd import synth
 from tests import helpers as hp
+from tests import test_gpu_fp8_cache as fp8
 from tests.test_gpu_batch_single_pass import _check, _lens
 
 pytestmark = pytest.mark.gpu
@@ -79,3 +80,24 @@ def test_a_sequence_longer_than_the_kernel_holds_gets_nan_scores():
     inside[cu[9]:cu[10]] = True
     assert np.isnan(got[inside]).all() and np.isnan(lse[:, 9]).all()
     hp.assert_scores_close(got[~inside], want[~inside], "the other sequences")
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads", [dict(H=8, N=8), dict(H=16, N=4), dict(H=6, N=3)])   # four, eight and three per KV head
+def test_8_bit_cache(heads, d, mode):
+    """Slots of two and four 32-key tiles: the edges of tiles and slots, paged and not."""
+    w = synth.scaled(synth.workload(4), seqlens=LENS, L=4, H_kv=2, d=d, salient_frac=0.02, salient_run=1, **heads)
+    for paged in (0, 16):
+        fp8._check(w, mode, False, max_seqlen=1100, paged=paged)
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("longest", [2048, 2049, 3072])
+def test_8_bit_cache_at_the_edges_of_what_the_registers_hold(longest, d, mode):
+    """Units of several slabs whose running maxima are read back beyond 2048 keys, with whole and ragged last slots."""
+    w = synth.scaled(synth.workload(4), seqlens=(longest, longest - 31, longest - 97) + _lens(longest, 77, 1, 90), L=8,
+                     H=8, H_kv=2, N=8, d=d, salient_frac=0.02, salient_run=1)
+    fp8._check(w, mode, False, max_seqlen=longest)
+    fp8._check(w, mode, False, max_seqlen=longest, paged=16)

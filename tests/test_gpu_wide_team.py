@@ -60,6 +60,30 @@ def test_8_bit_cache(d, paged, mode):
 
 
 @pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("d, paged", [(64, 0), (64, 16), (128, 8)])
+def test_8_bit_cache_eight_heads_per_kv_head(d, paged, mode):
+    w = synth.scaled(synth.workload(3), seqlens=(5003,), L=4, H=32, H_kv=4, N=4, d=d, salient_run=1)
+    fp8._check(w, mode, False, paged=paged)
+
+
+@pytest.mark.parametrize("d, bits, paged", [(128, 16, 0), (64, 16, 0), (128, 8, 0), (64, 8, 0), (128, 16, 16), (64, 16, 64), (64, 8, 16)])
+@pytest.mark.parametrize("shape", [
+    dict(tokens=33001, L=19, H=4, H_kv=1, N=8),    # eight teams: two rounds of whole layers, three layers left over
+    dict(tokens=32801, L=10, H=8, H_kv=2, N=3),    # one round, two layers left over, cut in halves
+    dict(tokens=66007, L=9, H=8, H_kv=1, N=2),     # four teams on two dies each, eight heads per KV head
+])
+def test_mean_over_whole_layers_and_left_over_parts(shape, d, bits, paged):
+    """At least as many layers as teams: a team adds each of its layers to what it stored before (the read-back on whole
+    and ragged slots of one, two and four tiles), the layers left over are merged from parts."""
+    shape = dict(shape)
+    w = synth.scaled(synth.workload(3), seqlens=(shape.pop("tokens"),), d=d, salient_run=1, **shape)
+    if bits == 8:
+        fp8._check(w, orc.LAYER_MEAN, False, paged=paged)
+    else:
+        _check(w, synth.make_qk(w), orc.LAYER_MEAN, max_seqlen=0, paged=paged, exclusive_device=True)
+
+
+@pytest.mark.parametrize("mode", MODES)
 def test_kept_workspace_and_changed_inputs_over_consecutive_calls(mode):
     """Both copies of the exchange lines in turn, on other keys each time."""
     import torch
