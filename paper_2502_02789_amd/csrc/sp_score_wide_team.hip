@@ -292,13 +292,15 @@ static size_t result_bytes(const WideTeamPlan& pl, const sp_score_args* a) {
 
 static WideTeamPlan make_plan(const sp_score_args* a) { return make_wide_team_plan(a, wide_team_wgs(seq_cu_count())); }
 bool wide_team_supported(const sp_score_args* a) { return make_plan(a).ok; }
+// Workspace: the lines' two copies, the status words, the results.  What a call hands on to the next (lines and status)
+// sits where the shape alone says, whatever the cut into result groups, which the kind of cache may change.
 size_t wide_team_workspace_bytes(const sp_score_args* a) {
   const WideTeamPlan pl = make_plan(a);
   return pl.ok ? align_up(2 * copy_bytes(pl), 256) + result_bytes(pl, a) + 256 : 0;
 }
 size_t wide_team_status_offset(const sp_score_args* a) {
   const WideTeamPlan pl = make_plan(a);
-  return pl.ok ? align_up(2 * copy_bytes(pl), 256) + result_bytes(pl, a) : 0;
+  return pl.ok ? align_up(2 * copy_bytes(pl), 256) : 0;
 }
 
 template <int D, int LG, bool FP8, bool PAGED>
@@ -363,8 +365,8 @@ sp_status wide_team_score(const sp_score_args* a, hipStream_t stream) {
   char* ws = static_cast<char*>(a->d_workspace);
   dev.lines = reinterpret_cast<uint32_t*>(ws);
   dev.copy_words = copy_bytes(pl) / 4;
-  dev.group_scores = reinterpret_cast<float*>(ws + align_up(2 * copy_bytes(pl), 256));
   dev.status = reinterpret_cast<uint32_t*>(ws + wide_team_status_offset(a));
+  dev.group_scores = reinterpret_cast<float*>(ws + wide_team_status_offset(a) + 256);
   if (!(a->flags & SP_SCORE_WORKSPACE_KEPT)) {
     const size_t n_vec = copy_bytes(pl) / 16;
     hipLaunchKernelGGL(wide_team_fill_kernel, dim3((unsigned)std::min<size_t>((n_vec + 255) / 256, 1024)), dim3(256), 0, stream,

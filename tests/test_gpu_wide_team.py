@@ -105,6 +105,32 @@ def test_kept_workspace_and_changed_inputs_over_consecutive_calls(mode):
         hp.assert_scores_close(s.scores.cpu().numpy(), want, f"call {turn}")
 
 
+def test_kept_workspace_shared_by_two_kinds_of_cache():
+    """SP_SCORE_WORKSPACE_KEPT asks for the same shape, not for the same kind of cache: calls on a bf16 and on an 8-bit
+    cache take turns on one workspace (their results are cut differently, 40 groups and ten)."""
+    import torch
+    from paper_2502_02789_amd import binding as sp, device as dev
+    w = synth.scaled(synth.workload(3), seqlens=(17000,), L=5, H=32, H_kv=8, N=1, d=64, salient_run=1)
+    inp = synth.make_qk(w)
+    scale = 1.0 / math.sqrt(w.d)
+    codes, k_scale = synth.quantize_k_fp8(inp["k"])
+    kw = dict(H_kv=w.H_kv, scale=scale, layer_reduce=orc.LAYER_MEAN)
+    q, cu = dev.bf16_from_bits(inp["q"]), torch.from_numpy(np.asarray(inp["cu_seqlens"], dtype=np.int32)).cuda()
+    both = [dev.Scorer(q, [dev.bf16_from_bits(k) for k in inp["k"]], cu, **kw),
+            dev.Scorer(q, [torch.from_numpy(c).cuda() for c in codes], cu, k_scale=torch.from_numpy(k_scale).cuda(), **kw)]
+    want = [orc.token_importance(inp["q"], inp["k"], inp["cu_seqlens"], scale, orc.LAYER_MEAN)[0],
+            orc.token_importance(inp["q"], codes, inp["cu_seqlens"], scale, orc.LAYER_MEAN, k_scale=k_scale)[0]]
+    room = torch.empty(max(s.workspace.numel() for s in both), dtype=torch.uint8, device="cuda")
+    for turn in range(6):
+        s = both[turn % 2]
+        s.args.d_workspace, s.args.workspace_bytes = room.data_ptr(), room.numel()
+        s.args.flags = sp.SP_SCORE_EXCLUSIVE_DEVICE | (sp.SP_SCORE_WORKSPACE_KEPT if turn else 0)
+        s.scores.fill_(float("nan"))
+        sp.sp_score(s.args)
+        sp.sp_score_check(s.args)
+        hp.assert_scores_close(s.scores.cpu().numpy(), want[turn % 2], f"turn {turn}")
+
+
 @pytest.mark.parametrize("mode", MODES)
 @pytest.mark.parametrize("shape", [
     dict(tokens=9001, L=3, H=8, H_kv=4, N=12, d=128),      # two heads per KV head
