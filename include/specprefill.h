@@ -76,7 +76,8 @@ typedef enum { SP_K_BF16 = 0, SP_K_FP8_E4M3 = 1 } sp_k_dtype;
                                         the K cache once but exchange softmax row statistics
                                         between workgroups that must all be resident together.
                                         Without the flag sp_score uses kernels that never wait for
-                                        another workgroup (two passes over K or kept logits).
+                                        another workgroup (one pass over K for short prompts, see
+                                        max_seqlen; two passes or kept logits beyond).
                                         If the promise is broken a bounded wait can expire; the
                                         call's scores are then NaN (see sp_score_check and
                                         sp_pool_select), never silently wrong. */
@@ -178,7 +179,9 @@ typedef struct {
  * (L*N*H*8 bytes per 64 tokens) always, plus, for batches whose KV heads have at most eight
  * query rows (H/H_kv * N <= 8), 16 or 32 bytes per token, layer and KV head of logits kept
  * between the two passes (0.7 GB for 167K tokens of a 32-layer, 8-KV-head model), or, for the
- * kernels that take up to 32 rows, one to 64 partial results of 4 bytes per token and query. */
+ * kernels that take up to 32 rows, a result of 4 bytes per token and query for every run of
+ * (layer, KV head) slabs the work is cut into (256 runs for one short prompt of a 32-layer, 8-KV-head
+ * model, 16 for 32K tokens on an idle device; never more than there are slabs). */
 SP_API size_t sp_score_workspace_bytes(const sp_score_args* args);
 
 /* Enqueue the scoring on hip_stream.  Errors: SP_ENULL, SP_EINVAL (shape limits above),

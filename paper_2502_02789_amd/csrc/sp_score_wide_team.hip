@@ -4,8 +4,7 @@
 // (Sec. 3.2 equation of arXiv 2502.02789), max over heads, max/mean over layers, mean over queries (Sec. 3.2.2).
 // Stream, products, statistics and the fold over heads are those of sp_score_wide.hip (sp_wide_core.h).  There one
 // workgroup owns a whole prompt; a longer prompt is cut into P pieces of up to 2048 keys (1024 with more than eight
-// queries), and the P workgroups of a
-// team walk together over the team's (layer, KV head) slabs:
+// queries), and the P workgroups of a team walk together over the team's (layer, KV head) slabs:
 //
 //   * per slab every member publishes ONE 128-byte line, the base-2 log-sum-exps of its keys for the 32 rows (agent
 //     scope); its first wave then reads the team's P lines (contiguous) until none is "empty" any more, folds them
