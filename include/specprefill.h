@@ -71,16 +71,21 @@ typedef enum { SP_K_BF16 = 0, SP_K_FP8_E4M3 = 1 } sp_k_dtype;
 
 /* sp_score_args.flags */
 #define SP_SCORE_EXCLUSIVE_DEVICE 1u /* The caller promises that nothing else runs on the GPU while
-                                        sp_score runs (no other stream, no other process).  Only
-                                        then may sp_score use its single-pass kernels, which read
-                                        the K cache once but exchange softmax row statistics
-                                        between workgroups that must all be resident together.
-                                        Without the flag sp_score uses kernels that never wait for
-                                        another workgroup (one pass over K for short prompts, see
-                                        max_seqlen; two passes or kept logits beyond).
-                                        If the promise is broken a bounded wait can expire; the
-                                        call's scores are then NaN (see sp_score_check and
-                                        sp_pool_select), never silently wrong. */
+                                        sp_score runs (no other stream, no other process).  The
+                                        single-pass kernels for one long prompt read the K cache
+                                        once but exchange softmax row statistics between
+                                        workgroups that must all be resident together; with the
+                                        flag they wait for one another as long as that can
+                                        sensibly take.  If the promise is broken a bounded wait can
+                                        expire; the call's scores are then NaN (see
+                                        sp_score_check and sp_pool_select), never silently
+                                        wrong.
+                                        Without the flag the scores are valid whatever else runs on
+                                        the GPU: workgroups that could not wait for one another
+                                        any longer give up early, and a second launch of the
+                                        same call (which returns at once otherwise) forms the
+                                        results again from the row statistics, which are all
+                                        there by then.  At worst K is read twice. */
 #define SP_SCORE_WORKSPACE_KEPT 2u   /* The caller promises that args->d_workspace was last written by
                                         an sp_score call with the same shape fields (B, T, N, L, H,
                                         H_kv, d, layer_reduce, paging) and SP_SCORE_EXCLUSIVE_DEVICE
@@ -197,15 +202,17 @@ SP_API sp_status sp_score_general(const sp_score_args* args, void* hip_stream);
  * single-pass kernels (SP_SCORE_EXCLUSIVE_DEVICE) exchange row statistics between workgroups
  * that must all be resident on the device at once.  Their waits are bounded: a workgroup whose
  * wait expired records the event in the workspace instead of hanging, and all of the call's scores
- * become NaN.  This call SYNCHRONISES hip_stream (the only entry point that does), reads
+ * become NaN.  (Without the flag such a call has completed itself: SP_OK.)  This call SYNCHRONISES hip_stream (the only entry point that does), reads
  * that record and returns SP_ETIMEOUT if a wait expired, SP_OK otherwise.  Recovery: call
  * sp_score again without the flag (or sp_score_general). */
 SP_API sp_status sp_score_check(const sp_score_args* args, void* hip_stream);
 
 /* Upper bound on the polls a workgroup may spend waiting for other workgroups during one sp_score
- * call (process-wide, applies to later calls; default 65536, about 0.1 s).  0 makes every wait
- * give up at once, which turns every score of a single-pass call into NaN: that is how the
- * failure path is exercised without ever making a kernel hang.  Returns the previous value;
+ * call (process-wide, applies to later calls; default 65536, about 0.1 s; calls without
+ * SP_SCORE_EXCLUSIVE_DEVICE have a smaller bound of their own, of the order of the time the call takes).
+ * 0 makes every wait give up at once, which turns every score of a single-pass call with that flag into
+ * NaN, and takes one without it through its second launch: that is how the failure paths are
+ * exercised without ever making a kernel hang.  Returns the previous value;
  * a negative argument only queries. */
 SP_API int32_t sp_set_wait_budget(int32_t polls);
 

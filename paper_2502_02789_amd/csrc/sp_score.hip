@@ -291,11 +291,15 @@ static bool shape_ok(const sp_score_args* a) {
 
 static int general_max_tiles(const sp_score_args* a) { return (int)(a->T / kTileKeys) + a->B; }
 
-// the single-pass kernels are taken only on the caller's promise of an otherwise idle device
+// The teams of workgroups (sp_score_wide_team.hip): on the caller's promise of an otherwise idle device, and without it
+// for prompts of more than 3072 keys.  (Shorter ones that the batch kernels below leave, with fewer than 64 slabs, stay
+// on the kernels that also take un-rotated caches: their scores are then bit for bit those of the same cache stored
+// un-rotated.  3500 keys, 8 KV heads, d = 128, whole step: 32 layers, eight queries 109 us in two passes, 72 here; one
+// query with d = 64 and 16 layers 61 us with the logits kept in memory, 40 here; nothing tried beyond was slower.)
 bool single_pass_wanted(const sp_score_args* a) {
   // (the batch kernels keep a sequence's logits inside a workgroup and need no exchange at all)
   if (tiled_supported(a) && (seq_supported(a) || wide_supported(a))) return false;
-  return (a->flags & SP_SCORE_EXCLUSIVE_DEVICE) != 0 && wide_team_supported(a);
+  return ((a->flags & SP_SCORE_EXCLUSIVE_DEVICE) != 0 || a->T > 3072) && wide_team_supported(a);
 }
 
 size_t general_workspace_bytes(const sp_score_args* a, bool with_tiled) {

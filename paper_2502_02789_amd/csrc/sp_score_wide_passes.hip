@@ -1,6 +1,6 @@
-// Two-pass MFMA scorer for many query rows per KV head where no single pass is possible: long prompts without the
-// promise of an idle device (nobody may wait for another workgroup), and batches with sequences longer than one
-// workgroup holds.
+// Two-pass MFMA scorer for many query rows per KV head where no single pass is possible: batches with sequences longer
+// than one workgroup holds, prompts longer than the teams of sp_score_wide_team.hip hold, and short prompts of few slabs
+// (fewer than 64, up to 3072 keys) without the promise of an idle device.
 //
 // Same quantity as the other scoring kernels: row softmax of the stored queries against the prompt keys
 // (Sec. 3.2 equation of arXiv 2502.02789), max over heads, max/mean over layers, mean over queries (Sec. 3.2.2).

@@ -22,8 +22,18 @@
 //
 // The lines exist twice: a call works in copy (epoch mod 2) and puts "empty" back into the other one as it publishes,
 // so the next call finds it clean; a small kernel sets that up in front of a call that cannot rely on the previous one
-// (no SP_SCORE_WORKSPACE_KEPT).  All workgroups must be resident together (SP_SCORE_EXCLUSIVE_DEVICE); every wait is
-// bounded, and an expired wait turns the call's scores into NaN.
+// (no SP_SCORE_WORKSPACE_KEPT).  The workgroups of a team must be resident together; every wait is bounded.
+//
+// On the promise of an idle device (SP_SCORE_EXCLUSIVE_DEVICE) an expired wait turns the call's scores into NaN.  Without
+// it the kernel is launched twice: a workgroup that has waited about as long as the whole call takes gives up, goes on
+// without waiting and notes that down.  Its line of statistics still goes out for every slab -- a line depends on nothing
+// but the member's own keys -- so after the first launch all lines are there, and the second one, which returns at once
+// where nobody gave up, forms all results again without any wait.  So nothing depends on what else runs on the device,
+// K is read once as a rule and twice at worst, and the scores have the same bits either way.  (Two passes over K before:
+// 24577 keys, 32 layers, 8 KV heads, d = 128, eight queries, whole step: 498 -> 290 us; 128K keys 2604 -> 1351; one query on
+// 20000 keys, logits kept in memory before, 311 -> 252.  Beside another stream's 4096^3 products: 9000 keys 655 -> 557 us,
+// 24577 keys 520 -> 298, 100000 keys 2228 -> 1607, the other stream no slower; four such calls at once on four streams,
+// 24577 keys, 504 -> 294 us each.)
 //
 // Bound by the HBM stream of K for bf16 caches (32 layers, 8 KV heads, d = 128, eight queries, before -> now: 32K keys
 // 349 -> 336 us = 6.4 TB/s, mean over layers 30011 keys 375 -> 337, 128K keys 1570 -> 1301, 9000 keys 168 -> 117;
@@ -49,8 +59,11 @@ struct WideTeamDev : TiledDev {
   int spin_budget;
   uint32_t* lines;         // two copies of [slab][member][32]
   size_t copy_words;
-  uint32_t* status;        // [epoch & 1] != 0: a wait of this call expired; [2]: epoch, calls since the last fill
+  uint32_t* status;        // [epoch & 1] != 0: a wait of this call expired; [2]: epoch, calls since the last fill;
+                           // [3] != 0: a wait of a shared call's first launch expired
+  int launch;              // kAlone; kFirst and kSecond: the launches of a call without the promise of an idle device
 };
+enum { kAlone = 0, kFirst = 1, kSecond = 2 };
 
 // the lines' first copy "empty", status and epoch 0
 __global__ __launch_bounds__(256) void wide_team_fill_kernel(uint4* lines, size_t n_vec, uint32_t* status) {
@@ -69,16 +82,21 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
   W w(p, smem);
   const uint32_t lse_lds = (uint32_t)reinterpret_cast<uintptr_t>(smem) + W::kSmem;  // 32 row log-sum-exps
   // The members of a team sit on one die where one has enough compute units (workgroups are dealt out to the dies
-  // in turn).
-  // (measured, whole call: 32K keys, 16 members, next to each other on one die 352 us, over all dies 363; 128K keys, 64
-  // members, on two dies 1457 us, over all dies 1390)
+  // in turn).  (Measured, whole call: 32K keys, 16 members, next to each other on one die 352 us, over all dies 363; 128K
+  // keys, 64 members, on two dies 1457 us, over all dies 1390.)  Without the promise of an idle device eight members on each
+  // of as many dies as that takes: workgroups start in their order, so of a call that gets a quarter of every die (four
+  // calls at once on four streams) whole teams are resident.  (24577 keys, one call / four at once, us per call: eight on
+  // a die 296 / 295, four 305 / 281, two 306 / 289, all on one die 298 / 563; two passes 498 / 504.)
   const int P = 1 << p.lgP, dies = (int)gridDim.x / kWideTeamDieWGs;
-  const int place = P > kWideTeamDieWGs ? (int)blockIdx.x : (int)blockIdx.x % dies * kWideTeamDieWGs + (int)blockIdx.x / dies;
+  const int most_on_die = p.launch == kAlone && P <= kWideTeamDieWGs ? kWideTeamDieWGs : kWideTeamDieWGs / 4;
+  const int over = min(dies, max(1, P / most_on_die)), share = P / over;  // dies of a team, members on each
+  const int die = (int)blockIdx.x % dies, nth = (int)blockIdx.x / dies;
+  const int place = (die / over * (kWideTeamDieWGs / share) + nth / share) * P + nth % share * over + die % over;
   const int team = place >> p.lgP, member = place & (P - 1);
   const WideTeamDeal& deal = p.deal;
   const bool mean = p.layer_reduce != SP_LAYER_MAX;
   int q = 0, s = deal.start(team, 0), s_end = deal.end(0, s);
-  if (s >= deal.n_slabs) return;
+  if (s >= deal.n_slabs || (p.launch == kSecond && p.status[3] == 0)) return;
   const uint32_t epoch = __builtin_amdgcn_readfirstlane(p.status[2]);  // (turned by the merge kernel)
   uint32_t* const lines_cur = p.lines + (size_t)(epoch & 1u) * p.copy_words;
   uint32_t* const lines_nxt = p.lines + (size_t)(~epoch & 1u) * p.copy_words;
@@ -171,7 +189,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
 #pragma unroll 1
       for (int i0 = 0; i0 < loads; i0 += 4) {  // four loads at a time: more registers are not free
         u32x4 x[4];
-        while (!expired) {
+        while (!expired && M > 0) {  // (a member without keys has no use for the rows' log-sum-exps)
           bool empty = false;
           asm volatile("" ::: "memory");  // (a new look at the lines every time)
 #pragma unroll
@@ -279,7 +297,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
     q = nq; s = ns; s_end = ns_end; l = nl; g = ng;
     buf ^= 1;
   }
-  if (w.wave == 0 && expired && W::lane_id() == 0) atomicOr(p.status + (epoch & 1u), 1u);
+  if (w.wave == 0 && expired && W::lane_id() == 0) atomicOr(p.status + (p.launch == kFirst ? 3u : epoch & 1u), 1u);
   wait_vmcnt<0>();
 }
 
@@ -289,6 +307,15 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
 static size_t copy_bytes(const WideTeamPlan& pl) { return (size_t)pl.deal.n_slabs * 128 << pl.lgP; }
 static size_t result_bytes(const WideTeamPlan& pl, const sp_score_args* a) {
   return align_up(sizeof(float) * 32 * (size_t)pl.n_groups * a->N * wide_tiles(a), 256);
+}
+
+// Polls of a workgroup in a call without the promise of an idle device.  A poll takes 0.5 us or more, a member's keys arrive
+// at 25 KB a us: a member with next to no keys waits for the others through the whole call, so that is allowed three times
+// over, and a millisecond for workgroups that other work keeps from starting.  (Not the 0.1 s of an exclusive call:
+// what an expired wait costs here is another pass over K, so nobody should wait much longer than that takes.)
+static int64_t shared_budget(const WideTeamPlan& pl, const sp_score_args* a) {
+  const int64_t slabs = (pl.deal.n_slabs + pl.deal.teams - 1) / pl.deal.teams;
+  return 2048 + slabs * pl.chunk * a->d * (a->k_dtype == SP_K_FP8_E4M3 ? 1 : 2) / 4096;
 }
 
 static WideTeamPlan make_plan(const sp_score_args* a) { return make_wide_team_plan(a, wide_team_wgs(seq_cu_count())); }
@@ -362,19 +389,27 @@ sp_status wide_team_score(const sp_score_args* a, hipStream_t stream) {
   dev.k_scale = a->d_k_scale;
   for (int l = 0; l < a->L; ++l) dev.k[l] = static_cast<const uint16_t*>(a->k_layers[l]);
   dev.lgP = pl.lgP; dev.chunk = pl.chunk;
+  const bool shared = !(a->flags & SP_SCORE_EXCLUSIVE_DEVICE);
+  dev.launch = shared ? kFirst : kAlone;
   dev.spin_budget = g_spin_budget.load(std::memory_order_relaxed);
+  if (shared) dev.spin_budget = (int)std::min<int64_t>(dev.spin_budget, shared_budget(pl, a));
   char* ws = static_cast<char*>(a->d_workspace);
   dev.lines = reinterpret_cast<uint32_t*>(ws);
   dev.copy_words = copy_bytes(pl) / 4;
   dev.status = reinterpret_cast<uint32_t*>(ws + wide_team_status_offset(a));
   dev.group_scores = reinterpret_cast<float*>(ws + wide_team_status_offset(a) + 256);
-  if (!(a->flags & SP_SCORE_WORKSPACE_KEPT)) {
+  if (shared || !(a->flags & SP_SCORE_WORKSPACE_KEPT)) {
     const size_t n_vec = copy_bytes(pl) / 16;
     hipLaunchKernelGGL(wide_team_fill_kernel, dim3((unsigned)std::min<size_t>((n_vec + 255) / 256, 1024)), dim3(256), 0, stream,
                        reinterpret_cast<uint4*>(ws), n_vec, dev.status);
     if (hipGetLastError() != hipSuccess) return SP_ELAUNCH;
   }
-  const sp_status st = a->d == 64 ? wide_team_by_kind<64>(a, dev, stream) : wide_team_by_kind<128>(a, dev, stream);
+  sp_status st = a->d == 64 ? wide_team_by_kind<64>(a, dev, stream) : wide_team_by_kind<128>(a, dev, stream);
+  if (st == SP_OK && shared) {
+    dev.launch = kSecond;
+    dev.spin_budget = kDefaultSpinBudget;  // (whatever the bound: the lines are all there, one poll per look is enough)
+    st = a->d == 64 ? wide_team_by_kind<64>(a, dev, stream) : wide_team_by_kind<128>(a, dev, stream);
+  }
   if (st != SP_OK) return st;
   return launch_wide_finish(dev, (unsigned)wide_tiles(a), dev.status, stream);
 }

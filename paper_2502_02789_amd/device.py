@@ -42,7 +42,7 @@ class Scorer:
                  exclusive_device: bool = True, keep_workspace: bool = False, max_seqlen: int = 0,
                  k_scale: Optional[torch.Tensor] = None):
         """exclusive_device: promise that nothing else runs on the GPU during the call
-        (SP_SCORE_EXCLUSIVE_DEVICE), which lets sp_score take its single-pass kernels.
+        (SP_SCORE_EXCLUSIVE_DEVICE), which lets the workgroups of its single-pass kernels rely on one another.
         keep_workspace: from the second run() on, pass SP_SCORE_WORKSPACE_KEPT (this object owns
         its workspace, so the promise holds as long as run() is the only thing that writes it;
         anything else that does -- run(general=True), score_pool_select, a failed check() --

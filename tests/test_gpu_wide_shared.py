@@ -1,0 +1,109 @@
+"""One long prompt without SP_SCORE_EXCLUSIVE_DEVICE: the teams of workgroups run without the promise of an idle device,
+and a call whose waits give up completes itself in its second launch (Sec. 3.2 equation, Sec. 3.2.2)."""
+import math
+
+import numpy as np
+import pytest
+
+from oracle import specprefill_oracle as orc
+from paper_2502_02789_amd import synth
+from tests import helpers as hp
+
+pytestmark = pytest.mark.gpu
+
+
+def _scorer(w, inp, mode, bits=16, page=0, n_valid=None, exclusive_device=False):
+    import torch
+    from paper_2502_02789_amd import device as dev
+    kw, k, k_scale = {}, inp["k"], None
+    if bits == 8:
+        k, k_scale = synth.quantize_k_fp8(k)
+        k_scale = torch.from_numpy(np.ascontiguousarray(k_scale)).cuda()
+    if page:
+        k, table = hp.paged_copy(k, inp["cu_seqlens"], page, seed=page, fill=0x7E if bits == 8 else 0x7F00)
+        kw = dict(block_table=torch.from_numpy(table).cuda(), page_size=page, total_tokens=w.T)
+    ks = [torch.from_numpy(x).cuda() if bits == 8 else dev.bf16_from_bits(x) for x in k]
+    nv = None if n_valid is None else torch.tensor([n_valid], dtype=torch.int32).cuda()
+    return dev.Scorer(dev.bf16_from_bits(inp["q"]), ks, torch.tensor([0, w.T], dtype=torch.int32).cuda(), H_kv=w.H_kv,
+                      scale=1.0 / math.sqrt(w.d), layer_reduce=mode, want_lse=True, n_valid=nv, k_scale=k_scale,
+                      exclusive_device=exclusive_device, **kw)
+
+
+@pytest.mark.parametrize("shape, opt", [
+    (dict(tokens=3073, L=4, N=8), {}),                                       # members with next to no keys, few slabs
+    (dict(tokens=4097, L=24, H=8, H_kv=4, N=5, d=64), dict(page=16)),        # one key in the last piece
+    (dict(tokens=6150, L=8, H=64, H_kv=8, N=4), dict(mode=orc.LAYER_MEAN)),  # whole layers and parts of layers
+    (dict(tokens=9000, L=3, H=16, H_kv=4, N=1), dict(mode=orc.LAYER_MEAN)),  # few rows: logits were kept in memory
+    (dict(tokens=5003, L=36, N=8, d=64), dict(mode=orc.LAYER_MEAN, bits=8)),
+    (dict(tokens=16385, L=2, N=2, H=8, H_kv=8), dict(bits=8, page=64)),
+    (dict(tokens=7001, L=5, H=8, H_kv=4, N=12), dict(n_valid=7)),            # heads padded to two columns
+    (dict(tokens=40000, L=1, H=4, H_kv=1, N=8, d=64), {}),                   # members without keys: nobody to wait for them
+])
+def test_a_call_whose_waits_give_up_completes_itself(shape, opt):
+    """The same bits whether every wait is answered (bound as it is), none (bound 0: the second launch does the work) or
+    the device is promised exclusive; the plain kernels' scores and log-sum-exps to tolerance."""
+    from paper_2502_02789_amd import binding as sp
+    shape, opt = dict(shape), dict(opt)
+    mode = opt.pop("mode", orc.LAYER_MAX)
+    w = synth.scaled(synth.workload(3), seqlens=(shape.pop("tokens"),), salient_run=1, **shape)
+    inp = synth.make_qk(w)
+    s = _scorer(w, inp, mode, **opt)
+
+    def call(**kw):
+        s.scores.fill_(float("nan"))
+        s.lse.fill_(float("nan"))
+        s.run(**kw)
+        s.check()                                   # (a call without the flag never reports a time-out)
+        return s.scores.cpu().numpy(), s.lse.cpu().numpy()
+
+    want, want_lse = call(general=True)
+    first = call()
+    hp.assert_scores_close(first[0], want, f"{w.name} {opt}")
+    np.testing.assert_allclose(first[1], want_lse, rtol=0, atol=2e-4)
+    before = sp.sp_set_wait_budget(0)
+    try:
+        runs = [call(), call()]
+    finally:
+        sp.sp_set_wait_budget(before)
+    runs.append(call())
+    e = _scorer(w, inp, mode, exclusive_device=True, **opt)
+    e.run()
+    e.check()
+    runs.append((e.scores.cpu().numpy(), e.lse.cpu().numpy()))
+    for scores, lse in runs:
+        assert np.array_equal(scores, first[0]) and np.array_equal(lse, first[1])
+
+
+def test_calls_on_four_streams_at_once():
+    """Four calls in flight together, each with a workspace of its own, more workgroups than the device holds."""
+    import torch
+    w = synth.scaled(synth.workload(3), seqlens=(20000,), L=4, salient_run=1)
+    inp = synth.make_qk(w)
+    calls = [(_scorer(w, dict(inp, q=np.roll(inp["q"], i, axis=0)), orc.LAYER_MAX), torch.cuda.Stream()) for i in range(4)]
+    want = []
+    for s, _ in calls:
+        s.run()
+        torch.cuda.synchronize()
+        want.append(s.scores.clone())
+        s.scores.fill_(float("nan"))
+    torch.cuda.synchronize()
+    for _ in range(6):
+        for s, stream in calls:
+            with torch.cuda.stream(stream):
+                s.run()
+    torch.cuda.synchronize()
+    for (s, _), x in zip(calls, want):
+        assert torch.equal(s.scores, x)
+
+
+@pytest.mark.parametrize("mode", [orc.LAYER_MAX, orc.LAYER_MEAN])
+@pytest.mark.parametrize("shape", [dict(tokens=3072, L=7, N=8), dict(tokens=2051, L=5, H=16, H_kv=2, N=4, d=64)])
+def test_short_prompts_of_few_slabs_stay_on_two_passes(shape, mode):
+    """One sequence on the two-pass kernels: up to 3072 keys and fewer than 64 slabs, against the oracle."""
+    shape = dict(shape)
+    w = synth.scaled(synth.workload(3), seqlens=(shape.pop("tokens"),), salient_run=1, **shape)
+    inp = synth.make_qk(w)
+    want, want_lse = orc.token_importance(inp["q"], inp["k"], inp["cu_seqlens"], 1.0 / math.sqrt(w.d), mode)
+    got, lse = hp.gpu_score(inp["q"], inp["k"], inp["cu_seqlens"], w.H_kv, 1.0 / math.sqrt(w.d), mode, exclusive_device=False)
+    hp.assert_scores_close(got, want, f"{w.name} mode={mode}")
+    np.testing.assert_allclose(lse, want_lse, rtol=0, atol=2e-4)
