@@ -16,8 +16,8 @@
 //     DPP row rotation and bank masks): a lane ends up with four consecutive keys of one query.
 //   * The query tile of a slab is fetched ONCE per workgroup (the tiled and exchange kernels fetch it once per
 //     wave and 64 keys, half as many bytes again as the keys) one slab ahead, and both operands are read from LDS.
-//   * A ring slot is 8 KiB whatever the element size and head dim (32, 64 or 128 keys), so the bytes in flight per
-//     compute unit are the same 64..128 KiB for all of them.  The loads go through a buffer descriptor per slot
+//   * A wave's ring holds 16 KiB whatever the element size and head dim (two, four or eight items of 32 keys), so the
+//     bytes in flight per compute unit are the same for all of them.  The loads go through a buffer descriptor per item
 //     whose range ends with the sequence: no address arithmetic per lane, and keys that do not exist are not read.
 //   * A wave takes its items of a slab from the last to the first, so that only one copy of the unrolled tile code
 //     (the first) has to know about the ragged end of a sequence; the code has to stay small, a kernel that makes
@@ -42,15 +42,15 @@
 
 namespace sp {
 
-constexpr int kWideTiles = 12;    // 32-key tiles per wave (whole ring slots of one, two or four tiles), and the first
+constexpr int kWideTiles = 12;    // 32-key tiles per wave, and the first
 constexpr int kWideRunTiles = 4;  // of them whose running maxima are in registers where not all fit
 
 template <int D, int LG, bool FP8, bool PAGED>
 __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDev p) {
   extern __shared__ __align__(1024) unsigned char smem[];
   using W = WideKernel<D, LG, FP8, PAGED>;
-  constexpr int KEEP = W::KEEP, SUB = W::SUB;
-  constexpr int kShort = SUB == 1 ? 9 : 8;  // tiles per wave that fit with all their running maxima in registers
+  constexpr int KEEP = W::KEEP;
+  constexpr int kShort = 9;  // tiles per wave that fit with all their running maxima in registers
   using vkeep = typename W::vkeep;
   W w(p, smem);
   SeqUnit cur;
@@ -59,10 +59,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDe
   int l = cur.s0 / p.H_kv, g = cur.s0 - l * p.H_kv;
   w.ah = {w.slab_keys(l, g, cur.seq0), cur.b, 0, cur.M, w.items_of(cur.M)};
   w.issue_queries(l, g, cur.b, 0);
-  if (w.ah.left > 0) w.issue_one();
-  if (w.ah.left > 0) w.issue_one();
-  if (w.sent == 2) wait_vmcnt<2 * kItemLoads>(); else wait_vmcnt<0>();  // the query tile
-  __builtin_amdgcn_s_barrier();
+  w.start_stream();
 
   int slabs = 0;  // slabs finished so far
   bool more = true;
@@ -71,7 +68,6 @@ __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDe
   // all slabs of unit `cur`, tiles_c tiles per wave of which the first run_c have their running maxima in registers
   auto do_unit = [&](auto tiles_c, auto run_c) __attribute__((always_inline)) {
     constexpr int MAXT = decltype(tiles_c)::value, RUN = decltype(run_c)::value;
-    static_assert(MAXT % SUB == 0, "whole items");
     f32x16 held[MAXT];
     vkeep run[RUN];
     const int M = cur.M, b = cur.b;
@@ -114,17 +110,13 @@ __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDe
 
       // log2-probabilities; maximum over the heads of a group and over the unit's slabs
       const int first = w.fold_key(), q_n = W::lane_id() & (W::NS - 1);
-      float* out = out0 + (SUB * (w.wave + (nt - 1) * kTiledWaves)) * out_step + q_n * 32 + first;
-      auto place = [&](int it, int sub) __attribute__((always_inline)) {  // of a tile's results
-        return reinterpret_cast<vkeep*>(out + (sub - it * (SUB * kTiledWaves)) * out_step);
-      };
-      auto live = [&](int it, int sub) __attribute__((always_inline)) {
-        // (sub-tiles of the ragged item that lie beyond the sequence have no place in the result array)
-        return it < nt && (SUB == 1 || it > 0 || (w.wave + (nt - 1) * kTiledWaves) * W::KPI + sub * 32 < M);
+      float* out = out0 + (w.wave + (nt - 1) * kTiledWaves) * out_step + q_n * 32 + first;
+      auto place = [&](int t) __attribute__((always_inline)) {  // of a tile's results
+        return reinterpret_cast<vkeep*>(out - t * kTiledWaves * out_step);
       };
       wide_static_for<0, RUN>([&](auto tc) __attribute__((always_inline)) {
         constexpr int t = decltype(tc)::value;
-        if (t / SUB < nt) {
+        if (t < nt) {
           float x[KEEP];
           w.fold_heads(held[t], neg_lse2, x);
 #pragma unroll
@@ -136,7 +128,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDe
       constexpr int STEP = 2;
       wide_static_for<0, (MAXT - RUN + STEP - 1) / STEP>([&](auto bc) __attribute__((always_inline)) {
         constexpr int t0 = RUN + decltype(bc)::value * STEP, tn = t0 + STEP <= MAXT ? STEP : MAXT - t0;
-        if (t0 / SUB < nt) {
+        if (t0 < nt) {
           vkeep old[tn];
 #pragma unroll
           for (int i = 0; i < tn; ++i)
@@ -145,7 +137,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDe
           if (s != cur.s0 && q_n < p.N) {
 #pragma unroll
             for (int i = 0; i < tn; ++i)
-              if (live((t0 + i) / SUB, (t0 + i) % SUB)) old[i] = *place((t0 + i) / SUB, (t0 + i) % SUB);
+              if (t0 + i < nt) old[i] = *place(t0 + i);
           }
 #pragma unroll
           for (int i = 0; i < tn; ++i) {
@@ -157,14 +149,14 @@ __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDe
           if (q_n < p.N) {
 #pragma unroll
             for (int i = 0; i < tn; ++i)
-              if (live((t0 + i) / SUB, (t0 + i) % SUB)) __builtin_nontemporal_store(old[i], place((t0 + i) / SUB, (t0 + i) % SUB));
+              if (t0 + i < nt) __builtin_nontemporal_store(old[i], place(t0 + i));
           }
         }
       });
       if (s + 1 == cur.s1 && q_n < p.N) {  // the unit's result
         wide_static_for<0, RUN>([&](auto tc) __attribute__((always_inline)) {
           constexpr int t = decltype(tc)::value;
-          if (live(t / SUB, t % SUB)) __builtin_nontemporal_store(run[t], place(t / SUB, t % SUB));
+          if (t < nt) __builtin_nontemporal_store(run[t], place(t));
         });
       }
       w.end_slab();

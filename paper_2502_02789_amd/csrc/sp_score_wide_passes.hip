@@ -24,7 +24,7 @@
 
 namespace sp {
 
-static_assert(kPassWaves == kTiledWaves && kPassSlotBytes == kItemBytes, "the plan counts in items of the stream");
+static_assert(kPassWaves == kTiledWaves, "the plan counts in items of the stream");
 
 struct WidePassDev : TiledDev {
   int chunk, slots;     // keys of a piece; places for pieces: sequence b's pieces start at place pass_first_place
@@ -68,7 +68,7 @@ template <int D, int LG, bool FP8, bool PAGED, int PASS>
 __global__ __launch_bounds__(kTiledThreads) void wide_pass_kernel(const WidePassDev p) {
   extern __shared__ __align__(1024) unsigned char smem[];
   using W = WideKernel<D, LG, FP8, PAGED>;
-  constexpr int KEEP = W::KEEP, SUB = W::SUB, MAXT = kPassTiles;
+  constexpr int KEEP = W::KEEP, MAXT = kPassTiles;
   using vkeep = typename W::vkeep;
   W w(p, smem);
   const uint32_t lse_lds = (uint32_t)reinterpret_cast<uintptr_t>(smem) + W::kSmem;  // PASS 1: two lines of 64 words
@@ -84,10 +84,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_pass_kernel(const WidePass
   int l = cur.s0 / p.H_kv, g = cur.s0 - l * p.H_kv;
   w.ah = {w.slab_keys(l, g, cur.u.seq0), cur.u.b, cur.u.key0, cur.u.M, w.items_of(cur.u.M)};
   issue_rows(l, g, cur.u.b, 0);
-  if (w.ah.left > 0) w.issue_one();
-  if (w.ah.left > 0) w.issue_one();
-  if (w.sent == 2) wait_vmcnt<2 * kItemLoads>(); else wait_vmcnt<0>();  // the query tile
-  __builtin_amdgcn_s_barrier();
+  w.start_stream();
 
   int buf = 0;
   bool more = true;
@@ -121,28 +118,22 @@ __global__ __launch_bounds__(kTiledThreads) void wide_pass_kernel(const WidePass
       w.slab_scale(l, g);
       if constexpr (PASS == 0) {
         float rm = -INFINITY, rs = 0.f;
-        f32x16 tile[SUB];
-        if (nt > 0) w.template item_logits<0>(tile, nt, M, buf, rm, rs);
+        if (nt > 0) w.template item_logits<0>(nt, M, buf, rm, rs);
 #pragma unroll 1
-        for (int it = 1; it < nt; ++it) w.template item_logits<1>(tile, nt, M, buf, rm, rs);
+        for (int it = 1; it < nt; ++it) w.template item_logits<1>(nt, M, buf, rm, rs);
         const float own = w.workgroup_lse(rm, rs, buf);
         const int ln = W::lane_id();
         if (w.wave == 0 && ln < 32) p.lines[((int64_t)(l * p.H_kv + g) * p.slots + cur.slot) * 32 + ln] = own;
       } else {
         const float lse2 = __uint_as_float(lds_peek(lse_lds + buf * 256 + (W::lane_id() & 31) * 4));
-        wide_static_for<0, MAXT / SUB>([&](auto ic) __attribute__((always_inline)) {
+        wide_static_for<0, MAXT>([&](auto ic) __attribute__((always_inline)) {
           constexpr int it = decltype(ic)::value;
           if (it < nt) {
-            f32x16 tile[SUB];
-            w.item_products(tile, buf);
+            float y[KEEP];
+            w.fold_heads(w.item_products(buf), -lse2, y);
+            vkeep& r = run[PASS == 1 ? it : 0];
 #pragma unroll
-            for (int sub = 0; sub < SUB; ++sub) {
-              float y[KEEP];
-              w.fold_heads(tile[sub], -lse2, y);
-              vkeep& r = run[PASS == 1 ? it * SUB + sub : 0];
-#pragma unroll
-              for (int k = 0; k < KEEP; ++k) r[k] = fmaxf(r[k], y[k]);  // (keys beyond the sequence: never read back)
-            }
+            for (int k = 0; k < KEEP; ++k) r[k] = fmaxf(r[k], y[k]);  // (keys beyond the sequence: never read back)
           }
         });
         w.slab_barrier();
@@ -156,13 +147,11 @@ __global__ __launch_bounds__(kTiledThreads) void wide_pass_kernel(const WidePass
       const int q_n = W::lane_id() & (W::NS - 1);
       const int64_t step = (int64_t)p.n_groups * p.N * 32;  // from tile to tile
       float* const out = p.group_scores +
-          ((int64_t)(wide_tile_base(cur.u.seq0, b) + (cur.u.key0 >> 5) + SUB * (w.wave + (nt - 1) * kTiledWaves)) * p.n_groups + cur.grp) * p.N * 32 +
+          ((int64_t)(wide_tile_base(cur.u.seq0, b) + (cur.u.key0 >> 5) + w.wave + (nt - 1) * kTiledWaves) * p.n_groups + cur.grp) * p.N * 32 +
           q_n * 32 + w.fold_key();
       wide_static_for<0, MAXT>([&](auto tc) __attribute__((always_inline)) {
-        constexpr int t = decltype(tc)::value, it = t / SUB, sub = t % SUB;
-        // (sub-tiles of the ragged item that lie beyond the piece have no place in the result array)
-        if (q_n < p.N && it < nt && (SUB == 1 || it > 0 || (w.wave + (nt - 1) * kTiledWaves) * W::KPI + sub * 32 < M))
-          __builtin_nontemporal_store(run[PASS == 1 ? t : 0], reinterpret_cast<vkeep*>(out + (sub - it * (SUB * kTiledWaves)) * step));
+        constexpr int t = decltype(tc)::value;
+        if (q_n < p.N && t < nt) __builtin_nontemporal_store(run[PASS == 1 ? t : 0], reinterpret_cast<vkeep*>(out - t * kTiledWaves * step));
       });
     }
     if (!more) break;

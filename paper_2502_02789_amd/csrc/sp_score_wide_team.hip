@@ -11,8 +11,7 @@
 //     into the rows' log-sum-exps and hands those to the other waves through LDS;
 //   * a slab is 18 us of stream for a workgroup (2048 keys, d = 128) and the ring holds 5 us of it, so the exchange
 //     is short against a slab, and the teams, which never meet, drift apart: while one waits the others have the
-//     memory.  Where an item is one tile (bf16, d = 128) the next slab's first item is computed while the lines
-//     travel, its logits in registers of their own: 32K keys 350 -> 339 us, 128K 1378 -> 1352 (now, with slabs in runs
+//     memory.  The next slab's first item is computed while the lines travel, its logits in registers of their own: 32K keys 350 -> 339 us, 128K 1378 -> 1352 (now, with slabs in runs
 //     of four, 336 and 1301; without any exchange, wrong results, 327 and 1256; with an exchange four times as often
 //     hidden behind three slabs of a quarter of the keys each, and the query tile fetched once per wave, as in the
 //     kernels before: 349 and 1570);
@@ -77,7 +76,7 @@ template <int D, int LG, bool FP8, bool PAGED>
 __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeamDev p) {
   extern __shared__ __align__(1024) unsigned char smem[];
   using W = WideKernel<D, LG, FP8, PAGED>;
-  constexpr int KEEP = W::KEEP, SUB = W::SUB, MAXT = wide_team_tiles(LG);
+  constexpr int KEEP = W::KEEP, MAXT = wide_team_tiles(LG);
   using vkeep = typename W::vkeep;
   W w(p, smem);
   const uint32_t lse_lds = (uint32_t)reinterpret_cast<uintptr_t>(smem) + W::kSmem;  // 32 row log-sum-exps
@@ -110,18 +109,14 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
   int l = s / p.H_kv, g = s - l * p.H_kv;
   w.ah = {w.slab_keys(l, g, 0), 0, key0, M, nt};
   w.issue_queries(l, g, 0, 0);
-  if (w.ah.left > 0) w.issue_one();
-  if (w.ah.left > 0) w.issue_one();
-  if (w.sent == 2) wait_vmcnt<2 * kItemLoads>(); else wait_vmcnt<0>();  // the query tile
-  __builtin_amdgcn_s_barrier();
+  w.start_stream();
 
   f32x16 held[MAXT];
   vkeep run[MAXT];
   // The first item of the next slab is computed while the lines of this one travel (its logits wait in registers of
-  // their own, so where an item is one tile).
-  constexpr bool EARLY = SUB == 1;
-  f32x16 spare[1];
-  bool early = false;  // the first item of the slab at hand is in spare[0], its statistics in (rm, rs)
+  // their own).
+  f32x16 spare;
+  bool early = false;  // the first item of the slab at hand is in `spare`, its statistics in (rm, rs)
   float rm = -INFINITY, rs = 0.f;
 #pragma unroll
   for (int t = 0; t < MAXT; ++t)
@@ -148,20 +143,14 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
     }
     w.begin_slab();
     w.slab_scale(l, g);
-    if constexpr (EARLY) {
-      if (early) {
-        held[0] = spare[0];
-      } else {
-        rm = -INFINITY;
-        rs = 0.f;
-        if (nt > 0) w.template item_logits<0>(&held[0], nt, M, buf, rm, rs);
-      }
-      w.template slab_logits<MAXT, 1>(held, nt, M, buf, rm, rs);
+    if (early) {
+      held[0] = spare;
     } else {
       rm = -INFINITY;
       rs = 0.f;
-      w.slab_logits(held, nt, M, buf, rm, rs);
+      if (nt > 0) held[0] = w.template item_logits<0>(nt, M, buf, rm, rs);
     }
+    w.template slab_logits<MAXT, 1>(held, nt, M, buf, rm, rs);
     const float own = w.workgroup_lse(rm, rs, buf);
     uint32_t* const line = lines_cur + ((size_t)s << (p.lgP + 5));
     if (w.wave == 0) {
@@ -171,13 +160,14 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
         lines_nxt[((size_t)s << (p.lgP + 5)) + member * 32 + ln] = kEmptyLine;
       }
     }
-    if constexpr (EARLY) {
-      early = more && nt > 0;
-      if (early) {
-        rm = -INFINITY;
-        rs = 0.f;
-        w.template item_logits<0>(&spare[0], nt, M, buf ^ 1, rm, rs);
-      }
+    early = more && nt > 0;
+    if (early) {
+      rm = -INFINITY;
+      rs = 0.f;
+      const float c2 = w.c2;
+      w.slab_scale(nl, ng);
+      spare = w.template item_logits<0>(nt, M, buf ^ 1, rm, rs);
+      w.c2 = c2;
     }
     if (w.wave == 0) {
       const int ln = W::lane_id();
@@ -242,7 +232,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
     // log2-probabilities; maximum over the heads of a group and over the slabs
     wide_static_for<0, MAXT>([&](auto tc) __attribute__((always_inline)) {
       constexpr int t = decltype(tc)::value;
-      if (t / SUB < nt) {
+      if (t < nt) {
         float y[KEEP];
         w.fold_heads(held[t], -lse2, y);
 #pragma unroll
@@ -257,14 +247,10 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
       const int group = !mean || sum ? team : p.plain_groups + (s - deal.base()) / deal.part;
       const int q_n = W::lane_id() & (W::NS - 1);
       const int64_t step = (int64_t)p.n_groups * p.N * 32;  // from tile to tile
-      float* const out = p.group_scores + ((int64_t)((key0 >> 5) + SUB * (w.wave + (nt - 1) * kTiledWaves)) * p.n_groups + group) * p.N * 32 +
+      float* const out = p.group_scores + ((int64_t)((key0 >> 5) + w.wave + (nt - 1) * kTiledWaves) * p.n_groups + group) * p.N * 32 +
                          q_n * 32 + w.fold_key();
       auto place_of = [&](int t) __attribute__((always_inline)) {
-        return out + (t % SUB - t / SUB * (SUB * kTiledWaves)) * step;
-      };
-      // (sub-tiles of the ragged item that lie beyond the prompt have no place in the result array)
-      auto live = [&](int t) __attribute__((always_inline)) {
-        return t / SUB < nt && (SUB == 1 || t >= SUB || (w.wave + (nt - 1) * kTiledWaves) * W::KPI + t % SUB * 32 < M);
+        return out - t * kTiledWaves * step;
       };
       if (sum) {
 #pragma unroll
@@ -278,16 +264,16 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
             vkeep old[STEP];
 #pragma unroll
             for (int i = 0; i < STEP; ++i)
-              if (live(t0 + i)) old[i] = W::load_keep(place_of(t0 + i));
+              if (t0 + i < nt) old[i] = W::load_keep(place_of(t0 + i));
 #pragma unroll
             for (int i = 0; i < STEP; ++i)
-              if (live(t0 + i)) run[t0 + i] += old[i];
+              if (t0 + i < nt) run[t0 + i] += old[i];
           }
         }
       }
 #pragma unroll
       for (int t = 0; t < MAXT; ++t) {
-        if (q_n < p.N && live(t)) W::store_keep(place_of(t), run[t]);
+        if (q_n < p.N && t < nt) W::store_keep(place_of(t), run[t]);
 #pragma unroll
         for (int k = 0; k < KEEP; ++k) run[t][k] = -INFINITY;
       }

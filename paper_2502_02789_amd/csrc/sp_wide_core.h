@@ -8,8 +8,12 @@
 
 namespace sp {
 
-constexpr int kItemBytes = 8192;  // a ring slot
-constexpr int kItemLoads = kItemBytes / 1024;
+// A wave's ring of key items, whatever their size.  An item is one 32-key tile: with items of 8 KiB (two or four tiles of
+// 8-bit keys or d = 64) a slot was held while all its tiles were multiplied, and the first of the next slab could not be
+// computed early by the teams.  (Whole call, 32 layers, 8 KV heads, eight queries: 8-bit keys, d = 128, 32K keys 238 -> 232 us,
+// 70000 605 -> 565; 16 layers of d = 64, 33000 keys 144 -> 134, 128K 423 -> 405; nothing beyond the noise where an item was
+// one tile before.)
+constexpr int kWaveRingBytes = 16384;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -33,8 +37,9 @@ struct WideKernel {
   static constexpr int KU = KROW_B / 16;          // its 16-byte units: 16, 8 or 4
   static constexpr int KSH = KU == 16 ? 0 : KU == 8 ? 1 : 2;
   static constexpr int RPI = 64 / KU;             // keys per wave-wide load
-  static constexpr int KPI = kItemBytes / KROW_B; // keys per ring slot: 32, 64 or 128
-  static constexpr int SUB = KPI / 32;            // 32-key tiles per ring slot
+  static constexpr int ITEM_B = 32 * KROW_B;      // an item: the 32 keys of a tile, 8, 4 or 2 KiB
+  static constexpr int LOADS = ITEM_B / 1024;     // wave-wide loads of an item
+  static constexpr int SLOTS = kWaveRingBytes / ITEM_B;  // items in the ring: 2, 4 or 8
   static constexpr int QROW_B = D * 2;
   static constexpr int QU = QROW_B / 16;
   static constexpr int QTILE_B = 32 * QROW_B;
@@ -42,29 +47,29 @@ struct WideKernel {
   static constexpr int NS = 32 >> LG;             // query slots
   static constexpr int KEEP = 16 >> LG;           // keys per lane and tile after the fold over heads: 8, 4 or 2
   typedef float vkeep __attribute__((ext_vector_type(KEEP)));
-  static constexpr int kRingB = kTiledWaves * 2 * kItemBytes;
+  static constexpr int kRingB = kTiledWaves * kWaveRingBytes;
   static constexpr int kSmem = kRingB + 2 * QTILE_B + 2 * kTiledWaves * 32 * 8;
 
   const TiledDev& p;
   int wave;
-  uint32_t ring, qbuf, xchg;  // LDS addresses: this wave's two slots, the two query tiles, the exchange table
+  uint32_t ring, qbuf, xchg;  // LDS addresses: this wave's slots, the two query tiles, the exchange table
   uint32_t ld_row, ld_unit, krd0, qrd0;  // this lane's key and 16-byte unit in a load; where it reads its operands
   uint32_t ts_b;              // bytes from key to key (the host checks that a slot's keys span less than 2 GiB)
   float c2;
 
-  // The stream of key items runs up to two items ahead of the arithmetic, on into the next slab: `ah` is where the
+  // The stream of key items runs up to a ringful ahead of the arithmetic, on into the next slab: `ah` is where the
   // next request comes from, `nx` the slab behind the one being computed (`fresh`: not moved to yet).  A wave takes
   // items wave, wave + 8, ... of the M keys its workgroup owns of a sequence, the last one first.
   struct Slab { const unsigned char* keys; int b, first, M, left; };  // first: of the owned keys; left: items not yet requested
   Slab ah, nx;
   bool fresh;
-  int sent, pos;  // items requested / consumed so far; item number x sits in ring slot x & 1
+  int sent, pos;  // items requested / consumed so far; item number x sits in ring slot x mod SLOTS
 
   __device__ __forceinline__ WideKernel(const TiledDev& p_, unsigned char* smem) : p(p_) {
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
     const uint32_t base = (uint32_t)reinterpret_cast<uintptr_t>(smem);
-    ring = base + wave * 2 * kItemBytes;
+    ring = base + wave * kWaveRingBytes;
     qbuf = base + kRingB;
     xchg = qbuf + 2 * QTILE_B;
     ts_b = (uint32_t)p.ts * ESZ;
@@ -106,15 +111,15 @@ struct WideKernel {
   __device__ __forceinline__ const unsigned char* slab_keys(int l, int g, int seq0) const {
     return reinterpret_cast<const unsigned char*>(p.k[l]) + ESZ * ((int64_t)g * p.hs + (PAGED ? 0 : (int64_t)seq0 * p.ts));
   }
-  // keys [key_first, key_first + KPI) of sequence b, of which the first `rows` (>= 1) exist -> ring slot
+  // keys [key_first, key_first + 32) of sequence b, of which the first `rows` (>= 1) exist -> ring slot
   __device__ __forceinline__ void issue_keys(const unsigned char* slab, int b, int key_first, int rows, int slot) {
-    const uint32_t dst = ring + slot * kItemBytes;
+    const uint32_t dst = ring + slot * ITEM_B;
     if constexpr (PAGED) {
       // (the RPI keys of one load lie in one page: pages hold a power of two >= 8 keys, >= RPI where the host checks)
       // Two loops that stay loops, the next page's entry fetched while a page's loads go out: unrolled, this is most
       // of the kernel's code, more than the instruction cache holds.
       const ScalarTable table = scalar_table(p.block_table + (int64_t)b * p.blocks_per_seq);
-      const int page = 1 << p.lg_page, last = (key_first + min(rows, KPI) - 1) >> p.lg_page;
+      const int page = 1 << p.lg_page, last = (key_first + min(rows, 32) - 1) >> p.lg_page;
       int pg = key_first >> p.lg_page, entry = table[pg];
       int in_page = key_first & (page - 1);
       const uint32_t lane_row = ld_row;
@@ -123,7 +128,7 @@ struct WideKernel {
       for (;;) {
         const unsigned char* base = slab + ESZ * ((int64_t)entry * p.page_stride) + (int64_t)in_page * (int64_t)ts_b;
         entry = table[min(pg + 1, last)];
-        const int j_end = min(kItemLoads, j + ((page - in_page) / RPI));
+        const int j_end = min(LOADS, j + ((page - in_page) / RPI));
 #pragma unroll 1
         for (; j < j_end; ++j) {
           const int left = min(rows - j * RPI, RPI);
@@ -131,27 +136,27 @@ struct WideKernel {
           load1k(base, bytes, lane_row + (ld_unit ^ (uint32_t)(((4 * j) & (KU - 1)) << 4)), dst + j * 1024);
           base += (int64_t)RPI * (int64_t)ts_b;
         }
-        if (j == kItemLoads) break;
+        if (j == LOADS) break;
         ++pg;
         in_page = 0;
       }
     } else {
       const unsigned char* base = slab + (int64_t)key_first * (int64_t)ts_b;
-      const uint32_t bytes = (uint32_t)(min(rows, KPI) - 1) * ts_b + KROW_B;
+      const uint32_t bytes = (uint32_t)(min(rows, 32) - 1) * ts_b + KROW_B;
 #pragma unroll
-      for (int j = 0; j < kItemLoads; ++j) {
+      for (int j = 0; j < LOADS; ++j) {
         load1k(base, bytes, lane_offset(j) + (uint32_t)(j * RPI) * ts_b, dst + j * 1024);
       }
     }
   }
 
   __device__ __forceinline__ int items_of(int M) const {
-    return __builtin_amdgcn_readfirstlane(((M + KPI - 1) / KPI - wave + kTiledWaves - 1) / kTiledWaves);
+    return __builtin_amdgcn_readfirstlane(((M + 31) / 32 - wave + kTiledWaves - 1) / kTiledWaves);
   }
   __device__ __forceinline__ void issue_one() {
     --ah.left;
-    const int key = (wave + ah.left * kTiledWaves) * KPI;
-    issue_keys(ah.keys, ah.b, ah.first + key, ah.M - key, sent & 1);
+    const int key = (wave + ah.left * kTiledWaves) * 32;
+    issue_keys(ah.keys, ah.b, ah.first + key, ah.M - key, sent & (SLOTS - 1));
     ++sent;
   }
   __device__ __forceinline__ void refill() {
@@ -161,7 +166,13 @@ struct WideKernel {
   // a slab begins: `nx` has been set to the one behind it (left = 0: there is none)
   __device__ __forceinline__ void begin_slab() {
     fresh = true;
-    while (sent - pos < 2 && (ah.left > 0 || (fresh && nx.left > 0))) refill();  // (waves with less than two items per slab)
+    while (sent - pos < SLOTS && (ah.left > 0 || (fresh && nx.left > 0))) refill();  // (waves with less than a ringful per slab)
+  }
+  // a workgroup's first slab: the first items on their way, the query tile (requested before them) here
+  __device__ __forceinline__ void start_stream() {
+    while (sent < SLOTS && ah.left > 0) issue_one();
+    wait_vmcnt_upto(sent * LOADS);
+    __builtin_amdgcn_s_barrier();
   }
   __device__ __forceinline__ void end_slab() {
     if (fresh && ah.left == 0) ah = nx;
@@ -185,21 +196,24 @@ struct WideKernel {
     }
   }
 
-  __device__ __forceinline__ void slab_scale(int l, int g) {
+  // logits -> base-2 domain for (l, g), an 8-bit cache's key scale included (through the scalar cache, as a block table)
+  __device__ __forceinline__ float scale_of(int l, int g) const {
     if constexpr (FP8) {
-      if (p.k_scale) c2 = p.c * p.k_scale[l * p.H_kv + g];
+      if (p.k_scale) return p.c * __int_as_float(scalar_table(reinterpret_cast<const int32_t*>(p.k_scale))[l * p.H_kv + g]);
     }
+    return p.c;
   }
+  __device__ __forceinline__ void slab_scale(int l, int g) { c2 = scale_of(l, g); }
 
   __device__ __forceinline__ bf16x8 read16(uint32_t addr) const {
     return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(lds_ptr(addr));
   }
-  // logits of 32-key tile `sub` of the slot against the 32 query rows of buffer `buf`
-  __device__ __forceinline__ f32x16 mfma_tile(int slot, int sub, int buf) {
+  // logits of the slot's keys against the 32 query rows of buffer `buf`
+  __device__ __forceinline__ f32x16 mfma_tile(int slot, int buf) {
     f32x16 a = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     uint32_t kb = krd0, qb = qrd0;
     asm volatile("" : "+v"(kb), "+v"(qb));
-    const uint32_t kadd = slot * kItemBytes + sub * 32 * KROW_B, qadd = buf * QTILE_B;
+    const uint32_t kadd = slot * ITEM_B, qadd = buf * QTILE_B;
     bf16x8 kf[KS], qf[KS];
     if constexpr (FP8) {
       u32x4 raw[KS / 2];
@@ -308,59 +322,56 @@ struct WideKernel {
     __builtin_amdgcn_global_load_lds(line + (lane_id() & 31), lds_ptr(dst), 4, 0, 0);
   }
 
-  // the next item's products with the query rows of buffer `buf`, tile by tile
-  __device__ __forceinline__ void item_products(f32x16* tile, int buf) {
-    const int slot = pos & 1;
-    // (vector-memory instructions of a wave complete in order; those of the next item are the only key loads behind
+  // the next item's products with the query rows of buffer `buf`
+  __device__ __forceinline__ f32x16 item_products(int buf) {
+    // (vector-memory instructions of a wave complete in order; those of later items are the only key loads behind
     // this one's; result stores there only make the wait stricter)
-    if (sent - pos == 2) wait_vmcnt<kItemLoads>(); else wait_vmcnt<0>();
-#pragma unroll
-    for (int sub = 0; sub < SUB; ++sub) tile[sub] = mfma_tile(slot, sub, buf);
+    const int later = sent - pos - 1;
+    if (later == SLOTS - 1) wait_vmcnt<(SLOTS - 1) * LOADS>(); else wait_vmcnt_upto(later * LOADS);
+    const f32x16 a = mfma_tile(pos & (SLOTS - 1), buf);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot's reads are done: it may be overwritten
     ++pos;
     refill();
+    return a;
   }
-  // Item IT of the wave's nt items of a slab: its logits into tile[], and the lane's row's statistics over the wave's
-  // keys so far: (rm, rs) = maximum of the base-2 logits (as rounded) and sum of exp2 relative to it
+  // Item IT of the wave's nt items of a slab: its logits, and the lane's row's statistics over the wave's keys so far:
+  // (rm, rs) = maximum of the base-2 logits (as rounded) and sum of exp2 relative to it
   template <int IT>
-  __device__ __forceinline__ void item_logits(f32x16* tile, int nt, int M, int buf, float& rm, float& rs) {
-    item_products(tile, buf);
+  __device__ __forceinline__ f32x16 item_logits(int nt, int M, int buf, float& rm, float& rs) {
+    f32x16 a = item_products(buf);
+    if constexpr (IT == 0) {  // the ragged end of the keys is in some wave's last item
+      const int left_wave = M - (wave + (nt - 1) * kTiledWaves) * 32;
+      if (left_wave < 32) {
+        const int left = left_wave - (lane_id() >> 5) * 4;
 #pragma unroll
-    for (int sub = 0; sub < SUB; ++sub) {
-      f32x16& a = tile[sub];
-      if constexpr (IT == 0) {  // the ragged end of the keys is in some wave's last item
-        const int left_wave = M - (wave + (nt - 1) * kTiledWaves) * KPI - sub * 32;
-        if (left_wave < 32) {
-          const int left = left_wave - (lane_id() >> 5) * 4;
-#pragma unroll
-          for (int i = 0; i < 16; ++i)
-            if ((i >> 2) * 8 + (i & 3) >= left) a[i] = -INFINITY;
-        }
+        for (int i = 0; i < 16; ++i)
+          if ((i >> 2) * 8 + (i & 3) >= left) a[i] = -INFINITY;
       }
-      float tm = a[0];
-#pragma unroll
-      for (int i = 1; i < 16; ++i) tm = fmaxf(tm, a[i]);
-      const float m_new = fmaxf(rm, tm * c2);
-      // (-inf: no key of the lane so far, or none whose logit fits fp32)
-      const float off = (m_new == -INFINITY) ? 0.f : -m_new;
-      float s0 = rs * fast_exp2(rm + off), s1 = 0.f, s2 = 0.f, s3 = 0.f;
-#pragma unroll
-      for (int i = 0; i < 16; i += 4) {
-        s0 += fast_exp2(fmaf(a[i], c2, off));
-        s1 += fast_exp2(fmaf(a[i + 1], c2, off));
-        s2 += fast_exp2(fmaf(a[i + 2], c2, off));
-        s3 += fast_exp2(fmaf(a[i + 3], c2, off));
-      }
-      rm = m_new;
-      rs = (s0 + s1) + (s2 + s3);
     }
+    float tm = a[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) tm = fmaxf(tm, a[i]);
+    const float m_new = fmaxf(rm, tm * c2);
+    // (-inf: no key of the lane so far, or none whose logit fits fp32)
+    const float off = (m_new == -INFINITY) ? 0.f : -m_new;
+    float s0 = rs * fast_exp2(rm + off), s1 = 0.f, s2 = 0.f, s3 = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; i += 4) {
+      s0 += fast_exp2(fmaf(a[i], c2, off));
+      s1 += fast_exp2(fmaf(a[i + 1], c2, off));
+      s2 += fast_exp2(fmaf(a[i + 2], c2, off));
+      s3 += fast_exp2(fmaf(a[i + 3], c2, off));
+    }
+    rm = m_new;
+    rs = (s0 + s1) + (s2 + s3);
+    return a;
   }
   // items FIRST and up into held[]
   template <int MAXT, int FIRST = 0>
   __device__ __forceinline__ void slab_logits(f32x16 (&held)[MAXT], int nt, int M, int buf, float& rm, float& rs) {
-    wide_static_for<FIRST, MAXT / SUB>([&](auto ic) __attribute__((always_inline)) {
+    wide_static_for<FIRST, MAXT>([&](auto ic) __attribute__((always_inline)) {
       constexpr int it = decltype(ic)::value;
-      if (it < nt) item_logits<it>(&held[it * SUB], nt, M, buf, rm, rs);
+      if (it < nt) held[it] = item_logits<it>(nt, M, buf, rm, rs);
     });
   }
   // (max, sum) pairs a and b -> one
@@ -376,7 +387,7 @@ struct WideKernel {
   __device__ __forceinline__ void slab_barrier() const {
     // this wave's share of the next slab's query tile has landed (it was sent before this slab's refills; a wave
     // whose items in flight are older than that waits for them too)
-    if (sent - pos == 2) wait_vmcnt<2 * kItemLoads>(); else if (sent - pos == 1) wait_vmcnt<kItemLoads>(); else wait_vmcnt<0>();
+    wait_vmcnt_upto((sent - pos) * LOADS);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
   }

@@ -17,7 +17,7 @@
 namespace sp {
 
 constexpr int kPassWaves = 8;
-constexpr int kPassSlotBytes = 8192;                             // of keys: what a wave takes at a time
+constexpr int kPassItemKeys = 32;                                // what a wave takes at a time
 constexpr int kPassTiles = 16;                                   // 32-key tiles per wave
 constexpr int kPassMaxKeys = kPassTiles * 32 * kPassWaves;       // keys of a piece
 constexpr int kPassBatchKeys = 2048;                             // ... where the sequences' lengths are not known here
@@ -28,7 +28,7 @@ SP_PLAN_FN int pass_first_place(int seq0, int b, int chunk) { return seq0 / chun
 struct WidePassPlan { int chunk, slots, per, n_groups, gpl; };
 
 inline WidePassPlan make_wide_pass_plan(const sp_score_args* a) {
-  const int slabs = a->L * a->H_kv, kpi = kPassSlotBytes / (a->d * (a->k_dtype == SP_K_FP8_E4M3 ? 1 : 2));
+  const int slabs = a->L * a->H_kv, round = kPassItemKeys * kPassWaves;
   const bool mean = a->layer_reduce == SP_LAYER_MEAN;
   WidePassPlan best = {};
   int64_t best_cost = INT64_MAX;
@@ -51,7 +51,7 @@ inline WidePassPlan make_wide_pass_plan(const sp_score_args* a) {
     pl.chunk = a->B > 1 ? chunk : (int)((a->T + n - 1) / n + 31) / 32 * 32;
     pl.slots = a->B > 1 ? (int)(a->T / chunk) + a->B : (int)((a->T + pl.chunk - 1) / pl.chunk);
     if (a->B > 1 && chunk < kPassBatchKeys && (int64_t)pl.slots * slabs > 256) break;
-    const int64_t keys = (int64_t)((pl.chunk + kpi * kPassWaves - 1) / (kpi * kPassWaves)) * kpi * kPassWaves;
+    const int64_t keys = (int64_t)((pl.chunk + round - 1) / round) * round;
     for (int per = 1; per <= (mean ? a->H_kv : slabs); per = per < 16 ? per + 1 : per + per / 8) {
       if (mean && a->H_kv % per != 0) continue;
       const int groups = (slabs + per - 1) / per;
