@@ -48,7 +48,7 @@ constexpr int kWideRunTiles = 4;  // of them whose running maxima are in registe
 template <int D, int LG, bool FP8, bool PAGED>
 __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDev p) {
   extern __shared__ __align__(1024) unsigned char smem[];
-  using W = WideKernel<D, LG, FP8, PAGED>;
+  using W = WideKernel<D, LG, FP8, PAGED, false>;
   constexpr int KEEP = W::KEEP;
   constexpr int kShort = 9;  // tiles per wave that fit with all their running maxima in registers
   using vkeep = typename W::vkeep;

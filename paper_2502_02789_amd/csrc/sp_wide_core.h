@@ -29,7 +29,8 @@ __device__ __forceinline__ void wide_static_for(F&& f) {
 // per sequence than the keys need, (T >> 5) + B in all)
 __device__ __forceinline__ int wide_tile_base(int seq0, int b) { return (seq0 >> 5) + b; }
 
-template <int D, int LG, bool FP8, bool PAGED>
+// READ_AHEAD: of 8-bit keys' operands (below); it takes registers that the kernel with twelve held tiles has not got
+template <int D, int LG, bool FP8, bool PAGED, bool READ_AHEAD = true>
 struct WideKernel {
   static constexpr int ESZ = FP8 ? 1 : 2;
   static constexpr int KS = D / 16;               // MFMA k-steps
@@ -231,6 +232,20 @@ struct WideKernel {
           o[2 * x + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw[t >> 1][2 * (t & 1) + x], 1.0f, true));
         }
         a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, o), qf[t], a, 0, 0, 0);
+      }
+      // All key units and two query units are read ahead: left to itself the compiler waits for every read in front of
+      // the product it is for, eight LDS round trips a tile (whole call, 32K keys, 8B shape 232 -> 224 us; three ahead 227,
+      // four spill: 294).  (The 8-bit matrix instructions, which would take the stored bytes with the queries split into
+      // two terms each, are no faster than that, 223 us, and round sums to 2^-17 of their terms; the bf16 ones to 2^-24.)
+      if constexpr (READ_AHEAD) {
+        constexpr int kAhead = 2;
+        __builtin_amdgcn_sched_group_barrier(0x100, KS / 2 + kAhead, 0);
+#pragma unroll
+        for (int t = 0; t < KS; ++t) {
+          __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          if (t < KS - kAhead) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
       }
       return a;
     }
