@@ -77,8 +77,8 @@ __device__ __forceinline__ void store_f32_agent(float* dst, float v) { store32_a
 template <int D>
 __global__ __launch_bounds__(kFusedThreads) void fused_short_kernel(const FusedDev p) {
   constexpr int KS = D / 32;  // MFMA steps along the head dim
-  __shared__ double wide[kFusedMaxKeys];  // first the pooled scores, then (as 64-bit keys) the selection's keys
-  static_assert(kFusedMaxKeys >= kSingleMaxChunks, "the selection's keys reuse the pooled scores' room");
+  __shared__ double wide[kPoolRoom];  // first the pooled scores, then (as 64-bit keys) the selection's keys
+  static_assert(kPoolRoom >= kSingleMaxChunks && kPoolSegment >= kFusedMaxKeys, "the selection's keys reuse the pooled scores' room");
   __shared__ float score_lds[kFusedMaxKeys];
   // the softmax rows' log-sum-exps, later the chunk scores
   __shared__ __align__(16) unsigned char lse_or_cs[kSingleMaxChunks * sizeof(double)];
@@ -251,27 +251,8 @@ __global__ __launch_bounds__(kFusedThreads) void fused_short_kernel(const FusedD
   __syncthreads();
 
   // ---- phase 2c: Sec. 3.2.3 on the scores in LDS; the same fp64 arithmetic in the same order as sp_pool_select ----
-  const SelDev& sp_ = p.sel;
-  for (int i = tid; i < p.M; i += kFusedThreads) {
-    const int a = max(0, i - sp_.radius), e = min(p.M - 1, i + sp_.radius);
-    double sum = 0.0;
-#pragma unroll 8
-    for (int x = a; x <= e; ++x) sum += (double)score_lds[x];
-    wide[i] = sum / (double)(e - a + 1);
-  }
-  __syncthreads();
-  const int n_chunks = (p.M + sp_.chunk - 1) / sp_.chunk;
-  for (int j = tid; j < n_chunks; j += kFusedThreads) {
-    const int s0 = j * sp_.chunk, s1 = min(s0 + sp_.chunk, p.M);
-    double t = 0.0;
-#pragma unroll 8
-    for (int x = s0; x < s1; ++x) t += wide[x];
-    const double mean = t / (double)(s1 - s0);
-    cs_lds[j] = mean;
-    if (sp_.chunk_scores_out) sp_.chunk_scores_out[j] = (float)mean;
-  }
-  __syncthreads();
-  select_emit_single(sp_, cs_lds, reinterpret_cast<uint64_t*>(wide));
+  pool_chunks_in_lds(p.sel, score_lds, wide, cs_lds);
+  select_emit_single(p.sel, cs_lds, reinterpret_cast<uint64_t*>(wide));
 }
 
 static bool fused_shape_ok(const sp_score_args* a) {

@@ -268,6 +268,19 @@ __global__ __launch_bounds__(1024) void select_emit_single_kernel(const SelDev p
   select_emit_single(p, p.cs, keys);
 }
 
+// One short sequence: pooling, selection and compaction by one workgroup, all in LDS.
+constexpr int kOneLaunchTokens = 2048;
+__global__ __launch_bounds__(1024) void pool_select_single_kernel(const SelDev p) {
+  __shared__ float score[kOneLaunchTokens];
+  __shared__ double wide[kPoolRoom];  // first the pooled scores, then (as 64-bit keys) the selection's keys
+  __shared__ double cs[kSingleMaxChunks];
+  static_assert(kPoolRoom >= kSingleMaxChunks && kPoolSegment >= kPoolThreads, "the selection's keys reuse the pooled scores' room");
+  for (int i = threadIdx.x; i < p.T; i += 1024) score[i] = p.scores[i];
+  __syncthreads();
+  pool_chunks_in_lds(p, score, wide, cs);
+  select_emit_single(p, cs, reinterpret_cast<uint64_t*>(wide));
+}
+
 __global__ __launch_bounds__(1024) void cu_keep_kernel(const SelDev p) { scan_seq_keep(p); }
 
 // one thread per prompt token: if its chunk is kept, write its flat index to its slot
@@ -351,7 +364,13 @@ static sp_status run_pool_select(const sp_pool_select_args* a, void* scratch, hi
   const size_t per_block = long_chunks ? 4 : kPoolThreads / a->chunk;
   const unsigned pool_blocks = (unsigned)std::max<size_t>(1, std::min<size_t>((mc + per_block - 1) / per_block, 65535));
   if (a->B == 1 && (a->T + a->chunk - 1) / a->chunk <= kSingleMaxChunks) {
-    // one sequence (its length is T, known here): no chunk table, no cross-sequence scan
+    // One sequence (its length is T, known here): no chunk table, no cross-sequence scan.  One launch while one workgroup
+    // pools in the time of a second launch (chunks of 32, window 13, one and two launches in us: 500 tokens 4.7 and 6.1,
+    // 1000 5.1 and 6.3, 2048 6.6 and 6.8, 3001 9.0 and 7.4).
+    if (a->T <= kOneLaunchTokens && !long_chunks) {
+      hipLaunchKernelGGL(pool_select_single_kernel, dim3(1), dim3(1024), 0, stream, p);
+      return launch_status();
+    }
     if (long_chunks) hipLaunchKernelGGL(pool_long_chunk_kernel<true>, dim3(pool_blocks), dim3(256), 0, stream, p);
     else hipLaunchKernelGGL(pool_chunk_kernel<true>, dim3(pool_blocks), dim3(kPoolThreads), 0, stream, p);
     hipLaunchKernelGGL(select_emit_single_kernel, dim3(1), dim3(1024), 0, stream, p);

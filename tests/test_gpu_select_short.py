@@ -1,0 +1,38 @@
+"""Selection of one short sequence: the forms of pooling (in one workgroup's LDS, by many workgroups) and of ranking (by
+counting, by digits) at their edges, against the oracle (Sec. 3.2.3)."""
+import numpy as np
+import pytest
+
+from oracle import specprefill_oracle as orc
+from tests import helpers as hp
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T, chunk, window, rate", [
+    (1, 1, 1, 1.0), (7, 8, 13, 0.5), (64, 1, 1, 0.1), (65, 1, 3, 0.9), (255, 1, 13, 0.3), (256, 1, 5, 0.01), (257, 1, 5, 0.3),
+    (2047, 7, 13, 0.3), (2048, 8, 13, 0.2), (2048, 1, 1, 0.05), (2048, 9, 4095, 0.5), (2048, 256, 13, 0.3), (1500, 257, 13, 0.5),
+    (2049, 8, 13, 0.2), (2049, 9, 13, 0.2), (8192, 32, 13, 0.1), (8191, 32, 13, 1.0), (8193, 33, 13, 0.1),
+])
+@pytest.mark.parametrize("kind", ["plain", "ties", "nan"])
+def test_one_short_sequence(T, chunk, window, rate, kind):
+    rng = np.random.default_rng(T + chunk)
+    x = np.exp(2.0 * rng.standard_normal(T)).astype(np.float32) / 16000
+    if kind == "ties":
+        x = (np.round(x * 4e4) / 4e4).astype(np.float32)
+    if kind == "nan":
+        x[T // 2] = np.nan
+    cu = np.array([0, T], dtype=np.int32)
+    sel = hp.gpu_pool_select(x, cu, chunk, window, rate)
+    if kind == "nan":
+        assert sel.cu_keep.cpu().tolist() == [0, -1] and (sel.kept_idx == -1).all()
+        return
+    kept, cu_keep, cs, _ = orc.pool_select(x, cu, chunk, window, rate)
+    assert sel.cu_keep.cpu().tolist() == cu_keep.tolist()
+    np.testing.assert_array_equal(sel.chunk_scores.cpu().numpy()[:len(cs)], cs.astype(np.float32))
+    got = sel.kept_idx.cpu().numpy()
+    # (chunk means are the oracle's to a rounding of fp64: what ties in exact arithmetic may differ there)
+    hp.selection_matches(got, sel.cu_keep.cpu().numpy(), x, cu, chunk, window, rate, 1e-12)
+    assert (got[int(cu_keep[1]):] == -1).all()
+    few = hp.gpu_pool_select(x, cu, chunk, window, rate, capacity=max(1, len(kept) // 2), want_chunk_scores=False)
+    np.testing.assert_array_equal(few.kept_idx.cpu().numpy(), got[:max(1, len(kept) // 2)])
