@@ -5,8 +5,8 @@
 //
 // All arithmetic is fp64 on the fp32 input scores, summed in index order with adds and
 // divides only, so the chunk scores (and therefore the kept set) do not depend on how the
-// work is split over lanes.  Top-k is a radix select on order-preserving 64-bit keys held in registers, followed by
-// an ordered count that resolves equal scores to the lower chunk index.
+// work is split over lanes.  Top-k is a selection of the k-th of order-preserving 64-bit keys held in registers, followed
+// by an ordered count; equal scores are resolved to the lower chunk index.
 #include <mutex>
 
 // the k formula below must stay a separate multiply and subtract
@@ -225,8 +225,8 @@ __device__ __forceinline__ int select_chunks_from_memory(const double* cs, int n
 // Without a chunk table the workgroup that finishes last (a word the pooling kernel has cleared counts them) adds the
 // sequences' counts up, which the table variant leaves to a launch of its own.
 __global__ __launch_bounds__(1024) void select_kernel(const SelDev p) {
-  __shared__ int hist[3 * 256];
-  __shared__ int sh[32];
+  __shared__ int hist[kSelectHist];
+  __shared__ int sh[48];
   const int b = blockIdx.x, t = threadIdx.x;
   const int M = p.cu[b + 1] - p.cu[b];
   const int c0 = chunk_base(p, b), n = (M + p.chunk - 1) / p.chunk;

@@ -95,69 +95,42 @@ __device__ __forceinline__ int reg_chunk(int i) {
   return ((int)(threadIdx.x >> 6) * I + i) * 64 + (int)(threadIdx.x & 63);
 }
 
-// Radix select over 64-bit keys in registers, eight bits a pass from the top: a chunk is kept if its key is above
-// `prefix`, or equal to it and among the first `need` of those in index order.  Stops as soon as all keys of the bucket
-// in hand are needed (usually after two or three passes; then need = n).  `skip_top`: all keys share their top
-// byte, which is prefix's.  Call with all 1024 threads; `hist` has room for 3 x 256 counters.  One barrier per
-// pass: the counters of pass i live in hist[i % 3], the next pass's are cleared meanwhile (their
-// last readers finished two barriers ago), and every wave finds the bucket for itself.
-template <int I>
-__device__ __forceinline__ void radix_select_kth(const uint64_t (&key)[I], int n, int k, bool skip_top, uint64_t top, int* hist,
-                                                 uint64_t* prefix_out, int* need_out) {
-  const int t = threadIdx.x;
-  const int first_pass = skip_top ? 1 : 0;
-  if (t < 256) hist[first_pass * 256 + t] = 0;
-  __syncthreads();
-  uint64_t prefix = skip_top ? top : 0;
-  int need = k;
-#pragma unroll 1
-  for (int pass = first_pass; pass < 8; ++pass) {
-    int* cur = hist + (pass % 3) * 256;
-    int* nxt = hist + ((pass + 1) % 3) * 256;
-    if (t < 256) nxt[t] = 0;
-    const int shift = (7 - pass) * 8;
-    const uint64_t himask = (pass == 0) ? 0ull : (~0ull << (shift + 8));
-#pragma unroll
-    for (int i = 0; i < I; ++i) {
-      const bool in_play = reg_chunk<I>(i) < n && (key[i] & himask) == prefix;
-      const int digit = (int)((key[i] >> shift) & 255u);
-      // Scores of one prompt share their sign and most exponent bits, so in the upper passes a
-      // whole wave lands in one counter, and 64 additions to one LDS word are done one after
-      // the other: where the wave's digits all agree, one lane adds the count.
-      const unsigned long long mask = __ballot(in_play);
-      if (mask == 0) continue;
-      const int leader = __builtin_amdgcn_readfirstlane(__ffsll(mask) - 1);
-      const int first = __builtin_amdgcn_readlane(digit, leader);
-      if (__ballot(in_play && digit != first) == 0) {
-        if ((t & 63) == leader) atomicAdd(&cur[first], __popcll(mask));
-      } else if (in_play) {
-        atomicAdd(&cur[digit], 1);
-      }
-    }
-    __syncthreads();
-    int bucket;
-    bool all;
-    find_bucket(cur, need, &bucket, &need, &all);
-    prefix |= (uint64_t)bucket << shift;
-    if (all) {  // every key with this prefix is kept, and none has smaller lower bits than zero
-      need = n;
-      break;
-    }
-  }
-  *prefix_out = prefix;
-  *need_out = need;
-}
-
 // The k best of n chunks (scores cs[0..n), equal scores to the lower index) by one workgroup of 1024 threads:
 // emit(j, rank) for every kept chunk j, the rank-th of them in index order, emit(j, -1) for the others; returns
 // the number of kept chunks (*last_kept: chunk n - 1 among them), or -1 if a score is NaN (nothing is emitted then).
+//
+// The k-th largest key by counting in classes of equal width between the smallest and the largest key (their
+// upper halves): the class that holds it is counted again in narrower classes until all of it is kept, all its keys are
+// equal, or it has no more than a wave's worth of chunks, which are ranked among themselves -- usually after one pass.
+// (Digits of eight fixed bits took three passes, the first of them with nearly all keys in one or two counters, whose
+// additions LDS performs one after the other.  Whole selection, window 1, single tokens: eight sequences of 8000 28.4 -> 22.9 us,
+// of 16000 36.9 -> 27.0, one of 2000 10.6 -> 8.5; 1024 and 2048 smoothed chunks of one sequence 9.6 -> 9.4 and 10.7 -> 10.2, with
+// three tenths kept 10.0 -> 11.5 and 12.8 -> 13.5.)
+// `hist` has room for kSelectHist counters, `sh` for 48.
+constexpr int kSelectHist = 1024 + 64;
+// the least (MAX: the largest) of a wave's values
+template <bool MAX>
+__device__ __forceinline__ uint32_t wave_extreme(uint32_t v) {
+  auto pick = [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return MAX ? max(a, b) : min(a, b); };
+  v = pick(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true));   // lane ^ 1, lane ^ 2 in the quad,
+  v = pick(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true));
+  v = pick(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, true));  // the mirrored half row and row
+  v = pick(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, true));
+  const uint32_t a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
+  const uint32_t c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
+  return pick(pick(a, b), pick(c, d));
+}
 template <int I, typename Emit>
 __device__ __forceinline__ int select_chunks(const double* cs, int n, int k, int* hist, int* sh, bool* last_kept, Emit emit) {
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-  __shared__ uint64_t key0;
-  __shared__ int last_sh;
+  // classes (a lane sums PER of them: a gap behind every PER)
+  constexpr int LG_BINS = I <= 2 ? 9 : 10, BINS = 1 << LG_BINS, PER = BINS / 64;
+  __shared__ uint64_t few_key[64];
+  __shared__ int few_chunk[64], few, kth_chunk_sh;
   uint64_t key[I];
   int bad = 0;
+  uint32_t least = ~0u, most = 0u;
+  const uint64_t last_key = order_key(cs[n - 1]);
 #pragma unroll
   for (int i = 0; i < I; ++i) {
     const int j = reg_chunk<I>(i);
@@ -165,53 +138,132 @@ __device__ __forceinline__ int select_chunks(const double* cs, int n, int k, int
     if (j < n) v = cs[j];
     bad |= is_nan_bits(v) ? 1 : 0;
     key[i] = order_key(v);
+    const uint32_t top = (uint32_t)(key[i] >> 32);
+    least = min(least, j < n ? top : ~0u);
+    most = max(most, j < n ? top : 0u);
   }
-  if (t == 0) { key0 = key[0]; last_sh = 0; }
+  least = wave_extreme<false>(least);
+  most = wave_extreme<true>(most);
+  if (lane == 0) { sh[wave] = (int)least; sh[16 + wave] = (int)most; }
+  if (t == 0) few = 0;
   if (__syncthreads_or(bad)) return -1;
-  const uint64_t top = key0 & (255ull << 56);
-  int differs = 0;
-#pragma unroll
-  for (int i = 0; i < I; ++i) differs |= (reg_chunk<I>(i) < n && (key[i] & (255ull << 56)) != top) ? 1 : 0;
-  const bool skip_top = !__syncthreads_or(differs);
-  uint64_t prefix;
-  int need;
-  radix_select_kth<I>(key, n, k, skip_top, top, hist, &prefix, &need);
-
-  // in index order: rows of 64 chunks by ballots, the waves' totals through LDS
-  int above = 0, equal = 0;
-#pragma unroll
-  for (int i = 0; i < I; ++i) {
-    const bool in = reg_chunk<I>(i) < n;
-    above += __popcll(__ballot(in && key[i] > prefix));
-    equal += __popcll(__ballot(in && key[i] == prefix));
-  }
-  if (lane == 0) { sh[wave] = above; sh[16 + wave] = equal; }
-  __syncthreads();
-  int kept_before = 0, eq_before = 0, total = 0, eq_total = 0;
 #pragma unroll
   for (int w = 0; w < 16; ++w) {
-    const int a = sh[w], e = sh[16 + w];
-    if (w < wave) { kept_before += a; eq_before += e; }
-    total += a;
-    eq_total += e;
+    least = min(least, (uint32_t)sh[w]);
+    most = max(most, (uint32_t)sh[16 + w]);
   }
-  kept_before += min(eq_before, need);
-  total += min(eq_total, need);
+
+  // keys in play: lo .. lo + span; the k-th largest of all is the need-th largest of them
+  uint64_t lo = (uint64_t)least << 32, span = ((uint64_t)(most - least) << 32) | 0xffffffffull;
+  int shift = 64 - LG_BINS - __clzll((long long)span), need = k;
+  // kept: key > kth, or == kth and the chunk no later than kth_chunk
+  uint64_t kth;
+  int kth_chunk = 0x7fffffff;
+#pragma unroll 1
+  for (;;) {
+    for (int x = t; x < BINS + 64; x += 1024) hist[x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < I; ++i)
+      if (reg_chunk<I>(i) < n && key[i] - lo <= span) {
+        const int bin = (int)((key[i] - lo) >> shift);
+        atomicAdd(&hist[bin + bin / PER], 1);
+      }
+    __syncthreads();
+    // every wave finds the class by itself, lane x looking at the classes [BINS - PER (x + 1), BINS - PER x)
+    const int group = 63 - lane;
+    int h[PER], own = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) own += h[u] = hist[(PER + 1) * group + u];
+    int all;
+    const int upto = wave_inclusive_scan(own, &all);
+    int above = upto - own, bin = -1, size = 0;
+    if (above < need && need <= upto) {  // exactly one lane
+#pragma unroll
+      for (int u = PER - 1; u >= 0; --u) {
+        if (bin < 0 && above + h[u] >= need) { bin = PER * group + u; size = h[u]; }
+        if (bin < 0) above += h[u];
+      }
+    }
+    const int src = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)__ballot(bin >= 0)) - 1);
+    need -= __builtin_amdgcn_readlane(above, src);
+    size = __builtin_amdgcn_readlane(size, src);
+    lo += (uint64_t)__builtin_amdgcn_readlane(bin, src) << shift;
+    span = (1ull << shift) - 1;
+    kth = lo;
+    if (size == need) break;
+    if (shift == 0) {
+      // equal keys, of which the first `need` are kept: the last of those
+      int equal = 0;
+#pragma unroll
+      for (int i = 0; i < I; ++i) equal += __popcll(__ballot(reg_chunk<I>(i) < n && key[i] == kth));
+      if (lane == 0) sh[wave] = equal;
+      __syncthreads();
+      int before = 0;
+#pragma unroll
+      for (int w = 0; w < 16; ++w)
+        if (w < wave) before += sh[w];
+#pragma unroll
+      for (int i = 0; i < I; ++i) {
+        const bool eq = reg_chunk<I>(i) < n && key[i] == kth;
+        const unsigned long long mask = __ballot(eq);
+        if (eq && before + __popcll(mask & ((1ull << lane) - 1ull)) == need - 1) kth_chunk_sh = reg_chunk<I>(i);
+        before += __popcll(mask);
+      }
+      __syncthreads();
+      kth_chunk = kth_chunk_sh;
+      break;
+    }
+    if (size <= 64) {
+#pragma unroll
+      for (int i = 0; i < I; ++i)
+        if (reg_chunk<I>(i) < n && key[i] - lo <= span) {
+          const int at = atomicAdd(&few, 1);
+          few_key[at] = key[i];
+          few_chunk[at] = reg_chunk<I>(i);
+        }
+      __syncthreads();
+      // every wave ranks them for itself, lane x the x-th
+      const uint64_t mine = few_key[lane];
+      const int chunk = few_chunk[lane];
+      int ahead = 0;
+      for (int x = 0; x < size; ++x) ahead += (few_key[x] > mine || (few_key[x] == mine && few_chunk[x] < chunk)) ? 1 : 0;
+      const int it = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)__ballot(lane < size && ahead == need - 1)) - 1);
+      kth = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(mine >> 32), it) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)mine, it);
+      kth_chunk = __builtin_amdgcn_readlane(chunk, it);
+      break;
+    }
+    shift = max(0, shift - LG_BINS);
+    __syncthreads();
+  }
+
+  // in index order: rows of 64 chunks by ballots, the waves' totals through LDS
+  int kept = 0;
+  unsigned long long mask[I];
+#pragma unroll
+  for (int i = 0; i < I; ++i) {
+    const int j = reg_chunk<I>(i);
+    mask[i] = __ballot(j < n && (key[i] > kth || (key[i] == kth && j <= kth_chunk)));
+    kept += __popcll(mask[i]);
+  }
+  if (lane == 0) sh[32 + wave] = kept;
+  __syncthreads();
+  int before = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    const int x = sh[32 + w];
+    if (w < wave) before += x;
+    total += x;
+  }
   const unsigned long long below = (1ull << lane) - 1ull;
 #pragma unroll
   for (int i = 0; i < I; ++i) {
     const int j = reg_chunk<I>(i);
-    const bool eq = j < n && key[i] == prefix;
-    const unsigned long long eq_mask = __ballot(eq);
-    const bool keep = j < n && (key[i] > prefix || (eq && eq_before + __popcll(eq_mask & below) < need));
-    const unsigned long long mask = __ballot(keep);
-    if (j < n) emit(j, keep ? kept_before + __popcll(mask & below) : -1);
-    if (keep && j == n - 1) last_sh = 1;
-    eq_before += __popcll(eq_mask);
-    kept_before += __popcll(mask);
+    const bool keep = (mask[i] >> lane) & 1ull;
+    if (j < n) emit(j, keep ? before + __popcll(mask[i] & below) : -1);
+    before += __popcll(mask[i]);
   }
-  __syncthreads();
-  *last_kept = last_sh != 0;
+  *last_kept = last_key > kth || (last_key == kth && n - 1 <= kth_chunk);
   return total;
 }
 
@@ -223,8 +275,8 @@ constexpr int kCountMaxChunks = 256;  // up to here the chunks are ranked by cou
 // `cs`: the chunk scores (global or LDS memory); `keys`: LDS room for kSingleMaxChunks 64-bit keys.
 // Call with all 1024 threads of the workgroup.
 __device__ __forceinline__ void select_emit_single(const SelDev& p, const double* cs, uint64_t* keys) {
-  __shared__ int hist[3 * 256];
-  __shared__ int sh[32];
+  __shared__ int hist[kSelectHist];
+  __shared__ int sh[48];
   const int t = threadIdx.x;
   const int M = p.T;
   const int n = (M + p.chunk - 1) / p.chunk;
