@@ -53,7 +53,7 @@ constexpr int kDefaultSpinBudget = 1 << 16;  // polls per workgroup and call bef
 static std::atomic<int> g_spin_budget{kDefaultSpinBudget};
 
 struct WideTeamDev : TiledDev {
-  int lgP, chunk;          // members of a team (a power of two), keys of a member
+  int lgP, share;          // members of a team (a power of two), keys of a member
   WideTeamDeal deal;
   int spin_budget;
   uint32_t* lines;         // two copies of [slab][member][32]
@@ -100,8 +100,8 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
   uint32_t* const lines_cur = p.lines + (size_t)(epoch & 1u) * p.copy_words;
   uint32_t* const lines_nxt = p.lines + (size_t)(~epoch & 1u) * p.copy_words;
   if (blockIdx.x == 0 && threadIdx.x == 0) p.status[~epoch & 1u] = 0;  // the next call's status word
-  const int key0 = member * p.chunk;
-  const int M = max(0, min((int)p.T - key0, p.chunk));
+  const int key0 = member * p.share;
+  const int M = max(0, min((int)p.T - key0, p.share));
   const int nt = w.items_of(M);
   int polls = p.spin_budget;
   bool expired = polls <= 0;
@@ -374,7 +374,7 @@ sp_status wide_team_score(const sp_score_args* a, hipStream_t stream) {
   dev.page_stride = a->k_page_stride;
   dev.k_scale = a->d_k_scale;
   for (int l = 0; l < a->L; ++l) dev.k[l] = static_cast<const uint16_t*>(a->k_layers[l]);
-  dev.lgP = pl.lgP; dev.chunk = pl.chunk;
+  dev.lgP = pl.lgP; dev.share = pl.share;
   const bool shared = !(a->flags & SP_SCORE_EXCLUSIVE_DEVICE);
   dev.launch = shared ? kFirst : kAlone;
   dev.spin_budget = g_spin_budget.load(std::memory_order_relaxed);
