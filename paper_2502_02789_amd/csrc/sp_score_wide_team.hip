@@ -11,10 +11,10 @@
 //     into the rows' log-sum-exps and hands those to the other waves through LDS;
 //   * a slab is 18 us of stream for a workgroup (2048 keys, d = 128) and the ring holds 5 us of it, so the exchange
 //     is short against a slab, and the teams, which never meet, drift apart: while one waits the others have the
-//     memory.  The next slab's first item is computed while the lines travel, its logits in registers of their own: 32K keys 350 -> 339 us, 128K 1378 -> 1352 (now, with slabs in runs
-//     of four, 336 and 1301; without any exchange, wrong results, 327 and 1256; with an exchange four times as often
-//     hidden behind three slabs of a quarter of the keys each, and the query tile fetched once per wave, as in the
-//     kernels before: 349 and 1570);
+//     memory.  The next slab's first item is computed while the lines travel, its logits in registers of their own:
+//     32K keys 350 -> 339 us, 128K 1378 -> 1352 (now, with slabs in runs of four, 336 and 1301; without
+//     any exchange, wrong results, 327 and 1256; with an exchange four times as often hidden behind three slabs of a
+//     quarter of the keys each, and the query tile fetched once per wave, as in the kernels before: 349 and 1570);
 //   * 256 / P teams are dealt the slabs in turn, a few at a time (sp_wide_team_plan.h); a team's maxima go out as one
 //     group of the result array, merged by the kernel that merges the units of short prompts.  Mean over layers: whole
 //     layers in turn, a team adds their maxima up; the layers left over in parts, each a group of its own.
@@ -36,8 +36,8 @@
 //
 // Bound by the HBM stream of K for bf16 caches (32 layers, 8 KV heads, d = 128, eight queries, before -> now: 32K keys
 // 349 -> 336 us = 6.4 TB/s, mean over layers 30011 keys 375 -> 337, 128K keys 1570 -> 1301, 9000 keys 168 -> 117;
-// 16 layers, d = 64, 8K keys 61 -> 43: two slabs per workgroup, their start and end), by latency for 8-bit caches
-// (32K keys 318 -> 226 us; the vector ALUs are busy half of the time, without the exchange 208).
+// 16 layers, d = 64, 8K keys 61 -> 43: two slabs per workgroup, their start and end), by latency and vector
+// instructions for 8-bit caches (32K keys 238 -> 224 us with one-tile items and operands read ahead).
 // Tried: polling by every wave instead of one and a barrier 355 against 350 us, polls that read the die's own L2 451.
 #include <atomic>
 #include <mutex>
