@@ -1,12 +1,12 @@
 /*
- * sp_probe.h -- measurement helpers of the benchmark (libspprobe.so), NOT part of the
+ * sp_probe.h -- helpers of the benchmark and the tests (libspprobe.so), NOT part of the
  * SpecPrefill path: two kernels that only READ a per-layer bf16 K cache [T, H_kv, d] and do no
  * arithmetic, so that a benchmark run can state, next to sp_score's own bandwidth, what plain
  * reading of the same bytes achieves on the same device in the same run.
  *
  * All pointers in h_layers[] are DEVICE pointers (the array itself is HOST memory); d_sink is a
  * device buffer of at least 256 bytes that the kernels may write a few words to (so the reads
- * cannot be optimised away).  Both calls only enqueue one kernel on hip_stream; they allocate
+ * cannot be optimised away).  The calls only enqueue one kernel on hip_stream; they allocate
  * nothing and never synchronise.  Return 0 on success, -1 on a bad argument, -6 if the launch
  * was refused.
  */
@@ -42,6 +42,11 @@ SP_PROBE_API int sp_probe_tiled(const void* const* h_layers, int32_t L, int32_t 
 SP_PROBE_API int sp_probe_tiled_default_policy(const void* const* h_layers, int32_t L, int32_t T, int32_t H_kv, int32_t d,
                                                int64_t k_token_stride, int64_t k_head_stride, void* d_sink,
                                                void* hip_stream);
+
+/* For tests: `workgroups` of one wave that do nothing but hold lds_bytes (up to 65536) of a compute unit's LDS each,
+ * for so many microseconds (up to 100000): another stream's long-lived kernel, as far as a kernel that needs most of
+ * a compute unit's LDS is concerned.  Reads and writes no memory. */
+SP_PROBE_API int sp_probe_occupy(int32_t workgroups, int32_t lds_bytes, int32_t microseconds, void* hip_stream);
 
 #ifdef __cplusplus
 }

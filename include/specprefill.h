@@ -81,11 +81,12 @@ typedef enum { SP_K_BF16 = 0, SP_K_FP8_E4M3 = 1 } sp_k_dtype;
                                         sp_score_check and sp_pool_select), never silently
                                         wrong.
                                         Without the flag the scores are valid whatever else runs on
-                                        the GPU: workgroups that could not wait for one another
-                                        any longer give up early, and a second launch of the
-                                        same call (which returns at once otherwise) forms the
-                                        results again from the row statistics, which are all
-                                        there by then.  At worst K is read twice. */
+                                        the GPU: where a workgroup has waited for the others about
+                                        one and a half to three times as long as the call takes
+                                        undisturbed (and 50 microseconds), the call gives up waiting
+                                        as a whole, and its second launch (which returns at once
+                                        otherwise) forms the results again from the row statistics,
+                                        which are all there by then.  At worst K is read twice. */
 #define SP_SCORE_WORKSPACE_KEPT 2u   /* The caller promises that args->d_workspace was last written by
                                         an sp_score call with the same shape fields (B, T, N, L, H,
                                         H_kv, d, layer_reduce, paging) and SP_SCORE_EXCLUSIVE_DEVICE
@@ -209,7 +210,7 @@ SP_API sp_status sp_score_check(const sp_score_args* args, void* hip_stream);
 
 /* Upper bound on the polls a workgroup may spend waiting for other workgroups during one sp_score
  * call (process-wide, applies to later calls; default 65536, about 0.1 s; calls without
- * SP_SCORE_EXCLUSIVE_DEVICE have a smaller bound of their own, of the order of the time the call takes).
+ * SP_SCORE_EXCLUSIVE_DEVICE also have a bound in time, see there).
  * 0 makes every wait give up at once, which turns every score of a single-pass call with that flag into
  * NaN, and takes one without it through its second launch: that is how the failure paths are
  * exercised without ever making a kernel hang.  Returns the previous value;

@@ -24,10 +24,11 @@
 // (no SP_SCORE_WORKSPACE_KEPT).  The workgroups of a team must be resident together; every wait is bounded.
 //
 // On the promise of an idle device (SP_SCORE_EXCLUSIVE_DEVICE) an expired wait turns the call's scores into NaN.  Without
-// it the kernel is launched twice: a workgroup that has waited about as long as the whole call takes gives up, goes on
-// without waiting and notes that down.  Its line of statistics still goes out for every slab -- a line depends on nothing
-// but the member's own keys -- so after the first launch all lines are there, and the second one, which returns at once
-// where nobody gave up, forms all results again without any wait.  So nothing depends on what else runs on the device,
+// it the kernel is launched twice: where a workgroup has waited for one slab's lines about as long as the whole call takes
+// (wide_team_patience_us) it notes that down for all to see, and from then on nobody waits any more.  The lines of
+// statistics still go out for every slab -- a line depends on nothing but the member's own keys -- so after the first
+// launch all of them are there, and the second one, which returns at once where nobody gave up, forms all results again
+// without any wait.  So nothing depends on what else runs on the device,
 // K is read once as a rule and twice at worst, and the scores have the same bits either way.  (Two passes over K before:
 // 24577 keys, 32 layers, 8 KV heads, d = 128, eight queries, whole step: 498 -> 290 us; 128K keys 2604 -> 1351; one query on
 // 20000 keys, logits kept in memory before, 311 -> 252.  Beside another stream's 4096^3 products: 9000 keys 655 -> 557 us,
@@ -59,7 +60,8 @@ struct WideTeamDev : TiledDev {
   uint32_t* lines;         // two copies of [slab][member][32]
   size_t copy_words;
   uint32_t* status;        // [epoch & 1] != 0: a wait of this call expired; [2]: epoch, calls since the last fill;
-                           // [3] != 0: a wait of a shared call's first launch expired
+                           // [3] != 0: a wait of a shared call's first launch expired, nobody waits any longer
+  uint64_t patience;       // kFirst: ticks of the 100 MHz clock that a workgroup waits for the lines of a slab
   int launch;              // kAlone; kFirst and kSecond: the launches of a call without the promise of an idle device
 };
 enum { kAlone = 0, kFirst = 1, kSecond = 2 };
@@ -175,6 +177,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
       // nothing and get zeros).
       const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(line, 0, (uint32_t)P * 128u, 0x00020000);
       const int loads = P <= 8 ? 1 : P >> 3;
+      uint64_t since = 0;  // when this slab's wait began
       float m[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY}, z[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
       for (int i0 = 0; i0 < loads; i0 += 4) {  // four loads at a time: more registers are not free
@@ -182,6 +185,8 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
         while (!expired && M > 0) {  // (a member without keys has no use for the rows' log-sum-exps)
           bool empty = false;
           asm volatile("" ::: "memory");  // (a new look at the lines every time)
+          uint32_t given_up = 0;
+          if (p.launch == kFirst) given_up = __hip_atomic_load(p.status + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
           for (int i = 0; i < 4; ++i)
             x[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, ln * 16 + (i0 + i) * 1024, 0, /*sc1*/ 16));
@@ -190,6 +195,12 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
             empty |= x[i].x == kEmptyLine || x[i].y == kEmptyLine || x[i].z == kEmptyLine || x[i].w == kEmptyLine;
           if (!__any(empty)) break;
           if (--polls <= 0) expired = true;
+          if (p.launch == kFirst) {
+            const uint64_t now = wall_clock64();
+            if (since == 0) since = now;
+            if (__builtin_amdgcn_readfirstlane(given_up) != 0 || now - since > p.patience) expired = true;
+            if (expired) __hip_atomic_store(p.status + 3, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
           __builtin_amdgcn_s_sleep(2);
         }
 #pragma unroll
@@ -295,15 +306,6 @@ static size_t result_bytes(const WideTeamPlan& pl, const sp_score_args* a) {
   return align_up(sizeof(float) * 32 * (size_t)pl.n_groups * a->N * wide_tiles(a), 256);
 }
 
-// Polls of a workgroup in a call without the promise of an idle device.  A poll takes 0.5 us or more, a member's keys arrive
-// at 25 KB a us: a member with next to no keys waits for the others through the whole call, so that is allowed three times
-// over, and a millisecond for workgroups that other work keeps from starting.  (Not the 0.1 s of an exclusive call:
-// what an expired wait costs here is another pass over K, so nobody should wait much longer than that takes.)
-static int64_t shared_budget(const WideTeamPlan& pl, const sp_score_args* a) {
-  const int64_t slabs = (pl.deal.n_slabs + pl.deal.teams - 1) / pl.deal.teams;
-  return 2048 + slabs * pl.chunk * a->d * (a->k_dtype == SP_K_FP8_E4M3 ? 1 : 2) / 4096;
-}
-
 static WideTeamPlan make_plan(const sp_score_args* a) { return make_wide_team_plan(a, wide_team_wgs(seq_cu_count())); }
 bool wide_team_supported(const sp_score_args* a) { return make_plan(a).ok; }
 // Workspace: the lines' two copies, the status words, the results.  What a call hands on to the next (lines and status)
@@ -378,7 +380,7 @@ sp_status wide_team_score(const sp_score_args* a, hipStream_t stream) {
   const bool shared = !(a->flags & SP_SCORE_EXCLUSIVE_DEVICE);
   dev.launch = shared ? kFirst : kAlone;
   dev.spin_budget = g_spin_budget.load(std::memory_order_relaxed);
-  if (shared) dev.spin_budget = (int)std::min<int64_t>(dev.spin_budget, shared_budget(pl, a));
+  dev.patience = shared ? (uint64_t)wide_team_patience_us(pl, a) * 100 : 0;
   char* ws = static_cast<char*>(a->d_workspace);
   dev.lines = reinterpret_cast<uint32_t*>(ws);
   dev.copy_words = copy_bytes(pl) / 4;

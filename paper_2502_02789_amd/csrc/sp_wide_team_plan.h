@@ -139,4 +139,19 @@ inline WideTeamPlan make_wide_team_plan(const sp_score_args* a, int wgs) {
   return pl;
 }
 
+// How long, in microseconds, a workgroup of a call without the promise of an idle device waits for the lines of a slab
+// before the call gives up waiting, as a whole.  What giving up costs is another pass over K, so nobody waits much longer
+// than one takes; and not much less either, because that is when the first teams are done and make room for members that
+// other work has kept out.  Reckoned with 16 KB of keys a us and workgroup (8-bit keys 12, which arithmetic holds up;
+// undisturbed 25 and 19), 3 us for the end of a slab, and 50 us for the tail of another stream's kernel.  (200 compute
+// units held by other work, which leaves no team of sixteen complete, us per call: every workgroup with a bound of its own
+// of a millisecond and more, one for all of them, two passes: 9000 keys 4492, 1288, 765; 24577 keys 5165, 3188, 1903.  Up
+// to 64 held, where teams that are done make room: 176, 176, 270 and 409, 409, 669; 24577 8-bit keys 309, 309, 273, with
+// 64 held 307, 308, 449.  Beside 4096^3 products, 3500 keys: 289, 290, 392, the same with 20, 100, 200 and 400 us for a tail.)
+inline int64_t wide_team_patience_us(const WideTeamPlan& pl, const sp_score_args* a) {
+  const int64_t slabs = (pl.deal.n_slabs + pl.deal.teams - 1) / pl.deal.teams;
+  const int64_t slab_bytes = (int64_t)pl.chunk * a->d * (a->k_dtype == SP_K_FP8_E4M3 ? 1 : 2);
+  return 50 + slabs * 3 + slabs * slab_bytes / (a->k_dtype == SP_K_FP8_E4M3 ? 12000 : 16000);
+}
+
 }  // namespace sp

@@ -1,5 +1,5 @@
-// Read-only probes for the benchmark: what plain streaming of the K cache achieves on this device
-// (see sp_probe.h).  No part of the scoring path uses anything in this file.
+// Read-only probes for the benchmark: what plain streaming of the K cache achieves on this device, and for the tests a
+// kernel that keeps compute units from other work for a while (see sp_probe.h).  No part of the scoring path uses anything in this file.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -80,7 +80,19 @@ __global__ __launch_bounds__(512) void tiled_default_policy_kernel(const Layers 
   tiled_body<0>(layers, L, ts_bytes, hs_bytes, sink, tile_ring);
 }
 
+// Every wave looks at the 100 MHz clock until `ticks` have passed (and so many times at most that it ends in any case).
+__global__ __launch_bounds__(64) void occupy_kernel(uint64_t ticks) {
+  const uint64_t start = wall_clock64();
+  for (int i = 0; i < (1 << 20) && wall_clock64() - start < ticks; ++i) __builtin_amdgcn_s_sleep(16);
+}
+
 }  // namespace
+
+extern "C" int sp_probe_occupy(int32_t workgroups, int32_t lds_bytes, int32_t microseconds, void* hip_stream) {
+  if (workgroups < 1 || workgroups > 65536 || lds_bytes < 0 || lds_bytes > 65536 || microseconds < 1 || microseconds > 100000) return -1;
+  hipLaunchKernelGGL(occupy_kernel, dim3(workgroups), dim3(64), lds_bytes, static_cast<hipStream_t>(hip_stream), (uint64_t)microseconds * 100);
+  return hipGetLastError() == hipSuccess ? 0 : -6;
+}
 
 extern "C" int sp_probe_read(const void* const* h_layers, int32_t L, size_t bytes_per_layer, int32_t blocks, void* d_sink,
                              void* hip_stream) {

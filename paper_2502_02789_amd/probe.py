@@ -6,7 +6,7 @@ import ctypes as C
 import os
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libspprobe.so")
-EXPORTS = ("sp_probe_read", "sp_probe_tiled", "sp_probe_tiled_default_policy")
+EXPORTS = ("sp_probe_read", "sp_probe_tiled", "sp_probe_tiled_default_policy", "sp_probe_occupy")
 _lib = None
 
 
@@ -22,6 +22,8 @@ def load_library() -> C.CDLL:
             fn.restype = C.c_int
             fn.argtypes = [C.POINTER(C.c_void_p), C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int64, C.c_int64, C.c_void_p,
                            C.c_void_p]
+        lib.sp_probe_occupy.restype = C.c_int
+        lib.sp_probe_occupy.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_void_p]
         _lib = lib
     return _lib
 

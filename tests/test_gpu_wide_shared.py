@@ -107,3 +107,40 @@ def test_short_prompts_of_few_slabs_stay_on_two_passes(shape, mode):
     got, lse = hp.gpu_score(inp["q"], inp["k"], inp["cu_seqlens"], w.H_kv, 1.0 / math.sqrt(w.d), mode, exclusive_device=False)
     hp.assert_scores_close(got, want, f"{w.name} mode={mode}")
     np.testing.assert_allclose(lse, want_lse, rtol=0, atol=2e-4)
+
+
+def test_other_work_on_most_compute_units_does_not_hold_a_call_up():
+    """200 compute units held by another stream leave no team of sixteen complete: the call must give up waiting as a
+    whole and soon.  256 workgroups on 56 compute units are five rounds, and both launches work: ten times the undisturbed
+    call, and the wait.  (Measured 10 times; 36 when every workgroup waited out a bound of its own.)"""
+    import torch
+    from paper_2502_02789_amd import binding as sp, device as dev, probe
+    T, L, H, H_kv, d = 9000, 32, 32, 8, 128
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    q = torch.randn((L, 1, 8, H, d), generator=g, device="cuda").to(torch.bfloat16)
+    k = [torch.randn((T, H_kv, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(L)]
+    s = dev.Scorer(q, k, torch.tensor([0, T], dtype=torch.int32, device="cuda"), H_kv=H_kv, scale=1.0 / math.sqrt(d),
+                   layer_reduce=sp.SP_LAYER_MAX, exclusive_device=False)
+    lib, other = probe.load_library(), torch.cuda.Stream()
+    start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+
+    def call(held):
+        torch.cuda.synchronize()
+        s.scores.fill_(float("nan"))
+        if held:
+            assert lib.sp_probe_occupy(held, 65536, 30000, other.cuda_stream) == 0
+        torch.cuda._sleep(200000)
+        start.record()
+        s.run()
+        end.record()
+        end.synchronize()
+        assert not held or not other.query()                        # (the other work is still there)
+        torch.cuda.synchronize()
+        return start.elapsed_time(end), s.scores.cpu().numpy()
+
+    call(0)
+    alone = sorted((call(0) for _ in range(5)), key=lambda x: x[0])[2]
+    beside = sorted((call(200) for _ in range(3)), key=lambda x: x[0])[1]
+    assert np.array_equal(beside[1], alone[1])
+    assert beside[0] < 20 * alone[0], (beside[0], alone[0])
