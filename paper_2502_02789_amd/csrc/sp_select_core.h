@@ -101,13 +101,15 @@ __device__ __forceinline__ int reg_chunk(int i) {
 //
 // The k-th largest key by counting in classes of equal width between the smallest and the largest key (their
 // upper halves): the class that holds it is counted again in narrower classes until all of it is kept, all its keys are
-// equal, or it has no more than a wave's worth of chunks, which are ranked among themselves -- usually after one pass.
+// equal, or it has no more than 64 chunks, which are ranked among themselves -- after one or two passes as a rule.
 // (Digits of eight fixed bits took three passes, the first of them with nearly all keys in one or two counters, whose
-// additions LDS performs one after the other.  Whole selection, window 1, single tokens: eight sequences of 8000 28.4 -> 22.9 us,
-// of 16000 36.9 -> 27.0, one of 2000 10.6 -> 8.5; 1024 and 2048 smoothed chunks of one sequence 9.6 -> 9.4 and 10.7 -> 10.2, with
-// three tenths kept 10.0 -> 11.5 and 12.8 -> 13.5.)
+// additions LDS performs one after the other.  Whole selection, window 1, single tokens: eight sequences of 8000 29.2 -> 22.0 us,
+// of 16000 36.1 -> 23.8, one of 2000 10.6 -> 7.8; 1024 and 2048 smoothed chunks of one sequence, a twentieth kept 9.2 -> 8.7 and
+// 10.1 -> 9.7, three tenths 10.7 -> 10.4 and 12.8 -> 12.2, half 11.8 -> 11.6 and 15.7 -> 14.9.  Ranking up to 128 chunks
+// takes longer than the second pass: 10.1, 12.1 and 13.2 for the 1024.)
 // `hist` has room for kSelectHist counters, `sh` for 48.
 constexpr int kSelectHist = 1024 + 64;
+constexpr int kFew = 64;  // chunks of a class that are ranked among themselves
 // the least (MAX: the largest) of a wave's values
 template <bool MAX>
 __device__ __forceinline__ uint32_t wave_extreme(uint32_t v) {
@@ -125,8 +127,8 @@ __device__ __forceinline__ int select_chunks(const double* cs, int n, int k, int
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
   // classes (a lane sums PER of them: a gap behind every PER)
   constexpr int LG_BINS = I <= 2 ? 9 : 10, BINS = 1 << LG_BINS, PER = BINS / 64;
-  __shared__ uint64_t few_key[64];
-  __shared__ int few_chunk[64], few, kth_chunk_sh;
+  __shared__ uint64_t few_key[kFew];
+  __shared__ int few_chunk[kFew], few_ahead[kFew], few, kth_chunk_sh;
   uint64_t key[I];
   int bad = 0;
   uint32_t least = ~0u, most = 0u;
@@ -146,6 +148,7 @@ __device__ __forceinline__ int select_chunks(const double* cs, int n, int k, int
   most = wave_extreme<true>(most);
   if (lane == 0) { sh[wave] = (int)least; sh[16 + wave] = (int)most; }
   if (t == 0) few = 0;
+  if (t < kFew) few_ahead[t] = 0;
   if (__syncthreads_or(bad)) return -1;
 #pragma unroll
   for (int w = 0; w < 16; ++w) {
@@ -214,7 +217,7 @@ __device__ __forceinline__ int select_chunks(const double* cs, int n, int k, int
       kth_chunk = kth_chunk_sh;
       break;
     }
-    if (size <= 64) {
+    if (size <= kFew) {
 #pragma unroll
       for (int i = 0; i < I; ++i)
         if (reg_chunk<I>(i) < n && key[i] - lo <= span) {
@@ -223,14 +226,33 @@ __device__ __forceinline__ int select_chunks(const double* cs, int n, int k, int
           few_chunk[at] = reg_chunk<I>(i);
         }
       __syncthreads();
-      // every wave ranks them for itself, lane x the x-th
-      const uint64_t mine = few_key[lane];
-      const int chunk = few_chunk[lane];
-      int ahead = 0;
-      for (int x = 0; x < size; ++x) ahead += (few_key[x] > mine || (few_key[x] == mine && few_chunk[x] < chunk)) ? 1 : 0;
-      const int it = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)__ballot(lane < size && ahead == need - 1)) - 1);
-      kth = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(mine >> 32), it) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)mine, it);
-      kth_chunk = __builtin_amdgcn_readlane(chunk, it);
+      // All threads rank them, each one chunk against four others, both words of those read before either is looked at.
+      // (Every wave all of them for itself, the second word's read behind the first's outcome, was a chain of two LDS
+      // round trips a chunk: 768 smoothed chunks with 50 left to rank 13.3 us, 9.2 this way; by digits 10.0.)
+      constexpr int PARTS = 1024 / kFew, OF_PART = kFew / PARTS;
+      {
+        const int c = t % kFew, x0 = t / kFew * OF_PART;
+        const uint64_t mine = few_key[c];
+        const int chunk = few_chunk[c];
+        int ahead = 0;
+#pragma unroll
+        for (int u = 0; u < OF_PART; ++u) {
+          const uint64_t other = few_key[x0 + u];
+          const int other_chunk = few_chunk[x0 + u];
+          ahead += (int)(x0 + u < size) & ((int)(other > mine) | ((int)(other == mine) & (int)(other_chunk < chunk)));
+        }
+        if (c < size && ahead != 0) atomicAdd(&few_ahead[c], ahead);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < kFew; r += 64) {
+        const unsigned long long hit = __ballot(r + lane < size && few_ahead[r + lane] == need - 1);
+        if (hit != 0) {
+          const int it = r + __builtin_amdgcn_readfirstlane(__ffsll(hit) - 1);
+          kth = few_key[it];
+          kth_chunk = few_chunk[it];
+        }
+      }
       break;
     }
     shift = max(0, shift - LG_BINS);
