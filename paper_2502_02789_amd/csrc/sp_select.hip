@@ -366,8 +366,12 @@ static sp_status run_pool_select(const sp_pool_select_args* a, void* scratch, hi
   if (a->B == 1 && (a->T + a->chunk - 1) / a->chunk <= kSingleMaxChunks) {
     // One sequence (its length is T, known here): no chunk table, no cross-sequence scan.  One launch while one workgroup
     // pools in the time of a second launch (chunks of 32, window 13, one and two launches in us: 500 tokens 4.7 and 6.1,
-    // 1000 5.1 and 6.3, 2048 6.6 and 6.8, 3001 9.0 and 7.4).
-    if (a->T <= kOneLaunchTokens && !long_chunks) {
+    // 1000 5.1 and 6.3, 2048 6.4 and 6.8, 3001 9.0 and 7.4).  Its work is tokens times window,
+    // which up to 1600 tokens it does as fast as many workgroups would, beyond for small windows only (windows 129, 513 and
+    // 4095: 1500 tokens 9.1 and 10.2, 18.9 and 20.5, 45.9 and 46.5; 1700 tokens 9.8 and 10.3, 20.1 and 20.7, 57.4 and 51.5; 2048
+    // tokens, window 33, 65, 129, 4095: 7.1 and 7.5, 8.3 and 8.3, 10.8 and 10.0, 84.0 and 60.4).
+    const int64_t over = a->T - 1600;
+    if (a->T <= kOneLaunchTokens && !long_chunks && (over <= 0 || over * a->pool_window <= 16000)) {
       hipLaunchKernelGGL(pool_select_single_kernel, dim3(1), dim3(1024), 0, stream, p);
       return launch_status();
     }

@@ -36,3 +36,17 @@ def test_one_short_sequence(T, chunk, window, rate, kind):
     assert (got[int(cu_keep[1]):] == -1).all()
     few = hp.gpu_pool_select(x, cu, chunk, window, rate, capacity=max(1, len(kept) // 2), want_chunk_scores=False)
     np.testing.assert_array_equal(few.kept_idx.cpu().numpy(), got[:max(1, len(kept) // 2)])
+
+
+@pytest.mark.parametrize("T, window", [(1600, 4095), (1601, 16001), (1601, 15999), (1700, 159), (1700, 161), (2048, 35), (2048, 37),
+                                       (2048, 2 ** 31 - 1)])
+@pytest.mark.parametrize("chunk", [1, 7, 32, 256])
+def test_wide_windows(T, window, chunk):
+    """On both sides of the line between pooling by one workgroup and by many: the same chunk scores, the oracle's."""
+    x = np.exp(2.0 * np.random.default_rng(T + window).standard_normal(T)).astype(np.float32) / 16000
+    cu = np.array([0, T], dtype=np.int32)
+    sel = hp.gpu_pool_select(x, cu, chunk, window, 0.3)
+    _, cu_keep, cs, _ = orc.pool_select(x, cu, chunk, min(window, 2 * T + 1), 0.3)
+    assert sel.cu_keep.cpu().tolist() == cu_keep.tolist()
+    np.testing.assert_allclose(sel.chunk_scores.cpu().numpy()[:len(cs)], cs.astype(np.float32), rtol=2e-7)   # (fp64 means, rounded)
+    hp.selection_matches(sel.kept_idx.cpu().numpy(), sel.cu_keep.cpu().numpy(), x, cu, chunk, min(window, 2 * T + 1), 0.3, 1e-12)
