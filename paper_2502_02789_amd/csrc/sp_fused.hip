@@ -74,7 +74,7 @@ __device__ __forceinline__ float reduce16(float v) {
 
 __device__ __forceinline__ void store_f32_agent(float* dst, float v) { store32_agent(dst, __float_as_uint(v)); }
 
-template <int D>
+template <int D, SingleForm FORM>
 __global__ __launch_bounds__(kFusedThreads) void fused_short_kernel(const FusedDev p) {
   constexpr int KS = D / 32;  // MFMA steps along the head dim
   __shared__ double wide[kPoolRoom];  // first the pooled scores, then (as 64-bit keys) the selection's keys
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(kFusedThreads) void fused_short_kernel(const FusedD
 
   // ---- phase 2c: Sec. 3.2.3 on the scores in LDS; the same fp64 arithmetic in the same order as sp_pool_select ----
   pool_chunks_in_lds(p.sel, score_lds, wide, cs_lds);
-  select_emit_single(p.sel, cs_lds, reinterpret_cast<uint64_t*>(wide));
+  select_emit_single<FORM>(p.sel, cs_lds, reinterpret_cast<uint64_t*>(wide));
 }
 
 static bool fused_shape_ok(const sp_score_args* a) {
@@ -328,7 +328,11 @@ extern "C" sp_status sp_score_pool_select(const sp_score_args* a, const sp_pool_
   p.cu_chunks = nullptr; p.seq_keep = nullptr; p.cs = nullptr; p.chunk_off = nullptr;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const dim3 grid(dev.M_pad / 64), block(kFusedThreads);
-  if (a->d == 64) hipLaunchKernelGGL((fused_short_kernel<64>), grid, block, 0, stream, dev);
-  else hipLaunchKernelGGL((fused_short_kernel<128>), grid, block, 0, stream, dev);
+  const SingleForm form = single_form((a->T + s->chunk - 1) / s->chunk);
+  auto kernel = a->d == 64 ? (form == kRankByWave ? fused_short_kernel<64, kRankByWave>
+                              : form == kRankByCount ? fused_short_kernel<64, kRankByCount> : fused_short_kernel<64, kRankByClasses>)
+                           : (form == kRankByWave ? fused_short_kernel<128, kRankByWave>
+                              : form == kRankByCount ? fused_short_kernel<128, kRankByCount> : fused_short_kernel<128, kRankByClasses>);
+  hipLaunchKernelGGL(kernel, grid, block, 0, stream, dev);
   return launch_status();
 }

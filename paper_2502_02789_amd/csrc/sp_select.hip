@@ -263,13 +263,15 @@ __global__ __launch_bounds__(1024) void select_kernel(const SelDev p) {
   if (arrived == p.B - 1) scan_seq_keep(p);
 }
 
+template <SingleForm FORM>
 __global__ __launch_bounds__(1024) void select_emit_single_kernel(const SelDev p) {
   __shared__ uint64_t keys[kSingleMaxChunks];
-  select_emit_single(p, p.cs, keys);
+  select_emit_single<FORM>(p, p.cs, keys);
 }
 
 // One short sequence: pooling, selection and compaction by one workgroup, all in LDS.
 constexpr int kOneLaunchTokens = 2048;
+template <SingleForm FORM>
 __global__ __launch_bounds__(1024) void pool_select_single_kernel(const SelDev p) {
   __shared__ float score[kOneLaunchTokens];
   __shared__ double wide[kPoolRoom];  // first the pooled scores, then (as 64-bit keys) the selection's keys
@@ -278,7 +280,7 @@ __global__ __launch_bounds__(1024) void pool_select_single_kernel(const SelDev p
   for (int i = threadIdx.x; i < p.T; i += 1024) score[i] = p.scores[i];
   __syncthreads();
   pool_chunks_in_lds(p, score, wide, cs);
-  select_emit_single(p, cs, reinterpret_cast<uint64_t*>(wide));
+  select_emit_single<FORM>(p, cs, reinterpret_cast<uint64_t*>(wide));
 }
 
 __global__ __launch_bounds__(1024) void cu_keep_kernel(const SelDev p) { scan_seq_keep(p); }
@@ -363,7 +365,9 @@ static sp_status run_pool_select(const sp_pool_select_args* a, void* scratch, hi
   const bool long_chunks = a->chunk > kPoolThreads;
   const size_t per_block = long_chunks ? 4 : kPoolThreads / a->chunk;
   const unsigned pool_blocks = (unsigned)std::max<size_t>(1, std::min<size_t>((mc + per_block - 1) / per_block, 65535));
-  if (a->B == 1 && (a->T + a->chunk - 1) / a->chunk <= kSingleMaxChunks) {
+  const int64_t chunks = (a->T + a->chunk - 1) / a->chunk;
+  if (a->B == 1 && chunks <= kSingleMaxChunks) {
+    const SingleForm form = single_form(chunks);
     // One sequence (its length is T, known here): no chunk table, no cross-sequence scan.  One launch while one workgroup
     // pools in the time of a second launch (chunks of 32, window 13, one and two launches in us: 500 tokens 4.7 and 6.1,
     // 1000 5.1 and 6.3, 2048 6.4 and 6.8, 3001 9.0 and 7.4).  Its work is tokens times window,
@@ -372,12 +376,16 @@ static sp_status run_pool_select(const sp_pool_select_args* a, void* scratch, hi
     // tokens, window 33, 65, 129, 4095: 7.1 and 7.5, 8.3 and 8.3, 10.8 and 10.0, 84.0 and 60.4).
     const int64_t over = a->T - 1600;
     if (a->T <= kOneLaunchTokens && !long_chunks && (over <= 0 || over * a->pool_window <= 16000)) {
-      hipLaunchKernelGGL(pool_select_single_kernel, dim3(1), dim3(1024), 0, stream, p);
+      auto kernel = form == kRankByWave ? pool_select_single_kernel<kRankByWave>
+                    : form == kRankByCount ? pool_select_single_kernel<kRankByCount> : pool_select_single_kernel<kRankByClasses>;
+      hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, stream, p);
       return launch_status();
     }
     if (long_chunks) hipLaunchKernelGGL(pool_long_chunk_kernel<true>, dim3(pool_blocks), dim3(256), 0, stream, p);
     else hipLaunchKernelGGL(pool_chunk_kernel<true>, dim3(pool_blocks), dim3(kPoolThreads), 0, stream, p);
-    hipLaunchKernelGGL(select_emit_single_kernel, dim3(1), dim3(1024), 0, stream, p);
+    auto kernel = form == kRankByWave ? select_emit_single_kernel<kRankByWave>
+                  : form == kRankByCount ? select_emit_single_kernel<kRankByCount> : select_emit_single_kernel<kRankByClasses>;
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, stream, p);
     return launch_status();
   }
   if (p.table) hipLaunchKernelGGL(chunk_table_kernel, dim3(1), dim3(1024), 0, stream, p);

@@ -290,15 +290,19 @@ __device__ __forceinline__ int select_chunks(const double* cs, int n, int k, int
 }
 
 // Single sequence with at most kSingleMaxChunks chunks: top-k, compaction and the kept-index
-// list in one workgroup and one launch.  Above kCountMaxChunks chunks the chunks are selected as in
-// select_kernel; kept tokens are written straight away.
+// list in one workgroup and one launch; kept tokens are written straight away.  The forms of the ranking: by one wave, a
+// chunk a lane; by counting, four threads a chunk; by classes as in select_kernel.  The host knows the number of chunks, so
+// a kernel has the code of one form only (all three in one: 0.2 us more for fetching instructions in between).
 constexpr int kSingleMaxChunks = 2048;
-constexpr int kCountMaxChunks = 256;  // up to here the chunks are ranked by counting instead
+constexpr int kWaveMaxChunks = 64, kCountMaxChunks = 256;
+enum SingleForm { kRankByWave, kRankByCount, kRankByClasses };
+inline SingleForm single_form(int64_t n_chunks) {
+  return n_chunks <= kWaveMaxChunks ? kRankByWave : n_chunks <= kCountMaxChunks ? kRankByCount : kRankByClasses;
+}
 // `cs`: the chunk scores (global or LDS memory); `keys`: LDS room for kSingleMaxChunks 64-bit keys.
 // Call with all 1024 threads of the workgroup.
+template <SingleForm FORM>
 __device__ __forceinline__ void select_emit_single(const SelDev& p, const double* cs, uint64_t* keys) {
-  __shared__ int hist[kSelectHist];
-  __shared__ int sh[48];
   const int t = threadIdx.x;
   const int M = p.T;
   const int n = (M + p.chunk - 1) / p.chunk;
@@ -314,10 +318,38 @@ __device__ __forceinline__ void select_emit_single(const SelDev& p, const double
   __shared__ unsigned short kept_list[kSingleMaxChunks];
   bool last_kept;
   int kept_chunks;
-  if (n <= kCountMaxChunks) {
+  if constexpr (FORM == kRankByWave) {
+    // One wave ranks a chunk a lane and writes the list: one barrier, where the counting form has four.  (Chunks of 32, pooling
+    // included, counting form and this one: 100 tokens 4.6 and 3.5 us, 1000 5.4 and 4.6, 64 chunks 6.4 and 6.2; the single-launch
+    // kernel with a gather behind it: 100 tokens 14.4 and 13.5, 500 16.4 and 15.4; with the two barriers of a thread a chunk
+    // in whole workgroups 14.1 and 16.1.)
+    __shared__ int verdict;  // -1: invalid scores; else whether chunk n - 1 is kept
+    if (t < 64) {
+      const double v = t < n ? cs[t] : 0.0;
+      const uint64_t mine = order_key(v);
+      keys[t] = mine;
+      const bool bad = __ballot(is_nan_bits(v)) != 0;
+      int ahead = 0;
+#pragma unroll 8
+      for (int j = 0; j < n; ++j) {
+        const uint64_t other = keys[j];
+        ahead += (other > mine || (other == mine && j < t)) ? 1 : 0;
+      }
+      const uint64_t kept = __ballot(t < n && ahead < k);
+      if ((kept >> t) & 1ull) kept_list[__popcll(kept & ((1ull << t) - 1ull))] = (unsigned short)t;
+      if (t == 0) verdict = bad ? -1 : (int)((kept >> (n - 1)) & 1ull);
+    }
+    __syncthreads();
+    if (verdict < 0) {  // reported in band, nothing kept
+      if (t == 0) p.cu_keep[1] = -1;
+      return;
+    }
+    kept_chunks = k;
+    last_kept = verdict != 0;
+  } else if constexpr (FORM == kRankByCount) {
     // Few chunks: a chunk is ranked by counting the chunks that come before it in the order (larger score, or equal score
     // and lower index), four threads a chunk, each a quarter of the others; the k first are kept.  (256 chunks of 32
-    // tokens, pooling included: 15.6 us with a thread per chunk and every token looked at, 8.8 now.)
+    // tokens, pooling included: 15.6 us with a thread per chunk and every token looked at, 8.7 now.)
     __shared__ uint64_t kept_mask[kCountMaxChunks / 64];
     __shared__ unsigned char ahead[4][kCountMaxChunks];
     int bad = 0;
@@ -353,6 +385,8 @@ __device__ __forceinline__ void select_emit_single(const SelDev& p, const double
     }
     last_kept = (kept_mask[(n - 1) >> 6] >> ((n - 1) & 63)) & 1ull;
   } else {
+    __shared__ int hist[kSelectHist];
+    __shared__ int sh[48];
     auto emit = [&](int j, int rank) __attribute__((always_inline)) {
       if (rank >= 0) kept_list[rank] = (unsigned short)j;
     };
@@ -363,12 +397,12 @@ __device__ __forceinline__ void select_emit_single(const SelDev& p, const double
     }
   }
   const int64_t total_tokens = (int64_t)kept_chunks * p.chunk - (last_kept ? (int64_t)n * p.chunk - M : 0);
-  __syncthreads();
+  if constexpr (FORM != kRankByWave) __syncthreads();
   // the kept tokens are written by all threads, a token each
-  const int64_t n_write = min(total_tokens, p.capacity);
-  for (int64_t pos = t; pos < n_write; pos += 1024) {
-    const int q = (int)(pos / p.chunk);
-    p.kept_idx[pos] = (int)kept_list[q] * p.chunk + (int)(pos - (int64_t)q * p.chunk);
+  const uint32_t n_write = (uint32_t)min(total_tokens, p.capacity), chunk = (uint32_t)p.chunk;
+  for (uint32_t pos = t; pos < n_write; pos += 1024) {
+    const uint32_t q = pos / chunk;
+    p.kept_idx[pos] = (int)(kept_list[q] * chunk + (pos - q * chunk));
   }
   if (t == 0) p.cu_keep[1] = (int32_t)total_tokens;
 }

@@ -50,3 +50,21 @@ def test_wide_windows(T, window, chunk):
     assert sel.cu_keep.cpu().tolist() == cu_keep.tolist()
     np.testing.assert_allclose(sel.chunk_scores.cpu().numpy()[:len(cs)], cs.astype(np.float32), rtol=2e-7)   # (fp64 means, rounded)
     hp.selection_matches(sel.kept_idx.cpu().numpy(), sel.cu_keep.cpu().numpy(), x, cu, chunk, min(window, 2 * T + 1), 0.3, 1e-12)
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 255, 256, 257, 1024, 1025, 2048])
+@pytest.mark.parametrize("chunk, T", [(1, 0), (8, 0), (40, 0), (300, -7)])
+def test_forms_of_ranking_at_their_edges(n, chunk, T):
+    """So many chunks (the last one cut short where T says so), a tenth, half and all of them kept, ties among them."""
+    T = n * chunk + (T if n * chunk > 7 else 0)
+    x = np.exp(np.random.default_rng(n + chunk).standard_normal(T)).astype(np.float32) / 16000
+    x = np.repeat(x[::4], 4)[:T] if chunk == 1 and n > 2 else x          # equal scores in fours
+    cu = np.array([0, T], dtype=np.int32)
+    for rate in (0.1, 0.5, 1.0):
+        kept, cu_keep, _, _ = orc.pool_select(x, cu, chunk, 1, rate)
+        sel = hp.gpu_pool_select(x, cu, chunk, 1, rate, want_chunk_scores=False)
+        assert sel.cu_keep.cpu().tolist() == cu_keep.tolist()
+        got = sel.kept_idx.cpu().numpy()
+        if chunk == 1:                                                   # (the scores themselves: no rounding at all)
+            np.testing.assert_array_equal(got[:len(kept)], kept)
+        hp.selection_matches(got, sel.cu_keep.cpu().numpy(), x, cu, chunk, 1, rate, 1e-12)
