@@ -21,7 +21,8 @@ BF16_1E25, BF16_MINUS_1E25 = 0x6904, 0xE904
     dict(lens=(3000,), L=8, H=32, H_kv=8, N=8, d=64),
     dict(lens=(5000,), L=4, H=32, H_kv=8, N=8, d=128),                                # teams of workgroups
     dict(lens=(5000,), L=4, H=32, H_kv=8, N=8, d=64),
-    dict(lens=(5000,), L=4, H=32, H_kv=8, N=8, d=128, exclusive_device=False),        # two passes, query tile once per workgroup
+    dict(lens=(5000,), L=4, H=32, H_kv=8, N=8, d=128, exclusive_device=False),        # teams without the promise of an idle device
+    dict(lens=(3000,), L=4, H=32, H_kv=8, N=8, d=128, exclusive_device=False),        # two passes, query tile once per workgroup
     dict(lens=(5000, 700), L=4, H=32, H_kv=8, N=8, d=64, max_seqlen=5000),
     dict(lens=(2500, 700) * 8, L=8, H=8, H_kv=2, N=1, d=128, max_seqlen=2500),        # whole sequence in a workgroup, four rows
     dict(lens=(5000, 700), L=2, H=32, H_kv=8, N=8, d=128),                            # two passes over tiles

@@ -190,8 +190,8 @@ def test_deep_prompt_three_calls_on_one_workspace(mode):
 
 @pytest.mark.parametrize("mode", MODES)
 def test_one_long_prompt_without_the_exclusive_device_promise(mode):
-    """Without SP_SCORE_EXCLUSIVE_DEVICE the same shape is scored by kernels that never wait for
-    another workgroup; same result (to tolerance) as the oracle and as the single-pass kernel."""
+    """Without SP_SCORE_EXCLUSIVE_DEVICE the call completes itself whatever happens to its waits for other
+    workgroups; same result (to tolerance) as the oracle."""
     w = synth.scaled(synth.workload(3), seqlens=(5003,), L=3)
     inp = synth.make_qk(w)
     scale = 1.0 / math.sqrt(w.d)

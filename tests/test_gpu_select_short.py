@@ -1,5 +1,5 @@
 """Selection of one short sequence: the forms of pooling (in one workgroup's LDS, by many workgroups) and of ranking (by
-counting, by digits) at their edges, against the oracle (Sec. 3.2.3)."""
+one wave, by counting, by classes) at their edges, against the oracle (Sec. 3.2.3)."""
 import numpy as np
 import pytest
 

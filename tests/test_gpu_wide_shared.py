@@ -74,6 +74,60 @@ def test_a_call_whose_waits_give_up_completes_itself(shape, opt):
         assert np.array_equal(scores, first[0]) and np.array_equal(lse, first[1])
 
 
+@pytest.mark.parametrize("shape, opt", [
+    (dict(tokens=9000, L=8, N=8), {}),
+    (dict(tokens=6150, L=12, H=64, H_kv=8, N=4), dict(mode=orc.LAYER_MEAN)),          # parts of layers
+    (dict(tokens=5003, L=75, H=8, H_kv=2, N=8, d=64), dict(mode=orc.LAYER_MEAN, bits=8)),   # sums over layers, then parts
+    (dict(tokens=40000, L=1, H=4, H_kv=1, N=8, d=64), {}),                            # members without keys
+])
+def test_a_call_some_of_whose_waits_give_up_completes_itself(shape, opt):
+    """Few looks allowed: some workgroups get their team's lines, others give up, in the first slab or a later one, with
+    valid slabs folded and sums written; the same bits as with every wait answered."""
+    from paper_2502_02789_amd import binding as sp
+    shape, opt = dict(shape), dict(opt)
+    mode = opt.pop("mode", orc.LAYER_MAX)
+    w = synth.scaled(synth.workload(3), seqlens=(shape.pop("tokens"),), salient_run=1, **shape)
+    s = _scorer(w, synth.make_qk(w), mode, **opt)
+
+    def call():
+        s.scores.fill_(float("nan"))
+        s.lse.fill_(float("nan"))
+        s.run()
+        s.check()
+        return s.scores.cpu().numpy(), s.lse.cpu().numpy()
+
+    want = call()
+    assert np.isfinite(want[0]).all()
+    for looks in (1, 2, 3, 5, 10, 20, 50):
+        before = sp.sp_set_wait_budget(looks)
+        try:
+            runs = [call() for _ in range(3)]
+        finally:
+            sp.sp_set_wait_budget(before)
+        for scores, lse in runs:
+            assert np.array_equal(scores, want[0]) and np.array_equal(lse, want[1]), looks
+
+
+@pytest.mark.parametrize("mode", [orc.LAYER_MAX, orc.LAYER_MEAN])
+@pytest.mark.parametrize("shape", [
+    dict(tokens=3073, L=4, H=32, H_kv=8, N=8, d=128),    # one key more than the kernel for whole sequences holds
+    dict(tokens=4096, L=2, H=16, H_kv=4, N=8, d=64),     # full shares
+    dict(tokens=4097, L=3, H=6, H_kv=2, N=5, d=128),     # three heads padded to four
+    dict(tokens=12345, L=2, H=64, H_kv=8, N=4, d=64),    # eight heads per KV head
+    dict(tokens=8225, L=5, H=8, H_kv=1, N=3, d=128),     # few slabs, ragged shares
+    dict(tokens=5001, L=3, H=4, H_kv=1, N=8, d=64),      # results that outweigh the keys
+])
+def test_one_prompt_on_a_shared_device(shape, mode):
+    """The teams against the oracle."""
+    shape = dict(shape)
+    w = synth.scaled(synth.workload(3), seqlens=(shape.pop("tokens"),), salient_run=1, **shape)
+    inp = synth.make_qk(w)
+    want, want_lse = orc.token_importance(inp["q"], inp["k"], inp["cu_seqlens"], 1.0 / math.sqrt(w.d), mode)
+    got, lse = hp.gpu_score(inp["q"], inp["k"], inp["cu_seqlens"], w.H_kv, 1.0 / math.sqrt(w.d), mode, exclusive_device=False)
+    hp.assert_scores_close(got, want, f"{w.name} mode={mode}")
+    np.testing.assert_allclose(lse, want_lse, rtol=0, atol=2e-4)
+
+
 def test_calls_on_four_streams_at_once():
     """Four calls in flight together, each with a workspace of its own, more workgroups than the device holds."""
     import torch

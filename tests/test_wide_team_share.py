@@ -36,8 +36,12 @@ def test_shares_cover_the_prompt(tmp_path, wgs):
         out = (C.c_int * 4)()
         lib.plan(C.byref(a), wgs, out)
         ok, lgP, chunk, share = out
-        if not ok:
+        if not ok:                                                  # refused: only what no team holds
+            assert T > min(64, wgs) * (2048 if n <= 8 else 1024), (T, n)
             continue
         P = 1 << lgP
         assert share % 32 == 0 and share <= chunk and P * share >= T, (T, n, lgP, share)
         assert (T + P - 1) // P > share - 32, (T, n, lgP, share)    # not a tile more than needed
+        keys = [max(0, min(T - m * share, share)) for m in range(P)]  # as the kernel has it
+        assert sum(keys) == T and keys == sorted(keys, reverse=True), (T, n, lgP, share)
+        assert sum(0 < k < share for k in keys) <= 1, (T, n, lgP, share)  # full ones, at most one cut short, then empty ones
