@@ -322,13 +322,14 @@ extern "C" sp_status sp_score_pool_select(const sp_score_args* a, const sp_pool_
   for (int l = 0; l < SP_MAX_LAYERS; ++l) dev.k[l] = l < a->L ? static_cast<const uint16_t*>(a->k_layers[l]) : nullptr;
   SelDev& p = dev.sel;
   p.B = 1; p.T = (int)a->T; p.chunk = s->chunk; p.radius = (s->pool_window - 1) / 2;
+  p.n_chunks = (int)((a->T + s->chunk - 1) / s->chunk);
   p.keep_rate = s->keep_rate; p.capacity = s->kept_capacity;
   p.cu = s->d_cu_seqlens; p.scores = s->d_scores; p.kept_idx = s->d_kept_idx; p.cu_keep = s->d_cu_keep;
   p.chunk_scores_out = s->d_chunk_scores;
   p.cu_chunks = nullptr; p.seq_keep = nullptr; p.cs = nullptr; p.chunk_off = nullptr;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const dim3 grid(dev.M_pad / 64), block(kFusedThreads);
-  const SingleForm form = single_form((a->T + s->chunk - 1) / s->chunk);
+  const SingleForm form = single_form(p.n_chunks);
   auto kernel = a->d == 64 ? (form == kRankByWave ? fused_short_kernel<64, kRankByWave>
                               : form == kRankByCount ? fused_short_kernel<64, kRankByCount> : fused_short_kernel<64, kRankByClasses>)
                            : (form == kRankByWave ? fused_short_kernel<128, kRankByWave>

@@ -32,7 +32,7 @@ __device__ __forceinline__ int sequence_of_chunk(const SelDev& p, int j) {
 }
 
 __global__ __launch_bounds__(1024) void chunk_table_kernel(const SelDev p) {
-  block_prefix_table(p.B, [&](int b) { return (p.cu[b + 1] - p.cu[b] + p.chunk - 1) / p.chunk; }, p.cu_chunks);
+  block_prefix_table(p.B, [&](int b) { return chunk_count(p.cu[b + 1] - p.cu[b], p.chunk); }, p.cu_chunks);
 }
 
 __device__ __forceinline__ double shfl_f64(double v, int src) {
@@ -60,7 +60,7 @@ template <bool SINGLE>  // SINGLE: one sequence of T tokens
 __global__ __launch_bounds__(kPoolThreads) void pool_chunk_kernel(const SelDev p) {
   __shared__ double pooled[2 * kPoolThreads];
   const int cpb = kPoolThreads / p.chunk;              // chunks per workgroup
-  const int n_chunks = SINGLE ? (p.T + p.chunk - 1) / p.chunk : p.table ? p.cu_chunks[p.B] : p.T / p.chunk + p.B;
+  const int n_chunks = SINGLE ? p.n_chunks : p.table ? p.cu_chunks[p.B] : p.T / p.chunk + p.B;
   const int t = threadIdx.x;
   if (!SINGLE && !p.table && blockIdx.x == 0 && t == 0) *p.arrived = 0;  // (for the selection kernel behind this one)
   const int q = t / p.chunk, t_in = t - q * p.chunk;
@@ -112,18 +112,18 @@ __global__ __launch_bounds__(kPoolThreads) void pool_chunk_kernel(const SelDev p
 template <bool SINGLE>
 __global__ __launch_bounds__(256) void pool_long_chunk_kernel(const SelDev p) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int n_chunks = SINGLE ? (p.T + p.chunk - 1) / p.chunk : p.table ? p.cu_chunks[p.B] : p.T / p.chunk + p.B;
+  const int n_chunks = SINGLE ? p.n_chunks : p.table ? p.cu_chunks[p.B] : p.T / p.chunk + p.B;
   if (!SINGLE && !p.table && blockIdx.x == 0 && threadIdx.x == 0) *p.arrived = 0;
   for (int j = blockIdx.x * 4 + wave; j < n_chunks; j += gridDim.x * 4) {
-    int lo = 0, hi = p.T, s0 = j * p.chunk;
+    int lo = 0, hi = p.T, nth = j;
     if (!SINGLE) {
       const int b = sequence_of_chunk(p, j);
       lo = p.cu[b];
       hi = p.cu[b + 1];
-      s0 = lo + (j - chunk_base(p, b)) * p.chunk;
+      nth = j - chunk_base(p, b);
     }
-    const int s1 = min(s0 + p.chunk, hi);
-    if (s1 <= s0) continue;
+    if (nth >= chunk_count(hi - lo, p.chunk)) continue;  // (a place without a chunk)
+    const int s0 = lo + nth * p.chunk, s1 = hi - s0 < p.chunk ? hi : s0 + p.chunk;
     double tot = 0.0;
     for (int seg = s0; seg < s1; seg += kWave) {
       const int i = seg + lane;
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(1024) void select_kernel(const SelDev p) {
   __shared__ int sh[48];
   const int b = blockIdx.x, t = threadIdx.x;
   const int M = p.cu[b + 1] - p.cu[b];
-  const int c0 = chunk_base(p, b), n = (M + p.chunk - 1) / p.chunk;
+  const int c0 = chunk_base(p, b), n = chunk_count(M, p.chunk);
   int keep_tokens = 0;
   if (n > 0) {
     const double scaled = p.keep_rate * (double)n;
@@ -366,6 +366,7 @@ static sp_status run_pool_select(const sp_pool_select_args* a, void* scratch, hi
   const size_t per_block = long_chunks ? 4 : kPoolThreads / a->chunk;
   const unsigned pool_blocks = (unsigned)std::max<size_t>(1, std::min<size_t>((mc + per_block - 1) / per_block, 65535));
   const int64_t chunks = (a->T + a->chunk - 1) / a->chunk;
+  p.n_chunks = a->B == 1 ? (int)chunks : 0;
   if (a->B == 1 && chunks <= kSingleMaxChunks) {
     const SingleForm form = single_form(chunks);
     // One sequence (its length is T, known here): no chunk table, no cross-sequence scan.  One launch while one workgroup

@@ -15,6 +15,7 @@ struct SelDev {
   int B;
   int T;
   int chunk, radius;
+  int n_chunks;         // one sequence: its chunks
   double keep_rate;
   int64_t capacity;
   const int32_t* cu;
@@ -29,6 +30,9 @@ struct SelDev {
   double* cs;           // [max_chunks]
   int32_t* chunk_off;   // [max_chunks]: rank of the chunk among its sequence's kept ones, or -1
 };
+
+// chunks of m tokens (a chunk may be as long as an int holds)
+__device__ __forceinline__ int chunk_count(int m, int chunk) { return m > 0 ? (m - 1) / chunk + 1 : 0; }
 
 // NaN, decided on the bit pattern (device code is compiled on the assumption that there are none)
 __device__ __forceinline__ bool is_nan_bits(double v) {
@@ -305,7 +309,7 @@ template <SingleForm FORM>
 __device__ __forceinline__ void select_emit_single(const SelDev& p, const double* cs, uint64_t* keys) {
   const int t = threadIdx.x;
   const int M = p.T;
-  const int n = (M + p.chunk - 1) / p.chunk;
+  const int n = p.n_chunks;
   if (t == 0) p.cu_keep[0] = 0;
   if (n == 0) {
     if (t == 0) p.cu_keep[1] = 0;
@@ -412,7 +416,7 @@ __device__ __forceinline__ void select_emit_single(const SelDev& p, const double
 constexpr int kPoolSegment = 2048;
 constexpr int kPoolRoom = kPoolSegment + kPoolSegment / 8;  // (chunks of eight and more tokens a double apart: no bank conflicts)
 __device__ __forceinline__ void pool_chunks_in_lds(const SelDev& p, const float* score, double* pooled, double* cs) {
-  const int n = (p.T + p.chunk - 1) / p.chunk, per_segment = max(1, kPoolSegment / p.chunk), pad = p.chunk >= 8 ? 1 : 0;
+  const int n = p.n_chunks, per_segment = max(1, kPoolSegment / p.chunk), pad = p.chunk >= 8 ? 1 : 0;
   const uint32_t inverse = 0xffffffffu / (uint32_t)p.chunk + 1u;  // x / chunk = x * inverse >> 32 for x below 2^32 / chunk
   for (int j0 = 0; j0 < n; j0 += per_segment) {
     const int first = j0 * p.chunk, chunks = min(per_segment, n - j0), end = j0 + chunks == n ? p.T : first + chunks * p.chunk;

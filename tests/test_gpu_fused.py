@@ -71,6 +71,20 @@ def test_fused_short_prompt_against_oracle(case, mode):
                          window, rate, hp.SCORE_RTOL)
 
 
+@pytest.mark.parametrize("chunk", [1, 4, 15, 16, 32, 1023, 2 ** 31 - 500, 2 ** 31 - 1])
+@pytest.mark.parametrize("d", [64, 128])
+def test_forms_of_ranking_and_long_chunks(chunk, d):
+    """1000 and 1024 tokens in 1000 chunks to one, ranked by classes, by counting and by one wave; chunks longer than the prompt."""
+    for T in (1000, 1024):
+        w = synth.scaled(synth.workload(1), seqlens=(T,), d=d, salient_frac=0.02, salient_run=1)
+        s, sel = _run_fused(w, synth.make_qk(w), orc.LAYER_MAX, chunk, 5, 0.3)
+        got = s.scores.cpu().numpy()
+        kept, cu_keep, cs, _ = orc.pool_select(got, np.array([0, T], dtype=np.int32), min(chunk, T), 5, 0.3)
+        assert sel.cu_keep.cpu().tolist() == cu_keep.tolist()
+        np.testing.assert_allclose(sel.chunk_scores.cpu().numpy()[:len(cs)], cs.astype(np.float32), rtol=2e-7)
+        hp.selection_matches(sel.kept_idx.cpu().numpy()[:len(kept)], cu_keep, got, np.array([0, T], dtype=np.int32), min(chunk, T), 5, 0.3, 1e-12)
+
+
 def test_fused_equals_the_separate_calls():
     import torch
     from paper_2502_02789_amd import device as dev

@@ -68,3 +68,16 @@ def test_forms_of_ranking_at_their_edges(n, chunk, T):
         if chunk == 1:                                                   # (the scores themselves: no rounding at all)
             np.testing.assert_array_equal(got[:len(kept)], kept)
         hp.selection_matches(got, sel.cu_keep.cpu().numpy(), x, cu, chunk, 1, rate, 1e-12)
+
+
+@pytest.mark.parametrize("chunk", [1 << 30, 2 ** 31 - 1001, 2 ** 31 - 500, 2 ** 31 - 1])
+@pytest.mark.parametrize("lens", [(1000,), (2047,), (1000, 0, 1, 1700)])
+def test_chunks_longer_than_any_sequence(chunk, lens):
+    """One chunk a sequence, all of it kept, up to the longest chunk an int holds."""
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T = int(cu[-1])
+    x = np.random.default_rng(7).random(T).astype(np.float32)
+    for want_chunk_scores in (False, True):
+        sel = hp.gpu_pool_select(x, cu, chunk, 1, 0.3, want_chunk_scores=want_chunk_scores)
+        assert sel.cu_keep.cpu().tolist() == cu.tolist()
+        assert sel.kept_idx.cpu().tolist() == list(range(T))
