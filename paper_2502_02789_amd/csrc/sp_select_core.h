@@ -412,7 +412,8 @@ __device__ __forceinline__ void select_emit_single(const SelDev& p, const double
 }
 
 // Pooling and chunk means of one sequence whose scores are in LDS, by one workgroup of 1024 threads: `pooled` has room for
-// kPoolRoom doubles, the chunks of up to kPoolSegment tokens at a time (a sequence with longer chunks must not be longer).  Window sums, chunk sums and divisions are those of pool_chunk_kernel, in its order.
+// kPoolRoom doubles, the chunks of up to kPoolSegment tokens at a time (a sequence with longer chunks must not be longer).
+// Window sums, chunk sums and divisions are those of pool_chunk_kernel, in its order.
 constexpr int kPoolSegment = 2048;
 constexpr int kPoolRoom = kPoolSegment + kPoolSegment / 8;  // (chunks of eight and more tokens a double apart: no bank conflicts)
 __device__ __forceinline__ void pool_chunks_in_lds(const SelDev& p, const float* score, double* pooled, double* cs) {

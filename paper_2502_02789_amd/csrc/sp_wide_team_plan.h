@@ -32,8 +32,7 @@ inline int wide_team_lg(const sp_score_args* a) {
   const int heads = a->H / a->H_kv;
   return heads > 4 ? 3 : heads <= 2 && a->N > 8 ? 1 : 2;
 }
-// 32-key tiles per wave, whole ring slots (one, two or four): what the registers hold of logits (16 each) and running
-// maxima (16 >> lg each).
+// 32-key tiles per wave: what the registers hold of logits (16 each) and running maxima (16 >> lg each).
 constexpr int wide_team_tiles(int lg) { return lg > 1 ? 8 : 4; }
 
 // The slabs are dealt out to the teams in turn: `rounds` rounds of `run` slabs to each team, the others in parts of
@@ -99,9 +98,10 @@ inline WideTeamPlan make_wide_team_plan(const sp_score_args* a, int wgs) {
   const int P = 1 << lgP, teams = wgs >> lgP;
   pl.lgP = lgP;
   pl.chunk = (int)(((a->T + P - 1) / P + 255) / 256 * 256);
-  // Whole tiles, not whole rounds of the eight waves: fewer keys for the busiest member, and all members have some.  (32
-  // layers, 8 KV heads, d = 128, eight queries, before -> now in us: 33000 keys 407 -> 384, 70000 821 -> 787, 100000 1118 -> 1073,
-  // 8-bit keys 269 -> 250 and 565 -> 544 for the first two; where the prompt fills whole rounds nothing changes.)
+  // Whole tiles, not whole rounds of the eight waves: fewer keys for the busiest member.  The last members may still have
+  // none (3073 keys, 32 members: 24 full shares of 128, one key in another, seven empty ones).  (32 layers, 8 KV heads,
+  // d = 128, eight queries, before -> now in us: 33000 keys 407 -> 384, 70000 821 -> 787, 100000 1118 -> 1073, 8-bit keys
+  // 269 -> 250 and 565 -> 544 for the first two; where the prompt fills whole rounds nothing changes.)
   pl.share = (int)((a->T + P - 1) / P + 31) / 32 * 32;
   WideTeamDeal& d = pl.deal;
   d.teams = teams;
@@ -110,7 +110,9 @@ inline WideTeamPlan make_wide_team_plan(const sp_score_args* a, int wgs) {
     // Whole layers, in turn, as long as there is one for every team; the layers left over (all of them, if there are
     // fewer than teams) in parts, cut so that the team with the most of them is done soonest: its slabs (with about 200
     // keys' time for the end of each), 300 keys' time for the end of a part and its results at eight times their bytes
-    // (written, read back, and they hold up the stream).  Left over as whole layers, or in the largest parts that give every
+    // (written, read back, and they hold up the stream).  Keys are counted in whole rounds of the eight waves, which is how
+    // the constants were fitted; by the members' shares the choice is the same for all usual numbers of KV heads (1, 2, 4, 8;
+    // 26000 shapes of 3073 to 131072 keys) and another one in fewer than one of 1000 others.  Left over as whole layers, or in the largest parts that give every
     // team one, where there are fewer: 24 layers of 32K keys 328 us against 267, 36 layers 492 against 410 (16000 keys
     // 315 against 215), 20 layers of 4 KV heads 114 against 84, 22 layers of 8192 keys with d = 64 68 against 62; the
     // exception among the shapes tried: 33 layers of 4000 keys 86.5 against 88.8.
