@@ -123,19 +123,21 @@ struct WideKernel {
       const int page = 1 << p.lg_page, last = (key_first + min(rows, 32) - 1) >> p.lg_page;
       int pg = key_first >> p.lg_page, entry = table[pg];
       int in_page = key_first & (page - 1);
+      // A page's descriptor starts where the item's first key would be if all of it lay in that page, so that offsets and
+      // range are the item's, as for a contiguous cache, and a load is left with little scalar work.
+      const uint32_t bytes = (uint32_t)(min(rows, 32) - 1) * ts_b + KROW_B;
       const uint32_t lane_row = ld_row;
+      uint32_t row_off = 0;
       int j = 0;
 #pragma unroll 1
       for (;;) {
-        const unsigned char* base = slab + ESZ * ((int64_t)entry * p.page_stride) + (int64_t)in_page * (int64_t)ts_b;
+        const unsigned char* base = slab + ESZ * ((int64_t)entry * p.page_stride) + (int64_t)(in_page - j * RPI) * (int64_t)ts_b;
         entry = table[min(pg + 1, last)];
         const int j_end = min(LOADS, j + ((page - in_page) / RPI));
 #pragma unroll 1
         for (; j < j_end; ++j) {
-          const int left = min(rows - j * RPI, RPI);
-          const uint32_t bytes = left <= 0 ? 0u : (uint32_t)(left - 1) * ts_b + KROW_B;
-          load1k(base, bytes, lane_row + (ld_unit ^ (uint32_t)(((4 * j) & (KU - 1)) << 4)), dst + j * 1024);
-          base += (int64_t)RPI * (int64_t)ts_b;
+          load1k(base, bytes, lane_row + (ld_unit ^ (uint32_t)(((4 * j) & (KU - 1)) << 4)) + row_off, dst + j * 1024);
+          row_off += (uint32_t)RPI * ts_b;
         }
         if (j == LOADS) break;
         ++pg;
