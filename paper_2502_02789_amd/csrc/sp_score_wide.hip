@@ -366,8 +366,11 @@ sp_status wide_score(const sp_score_args* a, const TiledDev& dev_, hipStream_t s
 sp_status launch_wide_finish(const TiledDev& dev, unsigned tiles, uint32_t* status, hipStream_t stream) {
   // Two workgroups per 32-key tile where the tiles alone would not give every compute unit two; small workgroups
   // where a tile has few rows to read (128K keys in four groups of eight queries: 24 us with 1024 threads) and at most
-  // eight queries (a thread per key and query).
-  if (tiles < 512) hipLaunchKernelGGL((wide_finish_kernel<16, 1024>), dim3(2 * tiles), dim3(1024), 0, stream, dev, status);
+  // eight queries (a thread per key and query).  With no more rows than a small workgroup reads in one step it is ahead
+  // for short prompts too (one layer, one KV head, d = 64, one query, whole call: 4500 keys 14.1 -> 12.2 us, 9000
+  // 16.7 -> 12.6, 15000 18.1 -> 12.8; four layers of four KV heads, two queries, 9000 keys 17.3 -> 14.1).
+  const bool few_rows = dev.n_groups * dev.N <= 32 && dev.N <= 8;
+  if (tiles < 512 && !few_rows) hipLaunchKernelGGL((wide_finish_kernel<16, 1024>), dim3(2 * tiles), dim3(1024), 0, stream, dev, status);
   else if (dev.n_groups * dev.N > 256 || dev.N > 8) hipLaunchKernelGGL((wide_finish_kernel<32, 1024>), dim3(tiles), dim3(1024), 0, stream, dev, status);
   else hipLaunchKernelGGL((wide_finish_kernel<32, 256>), dim3(tiles), dim3(256), 0, stream, dev, status);
   return launch_status();

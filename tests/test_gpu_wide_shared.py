@@ -198,3 +198,16 @@ def test_other_work_on_most_compute_units_does_not_hold_a_call_up():
     beside = sorted((call(200) for _ in range(3)), key=lambda x: x[0])[1]
     assert np.array_equal(beside[1], alone[1])
     assert beside[0] < 20 * alone[0], (beside[0], alone[0])
+
+
+@pytest.mark.parametrize("tokens", [3073, 9001, 16383])
+@pytest.mark.parametrize("L, H, H_kv, N", [(1, 4, 1, 1), (2, 4, 1, 8), (1, 8, 2, 8), (8, 16, 4, 1), (11, 3, 1, 3)])
+@pytest.mark.parametrize("mode", [orc.LAYER_MAX, orc.LAYER_MEAN])
+def test_merge_of_few_results(tokens, L, H, H_kv, N, mode):
+    """One to 33 rows of results a tile: on both sides of what a small workgroup of the merge reads in one step."""
+    w = synth.scaled(synth.workload(3), seqlens=(tokens,), salient_run=1, L=L, H=H, H_kv=H_kv, N=N, d=64)
+    inp = synth.make_qk(w)
+    want, want_lse = orc.token_importance(inp["q"], inp["k"], inp["cu_seqlens"], 1.0 / math.sqrt(w.d), mode)
+    got, lse = hp.gpu_score(inp["q"], inp["k"], inp["cu_seqlens"], w.H_kv, 1.0 / math.sqrt(w.d), mode, exclusive_device=False)
+    hp.assert_scores_close(got, want, f"{w.name} mode={mode}")
+    np.testing.assert_allclose(lse, want_lse, rtol=0, atol=2e-4)
