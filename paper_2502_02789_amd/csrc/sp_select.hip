@@ -20,7 +20,7 @@ namespace sp {
 // for its chunks that way, T / chunk + B places in all); with one (the caller wants the chunk scores, which are
 // numbered without gaps) where it says.
 __device__ __forceinline__ int chunk_base(const SelDev& p, int b) {
-  return p.table ? p.cu_chunks[b] : p.cu[b] / p.chunk + b;
+  return p.table ? p.cu_chunks[b] : (int)((uint32_t)p.cu[b] / (uint32_t)p.chunk) + b;
 }
 __device__ __forceinline__ int sequence_of_chunk(const SelDev& p, int j) {
   int lo = 0, hi = p.B;  // the largest b whose first chunk is <= j
@@ -224,6 +224,9 @@ __device__ __forceinline__ int select_chunks_from_memory(const double* cs, int n
 // One workgroup per sequence; chunk_off gets the rank of every kept chunk among its sequence's, -1 for the others.
 // Without a chunk table the workgroup that finishes last (a word the pooling kernel has cleared counts them) adds the
 // sequences' counts up, which the table variant leaves to a launch of its own.
+// MOST: chunks a sequence may have, as far as the host can tell from all the tokens: a kernel has the code for no more (all
+// forms in one cost 0.2 us for fetching what lies in between).
+template <int MOST>
 __global__ __launch_bounds__(1024) void select_kernel(const SelDev p) {
   __shared__ int hist[kSelectHist];
   __shared__ int sh[48];
@@ -240,8 +243,8 @@ __global__ __launch_bounds__(1024) void select_kernel(const SelDev p) {
     auto emit = [&](int j, int rank) __attribute__((always_inline)) { rank_out[j] = rank; };
     bool last_kept = false;
     int kept;
-    if (n <= 1024) kept = select_chunks<1>(cs, n, k, hist, sh, &last_kept, emit);
-    else if (n <= 4096) kept = select_chunks<4>(cs, n, k, hist, sh, &last_kept, emit);
+    if (MOST <= 1024 || n <= 1024) kept = select_chunks<1>(cs, n, k, hist, sh, &last_kept, emit);
+    else if (MOST <= 4096 || n <= 4096) kept = select_chunks<4>(cs, n, k, hist, sh, &last_kept, emit);
     else if (n <= 16384) kept = select_chunks<16>(cs, n, k, hist, sh, &last_kept, emit);
     else kept = select_chunks_from_memory(cs, n, k, hist, sh, &last_kept, rank_out);
     // invalid scores (NaN: the scorer's mark for "a device-side wait expired") are reported in band:
@@ -392,7 +395,8 @@ static sp_status run_pool_select(const sp_pool_select_args* a, void* scratch, hi
   if (p.table) hipLaunchKernelGGL(chunk_table_kernel, dim3(1), dim3(1024), 0, stream, p);
   if (long_chunks) hipLaunchKernelGGL(pool_long_chunk_kernel<false>, dim3(pool_blocks), dim3(256), 0, stream, p);
   else hipLaunchKernelGGL(pool_chunk_kernel<false>, dim3(pool_blocks), dim3(kPoolThreads), 0, stream, p);
-  hipLaunchKernelGGL(select_kernel, dim3(a->B), dim3(1024), 0, stream, p);
+  hipLaunchKernelGGL(chunks <= 1024 ? select_kernel<1024> : chunks <= 4096 ? select_kernel<4096> : select_kernel<INT32_MAX>, dim3(a->B),
+                     dim3(1024), 0, stream, p);
   if (p.table) hipLaunchKernelGGL(cu_keep_kernel, dim3(1), dim3(1024), 0, stream, p);
   if (a->T > 0)
     hipLaunchKernelGGL(emit_kernel, dim3((unsigned)((a->T + 255) / 256)), dim3(256), 0, stream, p);

@@ -15,7 +15,6 @@ struct SelDev {
   int B;
   int T;
   int chunk, radius;
-  int n_chunks;         // one sequence: its chunks
   double keep_rate;
   int64_t capacity;
   const int32_t* cu;
@@ -29,10 +28,12 @@ struct SelDev {
   int32_t* seq_keep;    // [B]
   double* cs;           // [max_chunks]
   int32_t* chunk_off;   // [max_chunks]: rank of the chunk among its sequence's kept ones, or -1
+  int n_chunks;         // one sequence: its chunks
 };
 
-// chunks of m tokens (a chunk may be as long as an int holds)
-__device__ __forceinline__ int chunk_count(int m, int chunk) { return m > 0 ? (m - 1) / chunk + 1 : 0; }
+// chunks of m tokens (a chunk may be as long as an int holds: the sum fits 32 bits without a sign, and no
+// more; a test for m > 0 and a division of m - 1 instead made the selection of a batch 0.25 us longer)
+__device__ __forceinline__ int chunk_count(int m, int chunk) { return (int)(((uint32_t)m + (uint32_t)chunk - 1u) / (uint32_t)chunk); }
 
 // NaN, decided on the bit pattern (device code is compiled on the assumption that there are none)
 __device__ __forceinline__ bool is_nan_bits(double v) {
@@ -107,13 +108,12 @@ __device__ __forceinline__ int reg_chunk(int i) {
 // upper halves): the class that holds it is counted again in narrower classes until all of it is kept, all its keys are
 // equal, or it has no more than 64 chunks, which are ranked among themselves -- after one or two passes as a rule.
 // (Digits of eight fixed bits took three passes, the first of them with nearly all keys in one or two counters, whose
-// additions LDS performs one after the other.  Whole selection, window 1, single tokens: eight sequences of 8000 29.2 -> 22.0 us,
-// of 16000 36.1 -> 23.8, one of 2000 10.6 -> 7.8; 1024 and 2048 smoothed chunks of one sequence, a twentieth kept 9.2 -> 8.7 and
-// 10.1 -> 9.7, three tenths 10.7 -> 10.4 and 12.8 -> 12.2, half 11.8 -> 11.6 and 15.7 -> 14.9.  Ranking up to 128 chunks
-// takes longer than the second pass: 10.1, 12.1 and 13.2 for the 1024.)
+// additions LDS performs one after the other.  Whole selection, window 1, single tokens: eight sequences of 8000 29.2 -> 22.2 us,
+// of 16000 36.1 -> 23.9, one of 2000 10.6 -> 7.6; 1024 and 2048 smoothed chunks of one sequence, a twentieth kept 9.2 -> 8.5 and
+// 10.1 -> 9.4, three tenths 10.7 -> 9.9 and 12.8 -> 11.5, half 11.8 -> 10.9 and 15.7 -> 13.7.  Ranking up to 128 chunks
+// took longer than the second pass.)
 // `hist` has room for kSelectHist counters, `sh` for 48.
 constexpr int kSelectHist = 1024 + 64;
-constexpr int kFew = 64;  // chunks of a class that are ranked among themselves
 // the least (MAX: the largest) of a wave's values
 template <bool MAX>
 __device__ __forceinline__ uint32_t wave_extreme(uint32_t v) {
@@ -131,8 +131,8 @@ __device__ __forceinline__ int select_chunks(const double* cs, int n, int k, int
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
   // classes (a lane sums PER of them: a gap behind every PER)
   constexpr int LG_BINS = I <= 2 ? 9 : 10, BINS = 1 << LG_BINS, PER = BINS / 64;
-  __shared__ uint64_t few_key[kFew];
-  __shared__ int few_chunk[kFew], few_ahead[kFew], few, kth_chunk_sh;
+  __shared__ uint64_t few_key[64], kth_sh;
+  __shared__ int few_chunk[64], few, kth_chunk_sh;
   uint64_t key[I];
   int bad = 0;
   uint32_t least = ~0u, most = 0u;
@@ -152,7 +152,6 @@ __device__ __forceinline__ int select_chunks(const double* cs, int n, int k, int
   most = wave_extreme<true>(most);
   if (lane == 0) { sh[wave] = (int)least; sh[16 + wave] = (int)most; }
   if (t == 0) few = 0;
-  if (t < kFew) few_ahead[t] = 0;
   if (__syncthreads_or(bad)) return -1;
 #pragma unroll
   for (int w = 0; w < 16; ++w) {
@@ -221,7 +220,7 @@ __device__ __forceinline__ int select_chunks(const double* cs, int n, int k, int
       kth_chunk = kth_chunk_sh;
       break;
     }
-    if (size <= kFew) {
+    if (size <= 64) {
 #pragma unroll
       for (int i = 0; i < I; ++i)
         if (reg_chunk<I>(i) < n && key[i] - lo <= span) {
@@ -230,33 +229,23 @@ __device__ __forceinline__ int select_chunks(const double* cs, int n, int k, int
           few_chunk[at] = reg_chunk<I>(i);
         }
       __syncthreads();
-      // All threads rank them, each one chunk against four others, both words of those read before either is looked at.
-      // (Every wave all of them for itself, the second word's read behind the first's outcome, was a chain of two LDS
-      // round trips a chunk: 768 smoothed chunks with 50 left to rank 13.3 us, 9.2 this way; by digits 10.0.)
-      constexpr int PARTS = 1024 / kFew, OF_PART = kFew / PARTS;
-      {
-        const int c = t % kFew, x0 = t / kFew * OF_PART;
-        const uint64_t mine = few_key[c];
-        const int chunk = few_chunk[c];
-        int ahead = 0;
+      // A wave ranks four of them: lane x holds the x-th, a ballot finds those ahead.  (Every wave all of them for itself, a
+      // key's index read behind the comparison of the keys, was a chain of two LDS round trips a chunk: 768 smoothed
+      // chunks with 50 left to rank 13.3 us, 9.1 this way; by digits 10.0.)
+      const uint64_t mine = few_key[lane];
+      const int chunk = few_chunk[lane];
 #pragma unroll
-        for (int u = 0; u < OF_PART; ++u) {
-          const uint64_t other = few_key[x0 + u];
-          const int other_chunk = few_chunk[x0 + u];
-          ahead += (int)(x0 + u < size) & ((int)(other > mine) | ((int)(other == mine) & (int)(other_chunk < chunk)));
-        }
-        if (c < size && ahead != 0) atomicAdd(&few_ahead[c], ahead);
+      for (int u = 0; u < 4; ++u) {
+        const int x = wave * 4 + u;
+        const uint64_t other = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(mine >> 32), x) << 32) |
+                               (uint32_t)__builtin_amdgcn_readlane((int)mine, x);
+        const int other_chunk = __builtin_amdgcn_readlane(chunk, x);
+        const bool ahead = (int)(lane < size) & ((int)(mine > other) | ((int)(mine == other) & (int)(chunk < other_chunk)));
+        if (x < size && __popcll(__ballot(ahead)) == need - 1 && lane == 0) { kth_sh = other; kth_chunk_sh = other_chunk; }
       }
       __syncthreads();
-#pragma unroll
-      for (int r = 0; r < kFew; r += 64) {
-        const unsigned long long hit = __ballot(r + lane < size && few_ahead[r + lane] == need - 1);
-        if (hit != 0) {
-          const int it = r + __builtin_amdgcn_readfirstlane(__ffsll(hit) - 1);
-          kth = few_key[it];
-          kth_chunk = few_chunk[it];
-        }
-      }
+      kth = kth_sh;
+      kth_chunk = kth_chunk_sh;
       break;
     }
     shift = max(0, shift - LG_BINS);

@@ -27,3 +27,16 @@ def test_close_scores(n, B, cluster, ties):
         sel = hp.gpu_pool_select(scores, cu, 1, 1, rate, want_chunk_scores=False)
         assert sel.cu_keep.cpu().tolist() == cu_keep.tolist() == [b * (above + last) for b in range(B + 1)]
         np.testing.assert_array_equal(sel.kept_idx.cpu().numpy()[:len(kept)], kept)
+
+
+@pytest.mark.parametrize("lens", [(1024, 0), (1025, 0, 0), (1000, 24), (1000, 25), (4096, 0), (0, 4097), (2000, 2096, 0), (1, 1, 1, 1, 1024)])
+@pytest.mark.parametrize("chunk", [1, 3])
+def test_batches_at_the_edges_of_what_a_kernel_holds(lens, chunk):
+    """All tokens of the batch decide which kernel runs: sequences of as many chunks as it holds, and one more."""
+    cu = np.concatenate([[0], np.cumsum(np.array(lens) * chunk)]).astype(np.int32)
+    scores = np.random.default_rng(len(lens)).random(int(cu[-1])).astype(np.float32)
+    kept, cu_keep, _, _ = orc.pool_select(scores, cu, chunk, 1, 0.3)
+    for want_chunk_scores in (False, True):
+        sel = hp.gpu_pool_select(scores, cu, chunk, 1, 0.3, want_chunk_scores=want_chunk_scores)
+        assert sel.cu_keep.cpu().tolist() == cu_keep.tolist()
+        hp.selection_matches(sel.kept_idx.cpu().numpy()[:len(kept)], cu_keep, scores, cu, chunk, 1, 0.3, 1e-12)
