@@ -61,8 +61,8 @@ struct WideTeamDev : TiledDev {
   size_t copy_words;
   uint32_t* status;        // [epoch & 1] != 0: a wait of this call expired; [2]: epoch, calls since the last fill;
                            // [3] != 0: a wait of a shared call's first launch expired, nobody waits any longer
-  uint64_t patience;       // kFirst: ticks of the 100 MHz clock that a workgroup waits for the lines of a slab
   int launch;              // kAlone; kFirst and kSecond: the launches of a call without the promise of an idle device
+  uint32_t patience;       // kFirst: ticks of the 100 MHz clock that a workgroup waits for the lines of a slab
 };
 enum { kAlone = 0, kFirst = 1, kSecond = 2 };
 
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
       // nothing and get zeros).
       const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(line, 0, (uint32_t)P * 128u, 0x00020000);
       const int loads = P <= 8 ? 1 : P >> 3;
-      uint64_t since = 0;  // when this slab's wait began
+      uint32_t since = 0;  // when this slab's wait began
       float m[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY}, z[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
       for (int i0 = 0; i0 < loads; i0 += 4) {  // four loads at a time: more registers are not free
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
           if (!__any(empty)) break;
           if (--polls <= 0) expired = true;
           if (p.launch == kFirst) {
-            const uint64_t now = wall_clock64();
+            const uint32_t now = (uint32_t)wall_clock64() | 1u;
             if (since == 0) since = now;
             if (__builtin_amdgcn_readfirstlane(given_up) != 0 || now - since > p.patience) expired = true;
             if (expired) __hip_atomic_store(p.status + 3, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -380,7 +380,7 @@ sp_status wide_team_score(const sp_score_args* a, hipStream_t stream) {
   const bool shared = !(a->flags & SP_SCORE_EXCLUSIVE_DEVICE);
   dev.launch = shared ? kFirst : kAlone;
   dev.spin_budget = g_spin_budget.load(std::memory_order_relaxed);
-  dev.patience = shared ? (uint64_t)wide_team_patience_us(pl, a) * 100 : 0;
+  dev.patience = shared ? (uint32_t)wide_team_patience_us(pl, a) * 100u : 0u;
   char* ws = static_cast<char*>(a->d_workspace);
   dev.lines = reinterpret_cast<uint32_t*>(ws);
   dev.copy_words = copy_bytes(pl) / 4;
