@@ -111,11 +111,11 @@ inline WideTeamPlan make_wide_team_plan(const sp_score_args* a, int wgs) {
     // fewer than teams) in parts, cut so that the team with the most of them is done soonest: its slabs (with about 200
     // keys' time for the end of each), 300 keys' time for the end of a part and its results at eight times their bytes
     // (written, read back, and they hold up the stream).  Keys are counted in whole rounds of the eight waves, which is how
-    // the constants were fitted; by the members' shares the choice is the same for all usual numbers of KV heads (1, 2, 4, 8;
-    // 26000 shapes of 3073 to 131072 keys) and another one in fewer than one of 1000 others.  Left over as whole layers, or in the largest parts that give every
-    // team one, where there are fewer: 24 layers of 32K keys 328 us against 267, 36 layers 492 against 410 (16000 keys
-    // 315 against 215), 20 layers of 4 KV heads 114 against 84, 22 layers of 8192 keys with d = 64 68 against 62; the
-    // exception among the shapes tried: 33 layers of 4000 keys 86.5 against 88.8.
+    // the constants were fitted; by the members' shares the choice is the same for all usual numbers of KV heads (1, 2, 4,
+    // 8; 26000 shapes of 3073 to 131072 keys) and another one in fewer than one of 1000 others.  Left over as whole layers,
+    // or in the largest parts that give every team one, where there are fewer: 24 layers of 32K keys 328 us against 267, 36
+    // layers 492 against 410 (16000 keys 315 against 215), 20 layers of 4 KV heads 114 against 84, 22 layers of 8192 keys
+    // with d = 64 68 against 62; the exception among the shapes tried: 33 layers of 4000 keys 86.5 against 88.8.
     d.run = a->H_kv;
     d.rounds = a->L / teams;
     d.part = a->H_kv;
