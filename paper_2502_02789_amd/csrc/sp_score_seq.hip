@@ -9,238 +9,294 @@
 //     the longest sequences first, and dealt out to one workgroup per compute unit in rounds whose
 //     direction alternates: every workgroup gets nearly the same number of keys without any shared
 //     counter, and nobody ever waits for another workgroup.
-//   * A workgroup walks over the (layer, KV head) slabs of its unit.  Inside a slab its eight waves
-//     take the sequence's 64-key tiles in turn (wave w: tiles w, w + 8, ...), stream them through
-//     the per-wave two-slot LDS ring of the tiled kernels and multiply them with the KV head's
-//     query rows on the matrix cores -- with the QUERY rows as the rows of the result, so that a
-//     lane ends up with all R <= 8 logits of one key (one v_permlane32_swap per register joins
-//     the two 32-key halves of a tile).
-//   * Those R logits per key stay in registers for the whole slab (R registers per tile), each
+//   * A workgroup walks over the (layer, KV head) slabs of its unit.  Inside a slab its eight waves take the sequence's
+//     32-key items in turn out of the ring of the wide kernels (sp_wide_core.h: loads through a buffer descriptor per
+//     item, the query rows once per workgroup and slab) and multiply them with the KV head's query rows on the matrix
+//     cores -- with the QUERY rows as the rows of the result, so that a lane ends up with all R <= 8 logits of one key
+//     (one v_permlane32_swap per register joins two items to 64 keys).
+//   * Those R logits per key stay in registers for the whole slab (R registers per pair of items), each
 //     lane keeps a running (max, sum exp2) per row, and at the end of the slab the lanes' and the
-//     eight waves' statistics are merged (shuffles, one small LDS table, ONE workgroup barrier):
+//     eight waves' statistics are merged (DPP, one small LDS table, ONE workgroup barrier):
 //     every wave then knows the rows' log-sum-exps and turns its held logits into
 //     log2-probabilities, folds the heads of a group and keeps the running maximum over KV heads
 //     and layers (or the sum over layers of the per-layer maxima) per key in registers.
-//   * The stream of tiles never stops, neither at a slab's end nor between units: the loads run two
-//     tiles ahead of the arithmetic straight into the next slab or unit, and the barrier is a bare
-//     s_barrier (no vector-memory wait in front of it).
+//   * The loop over the pairs is a loop: the pair's logits go to registers indexed by its number.  (Unrolled sixteen
+//     times, with 64-bit address arithmetic for every load, the kernel had 192 KB of code, three times what the instruction
+//     cache holds, for each slab anew; now 14.  Whole call, one query, 32 layers, 8 KV heads, d = 128, before -> now in us: one
+//     prompt of 700 keys 18.9 -> 15.4, 2048 33.1 -> 29.6, 5003 68.3 -> 62.1, 8000 106 -> 93; 12 prompts of 400 to 2400 keys,
+//     8-bit 156 -> 121, out of pages of 16 286 -> 198; 64 of 1024 to 4096 1622 -> 1600, which the HBM stream of K bounds.)
+//   * The stream of items never stops, neither at a slab's end nor between units: the loads run a ringful
+//     ahead of the arithmetic straight into the next slab or unit, and the barrier is a bare
+//     s_barrier (no vector-memory wait in front of it but for the next query rows).
 //   * Each unit writes its [N][M] partial result; units_finish_kernel merges the units of a sequence and
 //     averages over the valid queries.
 //
-// A sequence must fit the registers: 64 * 8 * SeqLimits<R>::kMaxTiles keys.  The host cannot see the
+// A sequence must fit the registers: 64 * 8 * SeqLimits<R>::kMaxPairs keys.  The host cannot see the
 // sequence lengths of a batch (they live on the device), so for B > 1 this path is taken only on the caller's
 // promise sp_score_args.max_seqlen; a sequence that breaks the promise gets NaN scores (units_finish_kernel).
 #include <mutex>
 
-#include "sp_tile_walker.h"
+#include "sp_wide_core.h"
 
 namespace sp {
 
-template <int R> struct SeqLimits { static constexpr int kMaxTiles = (R == 4) ? 16 : 8; };  // tiles per wave
+template <int R> struct SeqLimits { static constexpr int kMaxPairs = (R == 4) ? 16 : 8; };  // pairs of items per wave
 
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>): a loop whose counter is a constant in
-// every copy of the body (register arrays indexed by it must never be indexed at run time)
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
-  }
+// maximum / sum over the wave's lanes, in every lane: inside a row of sixteen by DPP (lane ^ 1, lane ^ 2, the mirrored half
+// row and row), then across rows and halves
+template <typename Op>
+__device__ __forceinline__ float wave_join(float v, Op op) {
+  v = op(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, true)));
+  v = op(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, true)));
+  v = op(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xF, 0xF, true)));
+  v = op(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x140, 0xF, 0xF, true)));
+  const auto rows = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = op(__uint_as_float(rows[0]), __uint_as_float(rows[1]));
+  const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return op(__uint_as_float(halves[0]), __uint_as_float(halves[1]));
 }
 
-template <int D, int R, int LG, bool MEAN, bool FP8>
+// The stream of the wide kernels with R query rows in LDS instead of 32, and the products turned round.
+template <int D, int R, int LG, bool FP8, bool PAGED>
+struct SeqKernel : WideKernel<D, 2, FP8, PAGED> {
+  using W = WideKernel<D, 2, FP8, PAGED>;
+  static constexpr int KS = W::KS;
+  static constexpr int QB = R * W::QROW_B;         // bytes of the query rows: 512 to 2048
+  static constexpr int QWAVES = (QB + 1023) / 1024;  // waves that fetch them
+  bf16x8 qf[KS];
+
+  __device__ __forceinline__ SeqKernel(const TiledDev& p_, unsigned char* smem) : W(p_, smem) {}
+
+  // the query rows of (l, g, b) -> query buffer `buf`: row n * 2^LG + j holds Q[l, b, n, g*G + j, :] (rows of queries
+  // beyond N and padding heads repeat query 0 / head 0: the former are never used, the latter change no maximum)
+  __device__ __forceinline__ void issue_queries(int l, int g, int b, int buf) {
+    if (this->wave >= QWAVES) return;
+    const int at = this->wave * 1024 + W::lane_id() * 16;
+    const int r = (at / W::QROW_B) & (R - 1);  // (lanes beyond the last row repeat rows)
+    const int n = (r >> LG) < this->p.N ? r >> LG : 0, j = (r & ((1 << LG) - 1)) < this->p.G ? r & ((1 << LG) - 1) : 0;
+    const int64_t row0 = (((int64_t)l * this->p.B + b) * this->p.N) * this->p.H + g * this->p.G;
+    const unsigned char* base = reinterpret_cast<const unsigned char*>(this->p.q) + row0 * W::QROW_B;
+    const uint32_t off = (uint32_t)((n * this->p.H + j) * W::QROW_B + at % W::QROW_B);
+    W::load16(base + off, this->qbuf + buf * W::QTILE_B + this->wave * 1024);
+  }
+  // the slab's query operand: lane column c holds row c mod R (rows of the result beyond R are never looked at)
+  __device__ __forceinline__ void read_queries(int buf) {
+    const int ln = W::lane_id();
+    const uint32_t row = this->qbuf + buf * W::QTILE_B + (ln & (R - 1)) * W::QROW_B, half = ln >> 5;
+#pragma unroll
+    for (int t = 0; t < KS; ++t) qf[t] = this->read16(row + (FP8 ? 4 * (t >> 1) + (t & 1) + 2 * half : 2 * t + half) * 16);
+  }
+  // The next item's logits: rows 0..3 of key `col` in registers 0..3 of the lower half-wave, rows 4..7 in the upper one.
+  __device__ __forceinline__ f32x16 item_rows() {
+    const int later = this->sent - this->pos - 1;
+    if (later == W::SLOTS - 1) wait_vmcnt<(W::SLOTS - 1) * W::LOADS>(); else W::wait_items(later);
+    f32x16 a = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    uint32_t k0 = this->krd0;
+    asm volatile("" : "+v"(k0));
+    const uint32_t kadd = (this->pos & (W::SLOTS - 1)) * W::ITEM_B;
+    if constexpr (FP8) {
+      u32x4 raw[KS / 2];
+#pragma unroll
+      for (int j = 0; j < KS / 2; ++j) raw[j] = __builtin_bit_cast(u32x4, this->read16((k0 ^ (uint32_t)((2 * j) << 4)) + kadd));
+#pragma unroll
+      for (int t = 0; t < KS; ++t) {
+        u32x4 o;
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          o[2 * x] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw[t >> 1][2 * (t & 1) + x], 1.0f, false));
+          o[2 * x + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw[t >> 1][2 * (t & 1) + x], 1.0f, true));
+        }
+        a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[t], __builtin_bit_cast(bf16x8, o), a, 0, 0, 0);
+      }
+    } else {
+      bf16x8 kf[KS];
+#pragma unroll
+      for (int t = 0; t < KS; ++t) kf[t] = this->read16((k0 ^ (uint32_t)(t << 5)) + kadd);
+#pragma unroll
+      for (int t = 0; t < KS; ++t) a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[t], kf[t], a, 0, 0, 0);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot's reads are done: it may be overwritten
+    ++this->pos;
+    this->refill();
+    return a;
+  }
+};
+
+template <int D, int R, int LG, bool MEAN, bool FP8, bool PAGED>
 __global__ __launch_bounds__(kTiledThreads) void seq_score_kernel(const TiledDev p) {
   extern __shared__ __align__(1024) unsigned char smem[];
-  using TW = TileWalker<D, false, FP8>;
-  constexpr int MAXT = SeqLimits<R>::kMaxTiles;
+  using W = SeqKernel<D, R, LG, FP8, PAGED>;
+  constexpr int MAXP = SeqLimits<R>::kMaxPairs;
   constexpr int GP = 1 << LG;   // heads of a KV group, padded to a power of two
   constexpr int NQ = R >> LG;   // queries whose rows fit the R held rows
-  TW w(p, smem, typename TW::WholeSequence{}, 0);
+  typedef float vpair __attribute__((ext_vector_type(MAXP)));
+  W w(p, smem);
   SeqUnit cur;
   if (!seq_next_unit(p, 0, &cur)) return;
-  auto tiles_of = [&](int M) __attribute__((always_inline)) {  // this wave's 64-key tiles
-    return __builtin_amdgcn_readfirstlane(((M + kWaveKeys - 1) / kWaveKeys - w.wave + kTiledWaves - 1) / kTiledWaves);
-  };
-  const uint32_t xchg = (uint32_t)reinterpret_cast<uintptr_t>(smem) + kTiledWaves * 2 * TW::TILE_B;  // [2][waves][R] (max, sum)
 
-  // The stream of tiles runs two items ahead of the arithmetic and straight on into the workgroup's
-  // next unit: `ah` is the unit, slab and item that is requested next.
-  SeqUnit ahu = cur;
-  int ah_nt = tiles_of(cur.M);
-  bool ah_live = true;  // false: past the last unit (the last slab is requested again, nobody consumes it)
-  int ah_s = cur.s0, ah_ph = -1;  // the slab; ph < 0: its query tile, else 32-key half-tile ph of this wave
-  auto issue_next = [&](int slot) __attribute__((always_inline)) {
-    w.b = ahu.b;
-    w.seq0 = ahu.seq0;
-    const int ah_l = ah_s / p.H_kv, ah_g = ah_s - ah_l * p.H_kv;
-    if (ah_ph < 0) {
-      w.template issue_queries<false>(ah_l, ah_g, slot, 0);
-    } else {
-      const int key_first = ((w.wave + (ah_ph >> 1) * kTiledWaves) * 2 + (ah_ph & 1)) * 32;
-      const int rows = min(32, ahu.M - key_first);
-      w.issue_key_rows(ah_l, ah_g, rows > 0 ? key_first : 0, rows, slot);
-    }
-    if (++ah_ph == 2 * ah_nt) {
-      ah_ph = -1;
-      if (++ah_s == ahu.s1) {
-        if (ah_live && seq_next_unit(p, ahu.k + 1, &ahu)) {
-          ah_s = ahu.s0;
-          ah_nt = tiles_of(ahu.M);
-        } else {
-          ah_live = false;
-          ah_s = ahu.s1 - 1;
-        }
-      }
-    }
-  };
-  issue_next(0);
-  issue_next(1);
-  int pos = 0;    // items consumed so far; item number x sits in ring slot x & 1
-  int slabs = 0;  // slabs finished so far (the exchange table has two halves used in turn)
+  int l = __builtin_amdgcn_readfirstlane(cur.s0 / p.H_kv), g = cur.s0 - l * p.H_kv;
+  w.ah = {w.slab_keys(l, g, cur.seq0), cur.b, 0, cur.M, w.items_of(cur.M)};
+  w.issue_queries(l, g, cur.b, 0);
+  w.start_stream();
 
-  float held[MAXT][R];
-  float smax[MAXT][NQ], tot[MEAN ? MAXT : 1][NQ];
+  int slabs = 0;  // slabs finished so far (the query and exchange buffers have two halves used in turn)
+  bool more = true;
+  SeqUnit nxt = cur;  // the unit of the slab behind the one at hand
+  vpair held[R];  // row r of the lane's key of pair t, not yet scaled
+  float smax[MAXP][NQ], tot[MEAN ? MAXP : 1][NQ];
 
 #pragma unroll 1
   for (;;) {
-  const int nt = tiles_of(cur.M), M = cur.M, b = cur.b;
+    const int M = cur.M, b = cur.b, nt = w.items_of(M);
 #pragma unroll
-  for (int t = 0; t < MAXT; ++t)
+    for (int t = 0; t < MAXP; ++t)
 #pragma unroll
-    for (int n = 0; n < NQ; ++n) {
-      smax[t][n] = -INFINITY;
-      if (MEAN) tot[MEAN ? t : 0][n] = 0.f;
-    }
+      for (int n = 0; n < NQ; ++n) {
+        smax[t][n] = -INFINITY;
+        if constexpr (MEAN) tot[t][n] = 0.f;
+      }
 #pragma unroll 1
-  for (int s = cur.s0; s < cur.s1; ++s) {
-    const int l = s / p.H_kv, g = s - l * p.H_kv;
-    {
-      const int slot = pos & 1;
-      w.wait_tile(slot);
-      w.read_queries(slot);
-      w.slot_free();
-      issue_next(slot);
-      ++pos;
-    }
-    w.slab_scale(l, g);
-    float rm[R], rs[R];  // this lane's running max and sum of exp2 per row, base-2 logits
+    for (int s = cur.s0; s < cur.s1; ++s) {
+      const int buf = slabs & 1;
+      // the next slab: its query rows go into the buffer the previous slab has just left (the barrier at its end);
+      // requests move on to it when this slab's items have all been sent
+      int nl = l, ng = g + 1;
+      if (ng == p.H_kv) { ng = 0; ++nl; }
+      if (s + 1 == cur.s1) {
+        more = seq_next_unit(p, cur.k + 1, &nxt);
+        nl = __builtin_amdgcn_readfirstlane(nxt.s0 / p.H_kv);
+        ng = nxt.s0 - nl * p.H_kv;
+      }
+      w.nx.left = 0;
+      if (more) {
+        w.nx = {w.slab_keys(nl, ng, nxt.seq0), nxt.b, 0, nxt.M, w.items_of(nxt.M)};
+        w.issue_queries(nl, ng, nxt.b, buf ^ 1);
+      }
+      w.read_queries(buf);
+      w.begin_slab();
+      w.slab_scale(l, g);
+      float rm[R], rs[R];  // this lane's running max and sum of exp2 per row, base-2 logits
 #pragma unroll
-    for (int r = 0; r < R; ++r) { rm[r] = -INFINITY; rs[r] = 0.f; }
+      for (int r = 0; r < R; ++r) { rm[r] = -INFINITY; rs[r] = 0.f; }
 
-    static_for<0, MAXT>([&](auto tc) __attribute__((always_inline)) {
-      constexpr int t = decltype(tc)::value;
-      if (t < nt) {
+      // Items come from the last to the first, so the ragged end of the keys is in some wave's first item; of an odd number
+      // the last pair has only one (the upper half-wave then has no keys).
+#pragma unroll 1
+      for (int t = 0; 2 * t < nt; ++t) {
+        f32x16 a = w.item_rows(), c;
+        if (t == 0) {
+          const int left = M - (w.wave + (nt - 1) * kTiledWaves) * 32 - (W::lane_id() & 31);  // > 0: the lane's key exists
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-          const int slot = pos & 1;
-          w.wait_tile(slot);
-          w.template mfma_tile<true>(kb, slot);
-          w.slot_free();
-          issue_next(slot);
-          ++pos;
+          for (int i = 0; i < 4; ++i) a[i] = left > 0 ? a[i] : -INFINITY;
         }
-        // rows 0..3 of a key sit in registers 0..3 of the lower half-wave (rows 4..7 in the upper one); joining
-        // the two 32-key halves gives lane x the rows of key x of the 64-key tile
-        int left = M - (w.wave + t * kTiledWaves) * kWaveKeys - w.lane;  // > 0: the lane's key exists
-        asm volatile("" : "+v"(left));
+        if (2 * t + 1 < nt) {
+          c = w.item_rows();
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) c[i] = -INFINITY;
+        }
+        float x[R];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(w.acc[0][i]), __float_as_uint(w.acc[1][i]), false, false);
-          held[t][i] = left > 0 ? __uint_as_float(sw[0]) * w.c2 : -INFINITY;
-          if (R == 8) held[t][4 + i] = left > 0 ? __uint_as_float(sw[1]) * w.c2 : -INFINITY;
+          const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(a[i]), __float_as_uint(c[i]), false, false);
+          x[i] = __uint_as_float(sw[0]);
+          if (R == 8) x[4 + i] = __uint_as_float(sw[1]);
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          const float m_new = fmaxf(rm[r], held[t][r]);
-          const float ref = (m_new == -INFINITY) ? 0.f : m_new;
-          rs[r] = rs[r] * fast_exp2(rm[r] - ref) + fast_exp2(held[t][r] - ref);
+          const float m_new = fmaxf(rm[r], x[r] * w.c2);
+          const float off = (m_new == -INFINITY) ? 0.f : -m_new;
+          rs[r] = rs[r] * fast_exp2(rm[r] + off) + fast_exp2(fmaf(x[r], w.c2, off));
           rm[r] = m_new;
+          held[r][t] = x[r];
         }
       }
-    });
 
-    // the rows' statistics over the wave's keys, then over the workgroup's
-    const int par = slabs & 1;
-    ++slabs;
+      // the rows' statistics over the wave's keys, then over the workgroup's
+      ++slabs;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const float mw = wave_max(rm[r]);
-      const float ref = (mw == -INFINITY) ? 0.f : mw;
-      const float sw = wave_sum(rs[r] * fast_exp2(rm[r] - ref));
-      int ln = w.lane;
-      asm volatile("" : "+v"(ln));
-      if (ln == 0)
-        lds_poke64<0>(xchg + ((par * kTiledWaves + w.wave) * R + r) * 8, ((uint64_t)__float_as_uint(sw) << 32) | __float_as_uint(mw));
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    float lse2[R];
-    {
-      int ln = w.lane;
-      asm volatile("" : "+v"(ln));
-      const uint64_t v = lds_peek64(xchg + (par * kTiledWaves * R + (ln & (kTiledWaves * R - 1))) * 8);  // entry wave * R + row
-      float m = __uint_as_float((uint32_t)v), z = __uint_as_float((uint32_t)(v >> 32));
-#pragma unroll
-      for (int off = R; off < kTiledWaves * R; off <<= 1) {
-        const float pm = __shfl_xor(m, off, kWave), pz = __shfl_xor(z, off, kWave);
-        const float mn = fmaxf(m, pm);
-        const float ref = (mn == -INFINITY) ? 0.f : mn;
-        z = z * fast_exp2(m - ref) + pz * fast_exp2(pm - ref);
-        m = mn;
+      for (int r = 0; r < R; ++r) {
+        const float mw = wave_join(rm[r], [](float x, float y) { return fmaxf(x, y); });
+        const float ref = (mw == -INFINITY) ? 0.f : mw;
+        const float sw = wave_join(rs[r] * fast_exp2(rm[r] - ref), [](float x, float y) { return x + y; });
+        if (W::lane_id() == 0)
+          lds_poke64<0>(w.xchg + ((buf * kTiledWaves + w.wave) * R + r) * 8, ((uint64_t)__float_as_uint(sw) << 32) | __float_as_uint(mw));
       }
-      const float lse = m + __builtin_amdgcn_logf(z);  // base 2; lanes x and x + R, x + 2R, ... all hold row x & (R - 1)
+      w.slab_barrier();
+      float lse2[R];
+      {
+        const int ln = W::lane_id();  // every lane folds the eight waves' pairs of row ln mod R
+        const uint32_t at = w.xchg + (buf * kTiledWaves * R + (ln & (R - 1))) * 8;
+        const u64x4 lo = lds_peek64x4<R * 8>(at), hi = lds_peek64x4<R * 8>(at + 4 * R * 8);
+        float m = -INFINITY, z = 0.f;
 #pragma unroll
-      for (int r = 0; r < R; ++r) lse2[r] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(lse), r));
-      if (p.lse_out && w.wave == 0) {
-        const int n = ln >> LG, j = ln & (GP - 1);
-        if (ln < R && n < p.N && j < p.G)  // (never empty: lane 0 is always inside)
-          p.lse_out[(((int64_t)l * p.B + b) * p.N + n) * p.H + g * p.G + j] = lse * 0.6931471805599453f;
-        w.note_issued(1);
+        for (int i = 0; i < 4; ++i) m = fmaxf(m, fmaxf(__uint_as_float((uint32_t)lo.v[i]), __uint_as_float((uint32_t)hi.v[i])));
+        const float ref = (m == -INFINITY) ? 0.f : m;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          z += __uint_as_float((uint32_t)(lo.v[i] >> 32)) * fast_exp2(__uint_as_float((uint32_t)lo.v[i]) - ref);
+          z += __uint_as_float((uint32_t)(hi.v[i] >> 32)) * fast_exp2(__uint_as_float((uint32_t)hi.v[i]) - ref);
+        }
+        const float lse = m + __builtin_amdgcn_logf(z);  // base 2
+#pragma unroll
+        for (int r = 0; r < R; ++r) lse2[r] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(lse), r));
+        if (p.lse_out && w.wave == 0) {
+          const int n = ln >> LG, j = ln & (GP - 1);
+          if (ln < R && n < p.N && j < p.G)
+            p.lse_out[(((int64_t)l * p.B + b) * p.N + n) * p.H + g * p.G + j] = lse * 0.6931471805599453f;
+        }
       }
+
+      // log2-probabilities; max over the heads of a group, over KV heads and layers
+      wide_static_for<0, MAXP>([&](auto tc) __attribute__((always_inline)) {
+        constexpr int t = decltype(tc)::value;
+        if (2 * t < nt) {
+#pragma unroll
+          for (int n = 0; n < NQ; ++n) {
+            float v = fmaf(held[n * GP][t], w.c2, -lse2[n * GP]);
+#pragma unroll
+            for (int j = 1; j < GP; ++j) v = fmaxf(v, fmaf(held[n * GP + j][t], w.c2, -lse2[n * GP + j]));
+            smax[t][n] = fmaxf(smax[t][n], v);
+          }
+        }
+      });
+      if constexpr (MEAN) {
+        if (g == p.H_kv - 1) {  // the layer is complete: its max probability joins the sum
+#pragma unroll
+          for (int t = 0; t < MAXP; ++t)
+#pragma unroll
+            for (int n = 0; n < NQ; ++n) {
+              tot[t][n] += fast_exp2(smax[t][n]);
+              smax[t][n] = -INFINITY;
+            }
+        }
+      }
+      w.end_slab();
+      l = nl;
+      g = ng;
     }
 
-    // log2-probabilities; max over the heads of a group, over KV heads and layers
-    static_for<0, MAXT>([&](auto tc) __attribute__((always_inline)) {
+    // the unit's result (stores only make the next items' waits stricter than they need be)
+    const int ln = W::lane_id(), in_tile = ln & 31, half = ln >> 5;
+    wide_static_for<0, MAXP>([&](auto tc) __attribute__((always_inline)) {
       constexpr int t = decltype(tc)::value;
-      if (t < nt) {
+      if (2 * t < nt) {
+        const int key = (w.wave + (nt - 1 - 2 * t - half) * kTiledWaves) * 32 + in_tile;
+        if (2 * t + half < nt && key < M) {
 #pragma unroll
-        for (int n = 0; n < NQ; ++n) {
-          float v = held[t][n * GP] - lse2[n * GP];
-#pragma unroll
-          for (int j = 1; j < GP; ++j) v = fmaxf(v, held[t][n * GP + j] - lse2[n * GP + j]);
-          smax[t][n] = fmaxf(smax[t][n], v);
+          for (int n = 0; n < NQ; ++n)
+            if (n < p.N) {
+              float v = smax[t][n];
+              if constexpr (MEAN) v = tot[t][n];
+              p.group_scores[((int64_t)cur.grp * p.N + n) * p.T + cur.seq0 + key] = v;
+            }
         }
       }
     });
-    if (MEAN && g == p.H_kv - 1) {  // the layer is complete: its max probability joins the sum
-#pragma unroll
-      for (int t = 0; t < MAXT; ++t)
-#pragma unroll
-        for (int n = 0; n < NQ; ++n) {
-          tot[MEAN ? t : 0][n] += fast_exp2(smax[t][n]);
-          smax[t][n] = -INFINITY;
-        }
-    }
+    if (!more) break;
+    cur = nxt;
   }
-
-  // the unit's result.  (These stores are left out of the count of vector-memory instructions in
-  // flight -- a store whose lanes are all beyond the sequence may not be issued at all --, which only
-  // makes the next tile waits stricter than they need be.)
-  static_for<0, MAXT>([&](auto tc) __attribute__((always_inline)) {
-    constexpr int t = decltype(tc)::value;
-    if (t < nt) {
-      const int key = (w.wave + t * kTiledWaves) * kWaveKeys + w.lane;
-      if (key < M) {
-#pragma unroll
-        for (int n = 0; n < NQ; ++n)
-          if (n < p.N)
-            p.group_scores[((int64_t)cur.grp * p.N + n) * p.T + cur.seq0 + key] = MEAN ? tot[MEAN ? t : 0][n] : smax[t][n];
-      }
-    }
-  });
-  if (!seq_next_unit(p, cur.k + 1, &cur)) break;
-  }
-  wait_vmcnt<0>();  // loads issued past the end land before the wave (and its LDS) goes away
+  wait_vmcnt<0>();
 }
 
 // order[r] = the sequence with the r-th most keys (equal lengths: lower index first); one workgroup,
@@ -380,7 +436,7 @@ static int seq_rows(const sp_score_args* a) {  // held rows per key: 4 or 8 (0: 
 }
 int seq_max_keys(const sp_score_args* a) {
   const int R = seq_rows(a);
-  return R == 0 ? 0 : kWaveKeys * kTiledWaves * (R == 4 ? SeqLimits<4>::kMaxTiles : SeqLimits<8>::kMaxTiles);
+  return R == 0 ? 0 : kWaveKeys * kTiledWaves * (R == 4 ? SeqLimits<4>::kMaxPairs : SeqLimits<8>::kMaxPairs);
 }
 
 // The cut along the (layer, KV head) slabs into units.  With the maximum over layers a
@@ -424,6 +480,7 @@ bool seq_supported(const sp_score_args* a) {
   if (a->k_dtype == SP_K_FP8_E4M3 && a->d_block_table && a->page_size < (a->d == 64 ? 16 : 8)) return false;
   const int R = seq_rows(a);
   if (R == 0 || seq_stated_max(a) > seq_max_keys(a)) return false;
+  if (a->k_token_stride > (INT32_MAX / 256)) return false;  // (a ring slot's keys must span less than 2 GiB)
   if (a->B > 8192) return false;                            // (the sequences are ranked by counting: quadratic in B)
   // too few units to fill the device?
   if ((int64_t)a->B * a->L * a->H_kv < 256) return false;
@@ -457,10 +514,10 @@ int seq_cu_count() {  // compute units of the current device
   return cached[slot];
 }
 
-template <int D, int R, int LG, bool MEAN, bool FP8>
+template <int D, int R, int LG, bool MEAN, bool FP8, bool PAGED>
 static sp_status launch_seq(const TiledDev& dev, hipStream_t stream) {
-  auto kernel = seq_score_kernel<D, R, LG, MEAN, FP8>;
-  const size_t smem = TileWalker<D, false, FP8>::smem_bytes();
+  auto kernel = seq_score_kernel<D, R, LG, MEAN, FP8, PAGED>;
+  const size_t smem = SeqKernel<D, R, LG, FP8, PAGED>::kSmem;
   static std::mutex mu;  // once per kernel and device
   static bool prepared[kMaxDevices] = {};
   {
@@ -479,10 +536,14 @@ static sp_status launch_seq(const TiledDev& dev, hipStream_t stream) {
   return launch_status();
 }
 
+template <int D, int R, int LG, bool MEAN, bool FP8>
+static sp_status seq_by_pages(const TiledDev& dev, hipStream_t stream) {
+  return dev.block_table ? launch_seq<D, R, LG, MEAN, FP8, true>(dev, stream) : launch_seq<D, R, LG, MEAN, FP8, false>(dev, stream);
+}
 template <int D, bool MEAN, bool FP8>
 static sp_status seq_by_rows(const TiledDev& dev, int R, hipStream_t stream) {
-  if (dev.lgG == 2) return R == 4 ? launch_seq<D, 4, 2, MEAN, FP8>(dev, stream) : launch_seq<D, 8, 2, MEAN, FP8>(dev, stream);
-  return launch_seq<D, 8, 3, MEAN, FP8>(dev, stream);
+  if (dev.lgG == 2) return R == 4 ? seq_by_pages<D, 4, 2, MEAN, FP8>(dev, stream) : seq_by_pages<D, 8, 2, MEAN, FP8>(dev, stream);
+  return seq_by_pages<D, 8, 3, MEAN, FP8>(dev, stream);
 }
 template <int D, bool FP8>
 static sp_status seq_by_mode(const TiledDev& dev, int R, bool mean, hipStream_t stream) {

@@ -101,23 +101,13 @@ struct TileWalker {
   float run_m, run_s;
   float4 cs[ROPE ? KS / 2 : 1][4];  // ROPE: the (cos, sin) pairs of the key tile that is rotated next
 
-  // a wave that owns 64-key tile `tile` (numbered over the whole batch) ...
+  // a wave that owns 64-key tile `tile` (numbered over the whole batch)
   __device__ __forceinline__ TileWalker(const TiledDev& p_, unsigned char* smem, int tile) : p(p_) {
     b = upper_segment(p.tile_cu, p.B, tile);
     seq0 = p.cu[b];
     key0 = (tile - p.tile_cu[b]) * kWaveKeys;
     rows_in = min(kWaveKeys, p.cu[b + 1] - seq0 - key0);
     tok0 = (int64_t)seq0 + key0;
-    set_up(smem);
-  }
-  // ... or a wave that walks over several tiles of sequence b_ (the caller names the keys of every load)
-  struct WholeSequence {};
-  __device__ __forceinline__ TileWalker(const TiledDev& p_, unsigned char* smem, WholeSequence, int b_) : p(p_) {
-    b = b_;
-    seq0 = p.cu[b];
-    key0 = 0;
-    rows_in = 0;
-    tok0 = seq0;
     set_up(smem);
   }
   __device__ __forceinline__ void set_up(unsigned char* smem) {
@@ -356,10 +346,7 @@ struct TileWalker {
       }
     }
   }
-  // QROWS = false: register i of acc[kb] holds key (i / 4) * 8 + (i % 4) (+ 4 for the upper half-wave) of the
-  // tile for query row `col`; QROWS = true: the operands change places, so that it holds that QUERY ROW for
-  // key `col` of the tile (a lane then has all of a key's first rows, see sp_score_seq.hip)
-  template <bool QROWS = false>
+  // Register i of acc[kb] holds key (i / 4) * 8 + (i % 4) (+ 4 for the upper half-wave) of the tile for query row `col`.
   __device__ __forceinline__ void mfma_tile(int kb, int slot) {
     f32x16 a = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     bf16x8 kf[KS];
@@ -367,8 +354,7 @@ struct TileWalker {
       read_keys_fp8(kf, slot);
 #pragma unroll
       for (int t = 0; t < KS; ++t)
-        a = QROWS ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[t], kf[t], a, 0, 0, 0)
-                  : __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t], qf[t], a, 0, 0, 0);
+        a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t], qf[t], a, 0, 0, 0);
       acc[kb] = a;
       return;
     }
@@ -378,14 +364,12 @@ struct TileWalker {
       rotate_keys(kf);
       issue_rope(kb ^ 1);
 #pragma unroll
-      for (int t = 0; t < KS; ++t) a = QROWS ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[t], kf[t], a, 0, 0, 0)
-                : __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t], qf[t], a, 0, 0, 0);
+      for (int t = 0; t < KS; ++t) a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t], qf[t], a, 0, 0, 0);
       acc[kb] = a;
       return;
     }
 #pragma unroll
-    for (int t = 0; t < KS; ++t) a = QROWS ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[t], kf[t], a, 0, 0, 0)
-                : __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t], qf[t], a, 0, 0, 0);
+    for (int t = 0; t < KS; ++t) a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t], qf[t], a, 0, 0, 0);
     constexpr int kAhead = KS < 4 ? KS : 4;
     __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
 #pragma unroll
@@ -511,10 +495,11 @@ __device__ __forceinline__ bool seq_next_unit(const TiledDev& p, int k, SeqUnit*
   for (;; ++k) {
     const int idx = k * W + ((k & 1) ? W - 1 - (int)blockIdx.x : (int)blockIdx.x);
     if (idx >= n_units) return false;
-    const int grp = idx % p.n_groups;
-    const int b = p.seq_order ? scalar_table(p.seq_order)[idx / p.n_groups] : idx / p.n_groups;  // (no table: batch order)
-    const int seq0 = scalar_table(p.cu)[b];
-    const int M = scalar_table(p.cu)[b + 1] - seq0;
+    // (the same for the whole workgroup, said so that it stays in scalar registers)
+    const int row = __builtin_amdgcn_readfirstlane(idx / p.n_groups), grp = idx - row * p.n_groups;
+    const int b = p.seq_order ? __builtin_amdgcn_readfirstlane(scalar_table(p.seq_order)[row]) : row;  // (no table: batch order)
+    const int seq0 = __builtin_amdgcn_readfirstlane(scalar_table(p.cu)[b]);
+    const int M = __builtin_amdgcn_readfirstlane(scalar_table(p.cu)[b + 1]) - seq0;
     const int s0 = grp * p.slabs_per_group;
     const int s1 = min(p.L * p.H_kv, s0 + p.slabs_per_group);
     // (no keys, or more than the kernel holds: nothing to do here, see seq_order_kernel and units_finish_kernel)

@@ -108,6 +108,11 @@ struct WideKernel {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, lds_ptr(dst), 16, lane_off, 0, 0, kKeyLoadPolicy);
   }
 
+  // 16 bytes per lane from where the lane says; `dst`: of the wave's first lane
+  __device__ __forceinline__ static void load16(const unsigned char* from, uint32_t dst) {
+    __builtin_amdgcn_global_load_lds(from, lds_ptr(dst), 16, 0, 0);
+  }
+
   // where the keys of (l, g) start: those of token seq0 (contiguous cache) or of the pool's first page
   __device__ __forceinline__ const unsigned char* slab_keys(int l, int g, int seq0) const {
     return reinterpret_cast<const unsigned char*>(p.k[l]) + ESZ * ((int64_t)g * p.hs + (PAGED ? 0 : (int64_t)seq0 * p.ts));
@@ -203,7 +208,7 @@ struct WideKernel {
       const int64_t row0 = (((int64_t)l * p.B + b) * p.N) * p.H + g * p.G;
       const unsigned char* base = reinterpret_cast<const unsigned char*>(p.q) + row0 * QROW_B;
       const uint32_t off = (uint32_t)((n * p.H + j) * QROW_B + unit * 16);
-      __builtin_amdgcn_global_load_lds(base + off, lds_ptr(qbuf + buf * QTILE_B + wave * 1024), 16, 0, 0);
+      load16(base + off, qbuf + buf * QTILE_B + wave * 1024);
     }
   }
 

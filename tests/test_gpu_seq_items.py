@@ -1,0 +1,34 @@
+"""The single-pass kernel for few query rows at the edges of its 32-key items and of the pairs they are held in: a wave with
+one item more than another, an odd number of items, a ragged first one, waves without keys; four and eight rows, both head
+dims, contiguous and paged (Sec. 3.2 equation of arXiv 2502.02789, fp64 oracle)."""
+import math
+
+import numpy as np
+import pytest
+
+from oracle import specprefill_oracle as orc
+from paper_2502_02789_amd import synth
+from tests import helpers as hp
+
+pytestmark = pytest.mark.gpu
+
+# items of 32 keys, dealt to eight waves: 1, 7, 8, 9, 15, 16, 17, 23, 24, 25, 32, 33 and one key more or fewer
+LENS = tuple(32 * i + e for i in (1, 7, 8, 9, 15, 16, 17, 23, 24, 25, 32, 33) for e in (-1, 0, 1)) + (1, 0, 5, 2047)
+
+
+@pytest.mark.parametrize("paged", [0, 16])
+@pytest.mark.parametrize("shape", [dict(H=4, H_kv=1, N=1, d=128), dict(H=4, H_kv=1, N=2, d=64), dict(H=8, H_kv=1, N=1, d=128),
+                                   dict(H=3, H_kv=1, N=1, d=64)])
+def test_items_and_pairs(shape, paged):
+    w = synth.scaled(synth.workload(4), seqlens=LENS, L=8, salient_frac=0.02, salient_run=1, **shape)
+    inp = synth.make_qk(w)
+    scale = 1.0 / math.sqrt(w.d)
+    for mode in (orc.LAYER_MAX, orc.LAYER_MEAN):
+        want, want_lse = orc.token_importance(inp["q"], inp["k"], inp["cu_seqlens"], scale, mode)
+        if paged:
+            pools, table = hp.paged_copy(inp["k"], inp["cu_seqlens"], paged, seed=3)
+            got, lse = hp.gpu_score_paged(inp["q"], pools, table, inp["cu_seqlens"], w.H_kv, scale, mode, max_seqlen=2047)
+        else:
+            got, lse = hp.gpu_score(inp["q"], inp["k"], inp["cu_seqlens"], w.H_kv, scale, mode, max_seqlen=2047)
+        hp.assert_scores_close(got, want, f"{shape} mode={mode} paged={paged}")
+        np.testing.assert_allclose(lse, want_lse, rtol=0, atol=2e-4)
