@@ -132,7 +132,7 @@ __global__ __launch_bounds__(kTiledThreads) void seq_score_kernel(const TiledDev
   typedef float vpair __attribute__((ext_vector_type(MAXP)));
   W w(p, smem);
   SeqUnit cur;
-  if (!seq_next_unit(p, 0, &cur)) return;
+  if (!seq_first_unit(p, &cur)) return;
 
   int l = __builtin_amdgcn_readfirstlane(cur.s0 / p.H_kv), g = cur.s0 - l * p.H_kv;
   w.ah = {w.slab_keys(l, g, cur.seq0), cur.b, 0, cur.M, w.items_of(cur.M)};
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kTiledThreads) void seq_score_kernel(const TiledDev
       int nl = l, ng = g + 1;
       if (ng == p.H_kv) { ng = 0; ++nl; }
       if (s + 1 == cur.s1) {
-        more = seq_next_unit(p, cur.k + 1, &nxt);
+        more = seq_next_unit(p, &nxt);
         nl = __builtin_amdgcn_readfirstlane(nxt.s0 / p.H_kv);
         ng = nxt.s0 - nl * p.H_kv;
       }
@@ -293,6 +293,7 @@ __global__ __launch_bounds__(kTiledThreads) void seq_score_kernel(const TiledDev
         }
       }
     });
+    note_group_count(p, cur);
     if (!more) break;
     cur = nxt;
   }
@@ -302,7 +303,7 @@ __global__ __launch_bounds__(kTiledThreads) void seq_score_kernel(const TiledDev
 // order[r] = the sequence with the r-th most keys (equal lengths: lower index first); one workgroup,
 // every thread ranks its sequences by counting those ahead of them
 // (and the log-sum-exp rows of the sequences the scoring kernel leaves out: 0 by convention where there are no
-// keys, NaN where there are more than `limit`)
+// keys, NaN where there are more than `limit`; order = null: only these)
 __global__ __launch_bounds__(1024) void seq_order_kernel(int B, const int32_t* __restrict__ cu, int32_t* __restrict__ order,
                                                          float* __restrict__ lse_out, int limit, int L, int rows) {
   constexpr int kChunk = 4096;
@@ -311,14 +312,14 @@ __global__ __launch_bounds__(1024) void seq_order_kernel(int B, const int32_t* _
     const int b = b0 + threadIdx.x;
     const int mine = b < B ? cu[b + 1] - cu[b] : 0;
     int rank = 0;
-    for (int c0 = 0; c0 < B; c0 += kChunk) {
+    for (int c0 = 0; order && c0 < B; c0 += kChunk) {
       const int n = min(kChunk, B - c0);
       __syncthreads();
       for (int i = threadIdx.x; i < n; i += 1024) len[i] = cu[c0 + i + 1] - cu[c0 + i];
       __syncthreads();
       for (int i = 0; i < n; ++i) rank += (len[i] > mine || (len[i] == mine && c0 + i < b)) ? 1 : 0;
     }
-    if (b < B) order[rank] = b;
+    if (order && b < B) order[rank] = b;
     if (b < B && lse_out && (mine <= 0 || mine > limit))
       for (int i = 0; i < L * rows; ++i)
         lse_out[((int64_t)(i / rows) * B + b) * rows + i % rows] = mine <= 0 ? 0.f : __uint_as_float(0x7FC00000u);
@@ -340,6 +341,11 @@ __global__ __launch_bounds__(64 * WAVES) void units_finish_kernel(const TiledDev
   const int64_t tok = (int64_t)blockIdx.x * TOK + k;
   const bool inside = tok < p.T;
   const bool mean = p.layer_reduce != SP_LAYER_MAX;
+  int n_groups = p.n_groups;
+  if (inside && p.group_count) {  // (none for a sequence that was left out)
+    const int b = upper_segment(p.cu, p.B, (int)tok);
+    n_groups = p.cu[b + 1] - p.cu[b] > p.seq_limit ? 0 : p.group_count[b];
+  }
   float v[NQ];
 #pragma unroll
   for (int n = 0; n < NQ; ++n) v[n] = mean ? 0.f : -INFINITY;
@@ -359,7 +365,7 @@ __global__ __launch_bounds__(64 * WAVES) void units_finish_kernel(const TiledDev
     }
   } else if (inside) {
 #pragma unroll 4
-    for (int g = part; g < p.n_groups; g += kParts)
+    for (int g = part; g < n_groups; g += kParts)
 #pragma unroll
       for (int n = 0; n < NQ; ++n)
         if (n < p.N) {
@@ -415,9 +421,13 @@ sp_status launch_units_finish(const TiledDev& dev, hipStream_t stream) {
        : dev.N <= 4 ? finish_by_tokens<4>(dev, stream) : dev.N <= 8 ? finish_by_tokens<8>(dev, stream) : finish_by_tokens<16>(dev, stream);
 }
 
-void launch_seq_order(const sp_score_args* a, int32_t* order, int limit, hipStream_t stream) {
-  hipLaunchKernelGGL(seq_order_kernel, dim3(1), dim3(1024), 0, stream, a->B, a->d_cu_seqlens, order, a->d_lse, limit,
-                     a->L, a->N * a->H);
+void prepare_units(const sp_score_args* a, TiledDev* dev, int32_t* words, int limit, hipStream_t stream) {
+  const bool rounds = dev->deal.stretch == 0;
+  dev->group_count = rounds ? nullptr : words;
+  dev->seq_order = rounds && a->B > 1 ? words : nullptr;
+  if (a->B > 1 && (rounds || a->d_lse))  // (one sequence: nothing to order, and the host has seen that its length fits)
+    hipLaunchKernelGGL(seq_order_kernel, dim3(1), dim3(1024), 0, stream, a->B, a->d_cu_seqlens, rounds ? words : nullptr, a->d_lse,
+                       limit, a->L, a->N * a->H);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -442,8 +452,13 @@ int seq_max_keys(const sp_score_args* a) {
 // The cut along the (layer, KV head) slabs into units.  With the maximum over layers a
 // group may be any run of slabs (a maximum can be completed in any order); with the mean over layers a group
 // holds whole layers (a layer's maximum over heads must be complete before it joins the sum).
+static UnitDeal seq_deal(const sp_score_args* a, int* n_groups) {
+  return make_unit_deal(a, seq_cu_count(), seq_max_keys(a), a->layer_reduce == SP_LAYER_MEAN, n_groups);
+}
 void seq_grouping(const sp_score_args* a, int* slabs_per_group, int* n_groups, int* groups_per_layer) {
   *groups_per_layer = 0;
+  *slabs_per_group = 1;
+  if (seq_deal(a, n_groups).stretch != 0) return;
   if (a->layer_reduce == SP_LAYER_MEAN && (int64_t)a->B * a->L < 256) {
     // too few whole layers to fill the device: units of a part of a layer's KV heads (the scoring kernel then
     // hands on maxima, as for the maximum over layers, and the merge adds the layers up)
@@ -495,7 +510,7 @@ static size_t seq_scores_bytes(const sp_score_args* a) {
 
 size_t seq_workspace_bytes(const sp_score_args* a) {
   if (!seq_supported(a)) return 0;
-  return seq_scores_bytes(a) + align_up(sizeof(int32_t) * (size_t)a->B, 256);  // partial results, then the sequence order
+  return seq_scores_bytes(a) + align_up(sizeof(int32_t) * (size_t)a->B, 256);  // partial results, then the sequence order or group counts
 }
 
 int seq_cu_count() {  // compute units of the current device
@@ -531,7 +546,7 @@ static sp_status launch_seq(const TiledDev& dev, hipStream_t stream) {
     }
   }
   // one workgroup per compute unit walks over its share of the (sequence, layer group) units
-  const int wgs = std::min(dev.B * dev.n_groups, seq_cu_count());
+  const int wgs = dev.deal.stretch != 0 ? seq_cu_count() : std::min(dev.B * dev.n_groups, seq_cu_count());
   hipLaunchKernelGGL(kernel, dim3(wgs), dim3(kTiledThreads), smem, stream, dev);
   return launch_status();
 }
@@ -554,12 +569,9 @@ static sp_status seq_by_mode(const TiledDev& dev, int R, bool mean, hipStream_t 
 // seq_limit set for this path
 sp_status seq_score(const sp_score_args* a, const TiledDev& dev_, hipStream_t stream) {
   TiledDev dev = dev_;
-  dev.seq_order = nullptr;
-  if (a->B > 1) {  // (one sequence: nothing to order, and the host has seen that its length fits)
-    int32_t* order = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(dev.group_scores) + seq_scores_bytes(a));
-    launch_seq_order(a, order, seq_max_keys(a), stream);
-    dev.seq_order = order;
-  }
+  int n_groups;
+  dev.deal = seq_deal(a, &n_groups);
+  prepare_units(a, &dev, reinterpret_cast<int32_t*>(reinterpret_cast<char*>(dev.group_scores) + seq_scores_bytes(a)), seq_max_keys(a), stream);
   const int R = seq_rows(a);
   // (units smaller than a layer: the kernel variant that hands on maxima, whatever the layer reduction)
   const bool mean = a->layer_reduce == SP_LAYER_MEAN && dev.groups_per_layer == 0;

@@ -415,6 +415,8 @@ sp_status tiled_score(const sp_score_args* a, const ScoreDev& gen, void* extra, 
   dev.seq_limit = 0;
   dev.groups_per_layer = dev.plain_groups = 0;
   dev.seq_order = nullptr;
+  dev.deal = {};
+  dev.group_count = nullptr;
   if (seq_supported(a) || wide_supported(a)) {  // one pass over K, a workgroup per (sequence, slab group)
     seq_grouping(a, &dev.slabs_per_group, &dev.n_groups, &dev.groups_per_layer);
     if (dev.lgG < 2) { dev.lgG = 2; dev.Gp = 4; }  // (one or two heads per KV head: padded to four on this path)

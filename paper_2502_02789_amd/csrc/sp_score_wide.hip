@@ -54,16 +54,16 @@ __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDe
   using vkeep = typename W::vkeep;
   W w(p, smem);
   SeqUnit cur;
-  if (!seq_next_unit(p, 0, &cur)) return;
+  if (!seq_first_unit(p, &cur)) return;
 
-  int l = cur.s0 / p.H_kv, g = cur.s0 - l * p.H_kv;
+  int l = __builtin_amdgcn_readfirstlane(cur.s0 / p.H_kv), g = cur.s0 - l * p.H_kv;
   w.ah = {w.slab_keys(l, g, cur.seq0), cur.b, 0, cur.M, w.items_of(cur.M)};
   w.issue_queries(l, g, cur.b, 0);
   w.start_stream();
 
   int slabs = 0;  // slabs finished so far
   bool more = true;
-  SeqUnit nxt = cur;
+  SeqUnit nxt = cur;  // the unit of the slab behind the one at hand
 
   // all slabs of unit `cur`, tiles_c tiles per wave of which the first run_c have their running maxima in registers
   auto do_unit = [&](auto tiles_c, auto run_c) __attribute__((always_inline)) {
@@ -86,18 +86,15 @@ __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDe
       // end); requests move on to it when this slab's items have all been sent
       int nl = l, ng = g + 1;
       if (ng == p.H_kv) { ng = 0; ++nl; }
+      if (s + 1 == cur.s1) {
+        more = seq_next_unit(p, &nxt);
+        nl = __builtin_amdgcn_readfirstlane(nxt.s0 / p.H_kv);
+        ng = nxt.s0 - nl * p.H_kv;
+      }
       w.nx.left = 0;
-      if (s + 1 < cur.s1) {
-        w.nx = {w.slab_keys(nl, ng, cur.seq0), b, 0, M, nt};
-        w.issue_queries(nl, ng, b, buf ^ 1);
-      } else {
-        more = seq_next_unit(p, cur.k + 1, &nxt);
-        if (more) {
-          nl = nxt.s0 / p.H_kv;
-          ng = nxt.s0 - nl * p.H_kv;
-          w.nx = {w.slab_keys(nl, ng, nxt.seq0), nxt.b, 0, nxt.M, w.items_of(nxt.M)};
-          w.issue_queries(nl, ng, nxt.b, buf ^ 1);
-        }
+      if (more) {
+        w.nx = {w.slab_keys(nl, ng, nxt.seq0), nxt.b, 0, nxt.M, w.items_of(nxt.M)};
+        w.issue_queries(nl, ng, nxt.b, buf ^ 1);
       }
       w.begin_slab();
       w.slab_scale(l, g);
@@ -159,6 +156,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDe
           if (t < nt) __builtin_nontemporal_store(run[t], place(t));
         });
       }
+      if (s + 1 == cur.s1) note_group_count(p, cur);
       w.end_slab();
       l = nl;
       g = ng;
@@ -190,6 +188,7 @@ __global__ __launch_bounds__(THREADS) void wide_finish_kernel(const TiledDev p, 
     if (wide_tile_base(p.cu[mid], mid) <= tile) lo = mid; else hi = mid;
   }
   const int seq0 = p.cu[lo], M = p.cu[lo + 1] - seq0;
+  const int n_groups = p.group_count ? p.group_count[lo] : p.n_groups;
   const int key0 = (tile - wide_tile_base(seq0, lo)) * 32 + part * KEYS;
   // (exchange kernels: words 0 and 1 say whether a wait of this call expired -- the other parity's word is clear --,
   // word 2 counts the calls)
@@ -225,7 +224,7 @@ __global__ __launch_bounds__(THREADS) void wide_finish_kernel(const TiledDev p, 
       }
     } else {
 #pragma unroll 8
-      for (int g = g0; g < p.n_groups; g += per) {
+      for (int g = g0; g < n_groups; g += per) {
         const f32x4 x = *reinterpret_cast<const f32x4*>(src + g * step);
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] = mean ? v[k] + x[k] : fmaxf(v[k], x[k]);  // (mean: sums over a group's layers)
@@ -286,7 +285,14 @@ bool wide_supported(const sp_score_args* a) {
 }
 
 // Units: runs of slabs; with the mean over layers parts of one layer (the merge adds the layers up).
+static UnitDeal wide_deal(const sp_score_args* a, int* n_groups) {
+  *n_groups = 0;
+  return a->layer_reduce == SP_LAYER_MEAN ? UnitDeal{} : make_unit_deal(a, seq_cu_count(), wide_max_keys(a), false, n_groups);
+}
 void wide_grouping(const sp_score_args* a, int* slabs_per_group, int* n_groups, int* groups_per_layer) {
+  *groups_per_layer = 0;
+  *slabs_per_group = 1;
+  if (wide_deal(a, n_groups).stretch != 0) return;
   if (a->layer_reduce == SP_LAYER_MEAN) {
     int per = 1;
     for (int cand = a->H_kv; cand >= 1; --cand)
@@ -331,7 +337,7 @@ static sp_status launch_wide(const TiledDev& dev, hipStream_t stream) {
       prepared[slot] = true;
     }
   }
-  const int wgs = std::min(dev.B * dev.n_groups, seq_cu_count());
+  const int wgs = dev.deal.stretch != 0 ? seq_cu_count() : std::min(dev.B * dev.n_groups, seq_cu_count());
   hipLaunchKernelGGL(kernel, dim3(wgs), dim3(kTiledThreads), smem, stream, dev);
   return launch_status();
 }
@@ -352,12 +358,9 @@ sp_status wide_score(const sp_score_args* a, const TiledDev& dev_, hipStream_t s
   dev.lgG = wide_lg(a);
   dev.Gp = 1 << dev.lgG;
   dev.seq_limit = wide_max_keys(a);
-  dev.seq_order = nullptr;
-  if (a->B > 1) {
-    int32_t* order = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(dev.group_scores) + wide_scores_bytes(a));
-    launch_seq_order(a, order, dev.seq_limit, stream);
-    dev.seq_order = order;
-  }
+  int n_groups;
+  dev.deal = wide_deal(a, &n_groups);
+  prepare_units(a, &dev, reinterpret_cast<int32_t*>(reinterpret_cast<char*>(dev.group_scores) + wide_scores_bytes(a)), dev.seq_limit, stream);
   const sp_status st = a->d == 64 ? wide_by_kind<64>(a, dev, stream) : wide_by_kind<128>(a, dev, stream);
   if (st != SP_OK) return st;
   return launch_wide_finish(dev, (unsigned)wide_tiles(a), nullptr, stream);

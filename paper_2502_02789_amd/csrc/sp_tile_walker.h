@@ -4,6 +4,7 @@
 #pragma once
 
 #include "sp_score_internal.h"
+#include "sp_unit_deal.h"
 #include "sp_lds.h"
 
 namespace sp {
@@ -43,6 +44,8 @@ struct TiledDev {
   int slabs_per_group;   // single-pass batch kernel: (layer, KV head) slabs per unit (n_groups of them cover the L * H_kv slabs)
   int groups_per_layer;  // single-pass batch kernel, mean over layers with units smaller than a layer: slab groups per layer, else 0
   int plain_groups;      // ... that many groups before them hold sums over whole layers
+  UnitDeal deal;         // single-pass batch kernels: stretch != 0: the slabs are dealt out in stretches of equal cost, and
+  int32_t* group_count;  // [B] gets the number of groups that hold results of a sequence (else all n_groups)
   int seq_limit;         // single-pass batch kernel: sequences longer than this many keys are not scored (NaN), 0 = no limit
   const int32_t* block_table;  // paged cache: [B][blocks_per_seq] page numbers, else null
   int lg_page, blocks_per_seq;
@@ -480,33 +483,84 @@ struct TileWalker {
 };
 
 // One unit of work of the single-pass batch kernels: sequence b for the slabs [s0, s1) of slab group grp (slab s =
-// KV head s % H_kv of layer s / H_kv).  Units are numbered with the longest sequences first (all groups of a
-// sequence next to each other).
+// KV head s % H_kv of layer s / H_kv).
 struct SeqUnit {
-  int k;  // position in this workgroup's list of units
+  int k;  // position in this workgroup's list of units (dealt out in rounds)
   int b, grp, seq0, M, s0, s1;
 };
 
-// Units are dealt out to the gridDim.x workgroups in rounds, the direction changing with every round
+// The largest b in [0, B) whose first grain does not start behind `at` (the first one starts at 0): 64 at a time, a lane each.
+__device__ __forceinline__ int deal_sequence(const TiledDev& p, int64_t at) {
+  int lo = 0, n = p.B;
+  for (;;) {
+    const int step = (n + kWave - 1) / kWave, i = (int)(threadIdx.x & 63) * step;
+    const bool before = i < n && p.deal.start(p.cu[min(lo + i, p.B)], lo + i) <= at;
+    const int last = __builtin_amdgcn_readfirstlane(__popcll(__ballot(before))) - 1;
+    lo += last * step;
+    n = min(step, n - last * step);
+    if (step == 1) return lo;
+  }
+}
+
+// Units in stretches of equal cost (sp_unit_deal.h): what the workgroup's stretch has of one sequence after the other.
+__device__ __forceinline__ bool unit_of_stretch(const TiledDev& p, int b, bool first, SeqUnit* u) {
+  const UnitDeal& deal = p.deal;
+  const int w = (int)blockIdx.x;
+#pragma unroll 1
+  for (; b < p.B; ++b) {
+    const int seq0 = __builtin_amdgcn_readfirstlane(scalar_table(p.cu)[b]);
+    const int M = __builtin_amdgcn_readfirstlane(scalar_table(p.cu)[b + 1]) - seq0;
+    const int64_t at = deal.start(seq0, b), c = deal.cost(M);
+    const int g1 = __builtin_amdgcn_readfirstlane(deal.first_grain(w + 1, at, c));
+    const int g0 = first ? __builtin_amdgcn_readfirstlane(deal.first_grain(w, at, c)) : 0;
+    if (g1 == 0) return false;
+    // (no keys, or more than the kernel holds: nothing to do here, see seq_order_kernel and units_finish_kernel)
+    if (g0 < g1 && M > 0 && M <= p.seq_limit) {
+      u->b = b; u->seq0 = seq0; u->M = M;
+      u->grp = g0 == 0 ? 0 : w - __builtin_amdgcn_readfirstlane(deal.owner(at, c, 0));
+      u->s0 = g0 * deal.slabs; u->s1 = g1 * deal.slabs;
+      return true;
+    }
+    if (g1 < deal.grains) return false;
+  }
+  return false;
+}
+// Units of slabs_per_group slabs, numbered with the longest sequences first (all groups of a sequence next to each
+// other), dealt out to the gridDim.x workgroups in rounds, the direction changing with every round
 // (workgroup j: units j, 2W-1-j, 2W+j, ...): with the sizes in descending order every workgroup gets
-// nearly the same number of keys, and no counter has to be shared.
-__device__ __forceinline__ bool seq_next_unit(const TiledDev& p, int k, SeqUnit* u) {
+// nearly the same number of keys.
+__device__ __forceinline__ bool unit_of_rounds(const TiledDev& p, int k, SeqUnit* u) {
+  // (the same for the whole workgroup, said so that it stays in scalar registers)
+  auto uniform = [](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(x); };
   const int W = gridDim.x, n_units = p.B * p.n_groups;
+#pragma unroll 1
   for (;; ++k) {
     const int idx = k * W + ((k & 1) ? W - 1 - (int)blockIdx.x : (int)blockIdx.x);
     if (idx >= n_units) return false;
-    // (the same for the whole workgroup, said so that it stays in scalar registers)
-    const int row = __builtin_amdgcn_readfirstlane(idx / p.n_groups), grp = idx - row * p.n_groups;
-    const int b = p.seq_order ? __builtin_amdgcn_readfirstlane(scalar_table(p.seq_order)[row]) : row;  // (no table: batch order)
-    const int seq0 = __builtin_amdgcn_readfirstlane(scalar_table(p.cu)[b]);
-    const int M = __builtin_amdgcn_readfirstlane(scalar_table(p.cu)[b + 1]) - seq0;
+    const int row = uniform(idx / p.n_groups), grp = idx - row * p.n_groups;
+    const int b = p.seq_order ? uniform(scalar_table(p.seq_order)[row]) : row;  // (no table: batch order)
+    const int seq0 = uniform(scalar_table(p.cu)[b]);
+    const int M = uniform(scalar_table(p.cu)[b + 1]) - seq0;
     const int s0 = grp * p.slabs_per_group;
     const int s1 = min(p.L * p.H_kv, s0 + p.slabs_per_group);
-    // (no keys, or more than the kernel holds: nothing to do here, see seq_order_kernel and units_finish_kernel)
     if (M <= 0 || M > p.seq_limit || s0 >= s1) continue;
     u->k = k; u->b = b; u->grp = grp; u->seq0 = seq0; u->M = M; u->s0 = s0; u->s1 = s1;
     return true;
   }
+}
+// The workgroup's first unit, and the one behind *u.  No counter has to be shared either way.
+__device__ __forceinline__ bool seq_first_unit(const TiledDev& p, SeqUnit* u) {
+  if (p.deal.stretch != 0) return unit_of_stretch(p, deal_sequence(p, (int)blockIdx.x * p.deal.stretch), true, u);
+  return unit_of_rounds(p, 0, u);
+}
+__device__ __forceinline__ bool seq_next_unit(const TiledDev& p, SeqUnit* u) {
+  if (p.deal.stretch != 0)  // (a sequence that is not finished goes on in the next stretch)
+    return u->s1 == p.L * p.H_kv && unit_of_stretch(p, u->b + 1, false, u);
+  return unit_of_rounds(p, u->k + 1, u);
+}
+// a unit's results are out: the last one of a sequence says how many there are
+__device__ __forceinline__ void note_group_count(const TiledDev& p, const SeqUnit& u) {
+  if (p.deal.stretch != 0 && u.s1 == p.L * p.H_kv && threadIdx.x == 0) p.group_count[u.b] = u.grp + 1;
 }
 
 // single-pass kernels for batches of short prompts: few query rows per KV head (sp_score_seq.hip) ...
@@ -521,7 +575,8 @@ sp_status wide_score(const sp_score_args* a, const TiledDev& dev, hipStream_t st
 size_t wide_passes_workspace_bytes(const sp_score_args* a);
 sp_status wide_passes_score(const sp_score_args* a, const TiledDev& dev, void* extra, hipStream_t stream);
 int seq_cu_count();
-void launch_seq_order(const sp_score_args* a, int32_t* order, int limit, hipStream_t stream);
+// what the units of a call need: dev->deal is set, `words` has room for B
+void prepare_units(const sp_score_args* a, TiledDev* dev, int32_t* words, int limit, hipStream_t stream);
 sp_status launch_units_finish(const TiledDev& dev, hipStream_t stream);
 
 }  // namespace sp

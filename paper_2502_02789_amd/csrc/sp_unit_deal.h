@@ -1,0 +1,89 @@
+// How the single-pass kernels for batches of short prompts (sp_score_seq.hip, sp_score_wide.hip) share a batch out evenly
+// without knowing the sequences' lengths on the host: the slabs of all sequences, one behind the other, are cut into as many
+// stretches of equal cost as there are workgroups.  Plain C++: host and kernels use the same functions, and a test without
+// a GPU goes through them.
+//
+// A grain is what is not cut: a (layer, KV head) slab, or a whole layer where layers are added up.  A grain of sequence b
+// (M keys) costs M + extra, so the first grain of b lies at grains * (cu[b] + extra * b), known from cu alone, and a
+// workgroup finds its stretch by itself.  A grain belongs to the stretch that its middle lies in.  All positions are
+// doubled, so that they are whole numbers.
+//
+// Against units of a fixed number of slabs, longest sequences first, in rounds of alternating direction, which leave some
+// workgroups a third unit where others have two, need a launch to rank the sequences and write twice as many results (whole
+// call, 32 layers, 8 KV heads, d = 128, before -> now in us): 12 prompts of 2656..3949 keys, one query 461 -> 407; 18 of
+// 1430..1988 406 -> 338; 22 of 1400..2100, eight queries 499 -> 400; 6 of 858..1723 111 -> 94; 56 of 596..1269, one query 631
+// -> 534; 64 of 1024..4096 1671 -> 1655; 16 of 300..3000, eight queries 335 -> 331, the same with 8-bit keys, which arithmetic
+// in rounds of 256 keys bounds, 210 -> 214, the one slower shape tried but 7 of 296..2444 (131 -> 135).
+#pragma once
+
+#include <stdint.h>
+
+#include <algorithm>
+
+#include "specprefill.h"
+
+#ifdef __HIPCC__  // (as in sp_wide_pass_plan.h)
+#define SP_PLAN_FN __host__ __device__ __forceinline__
+#else
+#define SP_PLAN_FN inline
+#endif
+
+namespace sp {
+
+struct UnitDeal {
+  int64_t stretch;   // twice the cost of a workgroup's share; 0: dealt out in rounds
+  double inverse;    // 1 / stretch
+  int grains, slabs; // of a sequence; slabs of a grain
+  int extra;         // keys' time that the end of a grain takes
+
+  SP_PLAN_FN int64_t cost(int M) const { return (int64_t)(M > 0 ? M : 0) + extra; }
+  // of sequence b's first grain
+  SP_PLAN_FN int64_t start(int cu_b, int b) const { return 2 * (int64_t)grains * (cu_b + (int64_t)extra * b); }
+  // first grain of a sequence (starting at `at`, cost c a grain) whose middle does not lie in front of workgroup w's
+  // stretch: 0 .. grains
+  SP_PLAN_FN int first_grain(int w, int64_t at, int64_t c) const {
+    const int64_t x = w * stretch - at - c;  // smallest s with 2 s c >= x
+    if (x <= 0) return 0;
+    if (x > 2 * c * (grains - 1)) return grains;
+    int64_t s = (int)((float)(double)x / (float)(double)(2 * c));  // (right to one: fewer than 2^20 grains)
+    while (2 * s * c < x) ++s;
+    while (s > 0 && 2 * (s - 1) * c >= x) --s;
+    return (int)s;
+  }
+  // the workgroup that has grain s
+  SP_PLAN_FN int owner(int64_t at, int64_t c, int s) const {
+    const int64_t x = at + (2 * (int64_t)s + 1) * c;
+    int64_t w = (int64_t)((double)x * inverse);
+    while (w > 0 && w * stretch > x) --w;
+    while ((w + 1) * stretch <= x) ++w;
+    return (int)w;
+  }
+};
+
+// The cut for W workgroups; sequences longer than `limit` keys (what the kernel holds) are not scored.  *n_groups: results a
+// sequence may get, one from each workgroup that has a grain of it.  stretch = 0: not worth it, or not possible.
+inline UnitDeal make_unit_deal(const sp_score_args* a, int W, int limit, bool whole_layers, int* n_groups) {
+  UnitDeal d = {};
+  d.slabs = whole_layers ? a->H_kv : 1;
+  d.grains = a->L * a->H_kv / d.slabs;
+  // (about 1.5 us for the end of a slab, at the 27 GB/s that a workgroup streams; 40 or 400 keys instead of 160: 8 prompts of
+  // 200..1277 keys 90 us against 100 and 92, 16 of 300..3000 331 against 335 and 344)
+  d.extra = 160 * 256 / (a->d * (a->k_dtype == SP_K_FP8_E4M3 ? 1 : 2));
+  *n_groups = 0;
+  if (a->T < 1 || d.grains > (1 << 20) || a->T + (int64_t)d.extra * a->B > ((int64_t)1 << 50) / d.grains) return d;
+  const int64_t stretch = (2 * d.grains * (a->T + (int64_t)d.extra * a->B) + W - 1) / W;
+  const int64_t held = std::min<int64_t>(limit, a->T) + d.extra;
+  // Every workgroup between the first and the last that has a grain of a sequence must have one: no grain longer than a stretch.
+  if (2 * held > stretch) return d;
+  // A stretch is right to half a grain on either side, so four of the longest have to fit (busiest workgroup over 1500 random
+  // batches, median against the rounds: three to four 1.10, four to five 0.98, seven to ten 0.96, more 0.79); one sequence,
+  // whose grains are equal, gains as soon as there are more of them than workgroups.
+  const int64_t longest = std::min<int64_t>(a->B == 1 ? a->T : a->max_seqlen, a->T) + d.extra;
+  if (a->B == 1 ? d.grains <= W : 4 * 2 * longest > stretch) return d;
+  d.stretch = stretch;
+  d.inverse = 1.0 / (double)stretch;
+  *n_groups = (int)std::min<int64_t>(W, 2 * (int64_t)(d.grains - 1) * held / stretch + 2);
+  return d;
+}
+
+}  // namespace sp

@@ -32,3 +32,25 @@ def test_items_and_pairs(shape, paged):
             got, lse = hp.gpu_score(inp["q"], inp["k"], inp["cu_seqlens"], w.H_kv, scale, mode, max_seqlen=2047)
         hp.assert_scores_close(got, want, f"{shape} mode={mode} paged={paged}")
         np.testing.assert_allclose(lse, want_lse, rtol=0, atol=2e-4)
+
+
+@pytest.mark.parametrize("n_queries,mode", [(1, orc.LAYER_MAX), (1, orc.LAYER_MEAN), (4, orc.LAYER_MAX), (8, orc.LAYER_MAX)])
+def test_stretches_of_equal_cost(n_queries, mode):
+    """Enough slabs for every workgroup to get a stretch of them: sequences that one workgroup has several of, that several
+    share, that are empty, and one that breaks the promise (NaN, and nobody else is touched)."""
+    lens = (700, 1, 0, 33, 650, 64, 300, 0, 257) * 6 + (699,)
+    over = 8193 if n_queries == 1 else 4097 if n_queries == 2 else 3073
+    for all_lens in (lens, lens[:20] + (over,) + lens[20:]):
+        w = synth.scaled(synth.workload(4), seqlens=all_lens, L=32, H=16, H_kv=4, N=n_queries, d=64, salient_frac=0.02, salient_run=1)
+        inp = synth.make_qk(w)
+        scale = 1.0 / math.sqrt(w.d)
+        want, want_lse = orc.token_importance(inp["q"], inp["k"], inp["cu_seqlens"], scale, mode)
+        got, lse = hp.gpu_score(inp["q"], inp["k"], inp["cu_seqlens"], w.H_kv, scale, mode, max_seqlen=700)
+        cu = np.asarray(inp["cu_seqlens"])
+        ok = np.ones(len(got), dtype=bool)
+        if len(all_lens) > len(lens):
+            ok[cu[20]:cu[21]] = False
+            assert np.isnan(got[~ok]).all() and np.isnan(lse[:, 20]).all()
+        hp.assert_scores_close(got[ok], want[ok], f"{n_queries} mode={mode}")
+        keep = [b for b in range(len(all_lens)) if all_lens[b] != over]
+        np.testing.assert_allclose(lse[:, keep], want_lse[:, keep], rtol=0, atol=2e-4)
