@@ -122,7 +122,7 @@ struct SeqKernel : WideKernel<D, 2, FP8, PAGED> {
   }
 };
 
-template <int D, int R, int LG, bool MEAN, bool FP8, bool PAGED>
+template <int D, int R, int LG, bool MEAN, bool FP8, bool PAGED, bool STRETCHES>
 __global__ __launch_bounds__(kTiledThreads) void seq_score_kernel(const TiledDev p) {
   extern __shared__ __align__(1024) unsigned char smem[];
   using W = SeqKernel<D, R, LG, FP8, PAGED>;
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(kTiledThreads) void seq_score_kernel(const TiledDev
   typedef float vpair __attribute__((ext_vector_type(MAXP)));
   W w(p, smem);
   SeqUnit cur;
-  if (!seq_first_unit(p, &cur)) return;
+  if (!seq_first_unit<STRETCHES>(p, &cur)) return;
 
   int l = __builtin_amdgcn_readfirstlane(cur.s0 / p.H_kv), g = cur.s0 - l * p.H_kv;
   w.ah = {w.slab_keys(l, g, cur.seq0), cur.b, 0, cur.M, w.items_of(cur.M)};
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kTiledThreads) void seq_score_kernel(const TiledDev
       int nl = l, ng = g + 1;
       if (ng == p.H_kv) { ng = 0; ++nl; }
       if (s + 1 == cur.s1) {
-        more = seq_next_unit(p, &nxt);
+        more = seq_next_unit<STRETCHES>(p, &nxt);
         nl = __builtin_amdgcn_readfirstlane(nxt.s0 / p.H_kv);
         ng = nxt.s0 - nl * p.H_kv;
       }
@@ -172,8 +172,9 @@ __global__ __launch_bounds__(kTiledThreads) void seq_score_kernel(const TiledDev
         w.nx = {w.slab_keys(nl, ng, nxt.seq0), nxt.b, 0, nxt.M, w.items_of(nxt.M)};
         w.issue_queries(nl, ng, nxt.b, buf ^ 1);
       }
-      w.read_queries(buf);
       w.begin_slab();
+      if (slabs == 0) w.first_queries();
+      w.read_queries(buf);
       w.slab_scale(l, g);
       float rm[R], rs[R];  // this lane's running max and sum of exp2 per row, base-2 logits
 #pragma unroll
@@ -293,7 +294,7 @@ __global__ __launch_bounds__(kTiledThreads) void seq_score_kernel(const TiledDev
         }
       }
     });
-    note_group_count(p, cur);
+    note_group_count<STRETCHES>(p, cur);
     if (!more) break;
     cur = nxt;
   }
@@ -529,9 +530,9 @@ int seq_cu_count() {  // compute units of the current device
   return cached[slot];
 }
 
-template <int D, int R, int LG, bool MEAN, bool FP8, bool PAGED>
+template <int D, int R, int LG, bool MEAN, bool FP8, bool PAGED, bool STRETCHES>
 static sp_status launch_seq(const TiledDev& dev, hipStream_t stream) {
-  auto kernel = seq_score_kernel<D, R, LG, MEAN, FP8, PAGED>;
+  auto kernel = seq_score_kernel<D, R, LG, MEAN, FP8, PAGED, STRETCHES>;
   const size_t smem = SeqKernel<D, R, LG, FP8, PAGED>::kSmem;
   static std::mutex mu;  // once per kernel and device
   static bool prepared[kMaxDevices] = {};
@@ -546,14 +547,18 @@ static sp_status launch_seq(const TiledDev& dev, hipStream_t stream) {
     }
   }
   // one workgroup per compute unit walks over its share of the (sequence, layer group) units
-  const int wgs = dev.deal.stretch != 0 ? seq_cu_count() : std::min(dev.B * dev.n_groups, seq_cu_count());
+  const int wgs = STRETCHES ? seq_cu_count() : std::min(dev.B * dev.n_groups, seq_cu_count());
   hipLaunchKernelGGL(kernel, dim3(wgs), dim3(kTiledThreads), smem, stream, dev);
   return launch_status();
 }
 
+template <int D, int R, int LG, bool MEAN, bool FP8, bool PAGED>
+static sp_status seq_by_deal(const TiledDev& dev, hipStream_t stream) {
+  return dev.deal.stretch != 0 ? launch_seq<D, R, LG, MEAN, FP8, PAGED, true>(dev, stream) : launch_seq<D, R, LG, MEAN, FP8, PAGED, false>(dev, stream);
+}
 template <int D, int R, int LG, bool MEAN, bool FP8>
 static sp_status seq_by_pages(const TiledDev& dev, hipStream_t stream) {
-  return dev.block_table ? launch_seq<D, R, LG, MEAN, FP8, true>(dev, stream) : launch_seq<D, R, LG, MEAN, FP8, false>(dev, stream);
+  return dev.block_table ? seq_by_deal<D, R, LG, MEAN, FP8, true>(dev, stream) : seq_by_deal<D, R, LG, MEAN, FP8, false>(dev, stream);
 }
 template <int D, bool MEAN, bool FP8>
 static sp_status seq_by_rows(const TiledDev& dev, int R, hipStream_t stream) {

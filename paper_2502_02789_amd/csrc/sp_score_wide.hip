@@ -45,7 +45,7 @@ namespace sp {
 constexpr int kWideTiles = 12;    // 32-key tiles per wave, and the first
 constexpr int kWideRunTiles = 4;  // of them whose running maxima are in registers where not all fit
 
-template <int D, int LG, bool FP8, bool PAGED>
+template <int D, int LG, bool FP8, bool PAGED, bool STRETCHES>
 __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDev p) {
   extern __shared__ __align__(1024) unsigned char smem[];
   using W = WideKernel<D, LG, FP8, PAGED, false>;
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDe
   using vkeep = typename W::vkeep;
   W w(p, smem);
   SeqUnit cur;
-  if (!seq_first_unit(p, &cur)) return;
+  if (!seq_first_unit<STRETCHES>(p, &cur)) return;
 
   int l = __builtin_amdgcn_readfirstlane(cur.s0 / p.H_kv), g = cur.s0 - l * p.H_kv;
   w.ah = {w.slab_keys(l, g, cur.seq0), cur.b, 0, cur.M, w.items_of(cur.M)};
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDe
       int nl = l, ng = g + 1;
       if (ng == p.H_kv) { ng = 0; ++nl; }
       if (s + 1 == cur.s1) {
-        more = seq_next_unit(p, &nxt);
+        more = seq_next_unit<STRETCHES>(p, &nxt);
         nl = __builtin_amdgcn_readfirstlane(nxt.s0 / p.H_kv);
         ng = nxt.s0 - nl * p.H_kv;
       }
@@ -98,6 +98,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDe
       }
       w.begin_slab();
       w.slab_scale(l, g);
+      if (slabs == 0) w.first_queries();
       float rm = -INFINITY, rs = 0.f;
       w.slab_logits(held, nt, M, buf, rm, rs);
       const float lse2 = w.workgroup_lse(rm, rs, buf);
@@ -156,7 +157,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDe
           if (t < nt) __builtin_nontemporal_store(run[t], place(t));
         });
       }
-      if (s + 1 == cur.s1) note_group_count(p, cur);
+      if (s + 1 == cur.s1) note_group_count<STRETCHES>(p, cur);
       w.end_slab();
       l = nl;
       g = ng;
@@ -321,9 +322,9 @@ size_t wide_workspace_bytes(const sp_score_args* a) {
   return wide_scores_bytes(a) + align_up(sizeof(int32_t) * (size_t)a->B, 256);
 }
 
-template <int D, int LG, bool FP8, bool PAGED>
+template <int D, int LG, bool FP8, bool PAGED, bool STRETCHES>
 static sp_status launch_wide(const TiledDev& dev, hipStream_t stream) {
-  auto kernel = wide_score_kernel<D, LG, FP8, PAGED>;
+  auto kernel = wide_score_kernel<D, LG, FP8, PAGED, STRETCHES>;
   const size_t smem = WideKernel<D, LG, FP8, PAGED>::kSmem;
   static std::mutex mu;  // once per kernel and device
   static bool prepared[kMaxDevices] = {};
@@ -337,13 +338,17 @@ static sp_status launch_wide(const TiledDev& dev, hipStream_t stream) {
       prepared[slot] = true;
     }
   }
-  const int wgs = dev.deal.stretch != 0 ? seq_cu_count() : std::min(dev.B * dev.n_groups, seq_cu_count());
+  const int wgs = STRETCHES ? seq_cu_count() : std::min(dev.B * dev.n_groups, seq_cu_count());
   hipLaunchKernelGGL(kernel, dim3(wgs), dim3(kTiledThreads), smem, stream, dev);
   return launch_status();
 }
+template <int D, int LG, bool FP8, bool PAGED>
+static sp_status wide_by_deal(const TiledDev& dev, hipStream_t stream) {
+  return dev.deal.stretch != 0 ? launch_wide<D, LG, FP8, PAGED, true>(dev, stream) : launch_wide<D, LG, FP8, PAGED, false>(dev, stream);
+}
 template <int D, int LG, bool FP8>
 static sp_status wide_by_pages(const TiledDev& dev, hipStream_t stream) {
-  return dev.block_table ? launch_wide<D, LG, FP8, true>(dev, stream) : launch_wide<D, LG, FP8, false>(dev, stream);
+  return dev.block_table ? wide_by_deal<D, LG, FP8, true>(dev, stream) : wide_by_deal<D, LG, FP8, false>(dev, stream);
 }
 template <int D>
 static sp_status wide_by_kind(const sp_score_args* a, const TiledDev& dev, hipStream_t stream) {

@@ -85,6 +85,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_pass_kernel(const WidePass
   w.ah = {w.slab_keys(l, g, cur.u.seq0), cur.u.b, cur.u.key0, cur.u.M, w.items_of(cur.u.M)};
   issue_rows(l, g, cur.u.b, 0);
   w.start_stream();
+  w.first_queries();
 
   int buf = 0;
   bool more = true;

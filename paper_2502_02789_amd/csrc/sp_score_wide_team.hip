@@ -118,6 +118,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
   // The first item of the next slab is computed while the lines of this one travel (its logits wait in registers of
   // their own).
   f32x16 spare;
+  bool first = true;   // no slab has been done yet
   bool early = false;  // the first item of the slab at hand is in `spare`, its statistics in (rm, rs)
   float rm = -INFINITY, rs = 0.f;
 #pragma unroll
@@ -145,6 +146,8 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
     }
     w.begin_slab();
     w.slab_scale(l, g);
+    if (first) w.first_queries();
+    first = false;
     if (early) {
       held[0] = spare;
     } else {

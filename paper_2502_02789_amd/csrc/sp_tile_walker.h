@@ -537,10 +537,14 @@ __device__ __forceinline__ bool unit_of_rounds(const TiledDev& p, int k, SeqUnit
   for (;; ++k) {
     const int idx = k * W + ((k & 1) ? W - 1 - (int)blockIdx.x : (int)blockIdx.x);
     if (idx >= n_units) return false;
-    const int row = uniform(idx / p.n_groups), grp = idx - row * p.n_groups;
-    const int b = p.seq_order ? uniform(scalar_table(p.seq_order)[row]) : row;  // (no table: batch order)
-    const int seq0 = uniform(scalar_table(p.cu)[b]);
-    const int M = uniform(scalar_table(p.cu)[b + 1]) - seq0;
+    int b = 0, grp = idx, seq0 = 0, M = (int)p.T;  // (one sequence: nothing to look up)
+    if (p.B > 1) {
+      const int row = uniform(idx / p.n_groups);
+      grp = idx - row * p.n_groups;
+      b = p.seq_order ? uniform(scalar_table(p.seq_order)[row]) : row;  // (no table: batch order)
+      seq0 = uniform(scalar_table(p.cu)[b]);
+      M = uniform(scalar_table(p.cu)[b + 1]) - seq0;
+    }
     const int s0 = grp * p.slabs_per_group;
     const int s1 = min(p.L * p.H_kv, s0 + p.slabs_per_group);
     if (M <= 0 || M > p.seq_limit || s0 >= s1) continue;
@@ -548,19 +552,23 @@ __device__ __forceinline__ bool unit_of_rounds(const TiledDev& p, int k, SeqUnit
     return true;
   }
 }
-// The workgroup's first unit, and the one behind *u.  No counter has to be shared either way.
+// The workgroup's first unit, and the one behind *u.  No counter has to be shared either way.  (A kernel has the code of one
+// way only: with both in it the kernels for 32 rows started 0.5 to 1 us later.)
+template <bool STRETCHES>
 __device__ __forceinline__ bool seq_first_unit(const TiledDev& p, SeqUnit* u) {
-  if (p.deal.stretch != 0) return unit_of_stretch(p, deal_sequence(p, (int)blockIdx.x * p.deal.stretch), true, u);
-  return unit_of_rounds(p, 0, u);
+  if constexpr (STRETCHES) return unit_of_stretch(p, deal_sequence(p, (int)blockIdx.x * p.deal.stretch), true, u);
+  else return unit_of_rounds(p, 0, u);
 }
+template <bool STRETCHES>
 __device__ __forceinline__ bool seq_next_unit(const TiledDev& p, SeqUnit* u) {
-  if (p.deal.stretch != 0)  // (a sequence that is not finished goes on in the next stretch)
+  if constexpr (STRETCHES)  // (a sequence that is not finished goes on in the next stretch)
     return u->s1 == p.L * p.H_kv && unit_of_stretch(p, u->b + 1, false, u);
-  return unit_of_rounds(p, u->k + 1, u);
+  else return unit_of_rounds(p, u->k + 1, u);
 }
 // a unit's results are out: the last one of a sequence says how many there are
+template <bool STRETCHES>
 __device__ __forceinline__ void note_group_count(const TiledDev& p, const SeqUnit& u) {
-  if (p.deal.stretch != 0 && u.s1 == p.L * p.H_kv && threadIdx.x == 0) p.group_count[u.b] = u.grp + 1;
+  if (STRETCHES && u.s1 == p.L * p.H_kv && threadIdx.x == 0) p.group_count[u.b] = u.grp + 1;
 }
 
 // single-pass kernels for batches of short prompts: few query rows per KV head (sp_score_seq.hip) ...

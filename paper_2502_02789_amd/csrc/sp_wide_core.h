@@ -184,9 +184,13 @@ struct WideKernel {
     fresh = true;
     while (sent - pos < SLOTS && (ah.left > 0 || (fresh && nx.left > 0))) refill();  // (waves with less than a ringful per slab)
   }
-  // a workgroup's first slab: the first items on their way, the query tile (requested before them) here
+  // a workgroup's first slab: the first items on their way ...
   __device__ __forceinline__ void start_stream() {
     while (sent < SLOTS && ah.left > 0) issue_one();
+  }
+  // ... and, in front of its products, the query tile (requested before them) here.  What comes between the two, the set-up
+  // of the loop and the next slab's requests, waits for instructions while the first loads travel.
+  __device__ __forceinline__ void first_queries() {
     wait_items(sent);
     __builtin_amdgcn_s_barrier();
   }
