@@ -174,22 +174,40 @@ __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDe
 }
 
 // Merge of the units' results and the average over the valid queries.  One workgroup per 32-key tile (or per half
-// of one: KEYS = 16, where a short prompt has too few tiles to fill the device): it reads one dense block,
-// KEYS / 4 threads per (group, query) row, every thread keeps to one query, the threads of a query meet in LDS.
-// Sequences the scoring kernel left out (longer than it holds) get NaN.
+// of one: KEYS = 16): it reads one dense block, KEYS / 4 threads per (group, query) row, every thread keeps to one query, the
+// threads of a query meet in LDS.  Sequences the scoring kernel left out (longer than it holds) get NaN.
+// Bound by its dependent steps: the first eight rows of a thread are requested before anything else is looked at (they lie
+// in the result array whatever it says), a single sequence is not looked up, and rows are divided by the number of queries
+// with one reciprocal.
 template <int KEYS, int THREADS>
 __global__ __launch_bounds__(THREADS) void wide_finish_kernel(const TiledDev p, uint32_t* status) {
   constexpr int TPR = KEYS / 4;            // threads per row
-  constexpr int ROWS = THREADS / TPR;         // rows per step
+  constexpr int ROWS = THREADS / TPR;      // rows per step
+  constexpr int AHEAD = 8;
   __shared__ float red[ROWS][KEYS];
   const int tile = blockIdx.x / (32 / KEYS), part = blockIdx.x % (32 / KEYS);
-  int lo = 0, hi = p.B;                    // the sequence: the largest b whose first tile is <= tile
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (wide_tile_base(p.cu[mid], mid) <= tile) lo = mid; else hi = mid;
+  const bool mean = p.layer_reduce != SP_LAYER_MAX;
+  const uint32_t inverse = 65536u / (uint32_t)p.N + 1u;  // x / N = x * inverse >> 16 for x below 4096
+  const int per = (int)(ROWS * inverse >> 16);           // groups (mean: layers) per step
+  const int row = threadIdx.x / TPR, quad = threadIdx.x % TPR;
+  const int g0 = (int)((uint32_t)row * inverse >> 16), n = row - g0 * p.N;
+  const bool by_layer = mean && p.groups_per_layer > 0;
+  const int64_t step = (int64_t)p.N * 32;
+  const float* src = p.group_scores + ((int64_t)tile * p.n_groups * p.N + n) * 32 + part * KEYS + quad * 4;
+  f32x4 ahead[AHEAD];
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) ahead[i] = *reinterpret_cast<const f32x4*>(src + min(g0 + i * per, p.n_groups - 1) * step);
+
+  int lo = 0, seq0 = 0, M = (int)p.T;
+  if (p.B > 1) {                           // the sequence: the largest b whose first tile is <= tile
+    int hi = p.B;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (wide_tile_base(p.cu[mid], mid) <= tile) lo = mid; else hi = mid;
+    }
+    seq0 = p.cu[lo];
+    M = p.cu[lo + 1] - seq0;
   }
-  const int seq0 = p.cu[lo], M = p.cu[lo + 1] - seq0;
-  const int n_groups = p.group_count ? p.group_count[lo] : p.n_groups;
   const int key0 = (tile - wide_tile_base(seq0, lo)) * 32 + part * KEYS;
   // (exchange kernels: words 0 and 1 say whether a wait of this call expired -- the other parity's word is clear --,
   // word 2 counts the calls)
@@ -200,16 +218,20 @@ __global__ __launch_bounds__(THREADS) void wide_finish_kernel(const TiledDev p, 
     if (threadIdx.x < KEYS && key0 + (int)threadIdx.x < M) p.scores[seq0 + key0 + threadIdx.x] = __uint_as_float(0x7FC00000u);
     return;
   }
-  const bool mean = p.layer_reduce != SP_LAYER_MAX;
-  const int per = ROWS / p.N;              // groups (mean: layers) per step
-  const int row = threadIdx.x / TPR, quad = threadIdx.x % TPR;
-  const int n = row % p.N, g0 = row / p.N;
+  const int n_groups = p.group_count ? p.group_count[lo] : p.n_groups;
   f32x4 v = mean ? f32x4{0.f, 0.f, 0.f, 0.f} : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
   if (g0 < per) {
-    const float* src = p.group_scores + ((int64_t)tile * p.n_groups * p.N + n) * 32 + part * KEYS + quad * 4;
-    const int64_t step = (int64_t)p.N * 32;
-    if (mean && p.groups_per_layer > 0) {  // the groups of a layer hold the log2 of its maxima over their KV heads; the layers' maxima add up
-      for (int g = g0; g < p.plain_groups; g += per) v += *reinterpret_cast<const f32x4*>(src + g * step);
+    auto take = [&](const f32x4& x) __attribute__((always_inline)) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = mean ? v[k] + x[k] : fmaxf(v[k], x[k]);  // (mean: sums over a group's layers)
+    };
+    const int plain = by_layer ? p.plain_groups : n_groups;
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i)
+      if (g0 + i * per < plain) take(ahead[i]);
+#pragma unroll 8
+    for (int g = g0 + AHEAD * per; g < plain; g += per) take(*reinterpret_cast<const f32x4*>(src + g * step));
+    if (by_layer) {  // the groups of a layer hold the log2 of its maxima over their KV heads; the layers' maxima add up
       const int layers = (p.n_groups - p.plain_groups) / p.groups_per_layer;
       src += p.plain_groups * step;
       for (int l = g0; l < layers; l += per) {
@@ -223,41 +245,40 @@ __global__ __launch_bounds__(THREADS) void wide_finish_kernel(const TiledDev p, 
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] += fast_exp2(m[k]);
       }
-    } else {
-#pragma unroll 8
-      for (int g = g0; g < n_groups; g += per) {
-        const f32x4 x = *reinterpret_cast<const f32x4*>(src + g * step);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = mean ? v[k] + x[k] : fmaxf(v[k], x[k]);  // (mean: sums over a group's layers)
-      }
     }
   }
   *reinterpret_cast<f32x4*>(&red[row][quad * 4]) = v;
   __syncthreads();
   // all threads fold the rows of a (query, key), then KEYS * N of them the THREADS / (KEYS * N) results of each
-  const int fk = threadIdx.x % KEYS, fn = threadIdx.x / KEYS % p.N, sub = threadIdx.x / KEYS / p.N;
-  const int subs = max(1, THREADS / KEYS / p.N);
+  const int fk = threadIdx.x % KEYS, fr = threadIdx.x / KEYS, sub = (int)((uint32_t)fr * inverse >> 16), fn = fr - sub * p.N;
+  const int subs = max(1, (int)((uint32_t)(THREADS / KEYS) * inverse >> 16));
   float x = mean ? 0.f : -INFINITY;
-  if (sub < subs)
+  if (sub < subs) {
+#pragma unroll 4
     for (int q = sub; q < per; q += subs) {
       const float y = red[q * p.N + fn][fk];
       x = mean ? x + y : fmaxf(x, y);
     }
-  __syncthreads();
-  if (sub < subs) red[sub * p.N + fn][fk] = x;
-  __syncthreads();
-  if (sub == 0) {
-    for (int q = 1; q < min(subs, per); ++q) {
-      const float y = red[q * p.N + fn][fk];
-      x = mean ? x + y : fmaxf(x, y);
-    }
-    red[fn][fk] = mean ? x : fast_exp2(x);  // (rows 0..N-1 are read by their own threads only)
   }
+  __syncthreads();
+  if (subs > 1) {
+    if (sub < subs) red[sub * p.N + fn][fk] = x;
+    __syncthreads();
+    if (sub == 0) {
+#pragma unroll 4
+      for (int q = 1; q < min(subs, per); ++q) {
+        const float y = red[q * p.N + fn][fk];
+        x = mean ? x + y : fmaxf(x, y);
+      }
+    }
+  }
+  if (sub == 0) red[fn][fk] = mean ? x : fast_exp2(x);  // (rows 0..N-1 are read by their own threads only)
   __syncthreads();
   if (threadIdx.x >= KEYS || key0 + fk >= M) return;
   int nv = p.n_valid ? p.n_valid[lo] : p.N;
   nv = max(1, min(nv, p.N));
   float sum = 0.f;
+#pragma unroll 8
   for (int q = 0; q < nv; ++q) sum += red[q][fk];
   p.scores[seq0 + key0 + fk] = sum / (mean ? (float)nv * (float)p.L : (float)nv);
 }
@@ -372,15 +393,14 @@ sp_status wide_score(const sp_score_args* a, const TiledDev& dev_, hipStream_t s
 }
 
 sp_status launch_wide_finish(const TiledDev& dev, unsigned tiles, uint32_t* status, hipStream_t stream) {
-  // Two workgroups per 32-key tile where the tiles alone would not give every compute unit two; small workgroups
-  // where a tile has few rows to read (128K keys in four groups of eight queries: 24 us with 1024 threads) and at most
-  // eight queries (a thread per key and query).  With no more rows than a small workgroup reads in one step it is ahead
-  // for short prompts too (one layer, one KV head, d = 64, one query, whole call: 4500 keys 14.1 -> 12.2 us, 9000
-  // 16.7 -> 12.6, 15000 18.1 -> 12.8; four layers of four KV heads, two queries, 9000 keys 17.3 -> 14.1).
-  const bool few_rows = dev.n_groups * dev.N <= 32 && dev.N <= 8;
-  if (tiles < 512 && !few_rows) hipLaunchKernelGGL((wide_finish_kernel<16, 1024>), dim3(2 * tiles), dim3(1024), 0, stream, dev, status);
-  else if (dev.n_groups * dev.N > 256 || dev.N > 8) hipLaunchKernelGGL((wide_finish_kernel<32, 1024>), dim3(tiles), dim3(1024), 0, stream, dev, status);
-  else hipLaunchKernelGGL((wide_finish_kernel<32, 256>), dim3(tiles), dim3(256), 0, stream, dev, status);
+  // A tile of many rows by 512 threads: 256 leave too little in flight, 1024 too few workgroups on a compute unit (whole
+  // call with 256, 512 and 1024 threads, in us: 16 layers of d = 64, eight queries, 4096 keys 28.8, 27.8, 28.0, 12000 keys 51.5,
+  // 51.3, 52.5; 32 layers of d = 128, 3001 keys 51.6, 50.2, 50.7, 8192 keys 101.2, 100.2, 100.8; with halves of tiles by 1024,
+  // as up to 512 tiles before, 30.0, 54.8, 51.7, 103.5).  Of few rows by 256: 32K keys 340.7, 342.6, 352.8, one query on 12000 keys
+  // 134.6, 135.4, 137.3.  Halves of tiles where there are so few that compute units would have none: 700 keys 20.5 against 21.2.
+  if (dev.n_groups * dev.N <= 256 && dev.N <= 8) hipLaunchKernelGGL((wide_finish_kernel<32, 256>), dim3(tiles), dim3(256), 0, stream, dev, status);
+  else if (tiles < 48) hipLaunchKernelGGL((wide_finish_kernel<16, 512>), dim3(2 * tiles), dim3(512), 0, stream, dev, status);
+  else hipLaunchKernelGGL((wide_finish_kernel<32, 512>), dim3(tiles), dim3(512), 0, stream, dev, status);
   return launch_status();
 }
 
