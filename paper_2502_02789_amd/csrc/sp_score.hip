@@ -297,9 +297,15 @@ static int general_max_tiles(const sp_score_args* a) { return (int)(a->T / kTile
 // un-rotated.  3500 keys, 8 KV heads, d = 128, whole step: 32 layers, eight queries 109 us in two passes, 72 here; one
 // query with d = 64 and 16 layers 61 us with the logits kept in memory, 40 here; nothing tried beyond was slower.)
 bool single_pass_wanted(const sp_score_args* a) {
-  // (the batch kernels keep a sequence's logits inside a workgroup and need no exchange at all)
-  if (tiled_supported(a) && (seq_supported(a) || wide_supported(a))) return false;
-  return ((a->flags & SP_SCORE_EXCLUSIVE_DEVICE) != 0 || a->T > 3072) && wide_team_supported(a);
+  const bool exclusive = (a->flags & SP_SCORE_EXCLUSIVE_DEVICE) != 0;
+  // The batch kernels keep a sequence's logits inside a workgroup and need no exchange at all, but every slab's results go
+  // out by themselves.  From 2048 keys on, two workgroups to a slab, whose results are half as many, are ahead on an idle
+  // device: 32 layers, 8 KV heads, d = 128, eight queries, 1500 keys 30.4 us and 30.6 by teams, 2048 38.7 and 35.1, 3001 50.6
+  // and 45.4 (8-bit keys 36.2 and 35.1, four queries 45.1 and 43.0); 16 layers of d = 64, 2048 keys 22.0 and 21.2, 3001 28.3
+  // and 24.1.  (Below 128 slabs one short prompt keeps the same scores, bit for bit, with and without the promise.)
+  const bool pairs = exclusive && a->B == 1 && a->T >= 2048 && (int64_t)a->L * a->H_kv >= 128;
+  if (tiled_supported(a) && (seq_supported(a) || (wide_supported(a) && !pairs))) return false;
+  return (exclusive || a->T > 3072) && wide_team_supported(a);
 }
 
 size_t general_workspace_bytes(const sp_score_args* a, bool with_tiled) {

@@ -101,3 +101,22 @@ def test_8_bit_cache_at_the_edges_of_what_the_registers_hold(longest, d, mode):
                      H=8, H_kv=2, N=8, d=d, salient_frac=0.02, salient_run=1)
     fp8._check(w, mode, False, max_seqlen=longest)
     fp8._check(w, mode, False, max_seqlen=longest, paged=16)
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("n_keys", [2047, 2048, 2081, 3072, 3073])
+def test_one_prompt_of_many_slabs_with_and_without_the_promise(n_keys, mode):
+    """128 slabs: on an idle device from 2048 keys on in teams of two workgroups, else a workgroup to a slab; the workspace handed on
+    from call to call either way."""
+    w = synth.scaled(synth.workload(3), seqlens=(n_keys,), L=32, H=16, H_kv=4, N=8, d=64)
+    inp = synth.make_qk(w)
+    a = _check(w, inp, mode, max_seqlen=0, exclusive_device=True)
+    b = _check(w, inp, mode, max_seqlen=0, exclusive_device=False)
+    np.testing.assert_allclose(a, b, rtol=2e-5)
+    import torch
+    from paper_2502_02789_amd import device as dev
+    cu = torch.from_numpy(inp["cu_seqlens"]).cuda()
+    s = dev.Scorer(dev.bf16_from_bits(inp["q"]), [dev.bf16_from_bits(k) for k in inp["k"]], cu, H_kv=w.H_kv, scale=1.0 / math.sqrt(w.d),
+                   layer_reduce=mode, keep_workspace=True)
+    for _ in range(3):
+        assert np.array_equal(s.run().cpu().numpy(), a)
