@@ -11,10 +11,8 @@
 //     into the rows' log-sum-exps and hands those to the other waves through LDS;
 //   * a slab is 18 us of stream for a workgroup (2048 keys, d = 128) and the ring holds 5 us of it, so the exchange
 //     is short against a slab, and the teams, which never meet, drift apart: while one waits the others have the
-//     memory.  The next slab's first item is computed while the lines travel, its logits in registers of their own:
-//     32K keys 350 -> 339 us, 128K 1378 -> 1352 (now, with slabs in runs of four, 336 and 1301; without
-//     any exchange, wrong results, 327 and 1256; with an exchange four times as often hidden behind three slabs of a
-//     quarter of the keys each, and the query tile fetched once per wave, as in the kernels before: 349 and 1570);
+//     memory.  The next slab's first item is computed while the lines travel, its logits in registers of their own
+//     (32K keys 350 -> 339 us), and bf16 keys' other items in turn with the fold of the slab before;
 //   * 256 / P teams are dealt the slabs in turn, a few at a time (sp_wide_team_plan.h); a team's maxima go out as one
 //     group of the result array, merged by the kernel that merges the units of short prompts.  Mean over layers: whole
 //     layers in turn, a team adds their maxima up; the layers left over in parts, each a group of its own.
@@ -112,73 +110,57 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
   w.ah = {w.slab_keys(l, g, 0), 0, key0, M, nt};
   w.issue_queries(l, g, 0, 0);
   w.start_stream();
+  w.first_queries();
 
   f32x16 held[MAXT];
   vkeep run[MAXT];
-  // The first item of the next slab is computed while the lines of this one travel (its logits wait in registers of
-  // their own).
-  f32x16 spare;
-  bool first = true;   // no slab has been done yet
-  bool early = false;  // the first item of the slab at hand is in `spare`, its statistics in (rm, rs)
-  float rm = -INFINITY, rs = 0.f;
 #pragma unroll
   for (int t = 0; t < MAXT; ++t)
 #pragma unroll
     for (int k = 0; k < KEEP; ++k) run[t][k] = -INFINITY;
-  int buf = 0;
-#pragma unroll 1
-  for (;;) {
-    // the slab behind this one: of this run or the team's next one
-    int nq = q, ns = s + 1, ns_end = s_end, nl = l, ng = g + 1;
+
+  struct Place { int q, s, s_end, l, g; };  // slab s = (l, g) of the team's q-th run, which ends at s_end
+  Place cur = {q, s, s_end, l, g}, nxt = cur;
+  auto line_of = [&](int slab) __attribute__((always_inline)) { return lines_cur + ((size_t)slab << (p.lgP + 5)); };
+  // the slab behind `cur`: of this run or the team's next one; its requests begin
+  auto move_on = [&](int buf) __attribute__((always_inline)) {
+    int nq = cur.q, ns = cur.s + 1, ns_end = cur.s_end, nl = cur.l, ng = cur.g + 1;
     if (ng == p.H_kv) { ng = 0; ++nl; }
-    if (ns == s_end) {
+    if (ns == cur.s_end) {
       ++nq;
       ns = deal.start(team, nq);
       ns_end = deal.end(nq, ns);
       nl = ns / p.H_kv;
       ng = ns - nl * p.H_kv;
     }
-    const bool more = ns < deal.n_slabs;
+    nxt = {nq, ns, ns_end, nl, ng};
+    const bool more = nxt.s < deal.n_slabs;
     w.nx.left = 0;
     if (more) {
-      w.nx = {w.slab_keys(nl, ng, 0), 0, key0, M, nt};
-      w.issue_queries(nl, ng, 0, buf ^ 1);
+      w.nx = {w.slab_keys(nxt.l, nxt.g, 0), 0, key0, M, nt};
+      w.issue_queries(nxt.l, nxt.g, 0, buf ^ 1);
     }
     w.begin_slab();
-    w.slab_scale(l, g);
-    if (first) w.first_queries();
-    first = false;
-    if (early) {
-      held[0] = spare;
-    } else {
-      rm = -INFINITY;
-      rs = 0.f;
-      if (nt > 0) held[0] = w.template item_logits<0>(nt, M, buf, rm, rs);
-    }
-    w.template slab_logits<MAXT, 1>(held, nt, M, buf, rm, rs);
-    const float own = w.workgroup_lse(rm, rs, buf);
-    uint32_t* const line = lines_cur + ((size_t)s << (p.lgP + 5));
+    w.slab_scale(cur.l, cur.g);
+    return more;
+  };
+  // this member's statistics of a slab for the others
+  auto publish = [&](int slab, float own) __attribute__((always_inline)) {
     if (w.wave == 0) {
       const int ln = W::lane_id();
       if (ln < 32) {  // (-inf -- no key of the prompt in this workgroup -- is a value, not "empty")
-        store32_agent(line + member * 32 + ln, __float_as_uint(own));
-        lines_nxt[((size_t)s << (p.lgP + 5)) + member * 32 + ln] = kEmptyLine;
+        store32_agent(line_of(slab) + member * 32 + ln, __float_as_uint(own));
+        lines_nxt[((size_t)slab << (p.lgP + 5)) + member * 32 + ln] = kEmptyLine;
       }
     }
-    early = more && nt > 0;
-    if (early) {
-      rm = -INFINITY;
-      rs = 0.f;
-      const float c2 = w.c2;
-      w.slab_scale(nl, ng);
-      spare = w.template item_logits<0>(nt, M, buf ^ 1, rm, rs);
-      w.c2 = c2;
-    }
+  };
+  // the whole team's: the lane's row's base-2 log-sum-exp
+  auto team_lse = [&](int slab, int sl, int sg) __attribute__((always_inline)) {
     if (w.wave == 0) {
       const int ln = W::lane_id();
       // Lane ln holds, of load i, rows 4 * (ln % 8) .. + 3 of member i * 8 + ln / 8 (lanes beyond the last member read
       // nothing and get zeros).
-      const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(line, 0, (uint32_t)P * 128u, 0x00020000);
+      const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(line_of(slab), 0, (uint32_t)P * 128u, 0x00020000);
       const int loads = P <= 8 ? 1 : P >> 3;
       uint32_t since = 0;  // when this slab's wait began
       float m[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY}, z[4] = {0.f, 0.f, 0.f, 0.f};
@@ -241,61 +223,138 @@ __global__ __launch_bounds__(kTiledThreads) void wide_team_kernel(const WideTeam
     }
     __builtin_amdgcn_s_barrier();
     const float lse2 = __uint_as_float(lds_peek(lse_lds + (W::lane_id() & 31) * 4));
-    if (p.lse_out && member == 0 && w.wave == 0) w.store_lse(l, g, 0, lse2);
-
-    // log2-probabilities; maximum over the heads of a group and over the slabs
+    if (p.lse_out && member == 0 && w.wave == 0) w.store_lse(sl, sg, 0, lse2);
+    return lse2;
+  };
+  // log2-probabilities of a held tile; maximum over the heads of a group and over the slabs
+  auto fold = [&](auto tc, float c2, float neg_lse2) __attribute__((always_inline)) {
+    constexpr int t = decltype(tc)::value;
+    float y[KEEP];
+    W::fold_heads(held[t], c2, neg_lse2, y);
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k) run[t][k] = fmaxf(run[t][k], y[k]);
+  };
+  // The results, behind the fold of slab `of`.  Maximum over layers: one group per team, at its end.  Mean: a run of a round
+  // is a layer, whose maxima join the sum in the team's group (registers for the sums would be a quarter of what the logits
+  // leave); a part of a layer has a group of its own behind the teams'.
+  auto results = [&](const Place& of, bool last) __attribute__((always_inline)) {
+    if (!(mean ? of.s + 1 == of.s_end : last)) return;
+    const bool sum = mean && of.q < deal.rounds;
+    const int group = !mean || sum ? team : p.plain_groups + (of.s - deal.base()) / deal.part;
+    const int q_n = W::lane_id() & (W::NS - 1);
+    const int64_t step = (int64_t)p.n_groups * p.N * 32;  // from tile to tile
+    float* const out = p.group_scores + ((int64_t)((key0 >> 5) + w.wave + (nt - 1) * kTiledWaves) * p.n_groups + group) * p.N * 32 +
+                       q_n * 32 + w.fold_key();
+    const int64_t back = kTiledWaves * step;              // from one of the wave's tiles to the next
+    if (sum) {
+      constexpr int STEP = LG == 1 ? 2 : 4;  // tiles whose loads go out together
+      wide_static_for<0, MAXT / STEP>([&](auto bc) __attribute__((always_inline)) {
+        constexpr int t0 = decltype(bc)::value * STEP;
+        vkeep old[STEP];
+#pragma unroll
+        for (int i = 0; i < STEP; ++i)
+#pragma unroll
+          for (int k = 0; k < KEEP; ++k) old[i][k] = 0.f;
+        if (of.q > 0 && q_n < p.N) {
+#pragma unroll
+          for (int i = 0; i < STEP; ++i)
+            if (t0 + i < nt) old[i] = W::load_keep(out - (t0 + i) * back);
+        }
+#pragma unroll
+        for (int i = 0; i < STEP; ++i)
+#pragma unroll
+          for (int k = 0; k < KEEP; ++k) run[t0 + i][k] = old[i][k] + fast_exp2(run[t0 + i][k]);
+      });
+    }
     wide_static_for<0, MAXT>([&](auto tc) __attribute__((always_inline)) {
       constexpr int t = decltype(tc)::value;
-      if (t < nt) {
-        float y[KEEP];
-        w.fold_heads(held[t], -lse2, y);
+      if (q_n < p.N && t < nt) W::store_keep(out - t * back, run[t]);
 #pragma unroll
-        for (int k = 0; k < KEEP; ++k) run[t][k] = fmaxf(run[t][k], y[k]);
-      }
+      for (int k = 0; k < KEEP; ++k) run[t][k] = -INFINITY;
     });
-    // The results.  Maximum over layers: one group per team, at its end.  Mean: a run of a round is a layer, whose
-    // maxima join the sum in the team's group (registers for the sums would be a quarter of what the logits leave); a
-    // part of a layer has a group of its own behind the teams'.
-    if (mean ? s + 1 == s_end : !more) {
-      const bool sum = mean && q < deal.rounds;
-      const int group = !mean || sum ? team : p.plain_groups + (s - deal.base()) / deal.part;
-      const int q_n = W::lane_id() & (W::NS - 1);
-      const int64_t step = (int64_t)p.n_groups * p.N * 32;  // from tile to tile
-      float* const out = p.group_scores + ((int64_t)((key0 >> 5) + w.wave + (nt - 1) * kTiledWaves) * p.n_groups + group) * p.N * 32 +
-                         q_n * 32 + w.fold_key();
-      auto place_of = [&](int t) __attribute__((always_inline)) {
-        return out - t * kTiledWaves * step;
-      };
-      if (sum) {
+  };
+  int buf = 0;
+  float rm = -INFINITY, rs = 0.f;
+  if constexpr (!FP8) {
+    // A turn takes a slab's products and, tile by tile in front of them, folds the slab before.  That one's log-sum-exps are
+    // waited for behind the first item's products, whose logits have registers of their own until then; the ring is emptied
+    // without a stop between slabs.  (With the fold of all tiles as soon as the log-sum-exps are there and the next slab's
+    // products behind it, in us: 32 layers of d = 128, 32K keys 349 -> 342, mean over 30011 keys 326 -> 319, 24577 keys
+    // without the promise 280 -> 272; 16 layers of d = 64, 33000 keys 133 -> 123.  8-bit keys lose by it, below.)  The first
+    // turn has nothing to fold -- its log-sum-exps are infinite, its logits zero --, the last one only that.
 #pragma unroll
-        for (int t = 0; t < MAXT; ++t)
+    for (int t = 0; t < MAXT; ++t)
 #pragma unroll
-          for (int k = 0; k < KEEP; ++k) run[t][k] = fast_exp2(run[t][k]);
-        constexpr int STEP = LG == 1 ? 2 : 4;  // tiles whose loads go out together
-        if (q > 0 && q_n < p.N) {
-#pragma unroll
-          for (int t0 = 0; t0 < MAXT; t0 += STEP) {
-            vkeep old[STEP];
-#pragma unroll
-            for (int i = 0; i < STEP; ++i)
-              if (t0 + i < nt) old[i] = W::load_keep(place_of(t0 + i));
-#pragma unroll
-            for (int i = 0; i < STEP; ++i)
-              if (t0 + i < nt) run[t0 + i] += old[i];
+      for (int i = 0; i < 16; ++i) held[t][i] = 0.f;
+    Place done = cur;
+    bool live = true, folds = false, more = true;
+#pragma unroll 1
+    for (;;) {
+      f32x16 spare;
+      rm = -INFINITY;
+      rs = 0.f;
+      if (live) {
+        more = move_on(buf);
+        if (nt > 0) spare = w.template item_logits<0>(nt, M, buf, rm, rs);
+      }
+      float neg_lse2 = -INFINITY;
+      if (folds) neg_lse2 = -team_lse(done.s, done.l, done.g);
+      wide_static_for<0, MAXT>([&](auto tc) __attribute__((always_inline)) {
+        constexpr int t = decltype(tc)::value;
+        if (t < nt) {
+          fold(tc, w.c2, neg_lse2);
+          if (live) {
+            if constexpr (t == 0) held[0] = spare;
+            else held[t] = w.template item_logits<t>(nt, M, buf, rm, rs);
           }
         }
-      }
-#pragma unroll
-      for (int t = 0; t < MAXT; ++t) {
-        if (q_n < p.N && t < nt) W::store_keep(place_of(t), run[t]);
-#pragma unroll
-        for (int k = 0; k < KEEP; ++k) run[t][k] = -INFINITY;
-      }
+      });
+      if (folds) results(done, !live);
+      if (!live) break;
+      publish(cur.s, w.workgroup_lse(rm, rs, buf));
+      w.end_slab();
+      done = cur;
+      cur = nxt;
+      folds = true;
+      live = more;
+      buf ^= 1;
     }
-    w.end_slab();
-    if (!more) break;
-    q = nq; s = ns; s_end = ns_end; l = nl; g = ng;
-    buf ^= 1;
+  } else {
+    // The first item of the next slab is computed while the lines of this one travel (its logits wait in registers of
+    // their own), the other tiles' fold comes before its other products: 8-bit keys, which arithmetic bounds, take 219 us so
+    // at 32K keys of 32 layers of d = 128 and 139 at 33000 of 16 layers of d = 64, 227 and 146 in the order above.
+    f32x16 spare;
+    bool early = false;  // the first item of the slab at hand is in `spare`, its statistics in (rm, rs)
+#pragma unroll 1
+    for (;;) {
+      const bool more = move_on(buf);
+      if (early) {
+        held[0] = spare;
+      } else {
+        rm = -INFINITY;
+        rs = 0.f;
+        if (nt > 0) held[0] = w.template item_logits<0>(nt, M, buf, rm, rs);
+      }
+      w.template slab_logits<MAXT, 1>(held, nt, M, buf, rm, rs);
+      publish(cur.s, w.workgroup_lse(rm, rs, buf));
+      const float c2 = w.c2;
+      early = more && nt > 0;
+      if (early) {
+        rm = -INFINITY;
+        rs = 0.f;
+        w.slab_scale(nxt.l, nxt.g);
+        spare = w.template item_logits<0>(nt, M, buf ^ 1, rm, rs);
+      }
+      const float lse2 = team_lse(cur.s, cur.l, cur.g);
+      wide_static_for<0, MAXT>([&](auto tc) __attribute__((always_inline)) {
+        if (decltype(tc)::value < nt) fold(tc, c2, -lse2);
+      });
+      results(cur, !more);
+      w.end_slab();
+      if (!more) break;
+      cur = nxt;
+      buf ^= 1;
+    }
   }
   if (w.wave == 0 && expired && W::lane_id() == 0) atomicOr(p.status + (p.launch == kFirst ? 3u : epoch & 1u), 1u);
   wait_vmcnt<0>();

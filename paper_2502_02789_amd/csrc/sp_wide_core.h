@@ -310,7 +310,8 @@ struct WideKernel {
       return *reinterpret_cast<const vkeep*>(at);
     }
   }
-  __device__ __forceinline__ void fold_heads(const f32x16& a, float neg_lse2, float (&out)[KEEP]) const {
+  __device__ __forceinline__ void fold_heads(const f32x16& a, float neg_lse2, float (&out)[KEEP]) const { fold_heads(a, c2, neg_lse2, out); }
+  __device__ __forceinline__ static void fold_heads(const f32x16& a, float c2, float neg_lse2, float (&out)[KEEP]) {
     float y[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {  // lanes with col bit 4 clear keep keys 0..15's registers, the others 16..31's
