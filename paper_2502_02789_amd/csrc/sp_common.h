@@ -64,6 +64,16 @@ __device__ __forceinline__ int upper_segment(const int32_t* __restrict__ table, 
   return lo;
 }
 
+// The offsets table[0..B] of up to kStagedOffsets - 1 sequences copied to LDS (a search in memory is a chain of round trips to
+// L2), else the table itself.  Call with all threads of a workgroup of at least kStagedOffsets; synchronises them.
+constexpr int kStagedOffsets = 256;
+__device__ __forceinline__ const int32_t* staged_offsets(const int32_t* table, int B, int32_t* lds) {
+  if (B >= kStagedOffsets) return table;
+  if ((int)threadIdx.x <= B) lds[threadIdx.x] = table[threadIdx.x];
+  __syncthreads();
+  return lds;
+}
+
 // Exclusive prefix over per-sequence counts f(b), b in [0,B), by one workgroup; writes out[0..B].
 // Call with all threads of a 1024-thread block.
 template <typename F>

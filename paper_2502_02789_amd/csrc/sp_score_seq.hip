@@ -337,6 +337,8 @@ template <int NQ, int TOK, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void units_finish_kernel(const TiledDev p) {
   __shared__ float red[WAVES][NQ][TOK];
   __shared__ float prob[NQ][TOK];
+  __shared__ int32_t cu_lds[kStagedOffsets];
+  const int32_t* const cu = p.B > 1 ? staged_offsets(p.cu, p.B, cu_lds) : p.cu;
   constexpr int kParts = 64 * WAVES / TOK;
   const int k = threadIdx.x % TOK, part = threadIdx.x / TOK;
   const int64_t tok = (int64_t)blockIdx.x * TOK + k;
@@ -344,8 +346,8 @@ __global__ __launch_bounds__(64 * WAVES) void units_finish_kernel(const TiledDev
   const bool mean = p.layer_reduce != SP_LAYER_MAX;
   int n_groups = p.n_groups;
   if (inside && p.group_count) {  // (none for a sequence that was left out)
-    const int b = upper_segment(p.cu, p.B, (int)tok);
-    n_groups = p.cu[b + 1] - p.cu[b] > p.seq_limit ? 0 : p.group_count[b];
+    const int b = upper_segment(cu, p.B, (int)tok);
+    n_groups = cu[b + 1] - cu[b] > p.seq_limit ? 0 : p.group_count[b];
   }
   float v[NQ];
 #pragma unroll
@@ -394,8 +396,8 @@ __global__ __launch_bounds__(64 * WAVES) void units_finish_kernel(const TiledDev
   }
   __syncthreads();
   if (threadIdx.x >= TOK || !inside) return;
-  const int b = upper_segment(p.cu, p.B, (int)tok);
-  if (p.seq_limit > 0 && p.cu[b + 1] - p.cu[b] > p.seq_limit) {
+  const int b = upper_segment(cu, p.B, (int)tok);
+  if (p.seq_limit > 0 && cu[b + 1] - cu[b] > p.seq_limit) {
     p.scores[tok] = __uint_as_float(0x7FC00000u);
     return;
   }

@@ -150,14 +150,18 @@ __device__ __forceinline__ int select_chunks(const double* cs, int n, int k, int
   }
   least = wave_extreme<false>(least);
   most = wave_extreme<true>(most);
-  if (lane == 0) { sh[wave] = (int)least; sh[16 + wave] = (int)most; }
+  const int bad_wave = __ballot(bad != 0) != 0 ? 1 : 0;
+  if (lane == 0) { sh[wave] = (int)least; sh[16 + wave] = (int)most; sh[32 + wave] = bad_wave; }
   if (t == 0) few = 0;
-  if (__syncthreads_or(bad)) return -1;
+  for (int x = t; x < BINS + 64; x += 1024) hist[x] = 0;  // (for the first pass)
+  __syncthreads();
 #pragma unroll
   for (int w = 0; w < 16; ++w) {
     least = min(least, (uint32_t)sh[w]);
     most = max(most, (uint32_t)sh[16 + w]);
+    bad |= sh[32 + w];
   }
+  if (bad) return -1;  // (the same for all threads)
 
   // keys in play: lo .. lo + span; the k-th largest of all is the need-th largest of them
   uint64_t lo = (uint64_t)least << 32, span = ((uint64_t)(most - least) << 32) | 0xffffffffull;
@@ -167,8 +171,6 @@ __device__ __forceinline__ int select_chunks(const double* cs, int n, int k, int
   int kth_chunk = 0x7fffffff;
 #pragma unroll 1
   for (;;) {
-    for (int x = t; x < BINS + 64; x += 1024) hist[x] = 0;
-    __syncthreads();
 #pragma unroll
     for (int i = 0; i < I; ++i)
       if (reg_chunk<I>(i) < n && key[i] - lo <= span) {
@@ -249,6 +251,8 @@ __device__ __forceinline__ int select_chunks(const double* cs, int n, int k, int
       break;
     }
     shift = max(0, shift - LG_BINS);
+    __syncthreads();
+    for (int x = t; x < BINS + 64; x += 1024) hist[x] = 0;
     __syncthreads();
   }
 
@@ -345,13 +349,17 @@ __device__ __forceinline__ void select_emit_single(const SelDev& p, const double
     // tokens, pooling included: 15.6 us with a thread per chunk and every token looked at, 8.7 now.)
     __shared__ uint64_t kept_mask[kCountMaxChunks / 64];
     __shared__ unsigned char ahead[4][kCountMaxChunks];
-    int bad = 0;
-    if (t < n) {
-      const double v = cs[t];
-      bad = is_nan_bits(v) ? 1 : 0;
+    __shared__ int bad_wave[kCountMaxChunks / 64];
+    if (t < kCountMaxChunks) {
+      const double v = t < n ? cs[t] : 0.0;
+      const bool bad = __ballot(is_nan_bits(v)) != 0;
+      if ((t & 63) == 0) bad_wave[t >> 6] = bad ? 1 : 0;
       keys[t] = order_key(v);
     }
-    if (__syncthreads_or(bad)) {  // invalid scores: reported in band, nothing kept
+    __syncthreads();
+    int bad = 0;
+    for (int x = 0; x < kCountMaxChunks / 64; ++x) bad |= bad_wave[x];
+    if (bad) {  // invalid scores: reported in band, nothing kept
       if (t == 0) p.cu_keep[1] = -1;
       return;
     }
