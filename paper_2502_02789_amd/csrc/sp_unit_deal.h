@@ -76,10 +76,12 @@ inline UnitDeal make_unit_deal(const sp_score_args* a, int W, int limit, bool wh
   // Every workgroup between the first and the last that has a grain of a sequence must have one: no grain longer than a stretch.
   if (2 * held > stretch) return d;
   // A stretch is right to half a grain on either side, so four of the longest have to fit (busiest workgroup over 1500 random
-  // batches, median against the rounds: three to four 1.10, four to five 0.98, seven to ten 0.96, more 0.79); one sequence,
-  // whose grains are equal, gains as soon as there are more of them than workgroups.
+  // batches, median against the rounds: three to four 1.10, four to five 0.98, seven to ten 0.96, more 0.79); ten layers (five of
+  // them: 64 prompts of 1024..4096 keys, one query, 1730 us against 1673 in rounds); one sequence, whose grains are equal,
+  // gains as soon as there are more of them than workgroups.  (Mean over layers in parts of layers, as many as let four fit, every
+  // part a unit with a result of its own: 22 prompts of 1400..2100 keys, eight queries, 508 us against 432 in rounds.)
   const int64_t longest = std::min<int64_t>(a->B == 1 ? a->T : a->max_seqlen, a->T) + d.extra;
-  if (a->B == 1 ? d.grains <= W : 4 * 2 * longest > stretch) return d;
+  if (a->B == 1 ? d.grains <= W : (whole_layers ? 10 : 4) * 2 * longest > stretch) return d;
   d.stretch = stretch;
   d.inverse = 1.0 / (double)stretch;
   *n_groups = (int)std::min<int64_t>(W, 2 * (int64_t)(d.grains - 1) * held / stretch + 2);

@@ -34,14 +34,16 @@ def test_items_and_pairs(shape, paged):
         np.testing.assert_allclose(lse, want_lse, rtol=0, atol=2e-4)
 
 
-@pytest.mark.parametrize("n_queries,mode", [(1, orc.LAYER_MAX), (1, orc.LAYER_MEAN), (4, orc.LAYER_MAX), (8, orc.LAYER_MAX)])
-def test_stretches_of_equal_cost(n_queries, mode):
+@pytest.mark.parametrize("n_queries,mode,layers", [
+    (1, orc.LAYER_MAX, 32), (1, orc.LAYER_MEAN, 32), (1, orc.LAYER_MEAN, 128),  # (mean: in rounds, and in stretches of layers)
+    (4, orc.LAYER_MAX, 32), (8, orc.LAYER_MAX, 32), (8, orc.LAYER_MEAN, 32)])
+def test_stretches_of_equal_cost(n_queries, mode, layers):
     """Enough slabs for every workgroup to get a stretch of them: sequences that one workgroup has several of, that several
     share, that are empty, and one that breaks the promise (NaN, and nobody else is touched)."""
     lens = (700, 1, 0, 33, 650, 64, 300, 0, 257) * 6 + (699,)
     over = 8193 if n_queries == 1 else 4097 if n_queries == 2 else 3073
     for all_lens in (lens, lens[:20] + (over,) + lens[20:]):
-        w = synth.scaled(synth.workload(4), seqlens=all_lens, L=32, H=16, H_kv=4, N=n_queries, d=64, salient_frac=0.02, salient_run=1)
+        w = synth.scaled(synth.workload(4), seqlens=all_lens, L=layers, H=16, H_kv=4, N=n_queries, d=64, salient_frac=0.02, salient_run=1)
         inp = synth.make_qk(w)
         scale = 1.0 / math.sqrt(w.d)
         want, want_lse = orc.token_importance(inp["q"], inp["k"], inp["cu_seqlens"], scale, mode)

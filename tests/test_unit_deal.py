@@ -42,11 +42,11 @@ def lib(tmp_path_factory):
 
 def _cases():
     rng = random.Random(7)
-    for _ in range(40):
+    for _ in range(60):
         B = rng.choice([1, 2, 5, 16, 22, 64, 100])
         hi = rng.randint(200, 3072)
         lens = [rng.choice([0, 1, rng.randint(1, hi), rng.randint(hi // 2, hi), hi]) for _ in range(B)]
-        yield lens, hi, rng.choice([8, 16, 32, 80]), rng.choice([1, 4, 8]), rng.choice([64, 128]), rng.choice([0, 1]), rng.choice([256, 304, 64])
+        yield lens, hi, rng.choice([8, 16, 32, 80, 128]), rng.choice([1, 4, 8]), rng.choice([64, 128]), rng.choice([0, 1]), rng.choice([256, 304, 64])
 
 
 @pytest.mark.parametrize("whole", [0, 1])
