@@ -120,10 +120,22 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else int(t.data_ptr())
 
 
+_raw_stream = None  # (current stream of a device, current device), once torch has initialised the GPU
+
+
 def _stream_handle(stream) -> Optional[int]:
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream) or None
+    """The HIP handle of `stream`, or of the current device's current stream.  The latter is asked for directly from the second
+    call on: making a torch.cuda.Stream object of it took 2.9 us a call, more than a launch, and a pass makes two or three."""
+    global _raw_stream
+    if stream is not None:
+        return int(stream.cuda_stream) or None
+    if _raw_stream is None:
+        import torch
+        handle = int(torch.cuda.current_stream().cuda_stream)
+        _raw_stream = (torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+        return handle or None
+    current, device = _raw_stream
+    return current(device()) or None
 
 
 def _check(fn: str, status: int) -> None:
