@@ -34,7 +34,7 @@
 // keys 374 us with all running maxima in memory and 338 this way.  Both forms of the slab loop are in the kernel.
 // Bound by the HBM stream of K and, beyond 2304 keys, by the result writes.  Measured (32 layers, 8 KV heads, d = 128,
 // eight queries; two-pass or exchange kernels before): 16 ragged prompts of 300..3000 keys (1.73 GB) out of a paged
-// cache 1005 -> 340 us, one prompt of 3001 keys 138 -> 43 us (+ merge 9 us).  Neither the matrix cores nor the
+// cache 1005 -> 331 us, one prompt of 3001 keys 138 -> 43 us (+ merge 7 us).  Neither the matrix cores nor the
 // exponentials limit it (either taken out: no change).
 #include <mutex>
 

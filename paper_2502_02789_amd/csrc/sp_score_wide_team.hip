@@ -33,10 +33,9 @@
 // 24577 keys 520 -> 298, 100000 keys 2228 -> 1607, the other stream no slower; four such calls at once on four streams,
 // 24577 keys, 504 -> 294 us each.)
 //
-// Bound by the HBM stream of K for bf16 caches (32 layers, 8 KV heads, d = 128, eight queries, before -> now: 32K keys
-// 349 -> 336 us = 6.4 TB/s, mean over layers 30011 keys 375 -> 337, 128K keys 1570 -> 1301, 9000 keys 168 -> 117;
-// 16 layers, d = 64, 8K keys 61 -> 43: two slabs per workgroup, their start and end), by latency and vector
-// instructions for 8-bit caches (32K keys 238 -> 224 us with one-tile items and operands read ahead).
+// Bound by the HBM stream of K for bf16 caches (32 layers, 8 KV heads, d = 128, eight queries, kernel and merge in a filled
+// queue: 32K keys 342 us = 6.3 TB/s, mean over layers 30011 keys 319, 8192 keys 99; 16 layers, d = 64, 8K keys 40: two slabs
+// per workgroup, their start and end), by latency and vector instructions for 8-bit caches (32K keys 220 us).
 // Tried: polling by every wave instead of one and a barrier 355 against 350 us, polls that read the die's own L2 451.
 #include <atomic>
 #include <mutex>
