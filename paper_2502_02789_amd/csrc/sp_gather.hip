@@ -20,13 +20,12 @@ struct GatherDev {
   u32x4* out_embed;
 };
 
-// Bound by its dependent reads: a thread's first kept index is requested before the number of them is known (the list has
-// room for `capacity`), and the offsets of up to 255 sequences are searched in LDS (one sequence
-// 2.3 -> 2.1 us, 64 sequences 2.9 -> 2.5).
+// Bound by its dependent reads: the offsets of up to 255 sequences are searched in LDS (64 sequences 2.9 -> 2.5 us).  A kept
+// index is requested behind the number of them only: the list may end with the last one, it is the outputs that have room
+// for `capacity`.
 __global__ __launch_bounds__(256) void gather_meta_kernel(const GatherDev p) {
   __shared__ int32_t keep_lds[kStagedOffsets], cu_lds[kStagedOffsets];
   const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
-  const int ahead = first < p.capacity ? p.kept_idx[first] : 0;
   const bool staged = p.B < kStagedOffsets;
   if (staged) {
     if ((int)threadIdx.x <= p.B) {
@@ -42,7 +41,7 @@ __global__ __launch_bounds__(256) void gather_meta_kernel(const GatherDev p) {
     if (s < p.B) p.decode_pos[s] = cu[s + 1] - cu[s];
     if (s < n_keep) {
       const int b = upper_segment(cu_keep, p.B, (int)s);
-      const int idx = s == first ? ahead : p.kept_idx[s];
+      const int idx = p.kept_idx[s];
       p.kept_pos[s] = idx - cu[b];
       if (p.token_ids) p.kept_ids[s] = p.token_ids[idx];
     }

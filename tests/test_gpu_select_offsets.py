@@ -43,3 +43,37 @@ def test_one_invalid_score_keeps_nothing(B):
     scores[int(cu[-1]) - 7] = np.nan
     sel = hp.gpu_pool_select(scores, cu, 4, 1, 0.5, want_chunk_scores=False)
     assert sel.cu_keep.cpu().numpy()[0] == 0 and (sel.cu_keep.cpu().numpy()[1:] == -1).all()
+
+
+@pytest.mark.parametrize("B,embed", [(1, 0), (3, 0), (255, 0), (256, 0), (3, 64)])
+def test_gather_from_a_list_that_ends_with_the_last_kept_index(B, embed):
+    """sp_gather with a list of exactly cu_keep[B] indices and outputs of more room: what lies behind the list (here indices
+    that no prompt has) goes nowhere, and the outputs behind the kept tokens stay as they were."""
+    import torch
+    from paper_2502_02789_amd import binding as sp
+    rng = np.random.default_rng(B)
+    lens = rng.integers(0, 40, size=B)
+    lens[0] = 900
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T = int(cu[-1])
+    kept, cu_keep = orc.pool_select(rng.random(T).astype(np.float32), cu, 8, 3, 0.2)[:2]
+    ids = rng.integers(0, 100, size=T).astype(np.int32)
+    table = rng.integers(0, 2 ** 15, size=(100, embed or 8)).astype(np.int16)
+    n, cap = len(kept), len(kept) + 1500
+    room = torch.full((n + 2000,), 2 ** 31 - 1, dtype=torch.int32, device="cuda")
+    room[:n] = torch.from_numpy(kept.astype(np.int32)).cuda()
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    out = {k: torch.full((cap,), -7, dtype=torch.int32, device="cuda") for k in ("kept_pos", "kept_ids")}
+    decode = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+    rows = torch.full((cap, embed), 7, dtype=torch.int16, device="cuda").view(torch.bfloat16) if embed else None
+    keep = [dev(cu), dev(cu_keep.astype(np.int32)), room[:n], dev(ids), dev(table).view(torch.bfloat16) if embed else None]
+    sp.sp_gather(sp.make_gather_args(keep[0], keep[1], keep[2], out["kept_pos"], decode, token_ids=keep[3],
+                                     kept_ids=out["kept_ids"], embed=keep[4], out_embed=rows))
+    want_ids, want_pos, want_decode, want_rows = orc.gather(kept, cu_keep, cu, ids, table.view(np.uint16))
+    np.testing.assert_array_equal(out["kept_ids"].cpu().numpy()[:n], want_ids)
+    np.testing.assert_array_equal(out["kept_pos"].cpu().numpy()[:n], want_pos)
+    np.testing.assert_array_equal(decode.cpu().numpy(), want_decode)
+    assert (out["kept_ids"][n:] == -7).all() and (out["kept_pos"][n:] == -7).all()
+    if embed:
+        np.testing.assert_array_equal(rows.view(torch.int16).cpu().numpy().view(np.uint16)[:n], want_rows)
+        assert (rows.view(torch.int16)[n:] == 7).all()
