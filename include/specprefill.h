@@ -176,7 +176,8 @@ typedef struct {
                                 (token, head, page) still count ELEMENTS and must then be multiples of 16;
                                 rope_theta must be 0 (SP_EUNSUPPORTED otherwise).  The same kernels run as for a
                                 bf16 cache (half the bytes per pass).                                    */
-  const float* d_k_scale;    /* fp32 [L, H_kv] scales of an SP_K_FP8_E4M3 cache, or NULL (all 1)          */
+  const float* d_k_scale;    /* fp32 [L, H_kv] scales of an SP_K_FP8_E4M3 cache, finite, zero and negative ones
+                                included, or NULL (all 1)                                                  */
 } sp_score_args;
 
 /* Bytes of workspace sp_score needs for these shapes (pointers are not read).

@@ -89,6 +89,19 @@ struct SeqKernel : WideKernel<D, 2, FP8, PAGED> {
 #pragma unroll
     for (int t = 0; t < KS; ++t) qf[t] = this->read16(row + (FP8 ? 4 * (t >> 1) + (t & 1) + 2 * half : 2 * t + half) * 16);
   }
+  // As in the wide kernels, but with the key scale's sign (every logit is scaled before anything is compared with it), a zero
+  // being the least number of either sign.
+  __device__ __forceinline__ void slab_scale(int l, int g) {
+    this->c2 = this->p.c;
+    if constexpr (FP8) {
+      if (this->p.k_scale) {
+        const float ks = __int_as_float(scalar_table(reinterpret_cast<const int32_t*>(this->p.k_scale))[l * this->p.H_kv + g]);
+        this->c2 = copysignf(positive_scale(this->p.c, ks), ks);
+      }
+    }
+  }
+  // the unscaled logit of a key that does not exist
+  __device__ __forceinline__ float none() const { return FP8 ? -copysignf(INFINITY, this->c2) : -INFINITY; }
   // The next item's logits: rows 0..3 of key `col` in registers 0..3 of the lower half-wave, rows 4..7 in the upper one.
   __device__ __forceinline__ f32x16 item_rows() {
     const int later = this->sent - this->pos - 1;
@@ -191,13 +204,13 @@ __global__ __launch_bounds__(kTiledThreads) void seq_score_kernel(const TiledDev
         if (t == 0) {
           const int left = M - (w.wave + (nt - 1) * kTiledWaves) * 32 - (W::lane_id() & 31);  // > 0: the lane's key exists
 #pragma unroll
-          for (int i = 0; i < 4; ++i) a[i] = left > 0 ? a[i] : -INFINITY;
+          for (int i = 0; i < 4; ++i) a[i] = left > 0 ? a[i] : w.none();
         }
         if (2 * t + 1 < nt) {
           c = w.item_rows();
         } else {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) c[i] = -INFINITY;
+          for (int i = 0; i < 4; ++i) c[i] = w.none();
         }
         float x[R];
 #pragma unroll

@@ -69,6 +69,20 @@ __device__ __forceinline__ void wait_vmcnt_upto_wide(int n) {
   else wait_vmcnt_upto(n);
 }
 
+// An 8-bit cache's key scale may be zero (a head whose keys are all zero) or negative.  The statistics take maxima of unscaled
+// logits and mark keys that do not exist by -infinity in front of the scale, so what multiplies them has to be positive: the
+// scale's size, or the least positive number where that is 0.  Its sign, or the zero, goes into the products, in a branch that
+// is the same for the whole wave and as a rule not taken.
+__device__ __forceinline__ float positive_scale(float c, float ks) { return fmaxf(c * fabsf(ks), 1.401298464e-45f); }
+// `bits`: of the scale, in a scalar register
+__device__ __forceinline__ void odd_products(f32x16& a, int bits) {
+  if (bits <= 0) {
+    asm volatile("");  // (stays a branch)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) a[i] = (bits << 1) != 0 ? -a[i] : 0.f;
+  }
+}
+
 // FP8: the keys are OCP E4M3 bytes (one byte per element, a scale per layer and KV head); the query
 // rows stay bf16.  A key row is then half as long; its 16-byte units hold 16 elements, i.e. TWO MFMA
 // k-steps, so a lane reads whole units (upper half-wave: the odd ones), widens the bytes to bf16 in
@@ -97,6 +111,7 @@ struct TileWalker {
   uint32_t ring_lds, lse_lds, part_lds, rd0, u0;
   uint32_t krd0, qrd0;   // FP8: where this lane reads its key units / its query units from (ring slot 0)
   float c2, scale;        // logits -> base-2 / natural-log domain for the current slab (an 8-bit cache's key scale included)
+  int scale_bits;         // FP8: of the current slab's key scale
   int part_n;            // slabs waiting in the statistics buffer
   uint32_t ld_off[4];
   bf16x8 qf[KS];
@@ -138,6 +153,7 @@ struct TileWalker {
       ld_off[jj] = (uint32_t)((int64_t)i * p.ts * 2) + (uint32_t)((u0 ^ ((4 * jj) & (UNITS - 1))) << 4);
     c2 = p.c;
     scale = p.scale;
+    scale_bits = 1;
     krd0 = qrd0 = 0;
     if constexpr (FP8) {
       // key tile: row r at r*KROW_B, unit u at position u ^ (r & (KUNITS - 1)); the lane of a wave-wide load
@@ -153,9 +169,10 @@ struct TileWalker {
   __device__ __forceinline__ void slab_scale(int l, int g) {
     if constexpr (FP8) {
       if (p.k_scale) {
-        const float ks = p.k_scale[l * p.H_kv + g];
-        c2 = p.c * ks;
-        scale = p.scale * ks;
+        const float stored = p.k_scale[l * p.H_kv + g];
+        c2 = positive_scale(p.c, stored);
+        scale = positive_scale(p.scale, stored);
+        scale_bits = __builtin_amdgcn_readfirstlane(__float_as_int(stored));
       }
     }
   }
@@ -358,6 +375,7 @@ struct TileWalker {
 #pragma unroll
       for (int t = 0; t < KS; ++t)
         a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t], qf[t], a, 0, 0, 0);
+      odd_products(a, scale_bits);
       acc[kb] = a;
       return;
     }

@@ -57,6 +57,7 @@ struct WideKernel {
   uint32_t ld_row, ld_unit, krd0, qrd0;  // this lane's key and 16-byte unit in a load; where it reads its operands
   uint32_t ts_b;              // bytes from key to key (the host checks that a slot's keys span less than 2 GiB)
   float c2;
+  int scale_bits;             // FP8: of the key scale of the slab at hand
 
   // The stream of key items runs up to a ringful ahead of the arithmetic, on into the next slab: `ah` is where the
   // next request comes from, `nx` the slab behind the one being computed (`fresh`: not moved to yet).  A wave takes
@@ -84,6 +85,7 @@ struct WideKernel {
     const int qkey = (QU == 16) ? (col & 15) : ((col >> 1) & 7);
     qrd0 = qbuf + col * QROW_B + (((FP8 ? 2 * half : half) ^ qkey) << 4);
     c2 = p.c;
+    scale_bits = 1;
     sent = pos = 0;
     fresh = false;
   }
@@ -217,13 +219,16 @@ struct WideKernel {
   }
 
   // logits -> base-2 domain for (l, g), an 8-bit cache's key scale included (through the scalar cache, as a block table)
-  __device__ __forceinline__ float scale_of(int l, int g) const {
+  __device__ __forceinline__ void slab_scale(int l, int g) {
     if constexpr (FP8) {
-      if (p.k_scale) return p.c * __int_as_float(scalar_table(reinterpret_cast<const int32_t*>(p.k_scale))[l * p.H_kv + g]);
+      if (p.k_scale) {
+        scale_bits = scalar_table(reinterpret_cast<const int32_t*>(p.k_scale))[l * p.H_kv + g];
+        c2 = positive_scale(p.c, __int_as_float(scale_bits));
+        return;
+      }
     }
-    return p.c;
+    c2 = p.c;
   }
-  __device__ __forceinline__ void slab_scale(int l, int g) { c2 = scale_of(l, g); }
 
   __device__ __forceinline__ bf16x8 read16(uint32_t addr) const {
     return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(lds_ptr(addr));
@@ -363,10 +368,11 @@ struct WideKernel {
     // this one's; result stores there only make the wait stricter)
     const int later = sent - pos - 1;
     if (later == SLOTS - 1) wait_vmcnt<(SLOTS - 1) * LOADS>(); else wait_items(later);
-    const f32x16 a = mfma_tile(pos & (SLOTS - 1), buf);
+    f32x16 a = mfma_tile(pos & (SLOTS - 1), buf);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot's reads are done: it may be overwritten
     ++pos;
     refill();
+    if constexpr (FP8) odd_products(a, scale_bits);
     return a;
   }
   // Item IT of the wave's nt items of a slab: its logits, and the lane's row's statistics over the wave's keys so far:

@@ -198,3 +198,39 @@ def test_seeded_sweep_of_batch_shapes_bf16_and_8bit_against_the_plain_kernels():
         g, lg = s.scores.cpu().numpy(), s.lse.cpu().numpy()
         np.testing.assert_allclose(a, g, rtol=2e-3, atol=1e-30, err_msg=what)
         np.testing.assert_allclose(la, lg, rtol=1e-6, atol=2e-4, err_msg=what)
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("route", [
+    dict(lens=(333, 1, 65, 31, 700, 289) * 6, L=8, H=4, H_kv=1, N=1, d=128, max_seqlen=700),      # batch kernel, four rows
+    dict(lens=(333, 1, 65, 31, 700, 289) * 6, L=8, H=8, H_kv=1, N=1, d=64, max_seqlen=700),       # eight rows
+    dict(lens=(333, 1, 65, 31, 700, 289), L=8, H=16, H_kv=4, N=1, d=64, paged=16, max_seqlen=700),
+    dict(lens=(2000,), L=8, H=32, H_kv=8, N=8, d=128, exclusive_device=False),                    # whole sequence in a workgroup, 32 rows
+    dict(lens=(333, 1, 65, 31, 700, 289), L=4, H=16, H_kv=4, N=8, d=64, paged=16, max_seqlen=700),
+    dict(lens=(5003,), L=4, H=16, H_kv=4, N=8, d=128),                                            # teams of workgroups
+    dict(lens=(5003,), L=4, H=16, H_kv=4, N=8, d=64, exclusive_device=False),
+    dict(lens=(5003, 31, 700), L=2, H=16, H_kv=4, N=8, d=128, max_seqlen=5003),                   # two passes, query tile once per workgroup
+    dict(lens=(1003, 31, 700), L=2, H=16, H_kv=4, N=8, d=64),                                     # two passes over tiles
+    dict(lens=(1003, 31, 700), L=2, H=16, H_kv=4, N=1, d=128),                                    # kept logits
+    dict(lens=(1003, 31, 700), L=2, H=16, H_kv=4, N=8, d=128, general=True),                      # the plain kernels
+])
+def test_scales_that_are_zero_or_negative(route, mode):
+    """A head whose keys are all zero is stored with the scale amax / 448 = 0 and gives every key 1 / M; nothing says that a
+    scale is positive either.  Ragged lengths and odd numbers of 32-key items, so that keys that do not exist are masked."""
+    r = dict(route)
+    lens = r.pop("lens")
+    kw = {k: r.pop(k) for k in ("max_seqlen", "exclusive_device", "paged", "general") if k in r}
+    w = synth.scaled(synth.workload(4), seqlens=lens, salient_frac=0.02, salient_run=1, **r)
+    inp = synth.make_qk(w)
+    codes, usual = synth.quantize_k_fp8(inp["k"])
+    cu, scale = inp["cu_seqlens"], 1.0 / math.sqrt(w.d)
+    some, layer, least, none = (usual.copy() for _ in range(4))
+    some[0, 0], some[w.L - 1, w.H_kv - 1] = 0.0, -usual[w.L - 1, w.H_kv - 1]
+    layer[w.L // 2], layer[0] = 0.0, -usual[0]
+    least[w.L // 2] = 1.4e-45                                 # 2^-149: times the logit scale it is 0
+    none[:] = 0.0
+    for name, k_scale in (("some", some), ("layer", layer), ("least", least), ("none", none)):
+        want, want_lse = orc.token_importance(inp["q"], codes, cu, scale, mode, k_scale=k_scale)
+        got, lse = gpu_score_fp8(inp["q"], codes, k_scale, cu, w.H_kv, scale, mode, **kw)
+        hp.assert_scores_close(got, want, f"{route} {name} mode={mode}")
+        np.testing.assert_allclose(lse, want_lse, rtol=0, atol=2e-4, err_msg=f"{route} {name}")
