@@ -109,6 +109,7 @@ typedef enum { SP_K_BF16 = 0, SP_K_FP8_E4M3 = 1 } sp_k_dtype;
  *     SP_LAYER_MAX : score[i] = mean_{n < n_valid[b]} max_{l,h} a               (Sec. 3.2.2)
  *     SP_LAYER_MEAN: score[i] = mean_{n < n_valid[b]} mean_l max_h a
  * The softmax runs over the prompt keys of the token's own sequence only.
+ * Probabilities below 2^-126 (fp32's subnormal range) may count as 0.
  * Q and K are taken as stored by the draft model (already position-encoded) unless
  * rope_theta > 0 asks for the rotary encoding to be applied here.
  * --------------------------------------------------------------------------- */
@@ -279,7 +280,8 @@ SP_API sp_status sp_pool_select_static(const sp_pool_select_args* args, void* hi
  * sp_score_workspace_bytes(score) bytes as for sp_score (the logits pass through it; SP_EWORKSPACE
  * otherwise); select's workspace fields are ignored.  Outputs: everything the two calls write
  * (scores, optional lse, kept_idx, cu_keep, optional chunk_scores); scores agree with sp_score's
- * to the tolerance of fp32 summation order, the selection is sp_pool_select's on these scores.
+ * to the tolerance of fp32 summation order (probabilities below 2^-126, which sp_score may return as 0, keep their
+ * subnormal values here), the selection is sp_pool_select's on these scores.
  * The workgroups of the launch never wait for one another (the last one to finish its share
  * completes the call), so nothing depends on what else runs on the device; they do count their
  * arrivals in one word per device, so two of these calls must not overlap on one GPU.

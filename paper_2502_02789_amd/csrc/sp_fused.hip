@@ -211,8 +211,9 @@ __global__ __launch_bounds__(kFusedThreads) void fused_short_kernel(const FusedD
   // ---- phase 2b: the scores, one key per thread at a time ----
   const float denom = (p.layer_reduce == SP_LAYER_MAX) ? (float)nv : (float)nv * (float)p.L;
   // One query and the maximum over layers need none of the marks: a fifth of the code, which the one workgroup that is left
-  // fetches cold (two layers of two KV heads, d = 64, whole step in us, before -> now: 100 tokens 13.5 -> 12.4, 1000 17.4 ->
-  // 14.9, 2048 21.8 -> 17.8, a third of a microsecond of it the exponentials without the denormal results' extra code).
+  // fetches cold (two layers of two KV heads, d = 64, whole step in us, before -> now: 100 tokens 13.4 -> 12.4, 1000 17.3 ->
+  // 14.6, 2048 21.6 -> 17.5).  The probabilities keep their subnormal range (the bare instruction gives 0 below 2^-126, and
+  // chunks of such tokens would tie); the sums above, of terms of which one is 1, lose nothing by that.
   const bool plain = nv == 1 && p.layer_reduce == SP_LAYER_MAX;
   for (int key = tid; key < p.M; key += kFusedThreads) {
     float acc = 0.f;
@@ -235,7 +236,7 @@ __global__ __launch_bounds__(kFusedThreads) void fused_short_kernel(const FusedD
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) lm = fmaxf(lm, v[u] - lse[u]);
       }
-      acc = fast_exp2(lm);
+      acc = exp2f(lm);
     } else {
       float over_layers = (p.layer_reduce == SP_LAYER_MAX) ? -INFINITY : 0.f;
       float lm = -INFINITY;  // max over the layer's heads of log2 p
@@ -260,11 +261,11 @@ __global__ __launch_bounds__(kFusedThreads) void fused_short_kernel(const FusedD
           lm = fmaxf(lm, v[u] - lse[u]);
           if (entry[u] & kLayerEnds) {
             if (p.layer_reduce == SP_LAYER_MAX) over_layers = fmaxf(over_layers, lm);
-            else over_layers += fast_exp2(lm);
+            else over_layers += exp2f(lm);
             lm = -INFINITY;
           }
           if (entry[u] & kQueryEnds) {
-            acc += (p.layer_reduce == SP_LAYER_MAX) ? fast_exp2(over_layers) : over_layers;
+            acc += (p.layer_reduce == SP_LAYER_MAX) ? exp2f(over_layers) : over_layers;
             over_layers = (p.layer_reduce == SP_LAYER_MAX) ? -INFINITY : 0.f;
           }
         }

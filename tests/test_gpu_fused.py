@@ -125,3 +125,28 @@ def test_fused_refuses_what_one_workgroup_cannot_hold():
     other = torch.zeros(w.T, dtype=torch.float32, device="cuda")
     sel = dev.Selector(other, cu, chunk=32, pool_window=13, keep_rate=0.25)
     assert lib.sp_score_pool_select(C.byref(s.args), C.byref(sel.args), None) == sp.SP_EINVAL
+
+
+@pytest.mark.parametrize("mode", [orc.LAYER_MAX, orc.LAYER_MEAN])
+@pytest.mark.parametrize("N", [1, 2])
+def test_probabilities_in_the_subnormal_range(N, mode):
+    """One key takes all the attention, the others are 88 to 100 below it: probabilities of 6e-39 to 2e-44, which fp32 has with
+    fewer bits, but has; the kept tokens are those with the largest, not the first ones."""
+    w = synth.scaled(synth.workload(1), seqlens=(200,), H=4, H_kv=1, N=N, d=64, salient_frac=0.02, salient_run=1)
+    inp = synth.make_qk(w)
+    bits = lambda x: (np.float32(x).view(np.uint32) >> 16).astype(np.uint16)  # (of values that bf16 has)
+    inp["q"][:] = 0
+    inp["q"][..., 0], inp["q"][..., 1] = bits(8.0), bits(0.5)                # times 1 / sqrt(d): 1 and 1 / 16
+    below = np.arange(w.T)[::-1].astype(np.float32)
+    for k in inp["k"]:
+        k[:] = 0
+        k[1:, :, 0] = bits(-88.0)
+        k[1:, :, 1] = bits(-below)[1:, None]
+    want, _ = orc.token_importance(inp["q"], inp["k"], inp["cu_seqlens"], 1.0 / math.sqrt(w.d), mode)
+    assert 1e-44 < want.min() and want[1:].max() < 1.1e-38
+    s, sel = _run_fused(w, inp, mode, 1, 1, 0.3)
+    got = s.scores.cpu().numpy().astype(np.float64)
+    # 2^-149 is the spacing there: half of it a probability, half again the average over layers and queries; logits of 145 in
+    # base 2 rounded to 2^-24
+    np.testing.assert_allclose(got, want, rtol=2e-5, atol=1.5 * 2.0 ** -149)
+    assert sel.kept_idx[:60].cpu().tolist() == [0] + list(range(141, 200))
