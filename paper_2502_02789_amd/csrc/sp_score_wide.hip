@@ -60,6 +60,7 @@ __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDe
   w.ah = {w.slab_keys(l, g, cur.seq0), cur.b, 0, cur.M, w.items_of(cur.M)};
   w.issue_queries(l, g, cur.b, 0);
   w.start_stream();
+  w.first_queries();
 
   int slabs = 0;  // slabs finished so far
   bool more = true;
@@ -86,19 +87,26 @@ __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDe
       // end); requests move on to it when this slab's items have all been sent
       int nl = l, ng = g + 1;
       if (ng == p.H_kv) { ng = 0; ++nl; }
-      if (s + 1 == cur.s1) {
-        more = seq_next_unit<STRETCHES>(p, &nxt);
-        nl = __builtin_amdgcn_readfirstlane(nxt.s0 / p.H_kv);
-        ng = nxt.s0 - nl * p.H_kv;
-      }
       w.nx.left = 0;
-      if (more) {
-        w.nx = {w.slab_keys(nl, ng, nxt.seq0), nxt.b, 0, nxt.M, w.items_of(nxt.M)};
-        w.issue_queries(nl, ng, nxt.b, buf ^ 1);
+      // (In rounds the slab of the same unit has a way of its own, without what a next unit looks up: 128 prompts of 125..250
+      // keys, eight queries, 390 us with one set-up behind both ways, 359 so; 64 of 320..400 8-bit keys 229 and 222.  In
+      // stretches, where it is the other way round, one: 64 of 100..700 342 and 357.)
+      if (!STRETCHES && s + 1 < cur.s1) {
+        w.nx = {w.slab_keys(nl, ng, cur.seq0), b, 0, M, nt};
+        w.issue_queries(nl, ng, b, buf ^ 1);
+      } else {
+        if (s + 1 == cur.s1) {
+          more = seq_next_unit<STRETCHES>(p, &nxt);
+          nl = __builtin_amdgcn_readfirstlane(nxt.s0 / p.H_kv);
+          ng = nxt.s0 - nl * p.H_kv;
+        }
+        if (more) {
+          w.nx = {w.slab_keys(nl, ng, nxt.seq0), nxt.b, 0, nxt.M, w.items_of(nxt.M)};
+          w.issue_queries(nl, ng, nxt.b, buf ^ 1);
+        }
       }
       w.begin_slab();
       w.slab_scale(l, g);
-      if (slabs == 0) w.first_queries();
       float rm = -INFINITY, rs = 0.f;
       w.slab_logits(held, nt, M, buf, rm, rs);
       const float lse2 = w.workgroup_lse(rm, rs, buf);
