@@ -186,8 +186,10 @@ __global__ __launch_bounds__(kTiledThreads) void wide_score_kernel(const TiledDe
 // threads of a query meet in LDS.  Sequences the scoring kernel left out (longer than it holds) get NaN.
 // Bound by its dependent steps: the first eight rows of a thread are requested before anything else is looked at (they lie
 // in the result array whatever it says), a single sequence is not looked up, and rows are divided by the number of queries
-// with one reciprocal.
-template <int KEYS, int THREADS>
+// with one reciprocal.  LAYERS: the mean over layers from parts of layers, a kernel of its own (the look at what the rows are
+// would come in front of the first request of the other: 178 keys 13.6 -> 14.7 us).  Whole call, eight queries, before -> now:
+// mean over layers 700 keys 21.1 -> 19.9 us, 16 layers of d = 64, 1800 keys 20.9 -> 19.8; 28 layers, 224 results a tile, 700 keys 18.9 -> 17.2.
+template <int KEYS, int THREADS, bool LAYERS>
 __global__ __launch_bounds__(THREADS) void wide_finish_kernel(const TiledDev p, uint32_t* status) {
   constexpr int TPR = KEYS / 4;            // threads per row
   constexpr int ROWS = THREADS / TPR;      // rows per step
@@ -199,12 +201,21 @@ __global__ __launch_bounds__(THREADS) void wide_finish_kernel(const TiledDev p, 
   const int per = (int)(ROWS * inverse >> 16);           // groups (mean: layers) per step
   const int row = threadIdx.x / TPR, quad = threadIdx.x % TPR;
   const int g0 = (int)((uint32_t)row * inverse >> 16), n = row - g0 * p.N;
-  const bool by_layer = mean && p.groups_per_layer > 0;
   const int64_t step = (int64_t)p.N * 32;
   const float* src = p.group_scores + ((int64_t)tile * p.n_groups * p.N + n) * 32 + part * KEYS + quad * 4;
+  // What is requested ahead: rows of the thread's groups, or, where parts of layers are all there is, of its first layer (whole
+  // layers then are rows like the others, but logarithms).
+  const int gpl = LAYERS ? p.groups_per_layer : 1;
+  const bool layers_only = LAYERS && p.plain_groups == 0, logs = layers_only && gpl == 1;
+  int row0 = g0, apart = per, row_max = p.n_groups - 1;
+  if (layers_only && !logs) {
+    row0 = min(g0 * gpl, p.n_groups - gpl);
+    apart = 1;
+    row_max = row0 + gpl - 1;
+  }
   f32x4 ahead[AHEAD];
 #pragma unroll
-  for (int i = 0; i < AHEAD; ++i) ahead[i] = *reinterpret_cast<const f32x4*>(src + min(g0 + i * per, p.n_groups - 1) * step);
+  for (int i = 0; i < AHEAD; ++i) ahead[i] = *reinterpret_cast<const f32x4*>(src + min(row0 + i * apart, row_max) * step);
 
   int lo = 0, seq0 = 0, M = (int)p.T;
   if (p.B > 1) {                           // the sequence: the largest b whose first tile is <= tile
@@ -231,25 +242,53 @@ __global__ __launch_bounds__(THREADS) void wide_finish_kernel(const TiledDev p, 
   if (g0 < per) {
     auto take = [&](const f32x4& x) __attribute__((always_inline)) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) v[k] = mean ? v[k] + x[k] : fmaxf(v[k], x[k]);  // (mean: sums over a group's layers)
+      for (int k = 0; k < 4; ++k)
+        v[k] = mean ? v[k] + (logs ? fast_exp2(x[k]) : x[k]) : fmaxf(v[k], x[k]);  // (mean: sums over a group's layers)
     };
-    const int plain = by_layer ? p.plain_groups : n_groups;
+    const int plain = LAYERS && !logs ? p.plain_groups : n_groups;
 #pragma unroll
     for (int i = 0; i < AHEAD; ++i)
       if (g0 + i * per < plain) take(ahead[i]);
-#pragma unroll 8
-    for (int g = g0 + AHEAD * per; g < plain; g += per) take(*reinterpret_cast<const f32x4*>(src + g * step));
-    if (by_layer) {  // the groups of a layer hold the log2 of its maxima over their KV heads; the layers' maxima add up
-      const int layers = (p.n_groups - p.plain_groups) / p.groups_per_layer;
+    int g = g0 + AHEAD * per;
+    for (; g + (AHEAD - 1) * per < plain; g += AHEAD * per) {
+      f32x4 x[AHEAD];
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) x[i] = *reinterpret_cast<const f32x4*>(src + (g + i * per) * step);
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) take(x[i]);
+    }
+    if (g < plain) {  // (what is left, all at once: of 192 or 224 groups four or six rows, which a loop waits for one by one)
+      f32x4 x[AHEAD - 1];
+#pragma unroll
+      for (int i = 0; i < AHEAD - 1; ++i) x[i] = *reinterpret_cast<const f32x4*>(src + min(g + i * per, plain - 1) * step);
+#pragma unroll
+      for (int i = 0; i < AHEAD - 1; ++i)
+        if (g + i * per < plain) take(x[i]);
+    }
+    if (LAYERS && !logs) {  // the groups of a layer hold the log2 of its maxima over their KV heads; the layers' maxima add up
       src += p.plain_groups * step;
+      const int layers = (p.n_groups - p.plain_groups) / gpl;
       for (int l = g0; l < layers; l += per) {
         f32x4 m = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-#pragma unroll 4
-        for (int j = 0; j < p.groups_per_layer; ++j) {
-          const f32x4 x = *reinterpret_cast<const f32x4*>(src + (int64_t)(l * p.groups_per_layer + j) * step);
+        auto larger = [&](const f32x4& x) __attribute__((always_inline)) {
 #pragma unroll
           for (int k = 0; k < 4; ++k) m[k] = fmaxf(m[k], x[k]);
+        };
+        int j = 0;
+        if (layers_only && l == g0) {
+#pragma unroll
+          for (int i = 0; i < AHEAD; ++i) larger(ahead[i]);  // (fewer than eight: the last one again, which changes no maximum)
+          j = AHEAD;
         }
+        for (; j + AHEAD <= gpl; j += AHEAD) {
+          f32x4 x[AHEAD];
+#pragma unroll
+          for (int i = 0; i < AHEAD; ++i) x[i] = *reinterpret_cast<const f32x4*>(src + (int64_t)(l * gpl + j + i) * step);
+#pragma unroll
+          for (int i = 0; i < AHEAD; ++i) larger(x[i]);
+        }
+#pragma unroll 4
+        for (; j < gpl; ++j) larger(*reinterpret_cast<const f32x4*>(src + (int64_t)(l * gpl + j) * step));
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] += fast_exp2(m[k]);
       }
@@ -400,16 +439,23 @@ sp_status wide_score(const sp_score_args* a, const TiledDev& dev_, hipStream_t s
   return launch_wide_finish(dev, (unsigned)wide_tiles(a), nullptr, stream);
 }
 
-sp_status launch_wide_finish(const TiledDev& dev, unsigned tiles, uint32_t* status, hipStream_t stream) {
+template <bool LAYERS>
+static sp_status launch_finish(const TiledDev& dev, unsigned tiles, uint32_t* status, hipStream_t stream) {
   // A tile of many rows by 512 threads: 256 leave too little in flight, 1024 too few workgroups on a compute unit (whole
   // call with 256, 512 and 1024 threads, in us: 16 layers of d = 64, eight queries, 4096 keys 28.8, 27.8, 28.0, 12000 keys 51.5,
   // 51.3, 52.5; 32 layers of d = 128, 3001 keys 51.6, 50.2, 50.7, 8192 keys 101.2, 100.2, 100.8; with halves of tiles by 1024,
   // as up to 512 tiles before, 30.0, 54.8, 51.7, 103.5).  Of few rows by 256: 32K keys 340.7, 342.6, 352.8, one query on 12000 keys
-  // 134.6, 135.4, 137.3.  Halves of tiles where there are so few that compute units would have none: 700 keys 20.5 against 21.2.
-  if (dev.n_groups * dev.N <= 256 && dev.N <= 8) hipLaunchKernelGGL((wide_finish_kernel<32, 256>), dim3(tiles), dim3(256), 0, stream, dev, status);
-  else if (tiles < 48) hipLaunchKernelGGL((wide_finish_kernel<16, 512>), dim3(2 * tiles), dim3(512), 0, stream, dev, status);
-  else hipLaunchKernelGGL((wide_finish_kernel<32, 512>), dim3(tiles), dim3(512), 0, stream, dev, status);
+  // 134.6, 135.4, 137.3.  Halves of tiles where there are so few that compute units would have none (700 keys 20.5 against 21.2; 28
+  // layers of d = 64, 1900 keys 27.3 and 28.3, 2200 29.1 and 31.4; level at 2600).
+  if (dev.n_groups * dev.N <= 256 && dev.N <= 8) hipLaunchKernelGGL((wide_finish_kernel<32, 256, LAYERS>), dim3(tiles), dim3(256), 0, stream, dev, status);
+  else if (tiles < 72) hipLaunchKernelGGL((wide_finish_kernel<16, 512, LAYERS>), dim3(2 * tiles), dim3(512), 0, stream, dev, status);
+  else hipLaunchKernelGGL((wide_finish_kernel<32, 512, LAYERS>), dim3(tiles), dim3(512), 0, stream, dev, status);
   return launch_status();
+}
+
+sp_status launch_wide_finish(const TiledDev& dev, unsigned tiles, uint32_t* status, hipStream_t stream) {
+  return dev.layer_reduce != SP_LAYER_MAX && dev.groups_per_layer > 0 ? launch_finish<true>(dev, tiles, status, stream)
+                                                                      : launch_finish<false>(dev, tiles, status, stream);
 }
 
 }  // namespace sp

@@ -120,3 +120,15 @@ def test_one_prompt_of_many_slabs_with_and_without_the_promise(n_keys, mode):
                    layer_reduce=mode, keep_workspace=True)
     for _ in range(3):
         assert np.array_equal(s.run().cpu().numpy(), a)
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("lens, L, H_kv, N", [
+    ((300,), 24, 8, 8), ((300,), 28, 8, 8), ((2500,), 28, 8, 8),  # 192 and 224 results a tile: a step of eight rows a thread and a part of one
+    ((90,), 17, 8, 5), ((33,), 33, 8, 3),                         # queries that do not divide the rows of a step, one result beyond two steps
+    ((500,), 5, 16, 8), ((500,), 11, 6, 8), ((500,), 16, 4, 8),   # parts of a layer: two steps of eight, fewer than eight, four
+    (_lens(3, 60, 1, 90), 12, 2, 8), (_lens(4, 20, 1, 300), 16, 4, 4),  # whole layers and halves of layers as parts
+])
+def test_merge_of_results(lens, L, H_kv, N, mode):
+    w = synth.scaled(synth.workload(4), seqlens=lens, L=L, H=4 * H_kv, H_kv=H_kv, N=N, d=64, salient_frac=0.02, salient_run=1)
+    _check(w, synth.make_qk(w), mode, max_seqlen=max(lens))
