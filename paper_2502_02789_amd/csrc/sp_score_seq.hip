@@ -491,20 +491,7 @@ void seq_grouping(const sp_score_args* a, int* slabs_per_group, int* n_groups, i
       return;
     }
   }
-  const int step = a->layer_reduce == SP_LAYER_MEAN ? a->H_kv : 1;
-  const int slabs = a->L * a->H_kv;
-  // Units per workgroup (of 256): a unit's end costs several microseconds (its results go out, the next unit's
-  // table entries come in), so few large units are better as long as the workgroups' shares stay even, which
-  // takes more units the more sequences of different lengths there are.  Measured best (32 layers, 8 KV
-  // heads, prompts of 1K to 4K keys): 2 per workgroup for 16 prompts, 2 to 4 for 64, 8 for 256.
-  const int per_wg = std::min(8, std::max(2, a->B / 32));
-  const int target = 256 * per_wg;
-  int groups = std::min(slabs / step, (target + a->B - 1) / a->B);
-  groups = std::max(groups, 1);
-  int per = (slabs + groups - 1) / groups;
-  per = (per + step - 1) / step * step;
-  *slabs_per_group = per;
-  *n_groups = (slabs + per - 1) / per;
+  *n_groups = round_groups(a, a->layer_reduce == SP_LAYER_MEAN ? a->H_kv : 1, slabs_per_group);
 }
 // the longest sequence the caller vouches for (one sequence: its length is the host's to see)
 static int64_t seq_stated_max(const sp_score_args* a) { return a->B == 1 ? a->T : a->max_seqlen; }

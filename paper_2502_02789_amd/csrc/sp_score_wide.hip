@@ -371,13 +371,7 @@ void wide_grouping(const sp_score_args* a, int* slabs_per_group, int* n_groups, 
     *n_groups = a->L * *groups_per_layer;
     return;
   }
-  *groups_per_layer = 0;
-  const int slabs = a->L * a->H_kv;
-  const int per_wg = std::min(8, std::max(2, a->B / 32));
-  int groups = std::max(1, std::min(slabs, (256 * per_wg + a->B - 1) / a->B));
-  const int per = (slabs + groups - 1) / groups;
-  *slabs_per_group = per;
-  *n_groups = (slabs + per - 1) / per;
+  *n_groups = round_groups(a, 1, slabs_per_group);
 }
 
 static size_t wide_scores_bytes(const sp_score_args* a) {

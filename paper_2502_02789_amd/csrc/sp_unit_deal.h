@@ -60,6 +60,17 @@ struct UnitDeal {
   }
 };
 
+// Units dealt out in rounds: results per sequence, and slabs per unit (a multiple of `step`).  A unit's end costs several
+// microseconds (its results go out, the next unit's table entries come in), so few large units are better as long as the
+// workgroups' shares stay even, which takes more units the more sequences of different lengths there are.  Measured best (32 layers,
+// 8 KV heads, prompts of 1K to 4K keys): 2 per workgroup (of 256) for 16 prompts, 2 to 4 for 64, 8 for 256.
+inline int round_groups(const sp_score_args* a, int step, int* slabs_per_group) {
+  const int per_wg = std::min(8, std::max(2, a->B / 32)), slabs = a->L * a->H_kv;
+  const int groups = std::max(1, std::min(slabs / step, (256 * per_wg + a->B - 1) / a->B));
+  *slabs_per_group = ((slabs + groups - 1) / groups + step - 1) / step * step;
+  return (slabs + *slabs_per_group - 1) / *slabs_per_group;
+}
+
 // The cut for W workgroups; sequences longer than `limit` keys (what the kernel holds) are not scored.  *n_groups: results a
 // sequence may get, one from each workgroup that has a grain of it.  stretch = 0: not worth it, or not possible.
 inline UnitDeal make_unit_deal(const sp_score_args* a, int W, int limit, bool whole_layers, int* n_groups) {
@@ -77,11 +88,22 @@ inline UnitDeal make_unit_deal(const sp_score_args* a, int W, int limit, bool wh
   if (2 * held > stretch) return d;
   // A stretch is right to half a grain on either side, so four of the longest have to fit (busiest workgroup over 1500 random
   // batches, median against the rounds: three to four 1.10, four to five 0.98, seven to ten 0.96, more 0.79); ten layers (five of
-  // them: 64 prompts of 1024..4096 keys, one query, 1730 us against 1673 in rounds); one sequence, whose grains are equal,
-  // gains as soon as there are more of them than workgroups.  (Mean over layers in parts of layers, as many as let four fit, every
-  // part a unit with a result of its own: 22 prompts of 1400..2100 keys, eight queries, 508 us against 432 in rounds.)
+  // them: 64 prompts of 1024..4096 keys, one query, 1730 us against 1673 in rounds).  (Mean over layers in parts of layers, as many as let
+  // four fit, every part a unit with a result of its own: 22 prompts of 1400..2100 keys, eight queries, 508 us against 432 in rounds.)
+  // One sequence, whose grains are equal: stretches save results, not time, as long as a workgroup has two grains either way (eight
+  // queries, d = 64, 1300 keys: 288 slabs 32.9 us against 29.5 in rounds, 384 29.0 and 30.6).
   const int64_t longest = std::min<int64_t>(a->B == 1 ? a->T : a->max_seqlen, a->T) + d.extra;
-  if (a->B == 1 ? d.grains <= W : (whole_layers ? 10 : 4) * 2 * longest > stretch) return d;
+  if (a->B == 1 ? 2 * (int64_t)d.grains < 3 * (int64_t)W : (whole_layers ? 10 : 4) * 2 * longest > stretch) return d;
+  // A slab's time is that of the rounds of 256 keys that a workgroup's waves take, which no sum over the offsets knows: short
+  // prompts of different lengths are off by up to half.  Rounds of units even that out where there are many sequences and no round is left partly
+  // filled (32, 64, 96 or 128 of them; us, stretches and rounds, 32 layers, 8 KV heads, d = 128: 128 prompts of up to 400 keys,
+  // eight queries 1.21 of the time in rounds, 64 of 100..700, four queries 357 and 308, one query and 8-bit keys 303 and 239; 32 of
+  // 200..1000, 8-bit 157 and 147); of 1500 keys and more stretches are ahead again (64 of up to 1594 0.97), and with any other number of
+  // sequences (40 of 100..700 0.78..0.98, 48 0.75..0.97).  Of d = 64 from 96 sequences on (128 of up to 700, 8-bit 1.08; 32 0.91..1.03, 64
+  // 0.93..1.02).
+  int per = 1;
+  const int groups = round_groups(a, d.slabs, &per);
+  if (a->B >= (a->d == 64 ? 96 : 32) && a->max_seqlen <= 1408 && (int64_t)a->B * groups % W == 0) return d;
   d.stretch = stretch;
   d.inverse = 1.0 / (double)stretch;
   *n_groups = (int)std::min<int64_t>(W, 2 * (int64_t)(d.grains - 1) * held / stretch + 2);

@@ -83,3 +83,29 @@ def test_every_grain_once(lib, whole):
         assert max(groups) <= n_groups <= W
         assert max(load) <= stretch.value + 2 * (max(lens) + extra.value)
     assert dealt >= 10 if not whole else dealt >= 3
+
+
+def _stretch(lib, lens, L, H_kv, longest=0, fp8=0, d=128, N=8, limit=3072, W=256):
+    a = sp.ScoreArgs()
+    for k, v in dict(B=len(lens), N=N, L=L, H=4 * H_kv, H_kv=H_kv, d=d, T=sum(lens), max_seqlen=longest or max(lens), k_dtype=fp8).items():
+        setattr(a, k, v)
+    stretch, grains, extra = C.c_long(), C.c_int(), C.c_int()
+    lib.deal(C.byref(a), W, limit, 0, C.byref(stretch), C.byref(grains), C.byref(extra))
+    return stretch.value
+
+
+@pytest.mark.parametrize("fp8", [0, 1])
+@pytest.mark.parametrize("B, lo, hi, stretches", [
+    (32, 200, 1000, False), (64, 100, 700, False), (96, 64, 308, False), (128, 72, 268, False),  # whole rounds of short prompts
+    (40, 100, 700, True), (48, 200, 1000, True), (100, 100, 300, True), (22, 1400, 2100, True),   # a round partly filled
+    (16, 300, 3000, True), (8, 200, 1277, True), (64, 1024, 3072, True), (32, 1000, 1500, True)])  # few prompts, long ones
+def test_whole_rounds_of_short_prompts_stay_rounds(lib, B, lo, hi, stretches, fp8):
+    rng = random.Random(B)
+    lens = [hi] + [rng.randint(lo, hi) for _ in range(B - 1)]
+    assert (_stretch(lib, lens, 32, 8, fp8=fp8) != 0) == stretches
+    assert (_stretch(lib, lens, 32, 8, fp8=fp8, d=64) != 0) == (stretches or B < 96)  # (a slab takes half the time)
+
+
+@pytest.mark.parametrize("L, stretches", [(32, False), (33, False), (36, False), (47, False), (48, True), (64, True)])
+def test_one_sequence_is_cut_into_stretches_from_three_slabs_for_two_workgroups_on(lib, L, stretches):
+    assert (_stretch(lib, [2300], L, 8) != 0) == stretches
