@@ -207,15 +207,20 @@ __global__ __launch_bounds__(THREADS) void wide_finish_kernel(const TiledDev p, 
   // layers then are rows like the others, but logarithms).
   const int gpl = LAYERS ? p.groups_per_layer : 1;
   const bool layers_only = LAYERS && p.plain_groups == 0, logs = layers_only && gpl == 1;
-  int row0 = g0, apart = per, row_max = p.n_groups - 1;
-  if (layers_only && !logs) {
-    row0 = min(g0 * gpl, p.n_groups - gpl);
-    apart = 1;
-    row_max = row0 + gpl - 1;
-  }
+  // Parts of a layer are taken eight at a time: two layers (the thread's next one lies `per` behind) of up to four parts, or one.
+  const bool pairs = gpl <= 4;
+  auto part_row = [&](int l, int j, int i) __attribute__((always_inline)) {  // (i: which of eight; beyond the last layer or part that one again)
+    const int first = min((pairs && i >= 4 ? l + per : l) * gpl, p.n_groups - p.plain_groups - gpl);
+    return first + min(pairs ? i & 3 : j + i, gpl - 1);
+  };
   f32x4 ahead[AHEAD];
+  if (layers_only && !logs) {
 #pragma unroll
-  for (int i = 0; i < AHEAD; ++i) ahead[i] = *reinterpret_cast<const f32x4*>(src + min(row0 + i * apart, row_max) * step);
+    for (int i = 0; i < AHEAD; ++i) ahead[i] = *reinterpret_cast<const f32x4*>(src + part_row(g0, 0, i) * step);
+  } else {
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) ahead[i] = *reinterpret_cast<const f32x4*>(src + min(g0 + i * per, p.n_groups - 1) * step);
+  }
 
   int lo = 0, seq0 = 0, M = (int)p.T;
   if (p.B > 1) {                           // the sequence: the largest b whose first tile is <= tile
@@ -268,29 +273,27 @@ __global__ __launch_bounds__(THREADS) void wide_finish_kernel(const TiledDev p, 
     if (LAYERS && !logs) {  // the groups of a layer hold the log2 of its maxima over their KV heads; the layers' maxima add up
       src += p.plain_groups * step;
       const int layers = (p.n_groups - p.plain_groups) / gpl;
-      for (int l = g0; l < layers; l += per) {
-        f32x4 m = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-        auto larger = [&](const f32x4& x) __attribute__((always_inline)) {
-#pragma unroll
-          for (int k = 0; k < 4; ++k) m[k] = fmaxf(m[k], x[k]);
-        };
-        int j = 0;
-        if (layers_only && l == g0) {
-#pragma unroll
-          for (int i = 0; i < AHEAD; ++i) larger(ahead[i]);  // (fewer than eight: the last one again, which changes no maximum)
-          j = AHEAD;
-        }
-        for (; j + AHEAD <= gpl; j += AHEAD) {
+      for (int l = g0; l < layers; l += pairs ? 2 * per : per) {
+        f32x4 m[2] = {{-INFINITY, -INFINITY, -INFINITY, -INFINITY}, {-INFINITY, -INFINITY, -INFINITY, -INFINITY}};
+        for (int j = 0; j < gpl; j += AHEAD) {
           f32x4 x[AHEAD];
+          if (layers_only && l == g0 && j == 0) {
 #pragma unroll
-          for (int i = 0; i < AHEAD; ++i) x[i] = *reinterpret_cast<const f32x4*>(src + (int64_t)(l * gpl + j + i) * step);
+            for (int i = 0; i < AHEAD; ++i) x[i] = ahead[i];
+          } else {
 #pragma unroll
-          for (int i = 0; i < AHEAD; ++i) larger(x[i]);
+            for (int i = 0; i < AHEAD; ++i) x[i] = *reinterpret_cast<const f32x4*>(src + part_row(l, j, i) * step);
+          }
+#pragma unroll
+          for (int i = 0; i < AHEAD; ++i)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) m[i / 4][k] = fmaxf(m[i / 4][k], x[i][k]);
         }
-#pragma unroll 4
-        for (; j < gpl; ++j) larger(*reinterpret_cast<const f32x4*>(src + (int64_t)(l * gpl + j) * step));
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] += fast_exp2(m[k]);
+        for (int k = 0; k < 4; ++k) {
+          if (!pairs) v[k] += fast_exp2(fmaxf(m[0][k], m[1][k]));
+          else v[k] += fast_exp2(m[0][k]) + (l + per < layers ? fast_exp2(m[1][k]) : 0.f);
+        }
       }
     }
   }
@@ -439,10 +442,11 @@ static sp_status launch_finish(const TiledDev& dev, unsigned tiles, uint32_t* st
   // call with 256, 512 and 1024 threads, in us: 16 layers of d = 64, eight queries, 4096 keys 28.8, 27.8, 28.0, 12000 keys 51.5,
   // 51.3, 52.5; 32 layers of d = 128, 3001 keys 51.6, 50.2, 50.7, 8192 keys 101.2, 100.2, 100.8; with halves of tiles by 1024,
   // as up to 512 tiles before, 30.0, 54.8, 51.7, 103.5).  Of few rows by 256: 32K keys 340.7, 342.6, 352.8, one query on 12000 keys
-  // 134.6, 135.4, 137.3.  Halves of tiles where there are so few that compute units would have none (700 keys 20.5 against 21.2; 28
-  // layers of d = 64, 1900 keys 27.3 and 28.3, 2200 29.1 and 31.4; level at 2600).
+  // 134.6, 135.4, 137.3.  Halves of tiles where there are so few that compute units would have none: 700 keys 20.5 against 21.2;
+  // of 1792 rows a tile (28 layers of d = 64, eight queries) 1900 keys 26.1 and 28.3, 2200 28.1 and 31.4, level at 2600, 82 tiles; of 1024 rows
+  // (32 layers of d = 128, four queries) level at 1300, 2200 35.8 and 35.2.
   if (dev.n_groups * dev.N <= 256 && dev.N <= 8) hipLaunchKernelGGL((wide_finish_kernel<32, 256, LAYERS>), dim3(tiles), dim3(256), 0, stream, dev, status);
-  else if (tiles < 72) hipLaunchKernelGGL((wide_finish_kernel<16, 512, LAYERS>), dim3(2 * tiles), dim3(512), 0, stream, dev, status);
+  else if (tiles < (dev.n_groups * dev.N > 1024 ? 77 : 48)) hipLaunchKernelGGL((wide_finish_kernel<16, 512, LAYERS>), dim3(2 * tiles), dim3(512), 0, stream, dev, status);
   else hipLaunchKernelGGL((wide_finish_kernel<32, 512, LAYERS>), dim3(tiles), dim3(512), 0, stream, dev, status);
   return launch_status();
 }
