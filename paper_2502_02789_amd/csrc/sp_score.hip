@@ -296,16 +296,29 @@ static int general_max_tiles(const sp_score_args* a) { return (int)(a->T / kTile
 // on the kernels that also take un-rotated caches: their scores are then bit for bit those of the same cache stored
 // un-rotated.  3500 keys, 8 KV heads, d = 128, whole step: 32 layers, eight queries 109 us in two passes, 72 here; one
 // query with d = 64 and 16 layers 61 us with the logits kept in memory, 40 here; nothing tried beyond was slower.)
+// One prompt of 2048 to 3072 keys on an idle device: a workgroup to a slab (sp_score_wide.hip), with no exchange at all but every
+// slab's results written out, or two, which halve the results.  Two cost 1.6 us for the start of their exchange where the caller does not
+// keep the workspace (whose promise must not change the way), and are ahead, without it, (us, one and two, eight queries unless said)
+//   - where a workgroup to a slab leaves half of the compute units without one in its last round: 16 layers, 8 KV heads, d = 128, 2048 keys
+//     27.0 and 25.9, 3072 35.6 and 31.3; 40 layers 50.8 and 46.2, 74 and 59; 36 of d = 64 44.5 and 35.6, 8-bit 41.2 and 36.7; of 16 layers of d = 64
+//     from 2800 keys on (2048 21.6 and 23.8, 2600 24.5 and 25.1, 2800 25.7 and 25.4; 8-bit keys 23.8 and 21.1, 28.2 and 25.6).  But not for the mean over
+//     more layers than one round has, of which some are cut into parts (40 layers, four queries, 2048 keys 46.8 and 53.8);
+//   - where both fill every round, bf16 keys and results enough: 32 layers, 8 KV heads, d = 128, 2048 keys 38.3 and 36.6, 3072
+//     50.5 and 46.9; six queries level from 2300, four from 2600 on (8-bit keys 25.0 and 28.4, 32.3 and 34.8); of d = 64, a slab half as long, later.
+// In between (24 layers 32.2 and 35.7, 28 of d = 64 29.2 and 31.0) two workgroups to a slab take a round more than half.
+// (Below 128 slabs one short prompt keeps the same scores, bit for bit, with and without the promise.)
+static bool two_to_a_slab(const sp_score_args* a) {
+  const int W = seq_cu_count(), slabs = a->L * a->H_kv, last = slabs % W;
+  if (!(a->flags & SP_SCORE_EXCLUSIVE_DEVICE) || a->B != 1 || a->T < 2048 || slabs < 128) return false;
+  const bool fp8 = a->k_dtype == SP_K_FP8_E4M3;
+  if (last == 0) return !fp8 && a->T + 144 * a->N >= (a->d == 64 ? 3900 : 3170);
+  if (last > W / 2 || (a->layer_reduce == SP_LAYER_MEAN && slabs > W)) return false;
+  return fp8 || a->d == 128 || slabs > W || a->T >= 2800;
+}
+
 bool single_pass_wanted(const sp_score_args* a) {
-  const bool exclusive = (a->flags & SP_SCORE_EXCLUSIVE_DEVICE) != 0;
-  // The batch kernels keep a sequence's logits inside a workgroup and need no exchange at all, but every slab's results go
-  // out by themselves.  From 2048 keys on, two workgroups to a slab, whose results are half as many, are ahead on an idle
-  // device: 32 layers, 8 KV heads, d = 128, eight queries, 1500 keys 30.4 us and 30.6 by teams, 2048 38.7 and 35.1, 3001 50.6
-  // and 45.4 (8-bit keys 36.2 and 35.1, four queries 45.1 and 43.0); 16 layers of d = 64, 2048 keys 22.0 and 21.2, 3001 28.3
-  // and 24.1.  (Below 128 slabs one short prompt keeps the same scores, bit for bit, with and without the promise.)
-  const bool pairs = exclusive && a->B == 1 && a->T >= 2048 && (int64_t)a->L * a->H_kv >= 128;
-  if (tiled_supported(a) && (seq_supported(a) || (wide_supported(a) && !pairs))) return false;
-  return (exclusive || a->T > 3072) && wide_team_supported(a);
+  if (tiled_supported(a) && (seq_supported(a) || (wide_supported(a) && !two_to_a_slab(a)))) return false;
+  return ((a->flags & SP_SCORE_EXCLUSIVE_DEVICE) != 0 || a->T > 3072) && wide_team_supported(a);
 }
 
 size_t general_workspace_bytes(const sp_score_args* a, bool with_tiled) {

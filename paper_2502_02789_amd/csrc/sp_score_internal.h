@@ -94,4 +94,6 @@ size_t wide_team_status_offset(const sp_score_args* a);
 // single-launch scoring + selection of one short prompt (sp_fused.hip); 0 if the shape is not covered
 size_t fused_workspace_bytes(const sp_score_args* a);
 
+int seq_cu_count();  // compute units of the current device (256 where there is none)
+
 }  // namespace sp

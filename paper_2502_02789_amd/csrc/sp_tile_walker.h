@@ -600,7 +600,6 @@ size_t wide_workspace_bytes(const sp_score_args* a);
 sp_status wide_score(const sp_score_args* a, const TiledDev& dev, hipStream_t stream);
 size_t wide_passes_workspace_bytes(const sp_score_args* a);
 sp_status wide_passes_score(const sp_score_args* a, const TiledDev& dev, void* extra, hipStream_t stream);
-int seq_cu_count();
 // what the units of a call need: dev->deal is set, `words` has room for B
 void prepare_units(const sp_score_args* a, TiledDev* dev, int32_t* words, int limit, hipStream_t stream);
 sp_status launch_units_finish(const TiledDev& dev, hipStream_t stream);
