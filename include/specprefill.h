@@ -72,11 +72,17 @@ typedef enum { SP_K_BF16 = 0, SP_K_FP8_E4M3 = 1 } sp_k_dtype;
 /* sp_score_args.flags */
 #define SP_SCORE_EXCLUSIVE_DEVICE 1u /* The caller promises that nothing else runs on the GPU while
                                         sp_score runs (no other stream, no other process).  The
-                                        single-pass kernels for one long prompt read the K cache
-                                        once but exchange softmax row statistics between
+                                        single-pass kernels that share one prompt among workgroups
+                                        read the K cache once but exchange softmax row statistics between
                                         workgroups that must all be resident together; with the
                                         flag they wait for one another as long as that can
-                                        sensibly take.  If the promise is broken a bounded wait can
+                                        sensibly take.  That may concern one prompt of more than 3072 keys,
+                                        from 2048 keys on where layers times KV heads are 128 or more,
+                                        and of any length where they are fewer than 64; no other call
+                                        waits.  (From 3073 keys on the same kernels run without the
+                                        flag; below, scores with and without it agree to the
+                                        tolerance of fp32 summation order, not bit for bit.)
+                                        If the promise is broken a bounded wait can
                                         expire; the call's scores are then NaN (see
                                         sp_score_check and sp_pool_select), never silently
                                         wrong.

@@ -9,6 +9,9 @@ import pytest
 from oracle import specprefill_oracle as orc
 from paper_2502_02789_amd import synth
 from tests import helpers as hp
+from tests import test_gpu_fp8_cache as fp8
+from tests.test_gpu_batch_single_pass import _check
+from tests.test_unit_deal import _stretch, lib  # noqa: F401 (lib: a fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -56,3 +59,20 @@ def test_stretches_of_equal_cost(n_queries, mode, layers):
         hp.assert_scores_close(got[ok], want[ok], f"{n_queries} mode={mode}")
         keep = [b for b in range(len(all_lens)) if all_lens[b] != over]
         np.testing.assert_allclose(lse[:, keep], want_lse[:, keep], rtol=0, atol=2e-4)
+
+
+@pytest.mark.parametrize("shape, bits, paged", [
+    (dict(H=16, N=2, d=64), 16, 16), (dict(H=16, N=2, d=64), 8, 0), (dict(H=32, N=1, d=128), 16, 0), (dict(H=32, N=1, d=128), 8, 16),  # eight rows
+    (dict(H=16, N=1, d=128, L=28), 16, 16), (dict(H=16, N=1, d=64, L=28), 8, 16),                                                      # four
+    (dict(H=16, N=8, d=128), 16, 16), (dict(H=16, N=8, d=128), 8, 0), (dict(H=16, N=8, d=64), 8, 16),  # the kernel for 32 rows, four ...
+    (dict(H=32, N=4, d=128), 16, 0), (dict(H=32, N=4, d=128), 8, 16), (dict(H=32, N=4, d=64), 16, 16)])  # ... and eight heads per KV head
+def test_stretches_in_every_form_of_the_kernels(lib, shape, bits, paged):  # noqa: F811
+    """Eight and 32 rows, both head dims, pages and 8-bit keys; the batch is one that is cut into stretches."""
+    lens = (700, 1, 0, 33, 650, 64, 300, 0, 257) * 6 + (699,)
+    w = synth.scaled(synth.workload(4), seqlens=lens, salient_frac=0.02, salient_run=1, **dict(dict(L=16, H_kv=4), **shape))
+    rows = (4 if w.H <= 16 else 8) * w.N
+    assert _stretch(lib, lens, w.L, w.H_kv, fp8=int(bits == 8), d=w.d, N=w.N, limit=8192 if rows <= 4 else 4096 if rows <= 8 else 3072) != 0
+    if bits == 8:
+        fp8._check(w, orc.LAYER_MAX, False, max_seqlen=700, paged=paged)
+    else:
+        _check(w, synth.make_qk(w), orc.LAYER_MAX, max_seqlen=700, paged=paged)

@@ -132,3 +132,24 @@ def test_one_prompt_of_many_slabs_with_and_without_the_promise(n_keys, mode):
 def test_merge_of_results(lens, L, H_kv, N, mode):
     w = synth.scaled(synth.workload(4), seqlens=lens, L=L, H=4 * H_kv, H_kv=H_kv, N=N, d=64, salient_frac=0.02, salient_run=1)
     _check(w, synth.make_qk(w), mode, max_seqlen=max(lens))
+
+
+@pytest.mark.parametrize("n_keys, L, H_kv, N, waits", [
+    (2047, 16, 8, 8, False), (2800, 16, 8, 8, True), (2048, 36, 8, 8, True), (3072, 24, 8, 8, False), (2048, 15, 8, 8, False),
+    (3073, 24, 8, 8, True), (500, 8, 8, 8, False), (500, 7, 8, 8, True), (3000, 40, 8, 1, False)])
+def test_which_calls_may_wait_on_the_promise_of_an_idle_device(n_keys, L, H_kv, N, waits):
+    """With no polls allowed a call that waits for other workgroups has NaN scores, the others do not notice."""
+    import torch
+    from paper_2502_02789_amd import binding as sp, device as dev
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n_keys)
+    q = torch.randn((L, 1, N, 4 * H_kv, 64), device="cuda", generator=g).to(torch.bfloat16)
+    ks = [torch.randn((n_keys, H_kv, 64), device="cuda", generator=g).to(torch.bfloat16) for _ in range(L)]
+    s = dev.Scorer(q, ks, torch.tensor([0, n_keys], dtype=torch.int32, device="cuda"), H_kv=H_kv, scale=0.125, exclusive_device=True)
+    before = sp.sp_set_wait_budget(0)
+    try:
+        got = s.run().clone()
+        torch.cuda.synchronize()
+    finally:
+        sp.sp_set_wait_budget(before)
+    assert bool(torch.isnan(got).all()) if waits else bool(torch.isfinite(got).all())
