@@ -351,7 +351,7 @@ bool wide_supported(const sp_score_args* a) {
   // queries: 500 keys 15 us against 23, 3000 keys 32 against 33; d = 64 13 against 18, 26 against 27).  The teams of
   // workgroups that the promise of an idle device allows would be ahead of both for 64 units beyond some 1000 keys too (3000
   // keys: 22 us); there they are not taken, so that one short prompt has the same scores, bit for bit, with and without the
-  // promise (from 128 units and 2048 keys on they are, single_pass_wanted).
+  // promise (from 128 units and 2048 keys on they may be, two_to_a_slab in sp_score.hip).
   if ((int64_t)a->B * a->L * a->H_kv < 64) return false;
   return true;
 }

@@ -12,8 +12,8 @@
 // workgroups a third unit where others have two, need a launch to rank the sequences and write twice as many results (whole
 // call, 32 layers, 8 KV heads, d = 128, before -> now in us): 12 prompts of 2656..3949 keys, one query 461 -> 407; 18 of
 // 1430..1988 406 -> 338; 22 of 1400..2100, eight queries 499 -> 400; 6 of 858..1723 111 -> 94; 56 of 596..1269, one query 631
-// -> 534; 64 of 1024..4096 1671 -> 1655; 16 of 300..3000, eight queries 335 -> 331, the same with 8-bit keys, which arithmetic
-// in rounds of 256 keys bounds, 210 -> 214, the one slower shape tried but 7 of 296..2444 (131 -> 135).
+// -> 534; 64 of 1024..4096 1671 -> 1655; 16 of 300..3000, eight queries 335 -> 331, 8-bit keys 200 -> 193; 7 of
+// 296..2444, 8-bit 67 -> 64.  Where rounds come out even and prompts are short it is the other way round (make_unit_deal).
 #pragma once
 
 #include <stdint.h>
