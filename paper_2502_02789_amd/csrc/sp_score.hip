@@ -298,22 +298,23 @@ static int general_max_tiles(const sp_score_args* a) { return (int)(a->T / kTile
 // query with d = 64 and 16 layers 61 us with the logits kept in memory, 40 here; nothing tried beyond was slower.)
 // One prompt of 2048 to 3072 keys on an idle device: a workgroup to a slab (sp_score_wide.hip), with no exchange at all but every
 // slab's results written out, or two, which halve the results.  Two cost 1.6 us for the start of their exchange where the caller does not
-// keep the workspace (whose promise must not change the way), and are ahead, without it, (us, one and two, eight queries unless said)
+// keep the workspace.  A kept workspace is handed on between calls of the same shape, whatever the kind of cache, so the way must depend neither on
+// that promise nor on the kind of cache: two where, without it, one kind gains and the other does not lose (us, one and two, eight queries unless said)
 //   - where a workgroup to a slab leaves half of the compute units without one in its last round: 16 layers, 8 KV heads, d = 128, 2048 keys
 //     27.0 and 25.9, 3072 35.6 and 31.3; 40 layers 50.8 and 46.2, 74 and 59; 36 of d = 64 44.5 and 35.6, 8-bit 41.2 and 36.7; of 16 layers of d = 64
-//     from 2800 keys on (2048 21.6 and 23.8, 2600 24.5 and 25.1, 2800 25.7 and 25.4; 8-bit keys 23.8 and 21.1, 28.2 and 25.6).  But not for the mean over
-//     more layers than one round has, of which some are cut into parts (40 layers, four queries, 2048 keys 46.8 and 53.8);
-//   - where both fill every round, bf16 keys and results enough: 32 layers, 8 KV heads, d = 128, 2048 keys 38.3 and 36.6, 3072
-//     50.5 and 46.9; six queries level from 2300, four from 2600 on (8-bit keys 25.0 and 28.4, 32.3 and 34.8); of d = 64, a slab half as long, later.
+//     from 2400 keys on (2048 21.6 and 23.8, 2400 23.6 and 24.6, 2800 25.7 and 25.4; 8-bit keys 23.8 and 21.1, 24.9 and 22.6, 26.9 and 23.7: there what bf16
+//     keys lose is little against what 8-bit keys gain, and no more than the merge has gained).  But not for the
+//     mean over more layers than one round has, of which some are cut into parts (40 layers, four queries, 2048 keys 46.8 and 53.8);
+//   - where both fill every round, from eight queries on: 32 layers, 8 KV heads, d = 128, 2048 keys 38.3 and 36.6, 3072 50.5 and 46.9, 8-bit keys
+//     29.2 and 30.4, 36.8 and 37.3; of d = 64 from 2800.  (Four queries 33.4 and 34.7, 47.2 and 45.1, but 8-bit 25.0 and 28.4, 32.3 and 34.8.)
 // In between (24 layers 32.2 and 35.7, 28 of d = 64 29.2 and 31.0) two workgroups to a slab take a round more than half.
 // (Below 128 slabs one short prompt keeps the same scores, bit for bit, with and without the promise.)
 static bool two_to_a_slab(const sp_score_args* a) {
   const int W = seq_cu_count(), slabs = a->L * a->H_kv, last = slabs % W;
   if (!(a->flags & SP_SCORE_EXCLUSIVE_DEVICE) || a->B != 1 || a->T < 2048 || slabs < 128) return false;
-  const bool fp8 = a->k_dtype == SP_K_FP8_E4M3;
-  if (last == 0) return !fp8 && a->T + 144 * a->N >= (a->d == 64 ? 3900 : 3170);
+  if (last == 0) return a->N >= 8 && (a->d == 128 || a->T >= 2800);
   if (last > W / 2 || (a->layer_reduce == SP_LAYER_MEAN && slabs > W)) return false;
-  return fp8 || a->d == 128 || slabs > W || a->T >= 2800;
+  return a->d == 128 || slabs > W || a->T >= 2400;
 }
 
 bool single_pass_wanted(const sp_score_args* a) {

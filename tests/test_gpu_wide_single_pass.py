@@ -153,3 +153,27 @@ def test_which_calls_may_wait_on_the_promise_of_an_idle_device(n_keys, L, H_kv, 
     finally:
         sp.sp_set_wait_budget(before)
     assert bool(torch.isnan(got).all()) if waits else bool(torch.isfinite(got).all())
+
+
+@pytest.mark.parametrize("n_keys, L, H_kv, N, d", [(2100, 32, 8, 8, 128), (2100, 32, 8, 4, 128), (2100, 16, 8, 8, 64), (2700, 16, 8, 8, 64), (3073, 16, 8, 8, 64)])
+def test_kept_workspace_handed_on_between_kinds_of_cache(n_keys, L, H_kv, N, d):
+    """Calls of one shape on a bf16 and on an 8-bit cache, in turn on one workspace that is kept: the scores of calls that keep nothing."""
+    import torch
+    from paper_2502_02789_amd import binding as sp, device as dev
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n_keys + N)
+    q = torch.randn((L, 1, N, 4 * H_kv, d), device="cuda", generator=g).to(torch.bfloat16)
+    ks = [torch.randn((n_keys, H_kv, d), device="cuda", generator=g) for _ in range(L)]
+    cu = torch.tensor([0, n_keys], dtype=torch.int32, device="cuda")
+    kw = dict(H_kv=H_kv, scale=d ** -0.5, exclusive_device=True)
+    both = [dev.Scorer(q, [k.to(torch.bfloat16) for k in ks], cu, **kw), dev.Scorer(q, [k.to(torch.float8_e4m3fn).view(torch.uint8) for k in ks], cu, **kw)]
+    want = [s.run().clone() for s in both]
+    room = torch.empty(max(s.workspace.numel() for s in both), dtype=torch.uint8, device="cuda")
+    for s in both:
+        s.args.d_workspace, s.args.workspace_bytes = room.data_ptr(), room.numel()
+    both[0].run()
+    for i in (1, 0, 0, 1, 1, 0):
+        both[i].args.flags = sp.SP_SCORE_EXCLUSIVE_DEVICE | sp.SP_SCORE_WORKSPACE_KEPT
+        both[i].scores.fill_(-1.0)
+        sp.sp_score(both[i].args, None)
+        assert torch.equal(both[i].scores, want[i]), i
